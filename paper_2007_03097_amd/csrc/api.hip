@@ -122,8 +122,7 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
     const size_t GC = N + 8;                             // a group holds at least one particle
     const size_t NBR = N * (size_t)c->nbr_cap + 64;      // group blocks tile n * nbr_cap words
     const size_t CH = N / CHUNK + S + 1;
-    const size_t RSB = (N + 2047) / 2048;
-    const size_t SCB = (std::max(N + 1, 256 * RSB) + 2047) / 2048 + 16;
+    const size_t SCB = (N + 1 + 2047) / 2048 + 16;
     const size_t LST = (NC + 2047) / 2048 + 1;
     Carver cv{base};
     DevPtrs d{};
@@ -132,8 +131,6 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
     d.key_b = cv.take<u64>(N);
     d.val_a = cv.take<u32>(N);
     d.val_b = cv.take<u32>(N);
-    d.rs_hist = cv.take<u32>(256 * RSB);
-    d.rs_dtot = cv.take<u32>(256);
     d.scan_tmp = cv.take<u64>(SCB);
     double** f1[] = {&d.x, &d.y, &d.z, &d.vx, &d.vy, &d.vz, &d.m, &d.h, &d.u, &d.vpx, &d.vpy, &d.vpz, &d.up,
                      &d.ax, &d.ay, &d.az, &d.du, &d.rho, &d.P, &d.cs, &d.hnext, &d.gx, &d.gy, &d.gz, &d.phi,
@@ -371,7 +368,7 @@ static sph_status build_from_caller(sph_ctx* c, const sph_particles* p, const do
         launch_set_box(c->stream, d, dm, 0);
     }
     launch_keys(c->stream, d, dm, p->x, p->y, p->z, p->vx, p->vy, p->vz, p->m, p->h, p->u, (u64*)keys_out, 1);
-    radix_sort(c->stream, d, dm.n);
+    sort_keys(c->stream, d, dm.n, nullptr);  // equal keys by caller index
     launch_gather_input(c->stream, d, dm, p->x, p->y, p->z, p->vx, p->vy, p->vz, p->m, p->h, p->u, order_out);
     build_octree(c->stream, d, dm);
     HIPCHK(c, hipGetLastError());
@@ -646,7 +643,7 @@ static void step_launches(sph_ctx* c, hipStream_t s, int p, bool later) {
     if (!later) launch_box_init(s, a, c->dm);  // later steps: the previous permute reset the box
     launch_kick_drift(s, a, c->dm, later, c->cfg.adaptive_h);  // also merges the new box
     launch_step_keys(s, a, c->dm);        // also derives L and S
-    radix_sort(s, a, n);
+    sort_keys(s, a, n, a.id);             // equal keys by particle ID
     launch_step_permute(s, a, n);         // also writes the pair records
     build_octree(s, b, c->dm);
     accel_pass(c, s, b, b.up, c->cfg.energy_form == SPH_ENERGY_THERMOKINETIC);

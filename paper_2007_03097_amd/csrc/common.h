@@ -60,8 +60,6 @@ struct DevPtrs {
     // sort
     u64 *key_a, *key_b;           // n_cap
     u32 *val_a, *val_b;           // n_cap
-    u32* rs_hist;                 // 256 * rs_blocks_cap
-    u32* rs_dtot;                 // 256 digit totals of the current pass
     void* scan_tmp;               // 8 * scan_blocks_cap (u64)
     // Morton-ordered particle data (SoA FP64)
     double *x, *y, *z, *vx, *vy, *vz, *m, *h, *u;
@@ -347,7 +345,7 @@ void launch_set_box(hipStream_t s, const DevPtrs& d, const Dims& dm, int from_ho
 void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
                  const double* z, const double* vx, const double* vy, const double* vz, const double* m,
                  const double* h, const double* u, u64* keys_out_caller, int caller_order);
-void radix_sort(hipStream_t s, const DevPtrs& d, int n);
+void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie);
 void scan_u64(hipStream_t s, const u64* in, u64* out, int n, void* tmp);
 void scan_u32_total(hipStream_t s, const u32* in, u32* out, int n, void* tmp);
 void launch_gather_input(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,

@@ -4,9 +4,10 @@
 //  * k_keys      quantise to B bits inside the cubic root cell, interleave (x lowest) or
 //                Hilbert index, sentinel bit 63, segment number in bits 54..62 for
 //                segmented sets
-//  * radix sort  stable LSD, 8 passes of 8-bit digits over (key, caller index); stability
-//                plus an identity initial order gives the (key, ID) order of the paper
+//  * merge sort  (key, value) with ties by particle ID: the (key, ID) order of the paper
 //  * gather      caller-order input -> key-ordered SoA + AoS records
+#include <utility>
+
 #include "common.h"
 
 // ---------------------------------------------------------------------------------------
@@ -149,13 +150,13 @@ __device__ __forceinline__ u64 make_key(double x, double y, double z, const doub
     return k;
 }
 
-// Caller-order keys + input validation.  val = caller index (identity).
+// Caller-order keys + input validation.
 __global__ void __launch_bounds__(256) k_keys(DevCtl* ctl, const int4* chunk, int batched, int curve,
                                                const double* __restrict__ x, const double* __restrict__ y,
                                                const double* __restrict__ z, const double* __restrict__ vx,
                                                const double* __restrict__ vy, const double* __restrict__ vz,
                                                const double* __restrict__ m, const double* __restrict__ h,
-                                               const double* __restrict__ u, u64* key, u32* val, u64* key_out) {
+                                               const double* __restrict__ u, u64* key, u64* key_out) {
     const int4 ch = chunk[blockIdx.x];
     u32 bad = 0;
     for (int i = ch.x + threadIdx.x; i < ch.y; i += blockDim.x) {
@@ -166,7 +167,6 @@ __global__ void __launch_bounds__(256) k_keys(DevCtl* ctl, const int4* chunk, in
         if (!(h[i] > 0.0) || !(m[i] > 0.0) || !isfinite(h[i]) || !isfinite(m[i])) bad |= ERR_NONPOSITIVE;
         u64 k = make_key(px, py, pz, ctl->box + 6 * ch.z, ctl->scale[ch.z], ch.z, batched, curve);
         key[i] = k;
-        val[i] = (u32)i;
         if (key_out) key_out[i] = k;
     }
     if (bad) set_err(ctl, bad);
@@ -177,18 +177,16 @@ void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* 
                  const double* h, const double* u, u64* keys_out_caller, int) {
     if (dm.n_chunks > 0)
         hipLaunchKernelGGL(k_keys, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, dm.curve, x, y, z, vx, vy,
-                           vz, m, h, u, d.key_a, d.val_a, keys_out_caller);
+                           vz, m, h, u, d.key_a, keys_out_caller);
 }
 
-// Step-loop keys: positions are in the previous key order; write the key at the caller
-// index (so the sort input is again in caller order) and remember where each caller
-// index sat.
+// Step-loop keys, in the previous key order, which the sort takes as it is (it orders equal
+// keys by ID itself): nearly sorted input, and no scatter to the caller's order.
 // (the positions, velocities and energies it keys were checked for non-finite values by the
 // kick-drift that wrote them)
 __global__ void __launch_bounds__(256) k_step_keys(DevCtl* ctl, const int4* chunk, int batched, int curve,
                                                     const double* __restrict__ x, const double* __restrict__ y,
-                                                    const double* __restrict__ z, const u32* __restrict__ id,
-                                                    u64* key, u32* val) {
+                                                    const double* __restrict__ z, u64* key) {
     const int4 ch = chunk[blockIdx.x];
     // the segment's box from the merged encodings, L and S = 2^B / L (one IEEE division);
     // the segment's first chunk publishes them for the tree build
@@ -210,16 +208,14 @@ __global__ void __launch_bounds__(256) k_step_keys(DevCtl* ctl, const int4* chun
     }
     for (int p = ch.x + threadIdx.x; p < ch.y; p += blockDim.x) {
         const double px = x[p], py = y[p], pz = z[p];
-        const u32 i = id[p];  // keys go to caller order, so the stable sort orders ties by ID
-        key[i] = make_key(px, py, pz, box, S, ch.z, batched, curve);
-        val[i] = (u32)p;      // the sort carries each particle's current position
+        key[p] = make_key(px, py, pz, box, S, ch.z, batched, curve);
     }
 }
 
 void launch_step_keys(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     if (dm.n_chunks > 0)
         hipLaunchKernelGGL(k_step_keys, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, dm.curve, d.x, d.y,
-                           d.z, d.id, d.key_a, d.val_a);
+                           d.z, d.key_a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -364,160 +360,268 @@ void scan_u64(hipStream_t s, const u64* in, u64* out, int n, void* tmp) { scan_i
 void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
     scan_impl<long long>(s, (const long long*)a, (long long*)a, n, tmp, 1);
 }
-static void scan_u32(hipStream_t s, u32* a, int n, void* tmp) { scan_impl<u32>(s, a, a, n, tmp, 0); }
 void scan_u32_total(hipStream_t s, const u32* in, u32* out, int n, void* tmp) { scan_impl<u32>(s, in, out, n, tmp, 1); }
 
 // ---------------------------------------------------------------------------------------
-// LSD radix sort of (u64 key, u32 value), 8-bit digits, 8 passes.  Each block owns a tile
-// of 2048 keys; wave w of the block owns keys [w*512, w*512 + 512) of the tile in 8 rounds
-// of 64, so (wave, round, lane) order is index order and ranks are stable.
-constexpr int RS_THREADS = 256, RS_ITEMS = 8, RS_TILE = RS_THREADS * RS_ITEMS, RS_WAVES = RS_THREADS / 64;
+// Merge sort of (u64 key, u32 value), value = the input index: tiles of MS_TILE keys sorted in
+// LDS by one workgroup each (three resident per CU), then 2-way merge passes over runs that double (merge path: every
+// workgroup finds where its MS_OUT outputs start in both runs and merges them in LDS).
+//
+// Equal keys are ordered by `tie[value]` (the particle ID; tie == nullptr: the value itself), in
+// the comparison, so the input may be in any order: the step sorts from the previous key order,
+// which needs no scatter of its keys to the caller's order, and nearly sorted input makes most
+// merge tiles plain copies.
+//
+// What bounds it: launches for small sets; LDS reads in the tiles, memory in the passes for
+// large ones.  Measured per sort against an LSD radix sort of 8-bit digits (8 passes of three
+// kernels at any size, for 63 key bits): 4,096 keys 134 -> 16-22 us, 123K 144 -> 69 us, 1M 183 ->
+// 116 us (a pass 10 us, 2.3 TB/s; the tiles 34 us), 4M 400 -> 375 us (a pass 29 us, 3.5 TB/s).
+// Tiles of 8,192 keys (one resident workgroup) save a pass and lose as much: 47 us at 1M.
+constexpr int MS_ITEMS = 8, MS_THREADS = 512, MS_TILE = MS_THREADS * MS_ITEMS;
+constexpr int MM_THREADS = 256, MS_OUT = MM_THREADS * MS_ITEMS;
+constexpr u32 MS_PAD = 0xffffffffu;  // value of a filler entry past the end of the last tile
 
-__global__ void __launch_bounds__(RS_THREADS) k_rs_hist(const u64* __restrict__ key, int n, int shift, u32* hist,
-                                                        int nb) {
-    __shared__ u32 h[RS_WAVES][256];
-    const int w = threadIdx.x >> 6, lane = lane_id();
-    for (int i = threadIdx.x; i < RS_WAVES * 256; i += RS_THREADS) (&h[0][0])[i] = 0;
-    __syncthreads();
-    const int base = blockIdx.x * RS_TILE + w * (64 * RS_ITEMS) + lane;
-#pragma unroll
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        int i = base + r * 64;
-        if (i < n) atomicAdd(&h[w][(key[i] >> shift) & 255u], 1u);
-    }
-    __syncthreads();
-    u32 t = 0;
-    for (int k = 0; k < RS_WAVES; ++k) t += h[k][threadIdx.x];
-    hist[threadIdx.x * nb + blockIdx.x] = t;
+// Slot of item i in LDS: one spare slot after every 8 items, so that the lanes of a wave, whose
+// items lie 8 apart, start in different banks.
+__device__ __forceinline__ int ms_slot(int i) { return i + (i >> 3); }
+
+// Order of two items with equal keys (rare: duplicates, and the fillers of the last tile).
+template <bool TIE>
+__device__ __forceinline__ bool ms_tie_less(u32 va, u32 vb, const u32* __restrict__ tie) {
+    if (va == MS_PAD || vb == MS_PAD) return va != MS_PAD;  // fillers come last
+    if constexpr (TIE) return tie[va] < tie[vb];
+    else return va < vb;
 }
 
-__global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const u64* __restrict__ kin, const u32* __restrict__ vin,
-                                                           u64* __restrict__ kout, u32* __restrict__ vout, int n,
-                                                           int shift, const u32* __restrict__ offs, int nb,
-                                                           const u32* __restrict__ digit_tot) {
-    __shared__ u32 wcnt[RS_WAVES][256];
-    __shared__ u32 woff[RS_WAVES][256];
-    __shared__ u32 dbase[256];
-    __shared__ u32 loff[256];
-    __shared__ u32 gbase[256];
-    __shared__ u64 sk[RS_TILE];
-    __shared__ u32 sv[RS_TILE];
-    const int w = threadIdx.x >> 6, lane = lane_id();
-    for (int i = threadIdx.x; i < RS_WAVES * 256; i += RS_THREADS) (&wcnt[0][0])[i] = 0;
-    {   // exclusive scan of the digit totals
-        u32 tot;
-        const u32 e = block_excl_scan<u32>(digit_tot[threadIdx.x], &tot);
-        dbase[threadIdx.x] = e;
-    }
-    __syncthreads();
-    const int base = blockIdx.x * RS_TILE + w * (64 * RS_ITEMS) + lane;
-    u64 k[RS_ITEMS];
-    u32 v[RS_ITEMS], rank[RS_ITEMS];
-    const u64 lt = lanemask_lt();
+// Merges MS_ITEMS outputs of the sorted runs A = [a, ae) and B = [b, be) of LDS items, from the
+// split (a, b) on.  One LDS read per output and no branch on which run it comes from; the read
+// past a run's end is in bounds (the arrays have a spare slot) and unused.
+template <bool TIE>
+__device__ __forceinline__ void ms_merge_items(const u64* sk, const u32* sv, int a, int ae, int b, int be,
+                                               const u32* __restrict__ tie, u64* k, u32* v) {
+    u64 ka = sk[ms_slot(a)], kb = sk[ms_slot(b)];
+    u32 va = sv[ms_slot(a)], vb = sv[ms_slot(b)];
 #pragma unroll
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        const int i = base + r * 64;
-        const bool ok = i < n;
-        k[r] = ok ? kin[i] : 0ull;
-        v[r] = ok ? vin[i] : 0u;
-        const u32 dg = (u32)(k[r] >> shift) & 255u;
-        u64 peers = __ballot(ok);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const bool bit = (dg >> b) & 1u;
-            const u64 bb = __ballot(bit);
-            peers &= bit ? bb : ~bb;
-        }
-        const u32 before = ok ? wcnt[w][dg] : 0u;
-        rank[r] = before + (u32)__popcll(peers & lt);
-        const bool leader = ok && ((peers & lt) == 0ull);
-        __builtin_amdgcn_wave_barrier();  // every lane has read its count before a leader updates it
-        if (leader) wcnt[w][dg] = before + (u32)__popcll(peers);
-    }
-    __syncthreads();
-    {   // per digit: local offsets of the tile's sorted order, per-wave offsets, global base
-        const int dg = threadIdx.x;
-        const u32 c0 = wcnt[0][dg], c1 = wcnt[1][dg], c2 = wcnt[2][dg], c3 = wcnt[3][dg];
-        u32 tot;
-        const u32 lo = block_excl_scan<u32>(c0 + c1 + c2 + c3, &tot);
-        loff[dg] = lo;
-        gbase[dg] = dbase[dg] + offs[dg * nb + blockIdx.x];
-        woff[0][dg] = lo;
-        woff[1][dg] = lo + c0;
-        woff[2][dg] = lo + c0 + c1;
-        woff[3][dg] = lo + c0 + c1 + c2;
-    }
-    __syncthreads();
-    // keys into LDS in the tile's sorted order, then written out from there so that
-    // consecutive lanes write consecutive addresses of a digit's run
-#pragma unroll
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        if (base + r * 64 < n) {
-            const u32 dg = (u32)(k[r] >> shift) & 255u;
-            const u32 pl = woff[w][dg] + rank[r];
-            sk[pl] = k[r];
-            sv[pl] = v[r];
-        }
-    }
-    __syncthreads();
-    const int t0 = blockIdx.x * RS_TILE;
-    const int tn = n - t0 < RS_TILE ? n - t0 : RS_TILE;
-#pragma unroll
-    for (int r = 0; r < RS_ITEMS; ++r) {
-        const int j = threadIdx.x + r * RS_THREADS;
-        if (j < tn) {
-            const u64 kk = sk[j];
-            const u32 dg = (u32)(kk >> shift) & 255u;
-            const u32 pos = gbase[dg] + ((u32)j - loff[dg]);
-            kout[pos] = kk;
-            vout[pos] = sv[j];
-        }
+    for (int r = 0; r < MS_ITEMS; ++r) {
+        bool b_less = kb < ka;
+        if (kb == ka && a < ae && b < be) b_less = ms_tie_less<TIE>(vb, va, tie);
+        const bool from_a = a < ae && (b >= be || !b_less);
+        k[r] = from_a ? ka : kb;
+        v[r] = from_a ? va : vb;
+        a += from_a ? 1 : 0;
+        b += from_a ? 0 : 1;
+        const int i = ms_slot(min(from_a ? a : b, from_a ? ae : be));
+        const u64 nk = sk[i];
+        const u32 nv = sv[i];
+        ka = from_a ? nk : ka;
+        va = from_a ? nv : va;
+        kb = from_a ? kb : nk;
+        vb = from_a ? vb : nv;
     }
 }
 
-// Per-digit exclusive scan of the per-block counts: one workgroup per digit scans that
-// digit's contiguous row (digit-major table) and records the digit total.
-__global__ void __launch_bounds__(SC_THREADS) k_rs_digit_scan(u32* hist, int nb, u32* digit_tot) {
-    u32* h = hist + (size_t)blockIdx.x * nb;
-    u32 carry = 0;
-    for (int b0 = 0; b0 < nb; b0 += SC_TILE) {
-        u32 v[SC_ITEMS];
-        u32 s = 0;
+// Number of items that the first d outputs of the merge take from A = [a0, a0 + na) (the rest
+// come from B = [b0, b0 + nb)); items of LDS.
+template <bool TIE>
+__device__ __forceinline__ int ms_split(const u64* sk, const u32* sv, int a0, int na, int b0, int nb, int d,
+                                        const u32* __restrict__ tie) {
+    int lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        const int ia = ms_slot(a0 + mid), ib = ms_slot(b0 + d - 1 - mid);
+        const u64 ka = sk[ia], kb = sk[ib];
+        bool b_less = kb < ka;
+        if (kb == ka) b_less = ms_tie_less<TIE>(sv[ib], sv[ia], tie);
+        hi = b_less ? mid : hi;
+        lo = b_less ? lo : mid + 1;
+    }
+    return lo;
+}
+
+// One tile: every thread sorts 8 keys in registers, then runs of 8, 16, ... merge in LDS.
+template <bool TIE>
+__global__ void __launch_bounds__(MS_THREADS) k_ms_tile(const u64* kin, u64* kout, u32* vout, int n,
+                                                        const u32* __restrict__ tie) {
+    __shared__ u64 sk[MS_TILE + MS_TILE / 8 + 1];
+    __shared__ u32 sv[MS_TILE + MS_TILE / 8 + 1];
+    const int t0 = blockIdx.x * MS_TILE;
+    const int cnt = n - t0 < MS_TILE ? n - t0 : MS_TILE;
+    const int i0 = threadIdx.x * MS_ITEMS;
+    u64 k[MS_ITEMS];
+    u32 v[MS_ITEMS];
 #pragma unroll
-        for (int k = 0; k < SC_ITEMS; ++k) {
-            const int i = b0 + threadIdx.x * SC_ITEMS + k;
-            v[k] = i < nb ? h[i] : 0u;
-            s += v[k];
-        }
-        u32 tot;
-        u32 e = block_excl_scan<u32>(s, &tot) + carry;
+    for (int r = 0; r < MS_ITEMS; ++r) {
+        const bool ok = i0 + r < cnt;
+        k[r] = ok ? kin[t0 + i0 + r] : ~0ull;
+        v[r] = ok ? (u32)(t0 + i0 + r) : MS_PAD;
+    }
+    if (i0 < cnt) {
 #pragma unroll
-        for (int k = 0; k < SC_ITEMS; ++k) {
-            const int i = b0 + threadIdx.x * SC_ITEMS + k;
-            if (i < nb) h[i] = e;
-            e += v[k];
+        for (int s = 0; s < MS_ITEMS; ++s) {  // odd-even transposition network
+#pragma unroll
+            for (int r = s & 1; r + 1 < MS_ITEMS; r += 2) {
+                const u64 ka = k[r], kb = k[r + 1];
+                const u32 va = v[r], vb = v[r + 1];
+                bool b_less = kb < ka;
+                if (kb == ka) b_less = ms_tie_less<TIE>(vb, va, tie);
+                k[r] = b_less ? kb : ka;
+                v[r] = b_less ? vb : va;
+                k[r + 1] = b_less ? ka : kb;
+                v[r + 1] = b_less ? va : vb;
+            }
         }
-        carry += tot;
+    }
+    const int pad = (cnt + MS_ITEMS - 1) / MS_ITEMS * MS_ITEMS;  // items with fillers up to a whole thread
+    for (int run = MS_ITEMS; run < pad; run *= 2) {
+        if (i0 < pad) {
+#pragma unroll
+            for (int r = 0; r < MS_ITEMS; ++r) {
+                sk[ms_slot(i0 + r)] = k[r];
+                sv[ms_slot(i0 + r)] = v[r];
+            }
+        }
+        __syncthreads();
+        if (i0 < pad) {
+            const int a0 = i0 & ~(2 * run - 1);
+            const int b0 = min(a0 + run, pad), e = min(a0 + 2 * run, pad);
+            const int d = i0 - a0;
+            // nearly sorted input (a step's): the thread's 8 items stay where they are when all
+            // of them precede the other run (in A) or follow it (in B)
+            const bool in_a = i0 < b0;
+            const bool stays = b0 == e || (in_a ? k[MS_ITEMS - 1] < sk[ms_slot(b0)] : sk[ms_slot(b0 - 1)] < k[0]);
+            if (!stays) {
+                const int a = ms_split<TIE>(sk, sv, a0, b0 - a0, b0, e - b0, d, tie);
+                ms_merge_items<TIE>(sk, sv, a0 + a, b0, b0 + d - a, e, tie, k, v);
+            }
+        }
         __syncthreads();
     }
-    if (threadIdx.x == 0) digit_tot[blockIdx.x] = carry;
+#pragma unroll
+    for (int r = 0; r < MS_ITEMS; ++r) {
+        if (i0 + r < cnt) {
+            kout[t0 + i0 + r] = k[r];
+            vout[t0 + i0 + r] = v[r];
+        }
+    }
 }
 
-// Sorts (key_a, val_a) in place (ping-pong through key_b / val_b; 8 passes end in _a).
-void radix_sort(hipStream_t s, const DevPtrs& d, int n) {
-    if (n <= 1) return;
-    const int nb = (n + RS_TILE - 1) / RS_TILE;
-    u64 *ki = d.key_a, *ko = d.key_b;
-    u32 *vi = d.val_a, *vo = d.val_b;
-    for (int pass = 0; pass < 8; ++pass) {
-        const int shift = 8 * pass;
-        hipLaunchKernelGGL(k_rs_hist, dim3(nb), dim3(RS_THREADS), 0, s, ki, n, shift, d.rs_hist, nb);
-        hipLaunchKernelGGL(k_rs_digit_scan, dim3(256), dim3(SC_THREADS), 0, s, d.rs_hist, nb, d.rs_dtot);
-        hipLaunchKernelGGL(k_rs_scatter, dim3(nb), dim3(RS_THREADS), 0, s, ki, vi, ko, vo, n, shift, d.rs_hist, nb,
-                           d.rs_dtot);
-        u64* tk = ki; ki = ko; ko = tk;
-        u32* tv = vi; vi = vo; vo = tv;
+// Splits of two diagonals of the same pair of runs in global memory, one per half wave: 32
+// probes per round, so a run of 2^20 keys takes four dependent rounds of loads.
+template <bool TIE>
+__device__ __forceinline__ int ms_split_global(const u64* __restrict__ key, const u32* __restrict__ val, int a0, int na,
+                                               int b0, int nb, int d, const u32* __restrict__ tie) {
+    const int half = lane_id() >> 5, j = lane_id() & 31;
+    int lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
+    while (__ballot(lo < hi)) {  // both halves take part until both are done
+        const int step = (hi - lo + 31) / 32;
+        const int c = lo + (j + 1) * step - 1;
+        bool past = false;  // A's item c is not among the first d outputs
+        if (lo < hi && c < hi) {
+            const int ia = a0 + c, ib = b0 + d - 1 - c;
+            const u64 ka = key[ia], kb = key[ib];
+            past = kb < ka;
+            if (kb == ka) past = ms_tie_less<TIE>(val[ib], val[ia], tie);
+        }
+        const u32 m = (u32)(__ballot(past) >> (32 * half));
+        if (lo < hi) {
+            if (m) {
+                const int f = __ffs((int)m) - 1;
+                hi = lo + (f + 1) * step - 1;
+                lo = lo + f * step;
+            } else {  // every probe below hi is taken from A
+                lo = min(hi, lo + ((hi - lo) / step) * step);
+            }
+        }
     }
+    return lo;
+}
+
+// One merge pass: pairs of runs of `run` keys.
+template <bool TIE>
+__global__ void __launch_bounds__(MM_THREADS) k_ms_merge(const u64* __restrict__ kin, const u32* __restrict__ vin,
+                                                         u64* __restrict__ kout, u32* __restrict__ vout, int n, int run,
+                                                         const u32* __restrict__ tie) {
+    __shared__ u64 sk[MS_OUT + MS_OUT / 8 + 1];
+    __shared__ u32 sv[MS_OUT + MS_OUT / 8 + 1];
+    __shared__ int split[2];
+    const int o = blockIdx.x * MS_OUT;
+    const int on = n - o < MS_OUT ? n - o : MS_OUT;
+    const int p0 = (int)((long long)o / (2ll * run) * (2ll * run));  // first key of the pair of runs
+    const int na = min(run, n - p0), nb = min(run, n - p0 - na);
+    const int d0 = o - p0;
+    if (threadIdx.x < 64) {
+        const int d = (lane_id() >> 5) ? d0 + on : d0;
+        const int a = ms_split_global<TIE>(kin, vin, p0, na, p0 + na, nb, d, tie);
+        if ((lane_id() & 31) == 0) split[lane_id() >> 5] = a;
+    }
+    __syncthreads();
+    const int a0 = split[0], ca = split[1] - a0, cb = on - ca, b0 = d0 - a0;
+    const u64* ka = kin + p0 + a0;
+    const u32* va = vin + p0 + a0;
+    const u64* kb = kin + p0 + na + b0;
+    const u32* vb = vin + p0 + na + b0;
+    if (ca == 0 || cb == 0) {  // the tile comes from one run
+        const u64* ks = cb == 0 ? ka : kb;
+        const u32* vs = cb == 0 ? va : vb;
+        for (int i = threadIdx.x; i < on; i += MM_THREADS) {
+            kout[o + i] = ks[i];
+            vout[o + i] = vs[i];
+        }
+        return;
+    }
+    for (int i = threadIdx.x; i < on; i += MM_THREADS) {
+        const bool A = i < ca;
+        sk[ms_slot(i)] = A ? ka[i] : kb[i - ca];
+        sv[ms_slot(i)] = A ? va[i] : vb[i - ca];
+    }
+    __syncthreads();
+    const int i0 = threadIdx.x * MS_ITEMS;
+    u64 k[MS_ITEMS];
+    u32 v[MS_ITEMS];
+    if (i0 < on) {
+        const int a = ms_split<TIE>(sk, sv, 0, ca, ca, cb, i0, tie);
+        ms_merge_items<TIE>(sk, sv, a, ca, ca + i0 - a, on, tie, k, v);
+    }
+    __syncthreads();
+    if (i0 < on) {
+#pragma unroll
+        for (int r = 0; r < MS_ITEMS; ++r) {
+            if (i0 + r < on) {
+                sk[ms_slot(i0 + r)] = k[r];
+                sv[ms_slot(i0 + r)] = v[r];
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < on; i += MM_THREADS) {
+        kout[o + i] = sk[ms_slot(i)];
+        vout[o + i] = sv[ms_slot(i)];
+    }
+}
+
+// Sorts key_a (any order) into key_a, with the input index of each sorted key in val_a.
+template <bool TIE>
+static void sort_keys_impl(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
+    int passes = 0;
+    for (long long run = MS_TILE; run < n; run *= 2) ++passes;
+    // the tile sort starts in the buffer from which the passes end in _a
+    u64 *ki = (passes & 1) ? d.key_b : d.key_a, *ko = (passes & 1) ? d.key_a : d.key_b;
+    u32 *vi = (passes & 1) ? d.val_b : d.val_a, *vo = (passes & 1) ? d.val_a : d.val_b;
+    hipLaunchKernelGGL(k_ms_tile<TIE>, dim3((n + MS_TILE - 1) / MS_TILE), dim3(MS_THREADS), 0, s, d.key_a, ki, vi, n,
+                       tie);
+    int run = MS_TILE;
+    for (int p = 0; p < passes; ++p, run *= 2) {
+        hipLaunchKernelGGL(k_ms_merge<TIE>, dim3((n + MS_OUT - 1) / MS_OUT), dim3(MM_THREADS), 0, s, ki, vi, ko, vo, n,
+                           run, tie);
+        std::swap(ki, ko);
+        std::swap(vi, vo);
+    }
+}
+
+void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
+    if (n <= 0) return;
+    if (tie) sort_keys_impl<true>(s, d, n, tie);
+    else sort_keys_impl<false>(s, d, n, nullptr);
 }
 
 // ---------------------------------------------------------------------------------------
