@@ -157,7 +157,6 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
     d.lsort_hist = cv.take<int>(24 * LST);
     d.topo = cv.take<int4>(NC);
     d.parent = cv.take<int>(NC);
-    d.counter = cv.take<int>(NC);
     d.range = cv.take<int2>(NC);
     d.nbox_lo = cv.take<double4>(NC);
     d.nbox_hi = cv.take<double4>(NC);

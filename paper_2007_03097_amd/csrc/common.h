@@ -90,7 +90,6 @@ struct DevPtrs {
     int* lsort_hist;              // 24 * lsort_tiles_cap
     int4* topo;                   // node_cap: {first, count, level, is_leaf}
     int* parent;                  // node_cap
-    int* counter;                 // node_cap
     int2* range;                  // node_cap: {start, count} in sorted order
     double4* nbox_lo;             // node_cap: lo.xyz, hmax
     double4* nbox_hi;             // node_cap: hi.xyz, cell side

@@ -15,7 +15,8 @@
 //   position i starts the nodes of levels lcp[i]+1 .. lvl[i]; an exclusive scan of those
 //   counts numbers the nodes in pre-order.  A stable counting sort by level turns that
 //   into breadth-first order, where the children of a node are a contiguous run of the
-//   next level.  Moments are aggregated bottom-up one level at a time.
+//   next level.  Leaves get their geometry and moments with the topology, internal nodes
+//   bottom-up from their children.
 //   The largest nodes holding at most 4 * group_size particles form compact "group cells";
 //   each is split into target groups of at most group_size consecutive particles, so a
 //   group never spans two distant cells of the space-filling curve.
@@ -300,210 +301,263 @@ __global__ void __launch_bounds__(LS_THREADS) k_lsort_scatter(const DevCtl* __re
     }
 }
 
-// Topology in breadth-first order: leaf -> particle range; internal -> children range.
-__global__ void __launch_bounds__(256) k_finalize(DevCtl* ctl, const unsigned char* __restrict__ pre_level,
-                                                   const unsigned char* __restrict__ pre_leaf,
-                                                   const int* __restrict__ pre_start, const int* __restrict__ pre_to_bfs,
-                                                   const int* __restrict__ bfs_to_pre, const signed char* __restrict__ lcp,
-                                                   const u64* __restrict__ scan, const int* __restrict__ leaf_start,
-                                                   int4* topo, int* parent, int* counter, int2* range) {
-    const int nn = ctl->n_nodes;
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < nn; b += gridDim.x * blockDim.x) {
-        const int pre = bfs_to_pre[b];
-        const int l = pre_level[pre], s = pre_start[pre];
-        counter[b] = 0;
-        if (b == 0) parent[0] = -1;
-        if (pre_leaf[pre]) {
-            const int lf = (int)(scan[s] & 0xffffffffu);
-            const int cnt = leaf_start[lf + 1] - s;
-            topo[b] = make_int4(s, cnt, l, 1);
-            range[b] = make_int2(s, cnt);
-        } else if (pre + 1 >= nn) {  // only with a truncated (over-capacity) tree
-            topo[b] = make_int4(s, 0, l, 1);
-            range[b] = make_int2(s, 0);
-        } else {
-            const int fc = pre_to_bfs[pre + 1];
-            const int end = ctl->level_off[l + 1] + ctl->level_count[l + 1];
-            int nc = 1;
-            while (nc < 8 && fc + nc < end && lcp[pre_start[bfs_to_pre[fc + nc]]] >= l) ++nc;
-            topo[b] = make_int4(fc, nc, l, 0);
-            for (int k = 0; k < nc; ++k) parent[fc + k] = b;
-        }
-    }
+// ---- nodes in breadth-first order: eight lanes per node
+//
+// Eight lanes read a node's children (at most eight), or an eighth of a leaf's particles, at
+// once: the work per node is short and what it costs is the latency of its loads, which one
+// thread per node paid in turn, child by child and particle by particle.  Sums run over the
+// eight lanes' partial sums in a fixed order.
+constexpr int NODE_LANES = 8;
+
+__device__ __forceinline__ double sum8(double v) {
+#pragma unroll
+    for (int d = 1; d < NODE_LANES; d <<= 1) v += __shfl_xor(v, d, NODE_LANES);
+    return v;
+}
+__device__ __forceinline__ double min8(double v) {
+#pragma unroll
+    for (int d = 1; d < NODE_LANES; d <<= 1) v = fmin(v, __shfl_xor(v, d, NODE_LANES));
+    return v;
+}
+__device__ __forceinline__ double max8(double v) {
+#pragma unroll
+    for (int d = 1; d < NODE_LANES; d <<= 1) v = fmax(v, __shfl_xor(v, d, NODE_LANES));
+    return v;
 }
 
-// Internal node from its children: box, largest h, mass, centre of mass, and second
-// moments about the centre of mass (parallel-axis shifts of the children's).
-__device__ void aggregate_node(int p, const int4 tp, double4* nbox_lo, double4* nbox_hi, double4* mom0,
-                               double4* mom1, double4* mom2, int2* range, double side, bool mass) {
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    double hmax = 0.0, M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
-    int cnt = 0;
-    for (int k = 0; k < tp.y; ++k) {
-        const int c = tp.x + k;
-        const double4 a = nbox_lo[c], b = nbox_hi[c];
-        lo[0] = fmin(lo[0], a.x); lo[1] = fmin(lo[1], a.y); lo[2] = fmin(lo[2], a.z);
-        hi[0] = fmax(hi[0], b.x); hi[1] = fmax(hi[1], b.y); hi[2] = fmax(hi[2], b.z);
-        hmax = fmax(hmax, a.w);
-        if (mass) {
-            const double4 m0 = mom0[c];
-            M += m0.x;
-            sx += m0.x * m0.y; sy += m0.x * m0.z; sz += m0.x * m0.w;
-        }
-        cnt += range[c].y;
-    }
-    nbox_lo[p] = make_double4(lo[0], lo[1], lo[2], hmax);
-    nbox_hi[p] = make_double4(hi[0], hi[1], hi[2], side);
-    range[p] = make_int2(range[tp.x].x, cnt);
-    if (!mass) return;
-    const double cx = sx / M, cy = sy / M, cz = sz / M;
-    double I[6] = {0, 0, 0, 0, 0, 0};
-    for (int k = 0; k < tp.y; ++k) {
-        const int c = tp.x + k;
-        const double4 m0 = mom0[c], m1 = mom1[c], m2 = mom2[c];
-        const double dx = m0.y - cx, dy = m0.z - cy, dz = m0.w - cz;
-        I[0] += m1.x + m0.x * dx * dx; I[1] += m1.y + m0.x * dy * dy; I[2] += m1.z + m0.x * dz * dz;
-        I[3] += m2.x + m0.x * dx * dy; I[4] += m2.y + m0.x * dx * dz; I[5] += m2.z + m0.x * dy * dz;
-    }
-    mom0[p] = make_double4(M, cx, cy, cz);
-    mom1[p] = make_double4(I[0], I[1], I[2], I[0] + I[1] + I[2]);
-    mom2[p] = make_double4(I[3], I[4], I[5], 0.0);
-}
-
-// Leaf geometry and moments from its particles [s, s + c).
-__device__ void leaf_node(int b, int s, int c, const double4* __restrict__ pos4, const double* __restrict__ m,
-                          double4* nbox_lo, double4* nbox_hi, double4* mom0, double4* mom1, double4* mom2,
-                          int2* range, double side, bool mass) {
-    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    double hmax = 0.0, M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
-    const int e = s + c;
-    if (!mass) {
-#pragma unroll 4
-        for (int j = s; j < e; ++j) {
-            const double4 p = pos4[j];
-            lo[0] = fmin(lo[0], p.x); lo[1] = fmin(lo[1], p.y); lo[2] = fmin(lo[2], p.z);
-            hi[0] = fmax(hi[0], p.x); hi[1] = fmax(hi[1], p.y); hi[2] = fmax(hi[2], p.z);
-            hmax = fmax(hmax, p.w);
-        }
-        nbox_lo[b] = make_double4(lo[0], lo[1], lo[2], hmax);
-        nbox_hi[b] = make_double4(hi[0], hi[1], hi[2], side);
-        range[b] = make_int2(s, c);
-        return;
-    }
-#pragma unroll 4
-    for (int j = s; j < e; ++j) {
-        const double4 p = pos4[j];
-        const double mj = m[j];
-        lo[0] = fmin(lo[0], p.x); lo[1] = fmin(lo[1], p.y); lo[2] = fmin(lo[2], p.z);
-        hi[0] = fmax(hi[0], p.x); hi[1] = fmax(hi[1], p.y); hi[2] = fmax(hi[2], p.z);
-        hmax = fmax(hmax, p.w);
-        M += mj; sx += mj * p.x; sy += mj * p.y; sz += mj * p.z;
-    }
-    const double cx = sx / M, cy = sy / M, cz = sz / M;
-    double I[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll 4
-    for (int j = s; j < e; ++j) {
-        const double4 p = pos4[j];
-        const double mj = m[j];
-        const double dx = p.x - cx, dy = p.y - cy, dz = p.z - cz;
-        I[0] += mj * dx * dx; I[1] += mj * dy * dy; I[2] += mj * dz * dz;
-        I[3] += mj * dx * dy; I[4] += mj * dx * dz; I[5] += mj * dy * dz;
-    }
-    nbox_lo[b] = make_double4(lo[0], lo[1], lo[2], hmax);
-    nbox_hi[b] = make_double4(hi[0], hi[1], hi[2], side);
-    mom0[b] = make_double4(M, cx, cy, cz);
-    mom1[b] = make_double4(I[0], I[1], I[2], I[0] + I[1] + I[2]);
-    mom2[b] = make_double4(I[3], I[4], I[5], 0.0);
-    range[b] = make_int2(s, c);
-}
-
-struct MomArgs {
+struct NodeArgs {
     const DevCtl* ctl;
     int batched;
     int mass;  // build masses and moments too (gravity on), else only boxes, h_max and ranges
     const u64* key;
-    const int4* topo;
+    int4* topo;
+    int* parent;
     const double4* pos4;
     const double* m;
     double4 *nbox_lo, *nbox_hi, *mom0, *mom1, *mom2;
     int2* range;
 };
 
-// Node b: a leaf from its particles, an internal node from its (finished) children.
-__device__ __forceinline__ void node_moments(const MomArgs& A, int b) {
-    const int4 tp = A.topo[b];
-    const int s = tp.w ? tp.x : A.range[tp.x].x;
+// Cell side of a node at level l whose first particle is at sorted position s.
+__device__ __forceinline__ double node_side(const NodeArgs& A, int s, int l) {
     const int seg = A.batched ? (int)((A.key[s] >> 54) & 511ull) : 0;
-    const double side = ldexp(A.ctl->side[seg], -tp.z);
-    if (tp.w)
-        leaf_node(b, tp.x, tp.y, A.pos4, A.m, A.nbox_lo, A.nbox_hi, A.mom0, A.mom1, A.mom2, A.range, side, A.mass);
-    else
-        aggregate_node(b, tp, A.nbox_lo, A.nbox_hi, A.mom0, A.mom1, A.mom2, A.range, side, A.mass);
+    return ldexp(A.ctl->side[seg], -l);
 }
 
-// Every node at level >= cut: one wavefront per level-cut cell finishes its whole subtree
-// bottom-up.  A subtree's nodes at each level are one contiguous run in breadth-first
-// order (from the first child of its first internal node to the last child of its last
-// internal node), so the runs are found top-down, then the levels are done deepest first
-// with the wavefront's own results as inputs.  The levels between the cut and the top
-// block go one launch each; large sets cut deeper, so that centrally concentrated ones do
-// not leave a few waves with very deep subtrees.  The top block is one workgroup on one CU:
-// it takes levels 3 .. 0 only, since a sparse outer shell (the polytrope's) puts thousands of
-// nodes and leaves at level 4, which a grid-wide launch handles faster.
-constexpr int TOP_LEVELS = 4;
-static int subtree_cut(int n) { return n >= (1 << 21) ? 9 : 6; }
-__global__ void __launch_bounds__(64) k_subtree_moments(MomArgs A, int cut) {
-    __shared__ int run_lo[MAX_LEVEL + 1], run_hi[MAX_LEVEL + 1];
-    const int lane = lane_id();
-    const int nroot = A.ctl->level_count[cut], r0 = A.ctl->level_off[cut];
-    for (int ri = blockIdx.x; ri < nroot; ri += gridDim.x) {
-        int lo = r0 + ri, hi = lo, deep = cut;
-        if (lane == 0) {
-            run_lo[cut] = lo;
-            run_hi[cut] = hi;
+// Leaf geometry and moments from its particles [s, s + c); lane j of the node's eight.
+__device__ __forceinline__ void leaf_node(const NodeArgs& A, int b, int s, int c, double side, int j) {
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    double hmax = 0.0, M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
+    const int e = s + c;
+#pragma unroll 2
+    for (int i = s + j; i < e; i += NODE_LANES) {
+        const double4 p = A.pos4[i];
+        lo[0] = fmin(lo[0], p.x); lo[1] = fmin(lo[1], p.y); lo[2] = fmin(lo[2], p.z);
+        hi[0] = fmax(hi[0], p.x); hi[1] = fmax(hi[1], p.y); hi[2] = fmax(hi[2], p.z);
+        hmax = fmax(hmax, p.w);
+        if (A.mass) {
+            const double mi = A.m[i];
+            M += mi; sx += mi * p.x; sy += mi * p.y; sz += mi * p.z;
         }
-        for (int l = cut; l < MAX_LEVEL; ++l) {
-            int first = -1, last = -1;
-            for (int k0 = lo; k0 <= hi && first < 0; k0 += 64) {  // first internal node
-                const int k = k0 + lane;
-                const u64 bl = __ballot(k <= hi && !A.topo[k].w);
-                if (bl) first = k0 + __ffsll((long long)bl) - 1;
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        lo[k] = min8(lo[k]);
+        hi[k] = max8(hi[k]);
+    }
+    hmax = max8(hmax);
+    if (j == 0) {
+        A.nbox_lo[b] = make_double4(lo[0], lo[1], lo[2], hmax);
+        A.nbox_hi[b] = make_double4(hi[0], hi[1], hi[2], side);
+    }
+    if (!A.mass) return;
+    M = sum8(M);
+    const double cx = sum8(sx) / M, cy = sum8(sy) / M, cz = sum8(sz) / M;
+    double I[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll 2
+    for (int i = s + j; i < e; i += NODE_LANES) {
+        const double4 p = A.pos4[i];
+        const double mi = A.m[i];
+        const double dx = p.x - cx, dy = p.y - cy, dz = p.z - cz;
+        I[0] += mi * dx * dx; I[1] += mi * dy * dy; I[2] += mi * dz * dz;
+        I[3] += mi * dx * dy; I[4] += mi * dx * dz; I[5] += mi * dy * dz;
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) I[k] = sum8(I[k]);
+    if (j == 0) {
+        A.mom0[b] = make_double4(M, cx, cy, cz);
+        A.mom1[b] = make_double4(I[0], I[1], I[2], I[0] + I[1] + I[2]);
+        A.mom2[b] = make_double4(I[3], I[4], I[5], 0.0);
+    }
+}
+
+// Internal node p from its finished children: box, largest h, particle range, mass, centre of
+// mass, and second moments about it (parallel-axis shifts of the children's); lane j has child j.
+__device__ __forceinline__ void internal_node(const NodeArgs& A, int p, const int4 tp, int j) {
+    const bool has = j < tp.y;
+    const int c = tp.x + (has ? j : 0);
+    const double4 a = A.nbox_lo[c], b = A.nbox_hi[c];
+    const int2 r = A.range[c];
+    double4 m0 = make_double4(0, 0, 0, 0), m1 = m0, m2 = m0;
+    if (A.mass) {
+        m0 = A.mom0[c];
+        m1 = A.mom1[c];
+        m2 = A.mom2[c];
+    }
+    int cnt = has ? r.y : 0;
+#pragma unroll
+    for (int d = 1; d < NODE_LANES; d <<= 1) cnt += __shfl_xor(cnt, d, NODE_LANES);
+    const int s = __shfl(r.x, 0, NODE_LANES);
+    // an absent child's lane repeats child 0, which changes no minimum or maximum
+    const double lx = min8(a.x), ly = min8(a.y), lz = min8(a.z), hm = max8(a.w);
+    const double hx = max8(b.x), hy = max8(b.y), hz = max8(b.z);
+    if (j == 0) {
+        A.range[p] = make_int2(s, cnt);
+        A.nbox_lo[p] = make_double4(lx, ly, lz, hm);
+        A.nbox_hi[p] = make_double4(hx, hy, hz, node_side(A, s, tp.z));
+    }
+    if (!A.mass) return;
+    const double mc = has ? m0.x : 0.0;
+    const double M = sum8(mc);
+    const double cx = sum8(mc * m0.y) / M, cy = sum8(mc * m0.z) / M, cz = sum8(mc * m0.w) / M;
+    const double dx = m0.y - cx, dy = m0.z - cy, dz = m0.w - cz;
+    const double I0 = sum8(has ? m1.x + mc * dx * dx : 0.0), I1 = sum8(has ? m1.y + mc * dy * dy : 0.0),
+                 I2 = sum8(has ? m1.z + mc * dz * dz : 0.0), I3 = sum8(has ? m2.x + mc * dx * dy : 0.0),
+                 I4 = sum8(has ? m2.y + mc * dx * dz : 0.0), I5 = sum8(has ? m2.z + mc * dy * dz : 0.0);
+    if (j == 0) {
+        A.mom0[p] = make_double4(M, cx, cy, cz);
+        A.mom1[p] = make_double4(I0, I1, I2, I0 + I1 + I2);
+        A.mom2[p] = make_double4(I3, I4, I5, 0.0);
+    }
+}
+
+// Topology of every node (leaf -> particle range; internal -> children range) and the leaves'
+// geometry and moments, whatever their level: the bottom-up kernels below then only combine
+// children.
+__global__ void __launch_bounds__(256) k_finalize(NodeArgs A, const unsigned char* __restrict__ pre_level,
+                                                   const unsigned char* __restrict__ pre_leaf,
+                                                   const int* __restrict__ pre_start, const int* __restrict__ pre_to_bfs,
+                                                   const int* __restrict__ bfs_to_pre, const signed char* __restrict__ lcp,
+                                                   const u64* __restrict__ scan, const int* __restrict__ leaf_start) {
+    const int nn = A.ctl->n_nodes;
+    const int j = threadIdx.x & (NODE_LANES - 1);
+    const int stride = gridDim.x * (blockDim.x / NODE_LANES);
+    for (int b = blockIdx.x * (blockDim.x / NODE_LANES) + threadIdx.x / NODE_LANES; b < nn; b += stride) {
+        const int pre = bfs_to_pre[b];
+        const int l = pre_level[pre], s = pre_start[pre];
+        if (b == 0 && j == 0) A.parent[0] = -1;
+        if (pre_leaf[pre]) {
+            const int lf = (int)(scan[s] & 0xffffffffu);
+            const int cnt = leaf_start[lf + 1] - s;
+            if (j == 0) {
+                A.topo[b] = make_int4(s, cnt, l, 1);
+                A.range[b] = make_int2(s, cnt);
             }
-            if (first < 0) break;
-            for (int k1 = hi; k1 >= lo && last < 0; k1 -= 64) {  // last internal node
-                const int k = k1 - lane;
-                const u64 bl = __ballot(k >= lo && !A.topo[k].w);
-                if (bl) last = k1 - (__ffsll((long long)bl) - 1);
+            leaf_node(A, b, s, cnt, node_side(A, s, l), j);
+        } else if (pre + 1 >= nn) {  // only with a truncated (over-capacity) tree
+            if (j == 0) {
+                A.topo[b] = make_int4(s, 0, l, 1);
+                A.range[b] = make_int2(s, 0);
             }
-            const int4 tf = A.topo[first], tl = A.topo[last];
-            lo = tf.x;
-            hi = tl.x + tl.y - 1;
-            deep = l + 1;
-            if (lane == 0) {
-                run_lo[deep] = lo;
-                run_hi[deep] = hi;
-            }
-        }
-        __syncthreads();
-        for (int l = deep; l >= cut; --l) {
-            const int a = run_lo[l], e = run_hi[l];
-            for (int k = a + lane; k <= e; k += 64) node_moments(A, k);
-            __syncthreads();
+            leaf_node(A, b, s, 0, node_side(A, s, l), j);
+        } else {
+            const int fc = pre_to_bfs[pre + 1];
+            const int end = A.ctl->level_off[l + 1] + A.ctl->level_count[l + 1];
+            const bool child = j == 0 || (fc + j < end && lcp[pre_start[bfs_to_pre[fc + j]]] >= l);
+            const u32 mask = (u32)(__ballot(child) >> (lane_id() & ~(NODE_LANES - 1))) & 0xffu;
+            const int nc = __ffs((int)~mask) - 1;  // children are the leading run (1 .. 8)
+            if (j < nc) A.parent[fc + j] = b;
+            if (j == 0) A.topo[b] = make_int4(fc, nc, l, 0);
         }
     }
 }
 
-// Nodes of one level (the level below it complete), one node per thread.
-__global__ void __launch_bounds__(256) k_level_moments(MomArgs A, int level) {
-    const int b0 = A.ctl->level_off[level], nb = A.ctl->level_count[level];
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < nb; k += gridDim.x * blockDim.x) node_moments(A, b0 + k);
+// Level from which whole subtrees are handed out: the first with at least SUB_ROOTS nodes, so that
+// flat sets (a tube fills 64 cells at level 4) still occupy the chip and the levels above, which
+// one workgroup finishes, hold few nodes.
+constexpr int SUB_ROOTS = 256;
+constexpr int SUB_THREADS = 256;
+__device__ __forceinline__ int subtree_cut(const DevCtl* ctl) {
+    int l = 3;
+    while (l < MAX_LEVEL && ctl->level_count[l] < SUB_ROOTS && ctl->level_count[l + 1] > 0) ++l;
+    return l;
 }
 
-// Levels TOP_LEVELS - 1 .. 0 in one workgroup, a barrier between levels (their nodes are few).
-__global__ void __launch_bounds__(1024) k_top_moments(MomArgs A) {
-    for (int level = TOP_LEVELS - 1; level >= 0; --level) {
+// Internal nodes at levels >= the cut: one workgroup per node of the cut finishes its whole subtree
+// bottom-up.  A subtree's nodes at each level are one contiguous run in breadth-first order
+// (from the first child of its first internal node to the last child of its last internal
+// node), so the runs are found top-down, then the levels are done deepest first with the
+// workgroup's own results as inputs.  The internal nodes are few (about one per 100 particles):
+// the levels' latency bounds this kernel and k_top_moments.  Moments and finalize together,
+// before (one thread per node, leaves summed in the level order, one launch per level between
+// a fixed cut and the top) and now: 105 -> 32 us (131K polytrope), 337 -> 83 us (1M Evrard
+// sphere), 125 -> 43 us (1.2M particles in 64 boxes), 63 -> 37 us (987,840 tube), 306 -> 245 us (4M
+// polytrope).  Workgroups of 1,024 threads lose on flat sets (tube 12 -> 17 us) and gain little
+// at 4M (107 -> 87 us).
+__global__ void __launch_bounds__(SUB_THREADS) k_subtree_moments(NodeArgs A) {
+    __shared__ int run_lo[MAX_LEVEL + 1], run_hi[MAX_LEVEL + 1], deepest;
+    const int lane = lane_id(), j = threadIdx.x & (NODE_LANES - 1);
+    const int cut = subtree_cut(A.ctl);
+    const int nroot = A.ctl->level_count[cut], r0 = A.ctl->level_off[cut];
+    for (int ri = blockIdx.x; ri < nroot; ri += gridDim.x) {
+        if (threadIdx.x < 64) {  // internal nodes of each level of the subtree lie in run_lo .. run_hi
+            int lo = r0 + ri, hi = lo, deep = cut - 1;
+            for (int l = cut; l < MAX_LEVEL; ++l) {
+                int first = -1, cfirst = 0, last = -1, clast = 0;
+                for (int k0 = lo; k0 <= hi && first < 0; k0 += 64) {
+                    const int4 t = A.topo[min(k0 + lane, hi)];
+                    const u64 bl = __ballot(k0 + lane <= hi && !t.w);
+                    if (!bl) continue;
+                    const int f = __ffsll((long long)bl) - 1;
+                    first = k0 + f;
+                    cfirst = __shfl(t.x, f, 64);
+                    if (hi - k0 < 64) {  // the chunk ends the run: it holds the last one too
+                        const int g = 63 - __clzll((long long)bl);
+                        last = k0 + g;
+                        clast = __shfl(t.x + t.y - 1, g, 64);
+                    }
+                }
+                if (first < 0) break;
+                for (int k1 = hi; last < 0; k1 -= 64) {
+                    const int4 t = A.topo[max(k1 - lane, lo)];
+                    const u64 bl = __ballot(k1 - lane >= lo && !t.w);
+                    if (!bl) continue;
+                    const int g = __ffsll((long long)bl) - 1;
+                    last = k1 - g;
+                    clast = __shfl(t.x + t.y - 1, g, 64);
+                }
+                deep = l;
+                if (lane == 0) {
+                    run_lo[l] = first;
+                    run_hi[l] = last;
+                }
+                lo = cfirst;
+                hi = clast;
+            }
+            if (lane == 0) deepest = deep;
+        }
+        __syncthreads();
+        for (int l = deepest; l >= cut; --l) {
+            const int a = run_lo[l], e = run_hi[l];
+            for (int k = a + threadIdx.x / NODE_LANES; k <= e; k += SUB_THREADS / NODE_LANES) {
+                const int4 tp = A.topo[k];
+                if (!tp.w) internal_node(A, k, tp, j);
+            }
+            __syncthreads();
+        }
+        __syncthreads();  // the runs are free for the next subtree
+    }
+}
+
+// Internal nodes of the levels above the cut in one workgroup, a barrier between levels.
+__global__ void __launch_bounds__(1024) k_top_moments(NodeArgs A) {
+    const int j = threadIdx.x & (NODE_LANES - 1);
+    for (int level = subtree_cut(A.ctl) - 1; level >= 0; --level) {
         const int b0 = A.ctl->level_off[level], nb = A.ctl->level_count[level];
-        for (int k = threadIdx.x; k < nb; k += blockDim.x) node_moments(A, b0 + k);
+        for (int k = threadIdx.x / NODE_LANES; k < nb; k += 1024 / NODE_LANES) {
+            const int4 tp = A.topo[b0 + k];
+            if (!tp.w) internal_node(A, b0 + k, tp, j);
+        }
         __syncthreads();
     }
 }
@@ -537,20 +591,17 @@ void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     hipLaunchKernelGGL(k_lsort_scan, dim3(24), dim3(64), 0, s, d.ctl, d.lsort_hist);
     hipLaunchKernelGGL(k_lsort_scatter, dim3(tiles_cap), dim3(LS_THREADS), 0, s, d.ctl, d.pre_level, d.lsort_hist,
                        d.pre_to_bfs, d.bfs_to_pre);
-    const int g = grid_cap(dm.node_cap, 256, 2048);
-    hipLaunchKernelGGL(k_finalize, dim3(g), dim3(256), 0, s, d.ctl, d.pre_level, d.pre_leaf, d.pre_start,
-                       d.pre_to_bfs, d.bfs_to_pre, d.lcp, d.scan_out, d.leaf_start, d.topo, d.parent, d.counter,
-                       d.range);
-    // moments: subtrees below the cut, then the levels between, then the top levels
-    const int cut = subtree_cut(n);
-    const MomArgs A{d.ctl, dm.batched, dm.mass_moments, d.key_a, d.topo, d.pos4, d.m,
-                    d.nbox_lo, d.nbox_hi, d.mom0, d.mom1, d.mom2, d.range};
-    hipLaunchKernelGGL(k_subtree_moments, dim3(grid_cap(n, 64, 8192)), dim3(64), 0, s, A, cut);
-    for (int lv = cut - 1; lv >= TOP_LEVELS; --lv)
-        hipLaunchKernelGGL(k_level_moments, dim3(grid_cap(n / 2 + 1, 256, 256)), dim3(256), 0, s, A, lv);
+    const NodeArgs A{d.ctl, dm.batched, dm.mass_moments, d.key_a, d.topo, d.parent, d.pos4, d.m,
+                     d.nbox_lo, d.nbox_hi, d.mom0, d.mom1, d.mom2, d.range};
+    // about 4 n / leaf_size nodes of eight lanes; the kernel loops over any beyond that
+    hipLaunchKernelGGL(k_finalize, dim3(grid_cap(4 * (n / dm.leaf_size) + 64, 256 / NODE_LANES, 8192)), dim3(256), 0, s,
+                       A, d.pre_level, d.pre_leaf, d.pre_start, d.pre_to_bfs, d.bfs_to_pre, d.lcp, d.scan_out,
+                       d.leaf_start);
+    hipLaunchKernelGGL(k_subtree_moments, dim3(grid_cap(n, 16, 2048)), dim3(SUB_THREADS), 0, s, A);
     hipLaunchKernelGGL(k_top_moments, dim3(1), dim3(1024), 0, s, A);
     // target groups: cells of at most 4 * group_size particles, cut into runs of group_size
     const int gcap = 4 * dm.group_size;
+    const int g = grid_cap(dm.node_cap, 256, 2048);
     hipLaunchKernelGGL(k_group_starts, dim3(g), dim3(256), 0, s, d.ctl, gcap, dm.group_size, dm.min_level, d.topo,
                        d.parent, d.range, d.gflag, d.gsize);
     scan_u32_total(s, d.gflag, d.gscan, n, d.scan_tmp);
