@@ -4,7 +4,7 @@ import pytest
 
 from workloads import polytrope_n1, uniform_random
 
-from gpu_helpers import gpu_gravity, gpu_keys_order, make_ctx, parts, to_np
+from gpu_helpers import gpu_gravity, gpu_keys_order, gpu_neighbors, make_ctx, parts, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -109,3 +109,18 @@ def test_node_moments(orc, case, leaf):
                                        np.array(gc))[:3], axis=1)
     d = np.linalg.norm(g - ref, axis=1) / np.linalg.norm(ref, axis=1)
     assert np.quantile(d, 0.99) <= 1e-9 and d.max() <= 1e-2, (np.quantile(d, 0.99), d.max())
+
+
+# ---------------------------------------------------------------------------- CSR lists
+@pytest.mark.parametrize("n,h,group", [(700, (0.10, 0.2), 8),     # lists around and over a wave's 64 entries
+                                       (64, 0.9, 64), (65, 0.9, 32), (129, 0.9, 64),   # exactly 64, 65, 129 entries
+                                       (7603, (0.18, 0.26), 16)])  # unions over the 4,096 staged IDs
+def test_csr_lists_of_any_length(orc, n, h, group):
+    ps = uniform_random(n, seed=61, h=h)
+    ctx = make_ctx(n, group_size=group, nbr_capacity=4096)
+    gpu_keys_order(ctx, parts(ps))
+    off, idx = gpu_neighbors(ctx, n)
+    ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+    assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
+    longest = np.diff(off).max()
+    assert longest == n if h == 0.9 else longest > 64
