@@ -305,14 +305,33 @@ __global__ void __launch_bounds__(LS_THREADS) k_lsort_scatter(const DevCtl* __re
 //
 // Eight lanes read a node's children (at most eight), or an eighth of a leaf's particles, at
 // once: the work per node is short and what it costs is the latency of its loads, which one
-// thread per node paid in turn, child by child and particle by particle.  Sums run over the
-// eight lanes' partial sums in a fixed order.
+// thread per node paid in turn, child by child and particle by particle.  The sums stay those of
+// one thread, term by term in child or particle order: the lanes put their terms of up to six
+// sums into LDS and lane q adds up the eight of sum q.
 constexpr int NODE_LANES = 8;
+constexpr int NODE_SUMS = 6;
+struct NodeSums {
+    double v[NODE_SUMS][NODE_LANES + 1];  // (a spare column against bank conflicts)
+};
 
-__device__ __forceinline__ double sum8(double v) {
+// Orders LDS accesses of one wave (its lanes run in step and LDS serves them in order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// acc (of lane q < Q) plus the eight lanes' terms t[q], in lane order.
+template <int Q>
+__device__ __forceinline__ void add_in_order(NodeSums& S, int j, const double (&t)[Q], double& acc) {
+    static_assert(Q <= NODE_SUMS, "one lane per sum");
 #pragma unroll
-    for (int d = 1; d < NODE_LANES; d <<= 1) v += __shfl_xor(v, d, NODE_LANES);
-    return v;
+    for (int q = 0; q < Q; ++q) S.v[q][j] = t[q];
+    wave_lds_fence();
+    const int q = j < Q ? j : 0;
+#pragma unroll
+    for (int k = 0; k < NODE_LANES; ++k) acc += S.v[q][k];
+    wave_lds_fence();
 }
 __device__ __forceinline__ double min8(double v) {
 #pragma unroll
@@ -344,20 +363,32 @@ __device__ __forceinline__ double node_side(const NodeArgs& A, int s, int l) {
     return ldexp(A.ctl->side[seg], -l);
 }
 
+// Mass, centre of mass and second moments of node b; lane q < 6 holds second moment q in acc.
+__device__ __forceinline__ void store_moments(const NodeArgs& A, int b, double M, double cx, double cy, double cz,
+                                              double acc, int j) {
+    const double I0 = __shfl(acc, 0, NODE_LANES), I1 = __shfl(acc, 1, NODE_LANES), I2 = __shfl(acc, 2, NODE_LANES),
+                 I3 = __shfl(acc, 3, NODE_LANES), I4 = __shfl(acc, 4, NODE_LANES), I5 = __shfl(acc, 5, NODE_LANES);
+    if (j != 0) return;
+    A.mom0[b] = make_double4(M, cx, cy, cz);
+    A.mom1[b] = make_double4(I0, I1, I2, I0 + I1 + I2);
+    A.mom2[b] = make_double4(I3, I4, I5, 0.0);
+}
+
 // Leaf geometry and moments from its particles [s, s + c); lane j of the node's eight.
-__device__ __forceinline__ void leaf_node(const NodeArgs& A, int b, int s, int c, double side, int j) {
+__device__ __forceinline__ void leaf_node(const NodeArgs& A, NodeSums& S, int b, int s, int c, double side, int j) {
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    double hmax = 0.0, M = 0.0, sx = 0.0, sy = 0.0, sz = 0.0;
+    double hmax = 0.0, acc = 0.0;
     const int e = s + c;
-#pragma unroll 2
-    for (int i = s + j; i < e; i += NODE_LANES) {
+    for (int i0 = s; i0 < e; i0 += NODE_LANES) {
+        const bool has = i0 + j < e;  // lanes past the end add zeros and repeat the first particle
+        const int i = has ? i0 + j : s;
         const double4 p = A.pos4[i];
         lo[0] = fmin(lo[0], p.x); lo[1] = fmin(lo[1], p.y); lo[2] = fmin(lo[2], p.z);
         hi[0] = fmax(hi[0], p.x); hi[1] = fmax(hi[1], p.y); hi[2] = fmax(hi[2], p.z);
         hmax = fmax(hmax, p.w);
         if (A.mass) {
-            const double mi = A.m[i];
-            M += mi; sx += mi * p.x; sy += mi * p.y; sz += mi * p.z;
+            const double mi = has ? A.m[i] : 0.0;
+            add_in_order<4>(S, j, {mi, mi * p.x, mi * p.y, mi * p.z}, acc);
         }
     }
 #pragma unroll
@@ -371,29 +402,24 @@ __device__ __forceinline__ void leaf_node(const NodeArgs& A, int b, int s, int c
         A.nbox_hi[b] = make_double4(hi[0], hi[1], hi[2], side);
     }
     if (!A.mass) return;
-    M = sum8(M);
-    const double cx = sum8(sx) / M, cy = sum8(sy) / M, cz = sum8(sz) / M;
-    double I[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll 2
-    for (int i = s + j; i < e; i += NODE_LANES) {
+    const double M = __shfl(acc, 0, NODE_LANES);
+    const double cx = __shfl(acc, 1, NODE_LANES) / M, cy = __shfl(acc, 2, NODE_LANES) / M,
+                 cz = __shfl(acc, 3, NODE_LANES) / M;
+    acc = 0.0;
+    for (int i0 = s; i0 < e; i0 += NODE_LANES) {
+        const bool has = i0 + j < e;
+        const int i = has ? i0 + j : s;
         const double4 p = A.pos4[i];
-        const double mi = A.m[i];
+        const double mi = has ? A.m[i] : 0.0;
         const double dx = p.x - cx, dy = p.y - cy, dz = p.z - cz;
-        I[0] += mi * dx * dx; I[1] += mi * dy * dy; I[2] += mi * dz * dz;
-        I[3] += mi * dx * dy; I[4] += mi * dx * dz; I[5] += mi * dy * dz;
+        add_in_order<6>(S, j, {mi * dx * dx, mi * dy * dy, mi * dz * dz, mi * dx * dy, mi * dx * dz, mi * dy * dz}, acc);
     }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) I[k] = sum8(I[k]);
-    if (j == 0) {
-        A.mom0[b] = make_double4(M, cx, cy, cz);
-        A.mom1[b] = make_double4(I[0], I[1], I[2], I[0] + I[1] + I[2]);
-        A.mom2[b] = make_double4(I[3], I[4], I[5], 0.0);
-    }
+    store_moments(A, b, M, cx, cy, cz, acc, j);
 }
 
 // Internal node p from its finished children: box, largest h, particle range, mass, centre of
 // mass, and second moments about it (parallel-axis shifts of the children's); lane j has child j.
-__device__ __forceinline__ void internal_node(const NodeArgs& A, int p, const int4 tp, int j) {
+__device__ __forceinline__ void internal_node(const NodeArgs& A, NodeSums& S, int p, const int4 tp, int j) {
     const bool has = j < tp.y;
     const int c = tp.x + (has ? j : 0);
     const double4 a = A.nbox_lo[c], b = A.nbox_hi[c];
@@ -418,17 +444,18 @@ __device__ __forceinline__ void internal_node(const NodeArgs& A, int p, const in
     }
     if (!A.mass) return;
     const double mc = has ? m0.x : 0.0;
-    const double M = sum8(mc);
-    const double cx = sum8(mc * m0.y) / M, cy = sum8(mc * m0.z) / M, cz = sum8(mc * m0.w) / M;
+    double acc = 0.0;
+    add_in_order<4>(S, j, {mc, mc * m0.y, mc * m0.z, mc * m0.w}, acc);
+    const double M = __shfl(acc, 0, NODE_LANES);
+    const double cx = __shfl(acc, 1, NODE_LANES) / M, cy = __shfl(acc, 2, NODE_LANES) / M,
+                 cz = __shfl(acc, 3, NODE_LANES) / M;
     const double dx = m0.y - cx, dy = m0.z - cy, dz = m0.w - cz;
-    const double I0 = sum8(has ? m1.x + mc * dx * dx : 0.0), I1 = sum8(has ? m1.y + mc * dy * dy : 0.0),
-                 I2 = sum8(has ? m1.z + mc * dz * dz : 0.0), I3 = sum8(has ? m2.x + mc * dx * dy : 0.0),
-                 I4 = sum8(has ? m2.y + mc * dx * dz : 0.0), I5 = sum8(has ? m2.z + mc * dy * dz : 0.0);
-    if (j == 0) {
-        A.mom0[p] = make_double4(M, cx, cy, cz);
-        A.mom1[p] = make_double4(I0, I1, I2, I0 + I1 + I2);
-        A.mom2[p] = make_double4(I3, I4, I5, 0.0);
-    }
+    acc = 0.0;
+    add_in_order<6>(S, j,
+                    {has ? m1.x + mc * dx * dx : 0.0, has ? m1.y + mc * dy * dy : 0.0, has ? m1.z + mc * dz * dz : 0.0,
+                     has ? m2.x + mc * dx * dy : 0.0, has ? m2.y + mc * dx * dz : 0.0, has ? m2.z + mc * dy * dz : 0.0},
+                    acc);
+    store_moments(A, p, M, cx, cy, cz, acc, j);
 }
 
 // Topology of every node (leaf -> particle range; internal -> children range) and the leaves'
@@ -439,6 +466,8 @@ __global__ void __launch_bounds__(256) k_finalize(NodeArgs A, const unsigned cha
                                                    const int* __restrict__ pre_start, const int* __restrict__ pre_to_bfs,
                                                    const int* __restrict__ bfs_to_pre, const signed char* __restrict__ lcp,
                                                    const u64* __restrict__ scan, const int* __restrict__ leaf_start) {
+    __shared__ NodeSums sums[256 / NODE_LANES];
+    NodeSums& S = sums[threadIdx.x / NODE_LANES];
     const int nn = A.ctl->n_nodes;
     const int j = threadIdx.x & (NODE_LANES - 1);
     const int stride = gridDim.x * (blockDim.x / NODE_LANES);
@@ -453,13 +482,13 @@ __global__ void __launch_bounds__(256) k_finalize(NodeArgs A, const unsigned cha
                 A.topo[b] = make_int4(s, cnt, l, 1);
                 A.range[b] = make_int2(s, cnt);
             }
-            leaf_node(A, b, s, cnt, node_side(A, s, l), j);
+            leaf_node(A, S, b, s, cnt, node_side(A, s, l), j);
         } else if (pre + 1 >= nn) {  // only with a truncated (over-capacity) tree
             if (j == 0) {
                 A.topo[b] = make_int4(s, 0, l, 1);
                 A.range[b] = make_int2(s, 0);
             }
-            leaf_node(A, b, s, 0, node_side(A, s, l), j);
+            leaf_node(A, S, b, s, 0, node_side(A, s, l), j);
         } else {
             const int fc = pre_to_bfs[pre + 1];
             const int end = A.ctl->level_off[l + 1] + A.ctl->level_count[l + 1];
@@ -495,6 +524,7 @@ __device__ __forceinline__ int subtree_cut(const DevCtl* ctl) {
 // polytrope).  Workgroups of 1,024 threads lose on flat sets (tube 12 -> 17 us) and gain little
 // at 4M (107 -> 87 us).
 __global__ void __launch_bounds__(SUB_THREADS) k_subtree_moments(NodeArgs A) {
+    __shared__ NodeSums S[SUB_THREADS / NODE_LANES];
     __shared__ int run_lo[MAX_LEVEL + 1], run_hi[MAX_LEVEL + 1], deepest;
     const int lane = lane_id(), j = threadIdx.x & (NODE_LANES - 1);
     const int cut = subtree_cut(A.ctl);
@@ -541,7 +571,7 @@ __global__ void __launch_bounds__(SUB_THREADS) k_subtree_moments(NodeArgs A) {
             const int a = run_lo[l], e = run_hi[l];
             for (int k = a + threadIdx.x / NODE_LANES; k <= e; k += SUB_THREADS / NODE_LANES) {
                 const int4 tp = A.topo[k];
-                if (!tp.w) internal_node(A, k, tp, j);
+                if (!tp.w) internal_node(A, S[threadIdx.x / NODE_LANES], k, tp, j);
             }
             __syncthreads();
         }
@@ -551,12 +581,13 @@ __global__ void __launch_bounds__(SUB_THREADS) k_subtree_moments(NodeArgs A) {
 
 // Internal nodes of the levels above the cut in one workgroup, a barrier between levels.
 __global__ void __launch_bounds__(1024) k_top_moments(NodeArgs A) {
+    __shared__ NodeSums S[1024 / NODE_LANES];
     const int j = threadIdx.x & (NODE_LANES - 1);
     for (int level = subtree_cut(A.ctl) - 1; level >= 0; --level) {
         const int b0 = A.ctl->level_off[level], nb = A.ctl->level_count[level];
         for (int k = threadIdx.x / NODE_LANES; k < nb; k += 1024 / NODE_LANES) {
             const int4 tp = A.topo[b0 + k];
-            if (!tp.w) internal_node(A, b0 + k, tp, j);
+            if (!tp.w) internal_node(A, S[threadIdx.x / NODE_LANES], b0 + k, tp, j);
         }
         __syncthreads();
     }
