@@ -21,7 +21,11 @@
 
 namespace {
 
-constexpr int CHUNK = 1024;
+// Particles per chunk (one 256-thread workgroup of the per-particle kernels that need the segment):
+// one per thread for sets that would not fill the chip otherwise (50,021 particles: keys 15 -> 6.6
+// us), four for larger ones, whose workgroups then merge a quarter of the boxes.
+constexpr int CHUNK = 1024, CHUNK_SMALL = 256;
+constexpr int64_t SMALL_SET = 1 << 18;
 
 struct Tables {
     int64_t n = -1;
@@ -121,7 +125,7 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
     const size_t NC = (size_t)node_cap_for((int64_t)N, c->leaf_min);
     const size_t GC = N + 8;                             // a group holds at least one particle
     const size_t NBR = N * (size_t)c->nbr_cap + 64;      // group blocks tile n * nbr_cap words
-    const size_t CH = N / CHUNK + S + 1;
+    const size_t CH = std::max(N / CHUNK, std::min(N, (size_t)SMALL_SET) / CHUNK_SMALL) + S + 1;
     const size_t SCB = (N + 1 + 2047) / 2048 + 16;
     const size_t LST = (NC + 2047) / 2048 + 1;
     Carver cv{base};
@@ -137,6 +141,7 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
                      &d.x2, &d.y2, &d.z2, &d.vx2, &d.vy2, &d.vz2, &d.m2, &d.h2, &d.u2, &d.vpx2, &d.vpy2, &d.vpz2,
                      &d.up2};
     for (double** p : f1) *p = cv.take<double>(N);
+    d.rec = (double4*)d.x2;  // 64 bytes a particle over x2 .. h2 (eight arrays, carved in a row)
     d.id = cv.take<u32>(N);
     d.id2 = cv.take<u32>(N);
     d.pos4 = cv.take<double4>(N);
@@ -258,11 +263,12 @@ static sph_status prepare(sph_ctx* c, const sph_particles* p) {
     std::vector<int4> chunks;
     std::vector<int> rank(n_seg, 0);
     int r = 0;
+    const int64_t step = p->n <= SMALL_SET ? CHUNK_SMALL : CHUNK;
     for (int s = 0; s < n_seg; ++s) {
         rank[s] = r;
         if (seg[s + 1] > seg[s]) ++r;
-        for (int64_t b = seg[s]; b < seg[s + 1]; b += CHUNK)
-            chunks.push_back(make_int4((int)b, (int)std::min<int64_t>(seg[s + 1], b + CHUNK), s, b == seg[s]));
+        for (int64_t b = seg[s]; b < seg[s + 1]; b += step)
+            chunks.push_back(make_int4((int)b, (int)std::min<int64_t>(seg[s + 1], b + step), s, b == seg[s]));
     }
     dm.n_chunks = (int)chunks.size();
     {   // grids of the per-group kernels: multiples of 8 (one share per XCD), one workgroup per
@@ -368,7 +374,7 @@ static sph_status build_from_caller(sph_ctx* c, const sph_particles* p, const do
     }
     launch_keys(c->stream, d, dm, p->x, p->y, p->z, p->vx, p->vy, p->vz, p->m, p->h, p->u, (u64*)keys_out, 1);
     sort_keys(c->stream, d, dm.n, nullptr);  // equal keys by caller index
-    launch_gather_input(c->stream, d, dm, p->x, p->y, p->z, p->vx, p->vy, p->vz, p->m, p->h, p->u, order_out);
+    launch_gather_input(c->stream, d, dm, p->u, order_out);
     build_octree(c->stream, d, dm);
     HIPCHK(c, hipGetLastError());
     c->tree_ok = true;
@@ -560,10 +566,7 @@ sph_status sph_compute_density(sph_ctx* c, double* rho, double* P, double* cs, d
     const DevPtrs& d = c->d[c->parity];
     const int n = c->dm.n;
     launch_density(c->stream, d, c->dm, c->cfg.precision == SPH_FP32C, c->cfg.gamma, c->cfg.h_coeff, d.u, 0);
-    launch_scatter_caller(c->stream, d, n, d.rho, rho);
-    launch_scatter_caller(c->stream, d, n, d.P, P);
-    launch_scatter_caller(c->stream, d, n, d.cs, cs);
-    launch_scatter_caller(c->stream, d, n, d.hnext, h_next);
+    launch_scatter_caller(c->stream, d, n, {{d.rho, d.P, d.cs, d.hnext}, {rho, P, cs, h_next}});
     HIPCHK(c, hipGetLastError());
     c->dens_ok = true;
     return SPH_OK;
@@ -586,10 +589,7 @@ sph_status sph_compute_forces(sph_ctx* c, const double* rho, const double* P, co
     }
     launch_forces(c->stream, d, c->dm, c->cfg.precision == SPH_FP32C, c->cfg.av_alpha, c->cfg.av_beta, c->cfg.av_eps,
                   c->cfg.energy_form == SPH_ENERGY_THERMOKINETIC);
-    launch_scatter_caller(c->stream, d, n, d.ax, ax);
-    launch_scatter_caller(c->stream, d, n, d.ay, ay);
-    launch_scatter_caller(c->stream, d, n, d.az, az);
-    launch_scatter_caller(c->stream, d, n, d.du, dudt);
+    launch_scatter_caller(c->stream, d, n, {{d.ax, d.ay, d.az, d.du}, {ax, ay, az, dudt}});
     HIPCHK(c, hipGetLastError());
     return SPH_OK;
 }
@@ -608,10 +608,7 @@ sph_status sph_compute_gravity(sph_ctx* c, double* gx, double* gy, double* gz, d
     const DevPtrs& d = c->d[c->parity];
     launch_fill_i32(c->stream, &d.ctl->skip_phi, 0, 1);  // this pass returns the potential
     gravity_pass(c, c->stream, d, 0, 0);
-    launch_scatter_caller(c->stream, d, n, d.gx, gx);
-    launch_scatter_caller(c->stream, d, n, d.gy, gy);
-    launch_scatter_caller(c->stream, d, n, d.gz, gz);
-    launch_scatter_caller(c->stream, d, n, d.phi, phi);
+    launch_scatter_caller(c->stream, d, n, {{d.gx, d.gy, d.gz, d.phi}, {gx, gy, gz, phi}});
     HIPCHK(c, hipGetLastError());
     return SPH_OK;
 }

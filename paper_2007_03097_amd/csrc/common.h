@@ -28,6 +28,10 @@ constexpr int UNION_MAX = 65536;
 constexpr int MAX_LEVEL = 21;   // 21 three-bit digits below the sentinel bit 63
 constexpr double M_1_PI_D = 0.318309886183790671537767526745028724;
 
+// Accumulators of a single set's bounding box in k_bbox: workgroups spread their atomics over
+// them, and k_set_box merges them (a segmented set has one per segment).
+constexpr int BOX_SLOTS = 64;
+
 // Counter slots of the gravity pass's term counts, one 128-byte line each.
 constexpr int GRAV_SLOTS = 64;
 
@@ -71,6 +75,7 @@ struct DevPtrs {
     double *x2, *y2, *z2, *vx2, *vy2, *vz2, *m2, *h2, *u2, *vpx2, *vpy2, *vpz2, *up2;
     u32* id;                      // caller index of each Morton position
     u32* id2;
+    double4* rec;                 // 2 n_cap, over the second copies: caller-order records of a build
     double4* pos4;                // x, y, z, h (Morton order)
     double4* vel4;                // vx(pred), vy, vz, m
     double4* thr4;                // rho, P/rho^2, c, u
@@ -347,9 +352,7 @@ void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* 
 void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie);
 void scan_u64(hipStream_t s, const u64* in, u64* out, int n, void* tmp);
 void scan_u32_total(hipStream_t s, const u32* in, u32* out, int n, void* tmp);
-void launch_gather_input(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
-                         const double* z, const double* vx, const double* vy, const double* vz, const double* m,
-                         const double* h, const double* u, int64_t* order_out);
+void launch_gather_input(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out);
 // k_tree.hip
 void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm);
 void launch_tree_export(hipStream_t s, const DevPtrs& d, const Dims& dm, u64* key, int32_t* level,
@@ -373,7 +376,11 @@ void launch_gravity(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
 void launch_fmm(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, double G, double eps, double theta,
                 int accumulate, int thermokinetic);
 // k_step.hip
-void launch_scatter_caller(hipStream_t s, const DevPtrs& d, int n, const double* src, double* dst);
+struct ScatterArgs {
+    const double* src[4];
+    double* dst[4];
+};
+void launch_scatter_caller(hipStream_t s, const DevPtrs& d, int n, const ScatterArgs& a);
 void launch_fill_zero(hipStream_t s, int n, double* dst);
 void launch_gather_caller(hipStream_t s, const DevPtrs& d, int n, const double* src_caller, double* dst);
 void launch_box_init(hipStream_t s, const DevPtrs& d, const Dims& dm);

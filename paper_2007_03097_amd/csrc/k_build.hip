@@ -43,19 +43,30 @@ __global__ void k_box_init(DevCtl* ctl, int n_seg) {
     }
 }
 
-__global__ void __launch_bounds__(256) k_bbox(DevCtl* ctl, const int4* chunk, const double* __restrict__ x,
+// With all atomics on one box 4M positions took 104 us, of which reading them is 20 (4,096 workgroups
+// x 6 atomics on the same addresses); over 64 boxes 28 us (1M: 28 -> 9 us).
+__global__ void __launch_bounds__(256) k_bbox(DevCtl* ctl, const int4* chunk, int batched, const double* __restrict__ x,
                                                const double* __restrict__ y, const double* __restrict__ z) {
     const int4 ch = chunk[blockIdx.x];
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int i = ch.x + threadIdx.x; i < ch.y; i += blockDim.x) {
-        double v[3] = {x[i], y[i], z[i]};
+    for (int i0 = ch.x; i0 < ch.y; i0 += 1024) {
+        double v[4][3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            lo[c] = fmin(lo[c], v[c]);
-            hi[c] = fmax(hi[c], v[c]);
+        for (int k = 0; k < 4; ++k) {  // twelve loads in flight; past the end the chunk's last particle again
+            const int i = min(i0 + k * 256 + (int)threadIdx.x, ch.y - 1);
+            v[k][0] = x[i];
+            v[k][1] = y[i];
+            v[k][2] = z[i];
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                lo[c] = fmin(lo[c], v[k][c]);
+                hi[c] = fmax(hi[c], v[k][c]);
+            }
     }
-    box_block_merge(ctl, ch.z, lo, hi, ch.y > ch.x);
+    box_block_merge(ctl, batched ? ch.z : (int)(blockIdx.x & (BOX_SLOTS - 1)), lo, hi, ch.y > ch.x);
 }
 
 void launch_box_init(hipStream_t s, const DevPtrs& d, const Dims& dm) {
@@ -64,15 +75,28 @@ void launch_box_init(hipStream_t s, const DevPtrs& d, const Dims& dm) {
 
 void launch_bbox(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
                  const double* z, const u32*) {
-    hipLaunchKernelGGL(k_box_init, dim3((dm.n_seg + 255) / 256), dim3(256), 0, s, d.ctl, dm.n_seg);
-    if (dm.n_chunks > 0) hipLaunchKernelGGL(k_bbox, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, x, y, z);
+    const int slots = dm.batched ? dm.n_seg : BOX_SLOTS;
+    hipLaunchKernelGGL(k_box_init, dim3((slots + 255) / 256), dim3(256), 0, s, d.ctl, slots);
+    if (dm.n_chunks > 0)
+        hipLaunchKernelGGL(k_bbox, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, x, y, z);
 }
 
 // Decode the boxes (unless the caller supplied them) and derive L and S = 2^B / L.
 __global__ void k_set_box(DevCtl* ctl, int n_seg, int bits, int from_host) {
     int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (!from_host && bits == 21) {  // one set: merge the BOX_SLOTS accumulators
+        for (int c = 0; c < 6; ++c) {
+            u64 e = c < 3 ? ~0ull : 0ull;
+            if (threadIdx.x < BOX_SLOTS) e = ctl->box_enc[6 * threadIdx.x + c];
+            for (int d = 32; d >= 1; d >>= 1) {
+                const u64 o = __shfl_xor(e, d, 64);
+                e = c < 3 ? (o < e ? o : e) : (o > e ? o : e);
+            }
+            if (threadIdx.x == 0) ctl->box[c] = dec_double(e);
+        }
+    }
     if (s >= n_seg) return;
-    if (!from_host)
+    if (!from_host && bits != 21)
         for (int c = 0; c < 6; ++c) ctl->box[6 * s + c] = dec_double(ctl->box_enc[6 * s + c]);
     double L = 0.0;
     for (int c = 0; c < 3; ++c) {
@@ -150,21 +174,27 @@ __device__ __forceinline__ u64 make_key(double x, double y, double z, const doub
     return k;
 }
 
-// Caller-order keys + input validation.
+// Caller-order keys + input validation.  Each particle is also written as one 64-byte record
+// (x, y, z, h), (vx, vy, vz, m) in caller order, from which k_gather_input reads it: a gather of
+// one line per particle and u instead of nine (see there).
 __global__ void __launch_bounds__(256) k_keys(DevCtl* ctl, const int4* chunk, int batched, int curve,
                                                const double* __restrict__ x, const double* __restrict__ y,
                                                const double* __restrict__ z, const double* __restrict__ vx,
                                                const double* __restrict__ vy, const double* __restrict__ vz,
                                                const double* __restrict__ m, const double* __restrict__ h,
-                                               const double* __restrict__ u, u64* key, u64* key_out) {
+                                               const double* __restrict__ u, u64* key, u64* key_out,
+                                               double4* __restrict__ rec) {
     const int4 ch = chunk[blockIdx.x];
     u32 bad = 0;
     for (int i = ch.x + threadIdx.x; i < ch.y; i += blockDim.x) {
         double px = x[i], py = y[i], pz = z[i];
-        if (!isfinite(px) || !isfinite(py) || !isfinite(pz) || !isfinite(vx[i]) || !isfinite(vy[i]) ||
-            !isfinite(vz[i]) || !isfinite(u[i]))
+        const double wx = vx[i], wy = vy[i], wz = vz[i], hh = h[i], mm = m[i];
+        if (!isfinite(px) || !isfinite(py) || !isfinite(pz) || !isfinite(wx) || !isfinite(wy) ||
+            !isfinite(wz) || !isfinite(u[i]))
             bad |= ERR_NONFINITE;
-        if (!(h[i] > 0.0) || !(m[i] > 0.0) || !isfinite(h[i]) || !isfinite(m[i])) bad |= ERR_NONPOSITIVE;
+        if (!(hh > 0.0) || !(mm > 0.0) || !isfinite(hh) || !isfinite(mm)) bad |= ERR_NONPOSITIVE;
+        rec[2 * (size_t)i] = make_double4(px, py, pz, hh);
+        rec[2 * (size_t)i + 1] = make_double4(wx, wy, wz, mm);
         u64 k = make_key(px, py, pz, ctl->box + 6 * ch.z, ctl->scale[ch.z], ch.z, batched, curve);
         key[i] = k;
         if (key_out) key_out[i] = k;
@@ -177,7 +207,7 @@ void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* 
                  const double* h, const double* u, u64* keys_out_caller, int) {
     if (dm.n_chunks > 0)
         hipLaunchKernelGGL(k_keys, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, dm.curve, x, y, z, vx, vy,
-                           vz, m, h, u, d.key_a, keys_out_caller);
+                           vz, m, h, u, d.key_a, keys_out_caller, d.rec);
 }
 
 // Step-loop keys, in the previous key order, which the sort takes as it is (it orders equal
@@ -625,31 +655,30 @@ void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
 }
 
 // ---------------------------------------------------------------------------------------
-// caller-order input -> key-ordered snapshot
+// Caller-order input -> key-ordered snapshot.  The caller's order is arbitrary: gathered array by
+// array, every 8-byte read costs a line, and the records of k_keys cost one line for eight of
+// the nine fields.
+// 4M particles in random order: the gather 784 -> 245 us and the keys, which write the records,
+// 83 -> 150 us; 1M: 179 -> 57 us and 18 -> 38 us.
 __global__ void __launch_bounds__(256) k_gather_input(int n, const u32* __restrict__ perm,
-                                                       const double* __restrict__ x, const double* __restrict__ y,
-                                                       const double* __restrict__ z, const double* __restrict__ vx,
-                                                       const double* __restrict__ vy, const double* __restrict__ vz,
-                                                       const double* __restrict__ m, const double* __restrict__ h,
-                                                       const double* __restrict__ u, DevPtrs d, int64_t* order_out) {
+                                                       const double4* __restrict__ rec, const double* __restrict__ u,
+                                                       DevPtrs d, int64_t* order_out) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= n) return;
     const u32 i = perm[q];
-    const double px = x[i], py = y[i], pz = z[i], ph = h[i], pm = m[i];
-    const double wx = vx[i], wy = vy[i], wz = vz[i], pu = u[i];
+    const double4 p = rec[2 * (size_t)i], v = rec[2 * (size_t)i + 1];
+    const double pu = u[i];
     d.id[q] = i;
-    d.x[q] = px; d.y[q] = py; d.z[q] = pz;
-    d.vx[q] = wx; d.vy[q] = wy; d.vz[q] = wz;
-    d.m[q] = pm; d.h[q] = ph; d.u[q] = pu;
-    d.pos4[q] = make_double4(px, py, pz, ph);
-    d.vel4[q] = make_double4(wx, wy, wz, pm);
+    d.x[q] = p.x; d.y[q] = p.y; d.z[q] = p.z;
+    d.vx[q] = v.x; d.vy[q] = v.y; d.vz[q] = v.z;
+    d.m[q] = v.w; d.h[q] = p.w; d.u[q] = pu;
+    d.pos4[q] = p;
+    d.vel4[q] = v;
     if (order_out) order_out[q] = (int64_t)i;
 }
 
-void launch_gather_input(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
-                         const double* z, const double* vx, const double* vy, const double* vz, const double* m,
-                         const double* h, const double* u, int64_t* order_out) {
+void launch_gather_input(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out) {
     if (dm.n > 0)
-        hipLaunchKernelGGL(k_gather_input, dim3((dm.n + 255) / 256), dim3(256), 0, s, dm.n, d.val_a, x, y, z, vx,
-                           vy, vz, m, h, u, d, order_out);
+        hipLaunchKernelGGL(k_gather_input, dim3((dm.n + 255) / 256), dim3(256), 0, s, dm.n, d.val_a, d.rec, u, d,
+                           order_out);
 }

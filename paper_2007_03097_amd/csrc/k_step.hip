@@ -4,12 +4,29 @@
 
 static inline dim3 g256(int n) { return dim3((n + 255) / 256); }
 
-__global__ void k_scatter_caller(int n, const u32* __restrict__ id, const double* __restrict__ src, double* dst) {
+// Up to four key-ordered arrays to the caller's order in one launch (a call's results; four
+// launches cost a small set more than the copies do: 50,021 particles 8 x 3.9 -> 2 x 5.5 us); a NULL destination is skipped.
+__global__ void k_scatter_caller(int n, const u32* __restrict__ id, ScatterArgs a) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < n) dst[id[q]] = src[q];
+    if (q >= n) return;
+    const u32 i = id[q];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (a.dst[k]) a.dst[k][i] = a.src[k][q];
 }
-void launch_scatter_caller(hipStream_t s, const DevPtrs& d, int n, const double* src, double* dst) {
-    if (n > 0 && dst) hipLaunchKernelGGL(k_scatter_caller, g256(n), dim3(256), 0, s, n, d.id, src, dst);
+void launch_scatter_caller(hipStream_t s, const DevPtrs& d, int n, const ScatterArgs& a) {
+    if (n <= 0) return;
+    // One array at a time above 2^20 particles: the random writes to one array then meet in the
+    // caches (4M particles: 4 x 72 us against 392 us together; 1M: 64 against 57 us).
+    const bool each = n > (1 << 20);
+    for (int k = 0; k < (each ? 4 : 1); ++k) {
+        ScatterArgs b = a;
+        if (each)
+            for (int j = 0; j < 4; ++j)
+                if (j != k) b.dst[j] = nullptr;
+        if (b.dst[0] || b.dst[1] || b.dst[2] || b.dst[3])
+            hipLaunchKernelGGL(k_scatter_caller, g256(n), dim3(256), 0, s, n, d.id, b);
+    }
 }
 
 __global__ void k_fill_zero(int n, double* dst) {
