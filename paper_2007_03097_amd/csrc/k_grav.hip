@@ -36,13 +36,13 @@ template <>
 struct GravStage<false> {
     union {
         struct {
-            // (M, com), (3 Ixx, 3 Iyy, 3 Izz, 3/2 tr I), (3 Ixy, 3 Ixz, 3 Iyz, 1/2 tr I)
-            double4 c0[32], c1[32], c2[32];
+            double4 c0[64], c1[64], c2[64];  // the record of cell_term
         } cell;
         struct {
             double4 pm[64];  // (x, y, z, m)
             int src[64];     // particle index (self test without softening)
         } part;
+        double red[4][64];   // a target's partial sums
     };
     int loff[GW_LEAVES + 1];  // particle offsets of the staged leaves
 };
@@ -88,10 +88,14 @@ struct TargetSums {
     }
 };
 
-// Monopole + quadrupole of a staged cell, with the expansion's constants folded into the
-// record at staging: a = (M, com), b = (3 Ixx, 3 Iyy, 3 Izz, 3/2 tr I), d = (3 Ixy, 3 Ixz,
-// 3 Iyz, 1/2 tr I).  With Q = 3 I: g += -M R/s^3 + Q.R/s^5 - (5/2) (R.Q.R) R/s^7 + (3/2) tr(I) R/s^5
-// and phi -= M/s + (1/2) R.Q.R/s^5 - (1/2) tr(I)/s^3.
+// Monopole + quadrupole of a staged cell (FP64).  With the traceless Q = 3 I - tr(I) 1 the trace terms
+// of the expansion cancel but for the softening's share: with u = R.Q.R - tr(I) eps^2,
+//   g += -R (M/s^3 + (5/2) u/s^7) + Q.R/s^5,   phi -= M/s + (1/2) u/s^5
+// (3 R.I.R = R.Q.R + tr(I) (s^2 - eps^2)), so u takes its constant from the record and starts the
+// sum for free.  Record: a = (M, com), b = (Qxx, Qyy, Qzz, -tr(I) eps^2), d = (Qxy, Qxz, Qyz, -).
+// The kernel is bound by its FP64 instructions (at 4M particles it runs at what the FMA probe
+// sustains of the issue rate): 36 per term, 38 with the potential, against 39 and 44 with the
+// trace carried along; TRACEFIG
 template <bool PH = true>
 __device__ __forceinline__ void cell_term(const double4 me, const double4 a, const double4 b, const double4 d,
                                           double e2, TargetSums& S) {
@@ -99,15 +103,15 @@ __device__ __forceinline__ void cell_term(const double4 me, const double4 a, con
     const double QRx = fma(b.x, Rx, fma(d.x, Ry, d.y * Rz));
     const double QRy = fma(d.x, Rx, fma(b.y, Ry, d.z * Rz));
     const double QRz = fma(d.y, Rx, fma(d.z, Ry, b.z * Rz));
-    const double RQR = fma(Rx, QRx, fma(Ry, QRy, Rz * QRz));
+    const double u = fma(Rx, QRx, fma(Ry, QRy, fma(Rz, QRz, b.w)));
     const double s2 = fma(Rx, Rx, fma(Ry, Ry, fma(Rz, Rz, e2)));
     const double i1 = rsq_nr1(s2);
-    const double i2 = i1 * i1, i3 = i1 * i2, i5 = i3 * i2, i7 = i5 * i2;
-    const double cR = fma(b.w, i5, fma(-2.5 * RQR, i7, -a.x * i3));
+    const double i2 = i1 * i1, i3 = i1 * i2, i5 = i3 * i2, u5 = u * i5;
+    const double cR = fma(-2.5, u5 * i2, -a.x * i3);
     S.gx = fma(cR, Rx, fma(i5, QRx, S.gx));
     S.gy = fma(cR, Ry, fma(i5, QRy, S.gy));
     S.gz = fma(cR, Rz, fma(i5, QRz, S.gz));
-    if constexpr (PH) S.ph -= fma(a.x, i1, fma(0.5 * RQR, i5, -d.w * i3));
+    if constexpr (PH) S.ph = fma(-0.5, u5, fma(-a.x, i1, S.ph));
 }
 
 // Softened particle term of source sb = (x, y, z, m).
@@ -135,7 +139,10 @@ __device__ __forceinline__ void part_term(const double4 me, const double4 sb, do
     }
 }
 
-// FP32C forms on group-origin offsets: the target and the cell's centre of mass (or the
+// FP32C forms; the cell record has the constants folded in: a = (M, com), b = (3 Ixx, 3 Iyy, 3 Izz,
+// 3/2 tr I), d = (3 Ixy, 3 Ixz, 3 Iyz, 1/2 tr I), so with Q = 3 I: g += -M R/s^3 + Q.R/s^5
+// - (5/2) (R.Q.R) R/s^7 + (3/2) tr(I) R/s^5 and phi -= M/s + (1/2) R.Q.R/s^5 - (1/2) tr(I)/s^3.
+// They work on group-origin offsets: the target and the cell's centre of mass (or the
 // source particle) are FP32 offsets from the group's first target, each formed in FP64 and
 // rounded once, so one FP32 subtraction gives R (its error is within u (|r_a - o| + |R_B - o|),
 // small against |R| for accepted cells, and softened for near particle pairs).
@@ -169,9 +176,10 @@ __device__ __forceinline__ void part_term_f(const float4 me, const float4 sb, fl
     if constexpr (PH) S.tph = fmaf(-sb.w, i1, S.tph);
 }
 
-// Two targets per lane: tp and tp + TP (TP = group_size / 2); the P = 64 / TP lanes with
-// the same tp split every staged tile, so each LDS read of a cell or particle feeds two
-// evaluations.
+// Two targets per lane: tp and tp + TP; the P = 64 / TP lanes with the same tp split every
+// staged tile, so each LDS read of a cell or particle feeds two evaluations.  FP64: TP is half
+// the group's targets, rounded up (lanes past P TP idle); FP32C, whose sums depend in their last
+// bits on how the tiles are split: the fewest power of two that holds them.
 struct GravTargets {
     double4 a, b;
     float4 fa, fb;  // FP32C: offsets from the group origin o
@@ -195,7 +203,7 @@ __device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C>& St, co
                            double e2, bool phi, TargetSums& A, TargetSums& B) {
     const int lane = lane_id();
     const bool any = T.va || T.vb;
-    constexpr int CS = FP32C ? 64 : 32;  // cells staged per round
+    constexpr int CS = 64;  // cells staged per round
     for (int k0 = 0; k0 < ncell; k0 += CS) {
         __syncthreads();
         if (lane < CS && k0 + lane < ncell) {
@@ -208,10 +216,11 @@ __device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C>& St, co
                                                 (float)(1.5 * c1.w));
                 St.cellf.c2[lane] = make_float4((float)(3.0 * c2.x), (float)(3.0 * c2.y), (float)(3.0 * c2.z),
                                                 (float)(0.5 * c1.w));
-            } else {  // the expansion's constants folded in (see cell_term)
+            } else {  // see cell_term
                 St.cell.c0[lane] = c0;
-                St.cell.c1[lane] = make_double4(3.0 * c1.x, 3.0 * c1.y, 3.0 * c1.z, 1.5 * c1.w);
-                St.cell.c2[lane] = make_double4(3.0 * c2.x, 3.0 * c2.y, 3.0 * c2.z, 0.5 * c1.w);
+                St.cell.c1[lane] = make_double4(fma(3.0, c1.x, -c1.w), fma(3.0, c1.y, -c1.w), fma(3.0, c1.z, -c1.w),
+                                                -e2 * c1.w);
+                St.cell.c2[lane] = make_double4(3.0 * c2.x, 3.0 * c2.y, 3.0 * c2.z, 0.0);
             }
         }
         __syncthreads();
@@ -452,18 +461,23 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
     group_range(ctl->n_groups, g0, g1, gstep);
     for (int gi = g0; gi < g1; gi += gstep) {
         const int4 g = group[gi];
-        // TP target pairs per wave, the fewest (a power of two) that hold the group's targets:
-        // the P = 64 / TP lanes of a pair split each staged tile, so a group with few
-        // targets keeps every lane busy
-        T.TP = 1;
-        while (2 * T.TP < g.y && T.TP < (gsz >> 1)) T.TP <<= 1;
+        // TP target pairs per wave: with few targets, more lanes split the tiles.  Halving the
+        // targets fills 92-94% of the lane slots (groups of at most 32, 23 on average at 4M),
+        // powers of two 87%.
+        if (FP32C) {
+            T.TP = 1;
+            while (2 * T.TP < g.y && T.TP < (gsz >> 1)) T.TP <<= 1;
+        } else {
+            T.TP = (g.y + 1) >> 1;
+        }
         T.P = 64 / T.TP;
-        T.tp = lane & (T.TP - 1);
+        T.tp = lane % T.TP;
         T.phi = lane / T.TP;
+        const bool works = T.phi < T.P;
         T.qa = g.x + T.tp;
         T.qb = g.x + T.tp + T.TP;
-        T.va = T.tp < g.y;
-        T.vb = T.tp + T.TP < g.y;
+        T.va = works && T.tp < g.y;
+        T.vb = works && T.tp + T.TP < g.y;
         T.a = T.va ? pos4[T.qa] : make_double4(0, 0, 0, 0);
         T.b = T.vb ? pos4[T.qb] : make_double4(0, 0, 0, 0);
         if (FP32C) {
@@ -552,18 +566,29 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
         __syncthreads();
         count_terms(nc, nl, leaves, topo, g.y, n_cells, n_pairs);
         eval_lists<FP32C>(nc, nl, cells, leaves, St, topo, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B);
-        // per target: lanes tp + TP*phi combine in a fixed butterfly order
+        // per target: lanes tp + TP*phi combine in a fixed order
         double r[8];
-        r[0] = FP32C ? A.kx.value() : A.gx;
-        r[1] = FP32C ? A.ky.value() : A.gy;
-        r[2] = FP32C ? A.kz.value() : A.gz;
-        r[3] = FP32C ? A.kp.value() : A.ph;
-        r[4] = FP32C ? B.kx.value() : B.gx;
-        r[5] = FP32C ? B.ky.value() : B.gy;
-        r[6] = FP32C ? B.kz.value() : B.gz;
-        r[7] = FP32C ? B.kp.value() : B.ph;
+        if constexpr (FP32C) {
+            r[0] = A.kx.value(); r[1] = A.ky.value(); r[2] = A.kz.value(); r[3] = A.kp.value();
+            r[4] = B.kx.value(); r[5] = B.ky.value(); r[6] = B.kz.value(); r[7] = B.kp.value();
 #pragma unroll
-        for (int i = 0; i < 8; ++i) r[i] = G * lanes_sum_d(r[i], T.TP);
+            for (int i = 0; i < 8; ++i) r[i] = G * lanes_sum_d(r[i], T.TP);
+        } else {
+            const double v[8] = {A.gx, A.gy, A.gz, A.ph, B.gx, B.gy, B.gz, B.ph};
+#pragma unroll
+            for (int h = 0; h < 8; h += 4) {
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) St.red[i][lane] = v[h + i];
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    double t = v[h + i];  // the lanes with phi = 0 use it
+                    for (int k = 1; k < T.P; ++k) t += St.red[i][min(lane + k * T.TP, 63)];
+                    r[h + i] = G * t;
+                }
+            }
+        }
         if (T.phi == 0) {
             for (int s = 0; s < 2; ++s) {
                 if (!(s ? T.vb : T.va)) continue;
