@@ -152,32 +152,65 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 
 __device__ __forceinline__ u64 lanemask_lt() { return (1ull << lane_id()) - 1ull; }
 
-__device__ __forceinline__ int wave_incl_scan(int v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int t = __shfl_up(v, d, 64);
-        if (lane >= d) v += t;
-    }
-    return v;
+// Scans and reductions over a full wave (all 64 lanes active) go through DPP operands of the vector
+// ALU: six short dependent steps, where __shfl's LDS permutes cost an LDS round trip each (the
+// one-wave walks do one scan a round and several reductions a group or tile).
+// Lanes without a source in a step keep `old`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ u32 dpp_move(u32 old, u32 v) {
+    return (u32)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
 }
+constexpr int DPP_SHR1 = 0x111, DPP_SHR2 = 0x112, DPP_SHR4 = 0x114, DPP_SHR8 = 0x118, DPP_BCAST15 = 0x142,
+              DPP_BCAST31 = 0x143;
 
+__device__ __forceinline__ int wave_incl_scan(int x) {
+    u32 v = (u32)x;
+    v += dpp_move<DPP_SHR1, 0xf>(0u, v);
+    v += dpp_move<DPP_SHR2, 0xf>(0u, v);
+    v += dpp_move<DPP_SHR4, 0xf>(0u, v);
+    v += dpp_move<DPP_SHR8, 0xf>(0u, v);
+    v += dpp_move<DPP_BCAST15, 0xa>(0u, v);  // rows 1 and 3 add the row before
+    v += dpp_move<DPP_BCAST31, 0xc>(0u, v);  // rows 2 and 3 add the first half
+    return (int)v;
+}
+// The last lane's value (an inclusive scan's total), in a scalar register.
+__device__ __forceinline__ int wave_last(int v) { return __builtin_amdgcn_readlane(v, 63); }
+
+// Reduction of 32-bit words by an idempotent op (a lane without a source combines with itself); the
+// result is in scalar registers.
+template <typename Op>
+__device__ __forceinline__ u32 wave_reduce_u32(u32 v, Op op) {
+    v = op(v, dpp_move<DPP_SHR1, 0xf>(v, v));
+    v = op(v, dpp_move<DPP_SHR2, 0xf>(v, v));
+    v = op(v, dpp_move<DPP_SHR4, 0xf>(v, v));
+    v = op(v, dpp_move<DPP_SHR8, 0xf>(v, v));
+    v = op(v, dpp_move<DPP_BCAST15, 0xa>(v, v));
+    v = op(v, dpp_move<DPP_BCAST31, 0xc>(v, v));
+    return (u32)__builtin_amdgcn_readlane((int)v, 63);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move_d(double v) {
+    const u64 b = (u64)__double_as_longlong(v);
+    const u32 lo = dpp_move<CTRL, ROWS>((u32)b, (u32)b), hi = dpp_move<CTRL, ROWS>((u32)(b >> 32), (u32)(b >> 32));
+    return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+}
+template <typename Op>
+__device__ __forceinline__ double wave_reduce_d(double v, Op op) {
+    v = op(v, dpp_move_d<DPP_SHR1, 0xf>(v));
+    v = op(v, dpp_move_d<DPP_SHR2, 0xf>(v));
+    v = op(v, dpp_move_d<DPP_SHR4, 0xf>(v));
+    v = op(v, dpp_move_d<DPP_SHR8, 0xf>(v));
+    v = op(v, dpp_move_d<DPP_BCAST15, 0xa>(v));
+    v = op(v, dpp_move_d<DPP_BCAST31, 0xc>(v));
+    const u64 b = (u64)__double_as_longlong(v);
+    const u32 lo = (u32)__builtin_amdgcn_readlane((int)(u32)b, 63), hi = (u32)__builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+}
 __device__ __forceinline__ double wave_min(double v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = fmin(v, __shfl_xor(v, d, 64));
-    return v;
+    return wave_reduce_d(v, [](double a, double b) { return fmin(a, b); });
 }
 __device__ __forceinline__ double wave_max(double v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = fmax(v, __shfl_xor(v, d, 64));
-    return v;
-}
-// A value every active lane holds (a wave reduction's result) moved to scalar registers, so
-// that it costs no vector registers where it is only read.
-__device__ __forceinline__ double uniform_d(double v) {
-    const u64 b = (u64)__double_as_longlong(v);
-    const u32 lo = __builtin_amdgcn_readfirstlane((u32)b), hi = __builtin_amdgcn_readfirstlane((u32)(b >> 32));
-    return __longlong_as_double((long long)(((u64)hi << 32) | lo));
+    return wave_reduce_d(v, [](double a, double b) { return fmax(a, b); });
 }
 
 // Sum over the 64/gsz lanes that serve one target (lanes t, t+gsz, ...), fixed order.

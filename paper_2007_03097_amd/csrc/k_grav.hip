@@ -274,7 +274,7 @@ __device__ void stage_leaves_put(int nleaf, int* leaves, Stage& St, const int4* 
             leaves[j] = st;
             St.loff[j] = carry + incl - c;
         }
-        carry += __shfl(incl, 63, 64);
+        carry += wave_last(incl);
     }
     __syncthreads();
     const int total = carry;
@@ -495,10 +495,6 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
         hi[0] = wave_max(fmax(T.va ? T.a.x : -INFINITY, T.vb ? T.b.x : -INFINITY));
         hi[1] = wave_max(fmax(T.va ? T.a.y : -INFINITY, T.vb ? T.b.y : -INFINITY));
         hi[2] = wave_max(fmax(T.va ? T.a.z : -INFINITY, T.vb ? T.b.z : -INFINITY));
-        for (int c = 0; c < 3; ++c) {  // the group box in scalar registers
-            lo[c] = uniform_d(lo[c]);
-            hi[c] = uniform_d(hi[c]);
-        }
         const double th2 = theta * theta;
         const u64 lt = lanemask_lt();
         TargetSums A, B;
@@ -554,7 +550,7 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
             nl += __popcll(bl);
             const int nch = kind == 3 ? tp.y : 0;
             const int incl = wave_incl_scan(nch);
-            const int tot = __shfl(incl, 63, 64);
+            const int tot = wave_last(incl);
             if (sp + tot > GW_STACK) {
                 if (lane == 0) set_err(ctl, ERR_GRAV_LIST);
                 break;
@@ -817,7 +813,7 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
             // initial pairs: (X_e+1, C) for every other child C of every ancestor X_e
             const int n0 = lane < D ? Pth.topo[lane].y - 1 : 0;
             const int incl = wave_incl_scan(n0);
-            int sp = __shfl(incl, 63, 64);
+            int sp = wave_last(incl);
             if (lane < D) {
                 const int4 t = Pth.topo[lane];
                 const int nxt = Pth.node[lane + 1];
@@ -891,7 +887,7 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
                 nl += __popcll(bl);
                 const int np = kind == 3 ? 1 : (kind == 4 ? ty.y : 0);
                 const int pin = wave_incl_scan(np);
-                const int tot = __shfl(pin, 63, 64);
+                const int tot = wave_last(pin);
                 if (sp + tot > FM_STACK) {
                     if (lane == 0) set_err(ctl, ERR_GRAV_LIST);
                     break;

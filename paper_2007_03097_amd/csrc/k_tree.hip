@@ -244,7 +244,7 @@ __global__ void __launch_bounds__(64) k_lsort_scan(DevCtl* ctl, int* hist) {
         const int v = t < ntiles ? hist[t * 24 + l] : 0;
         const int inc = wave_incl_scan(v);
         if (t < ntiles) hist[t * 24 + l] = carry + inc - v;
-        carry += __shfl(inc, 63, 64);
+        carry += wave_last(inc);
     }
 }
 

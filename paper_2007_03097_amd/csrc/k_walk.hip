@@ -99,10 +99,8 @@ __device__ __forceinline__ float screen_d(const float4& a, const float4& s) {
 // the bits of a non-negative float order as unsigned integers (a NaN above every number).
 __device__ __forceinline__ float tile_hmax(const float4* tile, int head, int tn) {
     const int lane = lane_id();
-    u32 v = lane < tn ? __float_as_uint(fabsf(tile[(head + lane) & (TILE_RING - 1)].w)) : 0u;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = max(v, (u32)__shfl_xor((int)v, d, 64));
-    return __uint_as_float(v);
+    const u32 v = lane < tn ? __float_as_uint(fabsf(tile[(head + lane) & (TILE_RING - 1)].w)) : 0u;
+    return __uint_as_float(wave_reduce_u32(v, [](u32 a, u32 b) { return max(a, b); }));
 }
 
 // The exact FP64 predicate for the pairs the screen left undecided (bit i = tile source i).
@@ -192,8 +190,9 @@ __device__ __forceinline__ void test_tile(int head, int tn, const float4* tile, 
         if (qb) resolve_exact(qb, pos4[gx + L.tp + TP], head, j0, tsrc, pos4, bb);
     }
     // union of the tile, bit j = ring entry head + j
-    u64 ub = (u64)(ba | bb) << j0;
-    for (int d = 1; d < 64; d <<= 1) ub |= __shfl_xor(ub, d, 64);
+    const u64 mine = (u64)(ba | bb) << j0;
+    auto either = [](u32 a, u32 b) { return a | b; };
+    const u64 ub = (u64)wave_reduce_u32((u32)mine, either) | ((u64)wave_reduce_u32((u32)(mine >> 32), either) << 32);
     if ((ub >> lane) & 1ull) {
         const int r = ucnt + __popcll(ub & lanemask_lt());
         if (r < ulim) myuni[r] = tsrc[(head + lane) & (TILE_RING - 1)];
@@ -231,7 +230,7 @@ __device__ void match_candidates(int nc, int* cand, int* coff, float4* tile, int
             cand[j] = st;
             coff[j] = carry + incl - c;
         }
-        carry += __shfl(incl, 63, 64);
+        carry += wave_last(incl);
     }
     if (lane == 0) coff[nc] = carry;
     __syncthreads();
@@ -371,7 +370,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
             nc += __popcll(bl);
             const int nch = (hit && !tp.w) ? tp.y : 0;
             const int incl = wave_incl_scan(nch);
-            const int tot = __shfl(incl, 63, 64);
+            const int tot = wave_last(incl);
             if (sp + tot > WALK_STACK) {
                 overflow = true;
                 break;
