@@ -213,6 +213,23 @@ __device__ __forceinline__ double wave_max(double v) {
     return wave_reduce_d(v, [](double a, double b) { return fmax(a, b); });
 }
 
+// Owner of each of 64 consecutive items p0 + lane of a concatenation whose parts start at the
+// ascending LDS offsets off[0 .. n): the last part that starts at or before the item.  `last` is the
+// owner of item p0 - 1 (-1 at the start; updated): no part is empty, so at most 64 parts start among
+// these items, the next ones after `last`, and an item's owner is `last` plus the starts up to it.
+// One LDS read in place of a binary search's eight dependent ones.
+__device__ __forceinline__ int tile_owner(const int* off, int n, int p0, int& last) {
+    const int lane = lane_id();
+    const int j = last + 1 + lane;
+    const int o = j < n ? off[j] - p0 : 64;
+    const u64 bit = o < 64 ? 1ull << o : 0ull;
+    auto either = [](u32 a, u32 b) { return a | b; };
+    const u64 starts = (u64)wave_reduce_u32((u32)bit, either) | ((u64)wave_reduce_u32((u32)(bit >> 32), either) << 32);
+    const int own = last + __popcll(starts & (lanemask_lt() | (1ull << lane)));
+    last += __popcll(starts);
+    return own;
+}
+
 // Sum over the 64/gsz lanes that serve one target (lanes t, t+gsz, ...), fixed order.
 __device__ __forceinline__ double lanes_sum_d(double v, int gsz) {
     for (int off = gsz; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);

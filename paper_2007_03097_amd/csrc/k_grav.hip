@@ -253,9 +253,9 @@ __device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C>& St, co
 // Particles of the listed leaves, concatenated and staged through LDS 64 at a time (one
 // load per lane per round): put(lane, position, mass, index) writes the staged record,
 // tile(tn) evaluates each staged tile of tn particles.  leaves[] is overwritten with the
-// leaves' first particles.
+// leaves' first particles.  Returns the number of particles.
 template <typename Stage, typename Tile, typename Put>
-__device__ void stage_leaves_put(int nleaf, int* leaves, Stage& St, const int4* __restrict__ topo,
+__device__ int stage_leaves_put(int nleaf, int* leaves, Stage& St, const int4* __restrict__ topo,
                                  const double4* __restrict__ pos4, const double* __restrict__ m, Tile&& tile,
                                  Put&& put) {
     const int lane = lane_id();
@@ -278,29 +278,26 @@ __device__ void stage_leaves_put(int nleaf, int* leaves, Stage& St, const int4* 
     }
     __syncthreads();
     const int total = carry;
+    int last = -1;
     for (int p0 = 0; p0 < total; p0 += 64) {
         const int p = p0 + lane;
         __syncthreads();
+        const int a = tile_owner(St.loff, nleaf, p0, last);
         if (p < total) {
-            int a = 0, b = nleaf - 1;
-            while (a < b) {  // largest j with loff[j] <= p
-                const int mid = (a + b + 1) >> 1;
-                if (St.loff[mid] <= p) a = mid;
-                else b = mid - 1;
-            }
             const int src = leaves[a] + (p - St.loff[a]);
             put(lane, pos4[src], m[src], src);
         }
         __syncthreads();
         tile(total - p0 < 64 ? total - p0 : 64);
     }
+    return total;
 }
 
 // stage_leaves_put with (x, y, z, m) records in FP64.
 template <typename Stage, typename Tile>
-__device__ void stage_leaves(int nleaf, int* leaves, Stage& St, const int4* __restrict__ topo,
+__device__ int stage_leaves(int nleaf, int* leaves, Stage& St, const int4* __restrict__ topo,
                              const double4* __restrict__ pos4, const double* __restrict__ m, Tile&& tile) {
-    stage_leaves_put(nleaf, leaves, St, topo, pos4, m, tile, [&](int lane, const double4& ps, double mass, int src) {
+    return stage_leaves_put(nleaf, leaves, St, topo, pos4, m, tile, [&](int lane, const double4& ps, double mass, int src) {
         St.part.pm[lane] = make_double4(ps.x, ps.y, ps.z, mass);
         St.part.src[lane] = src;
     });
@@ -308,9 +305,9 @@ __device__ void stage_leaves(int nleaf, int* leaves, Stage& St, const int4* __re
 
 // Leaves evaluated by softened particle sums (self excluded) for the lane's two targets.
 // With softening the self pair is evaluated like any other (it adds no force) and its
-// potential term -m_q/eps is taken out by the caller.
+// potential term -m_q/eps is taken out by the caller.  Returns the number of sources.
 template <bool FP32C>
-__device__ void eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const int4* __restrict__ topo,
+__device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const int4* __restrict__ topo,
                             const double4* __restrict__ pos4, const double* __restrict__ m, const GravTargets& T,
                             double e2, bool phi, TargetSums& A, TargetSums& B) {
     const bool any = T.va || T.vb;
@@ -334,7 +331,7 @@ __device__ void eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const 
                 }
             }
         };
-        stage_leaves_put(
+        return stage_leaves_put(
             nleaf, leaves, St, topo, pos4, m,
             [&](int tn) {
                 if (!any) return;
@@ -348,7 +345,6 @@ __device__ void eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const 
                                                 (float)mass);
                 St.partf.src[lane] = src;
             });
-        return;
     }
     auto run = [&](int tn, auto ph) {
         constexpr bool PH = decltype(ph)::value;
@@ -367,7 +363,7 @@ __device__ void eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const 
             }
         }
     };
-    stage_leaves(nleaf, leaves, St, topo, pos4, m, [&](int tn) {
+    return stage_leaves(nleaf, leaves, St, topo, pos4, m, [&](int tn) {
         if (!any) return;
         if (phi) run(tn, BoolC<true>());
         else run(tn, BoolC<false>());
@@ -405,21 +401,6 @@ __device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const int4* __re
     });
 }
 
-// Terms one flush of the lists evaluates: ncell cells and the particles of nleaf leaves, each
-// against the group's ng targets (leaves still unstaged), added to the group's running counts
-// (the same in every lane).  A group adds them to the pass's counters once, at its end: a
-// returnless atomic still holds the wave's next memory wait, and one per flush on two
-// addresses shared by the whole grid cost ~12% of the 4M-particle pass.
-__device__ __forceinline__ void count_terms(int ncell, int nleaf, const int* leaves, const int4* __restrict__ topo,
-                                            int ng, u64& cells, u64& pairs) {
-    u64 np = 0;
-    for (int i = lane_id(); i < nleaf; i += 64) np += (u64)topo[leaves[i]].y;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) np += __shfl_xor(np, d, 64);
-    cells += (u64)ncell * (u64)ng;
-    pairs += np * (u64)ng;
-}
-
 __global__ void k_zero_grav_counts(DevCtl* ctl) {
     const int s = threadIdx.x;
     if (s < GRAV_SLOTS) {
@@ -428,14 +409,20 @@ __global__ void k_zero_grav_counts(DevCtl* ctl) {
     }
 }
 
+// Evaluates the lists: ncell cells and the particles of nleaf leaves, each against the group's ng
+// targets, and adds these numbers of terms to the group's running counts (the same in every
+// lane).  A group adds them to the pass's counters once, at its end: a returnless atomic still
+// holds the wave's next memory wait, and one per flush on two addresses shared by the whole
+// grid cost ~12% of the 4M-particle pass.
 template <bool FP32C>
 __device__ void eval_lists(int ncell, int nleaf, const int* cells, int* leaves, GravStage<FP32C>& St,
                            const int4* __restrict__ topo, const double4* __restrict__ mom0,
                            const double4* __restrict__ mom1, const double4* __restrict__ mom2,
                            const double4* __restrict__ pos4, const double* __restrict__ m, const GravTargets& T,
-                           double eps, bool phi, TargetSums& A, TargetSums& B) {
+                           double eps, bool phi, TargetSums& A, TargetSums& B, int ng, u64& n_cells, u64& n_pairs) {
     eval_cells<FP32C>(ncell, cells, St, mom0, mom1, mom2, T, eps * eps, phi, A, B);
-    eval_leaves<FP32C>(nleaf, leaves, St, topo, pos4, m, T, eps * eps, phi, A, B);
+    n_cells += (u64)ncell * (u64)ng;
+    n_pairs += (u64)eval_leaves<FP32C>(nleaf, leaves, St, topo, pos4, m, T, eps * eps, phi, A, B) * (u64)ng;
 }
 
 template <bool FP32C>
@@ -510,8 +497,8 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
                 break;
             }
             if (nc + 64 > GW_CELLS || nl + 64 > GW_LEAVES) {
-                count_terms(nc, nl, leaves, topo, g.y, n_cells, n_pairs);
-                eval_lists<FP32C>(nc, nl, cells, leaves, St, topo, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B);
+                eval_lists<FP32C>(nc, nl, cells, leaves, St, topo, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B,
+                                  g.y, n_cells, n_pairs);
                 nc = nl = 0;
                 __syncthreads();
             }
@@ -560,8 +547,8 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
             __syncthreads();
         }
         __syncthreads();
-        count_terms(nc, nl, leaves, topo, g.y, n_cells, n_pairs);
-        eval_lists<FP32C>(nc, nl, cells, leaves, St, topo, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B);
+        eval_lists<FP32C>(nc, nl, cells, leaves, St, topo, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B,
+                                  g.y, n_cells, n_pairs);
         // per target: lanes tp + TP*phi combine in a fixed order
         double r[8];
         if constexpr (FP32C) {

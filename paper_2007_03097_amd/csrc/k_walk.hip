@@ -232,21 +232,16 @@ __device__ void match_candidates(int nc, int* cand, int* coff, float4* tile, int
         }
         carry += wave_last(incl);
     }
-    if (lane == 0) coff[nc] = carry;
     __syncthreads();
     const int total = carry;
+    int last = -1;
     for (int p0 = 0; p0 < total; p0 += 64) {
         const int p = p0 + lane;
         bool pass = false;
         int src = 0;
         double4 b = make_double4(0, 0, 0, 0);
+        const int a = tile_owner(coff, nc, p0, last);
         if (p < total) {
-            int a = 0, bb = nc - 1;
-            while (a < bb) {  // largest j with coff[j] <= p
-                const int mid = (a + bb + 1) >> 1;
-                if (coff[mid] <= p) a = mid;
-                else bb = mid - 1;
-            }
             src = cand[a] + (p - coff[a]);
             b = pos4[src];
             const double gx = fmax(0.0, fmax(b.x - gb.hi[0], gb.lo[0] - b.x));
@@ -284,7 +279,7 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
                                                   int* __restrict__ ucnt_out) {
     __shared__ int stack[WALK_STACK];
     __shared__ int cand[WALK_CAND];
-    __shared__ int coff[WALK_CAND + 1];
+    __shared__ int coff[WALK_CAND];
     __shared__ float4 tile[TILE_RING];
     __shared__ int tsrc[TILE_RING];
     const int lane = lane_id();
