@@ -127,7 +127,6 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
     const size_t NBR = N * (size_t)c->nbr_cap + 64;      // group blocks tile n * nbr_cap words
     const size_t CH = std::max(N / CHUNK, std::min(N, (size_t)SMALL_SET) / CHUNK_SMALL) + S + 1;
     const size_t SCB = (N + 1 + 2047) / 2048 + 16;
-    const size_t LST = (NC + 2047) / 2048 + 1;
     Carver cv{base};
     DevPtrs d{};
     d.ctl = cv.take<DevCtl>(1);
@@ -150,16 +149,12 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
     d.thrf = cv.take<float4>(N);
     d.lcp = cv.take<signed char>(N + 1);
     d.lvl = cv.take<unsigned char>(N);
-    d.scan_in = cv.take<u64>(N + 1);
-    d.scan_out = cv.take<u64>(N + 1);
+    d.tree_hist = cv.take<int>((size_t)tree_hist_words((int64_t)N));
     d.leaf_start = cv.take<int>(N + 1);
-    d.leaf_pre = cv.take<int>(N);
-    d.pre_level = cv.take<unsigned char>(NC);
-    d.pre_leaf = cv.take<unsigned char>(NC);
-    d.pre_start = cv.take<int>(NC);
-    d.pre_to_bfs = cv.take<int>(NC);
-    d.bfs_to_pre = cv.take<int>(NC);
-    d.lsort_hist = cv.take<int>(24 * LST);
+    d.leaf_node = cv.take<int>(N);
+    d.node_level = cv.take<unsigned char>(NC);
+    d.node_start = cv.take<int>(NC);
+    d.node_first = cv.take<int>(NC);
     d.topo = cv.take<int4>(NC);
     d.parent = cv.take<int>(NC);
     d.range = cv.take<int2>(NC);
@@ -169,9 +164,8 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
     d.mom1 = cv.take<double4>(NC);
     d.mom2 = cv.take<double4>(NC);
     d.group = cv.take<int4>(GC);
-    d.gflag = cv.take<u32>(N + 1);
-    d.gscan = cv.take<u32>(N + 1);
-    d.gsize = cv.take<u32>(N + 1);
+    d.gsize = cv.take<u32>(N);
+    d.gcount = cv.take<int>((size_t)group_hist_words((int64_t)N));
     d.nbr = cv.take<u16>(NBR);
     d.nbr_cnt = cv.take<int>(N);
     d.nbr_base = cv.take<int>(N);

@@ -83,16 +83,12 @@ struct DevPtrs {
     // tree
     signed char* lcp;             // n_cap + 1: shared leading digits with the previous key
     unsigned char* lvl;           // n_cap: leaf level of each sorted position
-    u64* scan_in;                 // n_cap + 1: (nodes at position << 32) | leaf start
-    u64* scan_out;                // n_cap + 1
+    int* tree_hist;               // tree_hist_words(n_cap): per-level node counts of the position tiles
     int* leaf_start;              // n_cap + 1 (sorted position of each leaf, then n)
-    int* leaf_pre;                // n_cap: pre-order node of each leaf
-    unsigned char* pre_level;     // node_cap (pre-order)
-    unsigned char* pre_leaf;      // node_cap
-    int* pre_start;               // node_cap
-    int* pre_to_bfs;              // node_cap
-    int* bfs_to_pre;              // node_cap
-    int* lsort_hist;              // 24 * lsort_tiles_cap
+    int* leaf_node;               // n_cap: breadth-first node of each leaf
+    unsigned char* node_level;    // node_cap (breadth-first, as all node arrays)
+    int* node_start;              // node_cap: first sorted position
+    int* node_first;              // node_cap: first child, or ~(number among the leaves)
     int4* topo;                   // node_cap: {first, count, level, is_leaf}
     int* parent;                  // node_cap
     int2* range;                  // node_cap: {start, count} in sorted order
@@ -103,9 +99,8 @@ struct DevPtrs {
     double4* mom2;                // node_cap: Ixy, Ixz, Iyz, cell (bits; node-node gravity only)
     // groups and neighbour lists
     int4* group;                  // group_cap: {start, count, segment root rank (-1 = root), 0}
-    u32* gflag;                   // n_cap + 1: 1 where a target group starts
-    u32* gscan;                   // n_cap + 1
-    u32* gsize;                   // n_cap + 1: size of the target group starting at a flagged position
+    u32* gsize;                   // n_cap: size of the target group starting at a position, else 0
+    int* gcount;                  // group_hist_words(n_cap): groups starting in each tile of positions
     u16* nbr;                     // n_cap * nbr_cap: list slots, indices into the group's union
     int* nbr_cnt;                 // n_cap
     int* nbr_base;                // n_cap: group whose lists hold the particle (-1 = none)
@@ -400,10 +395,10 @@ void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* 
                  const double* z, const double* vx, const double* vy, const double* vz, const double* m,
                  const double* h, const double* u, u64* keys_out_caller, int caller_order);
 void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie);
-void scan_u64(hipStream_t s, const u64* in, u64* out, int n, void* tmp);
-void scan_u32_total(hipStream_t s, const u32* in, u32* out, int n, void* tmp);
 void launch_gather_input(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out);
 // k_tree.hip
+int64_t tree_hist_words(int64_t n);
+int64_t group_hist_words(int64_t n);
 void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm);
 void launch_tree_export(hipStream_t s, const DevPtrs& d, const Dims& dm, u64* key, int32_t* level,
                         int32_t* leaf, int64_t* start, int64_t* count);

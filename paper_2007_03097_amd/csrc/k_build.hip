@@ -386,11 +386,9 @@ static void scan_impl(hipStream_t s, const T* in, T* out, int n, void* tmp, int 
 }
 
 // out[0..n) = exclusive scan, out[n] = total
-void scan_u64(hipStream_t s, const u64* in, u64* out, int n, void* tmp) { scan_impl<u64>(s, in, out, n, tmp, 1); }
 void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
     scan_impl<long long>(s, (const long long*)a, (long long*)a, n, tmp, 1);
 }
-void scan_u32_total(hipStream_t s, const u32* in, u32* out, int n, void* tmp) { scan_impl<u32>(s, in, out, n, tmp, 1); }
 
 // ---------------------------------------------------------------------------------------
 // Merge sort of (u64 key, u32 value), value = the input index: tiles of MS_TILE keys sorted in

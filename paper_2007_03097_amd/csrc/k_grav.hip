@@ -743,8 +743,8 @@ __device__ __forceinline__ void fmm_eval_terms(int nt, const int* tnode, const u
 }
 
 template <bool FP32C>
-__global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__ leaf_pre,
-                                            const int* __restrict__ pre_to_bfs, const int* __restrict__ parent,
+__global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__ leaf_node,
+                                            const int* __restrict__ parent,
                                             const int4* __restrict__ topo, const int2* __restrict__ range,
                                             const double4* __restrict__ mom0, const double* __restrict__ ncell,
                                             const double4* __restrict__ pos4, const double* __restrict__ m, double G,
@@ -766,7 +766,7 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
     int l0, l1, lstep;
     group_range(ctl->n_leaves, l0, l1, lstep);
     for (int li = l0; li < l1; li += lstep) {
-        const int L = pre_to_bfs[leaf_pre[li]];
+        const int L = leaf_node[li];
         const int4 tl = topo[L];
         const int D = tl.z;  // one set: the root is at level 0
         __syncthreads();
@@ -956,11 +956,11 @@ void launch_fmm(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, doub
     hipLaunchKernelGGL(k_fmm_cells, dim3(cg), dim3(256), 0, s, d.ctl, d.topo, d.range,
                        d.pos4, d.mom2);
     if (fp32c)
-        hipLaunchKernelGGL(k_fmm<true>, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.leaf_pre, d.pre_to_bfs, d.parent,
+        hipLaunchKernelGGL(k_fmm<true>, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.leaf_node, d.parent,
                            d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4, accumulate, gx, gy, gz, d.phi,
                            d.vel4, de);
     else
-        hipLaunchKernelGGL(k_fmm<false>, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.leaf_pre, d.pre_to_bfs,
-                           d.parent, d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4, accumulate, gx, gy, gz,
+        hipLaunchKernelGGL(k_fmm<false>, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.leaf_node, d.parent,
+                           d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4, accumulate, gx, gy, gz,
                            d.phi, d.vel4, de);
 }

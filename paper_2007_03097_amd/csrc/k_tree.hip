@@ -12,18 +12,34 @@
 //   lvl[i]   = level of the leaf holding i = 1 + min{v : the nearest boundaries with
 //              lcp <= v on both sides of i are at most leaf_size apart}, found in one
 //              pass over a window of lcp values in LDS (see window_level).
-//   position i starts the nodes of levels lcp[i]+1 .. lvl[i]; an exclusive scan of those
-//   counts numbers the nodes in pre-order.  A stable counting sort by level turns that
-//   into breadth-first order, where the children of a node are a contiguous run of the
-//   next level.  Leaves get their geometry and moments with the topology, internal nodes
-//   bottom-up from their children.
+//   position i starts the nodes of levels lcp[i]+1 .. lvl[i].  Breadth-first order is level by
+//   level, by position within a level, so a node's index is the number of nodes at lower levels
+//   plus the number of positions before it that start a node at its level: per-level counts
+//   of each tile of positions, one scan of them per level, and ballots within the tile.  The
+//   children of a node are then contiguous, the first one starting at the node's own position.
+//   Leaves get their geometry and moments with the topology, internal nodes bottom-up from their
+//   children.
 //   The largest nodes holding at most 4 * group_size particles form compact "group cells";
 //   each is split into target groups of at most group_size consecutive particles, so a
 //   group never spans two distant cells of the space-filling curve.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.h"
 
-constexpr int TB = 256;          // positions per block in the leaf-level kernel
 constexpr int MAX_WIN = 64;      // largest supported leaf_size
+// Positions per workgroup and tile of the kernels that number the nodes: few for small sets, which
+// would not fill the chip otherwise, more for larger ones, whose tile counts are then shorter.
+constexpr int TB_SMALL = 256, TB_LARGE = 1024;
+constexpr int TREE_ROWS = MAX_LEVEL + 2;  // counts of a tile: nodes at levels 0 .. 21, and leaves
+constexpr int GROUP_TILE = 1024;          // positions per group count
+
+int tree_tile(int64_t n) { return n <= (1 << 18) ? TB_SMALL : TB_LARGE; }
+int64_t tree_hist_words(int64_t n) {
+    const int64_t small = std::min<int64_t>(n, 1 << 18);
+    return TREE_ROWS * (std::max((n + TB_LARGE - 1) / TB_LARGE, (small + TB_SMALL - 1) / TB_SMALL) + 1);
+}
+int64_t group_hist_words(int64_t n) { return (n + GROUP_TILE - 1) / GROUP_TILE + 1; }
 
 // Level of the smallest cell around position ci that holds at most win particles:
 // 1 + min{v : the nearest boundaries with lcp <= v on both sides are at most win apart}.
@@ -32,6 +48,7 @@ constexpr int MAX_WIN = 64;      // largest supported leaf_size
 // minima only fall as t, k grow, so the smallest v is min over t of max(ML(t), MR(win - t)).
 // One branch-free pass; this thread's MR(k) sits at mr[(k - 1) * TB] in LDS (threads of a
 // wave write neighbouring bytes).
+template <int TB>
 __device__ __forceinline__ int window_level(const signed char* c, int ci, int win, signed char* mr) {
     int m = 127;
     for (int k = 1; k <= win; ++k) {
@@ -76,18 +93,33 @@ __device__ __forceinline__ int window_level_w(const signed char* c, int ci) {
     return L > MAX_LEVEL ? MAX_LEVEL : L;
 }
 
-// Per sorted position: lcp, leaf level (leaf capacity win) and the node / leaf-start counts
-// for the pre-order scan.  Also clears the per-level node counters (block 0) and the
-// group-cell flags of every position, which later kernels of the build fill in.  W > 0: the
-// leaf capacity is W (= win) and the window runs in registers; W = 0: any win, through LDS.
-template <int W>
+// Nodes per level (lane l < 22) and leaves (lane 22) that the wave's positions start, position
+// (c, L) starting one node at each of the levels c+1 .. L, the last one a leaf (none if L <= c).
+__device__ __forceinline__ int wave_level_counts(int c, int L) {
+    const int lane = lane_id();
+    int mine = 0;
+#pragma unroll
+    for (int l = 0; l <= MAX_LEVEL; ++l) {
+        const int k = __popcll(__ballot(c < l && l <= L));
+        if (lane == l) mine = k;
+    }
+    const int k = __popcll(__ballot(L > c));
+    return lane == MAX_LEVEL + 1 ? k : mine;
+}
+
+// Per sorted position: lcp and leaf level (leaf capacity win); per tile: nodes per level and
+// leaves, hist[row * (ntiles + 1) + tile].  Also clears what later kernels of the build count
+// into: the group sizes of every position and the group counts.  W > 0: the leaf capacity is
+// W (= win) and the window runs in registers; W = 0: any win, through LDS.
+template <int W, int TB>
 __global__ void __launch_bounds__(TB) k_leaf_levels(const u64* __restrict__ key, int n, int win, int min_level,
-                                                    signed char* lcp, unsigned char* lvl, u64* scan_in, DevCtl* ctl,
-                                                    u32* gflag) {
-    if (blockIdx.x == 0 && threadIdx.x < 24) ctl->level_count[threadIdx.x] = 0;
+                                                    signed char* lcp, unsigned char* lvl, int* hist, int ntiles,
+                                                    u32* gsize, int* gcount) {
     __shared__ signed char c[TB + 2 * MAX_WIN + 2];
     __shared__ signed char mrow[W > 0 ? 1 : TB * MAX_WIN];
+    __shared__ int wcnt[TB / 64][TREE_ROWS];
     const int b0 = blockIdx.x * TB;
+    if (threadIdx.x == 0 && b0 % GROUP_TILE == 0) gcount[b0 / GROUP_TILE] = 0;
     const int lo = b0 - win;                      // c[j] holds position lo + j
     const int cnt = TB + 2 * win + 1;
     for (int j = threadIdx.x; j < cnt; j += TB) {
@@ -98,207 +130,180 @@ __global__ void __launch_bounds__(TB) k_leaf_levels(const u64* __restrict__ key,
     }
     __syncthreads();
     const int i = b0 + threadIdx.x;
-    if (i >= n) return;
     const int ci = i - lo;
-    int L;
-    if constexpr (W > 0) L = window_level_w<W>(c, ci);
-    else L = window_level(c, ci, win, mrow + threadIdx.x);
-    if (L < min_level) L = min_level;
-    const int cc = c[ci];
-    const int nodes = L > cc ? L - cc : 0;
-    lcp[i] = (signed char)cc;
-    lvl[i] = (unsigned char)L;
-    scan_in[i] = ((u64)nodes << 32) | (u64)(nodes > 0 ? 1u : 0u);
-    gflag[i] = 0u;
-    if (i == n - 1) {
-        lcp[n] = -1;
-        gflag[n] = 0u;
+    int L = -1, cc = MAX_LEVEL;
+    if (i < n) {
+        if constexpr (W > 0) L = window_level_w<W>(c, ci);
+        else L = window_level<TB>(c, ci, win, mrow + threadIdx.x);
+        if (L < min_level) L = min_level;
+        cc = c[ci];
+        lcp[i] = (signed char)cc;
+        lvl[i] = (unsigned char)L;
+        gsize[i] = 0u;
+        if (i == n - 1) lcp[n] = -1;
+    }
+    const int mine = wave_level_counts(cc, L);
+    if (lane_id() < TREE_ROWS) wcnt[threadIdx.x >> 6][lane_id()] = mine;
+    __syncthreads();
+    if (threadIdx.x < TREE_ROWS) {
+        int t = 0;
+        for (int w = 0; w < TB / 64; ++w) t += wcnt[w][threadIdx.x];
+        hist[threadIdx.x * (ntiles + 1) + blockIdx.x] = t;
+    }
+}
+
+// Exclusive scan over a workgroup of up to 16 full waves; total gets the sum.
+__device__ __forceinline__ int block_scan(int v, int& total) {
+    __shared__ int wsum[16];
+    const int incl = wave_incl_scan(v), w = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+    if (lane_id() == 63) wsum[w] = incl;
+    __syncthreads();
+    int off = 0, tot = 0;
+    for (int k = 0; k < nw; ++k) {
+        if (k < w) off += wsum[k];
+        tot += wsum[k];
+    }
+    __syncthreads();
+    total = tot;
+    return off + incl - v;
+}
+
+// One workgroup per row: its tile counts become offsets, their total goes to the row's last word.
+__global__ void __launch_bounds__(1024) k_level_scan(int* hist, int ntiles) {
+    int* h = hist + (size_t)blockIdx.x * (ntiles + 1);
+    const int per = (ntiles + (int)blockDim.x - 1) / (int)blockDim.x;
+    const int a = min(ntiles, (int)threadIdx.x * per), e = min(ntiles, a + per);
+    int t = 0;
+    for (int k = a; k < e; ++k) t += h[k];
+    int total;
+    int off = block_scan(t, total);
+    for (int k = a; k < e; ++k) {
+        const int v = h[k];
+        h[k] = off;
+        off += v;
+    }
+    if (threadIdx.x == 0) h[ntiles] = total;
+}
+
+// Nodes in breadth-first order: level, first position, and the first child's index or, for a
+// leaf, ~(its number among the leaves); the leaf tables; the level table of the control block.
+// A tile's base index per level comes from the scanned counts, the rank within it from ballots.
+// Launch latency bounds the numbering of small sets and the leaf-level window that of large ones:
+// levels, counts and emission take 13 us at 4,096 particles and 34 us at 1M, where a pre-order
+// numbering (scan in two launches) sorted by level (three more) took 27 and 60 us.
+template <int TB>
+__global__ void __launch_bounds__(TB) k_emit_nodes(int n, const signed char* __restrict__ lcp,
+                                                   const unsigned char* __restrict__ lvl, const int* __restrict__ hist,
+                                                   int ntiles, unsigned char* node_level, int* node_start,
+                                                   int* node_first, int* leaf_start, int* leaf_node, DevCtl* ctl,
+                                                   int node_cap) {
+    __shared__ int base[TREE_ROWS];
+    __shared__ int wcnt[TB / 64][TREE_ROWS];
+    const int w = threadIdx.x >> 6, lane = lane_id();
+    const u64 lt = lanemask_lt();
+    const int i = blockIdx.x * TB + threadIdx.x;
+    int c = MAX_LEVEL, L = -1;
+    if (i < n) {
+        c = lcp[i];
+        L = lvl[i];
+    }
+    if (w == 0) {
+        const int* row = hist + (size_t)min(lane, TREE_ROWS - 1) * (ntiles + 1);
+        const int tot = lane < TREE_ROWS ? row[ntiles] : 0;
+        const int nodes = lane <= MAX_LEVEL ? tot : 0;
+        const int off = wave_incl_scan(nodes) - nodes;  // nodes at lower levels; all of them past the last
+        if (lane < TREE_ROWS) base[lane] = row[blockIdx.x] + (lane <= MAX_LEVEL ? off : 0);
+        if (blockIdx.x == 0) {
+            if (lane < 24) {
+                ctl->level_count[lane] = nodes;
+                ctl->level_off[lane] = off;
+            }
+            if (lane == TREE_ROWS - 1) {
+                ctl->n_nodes = off < node_cap ? off : node_cap;
+                ctl->n_leaves = tot;
+                leaf_start[tot] = n;
+                if (off > node_cap) set_err(ctl, ERR_NODE_CAP);
+            }
+        }
+    }
+    const int mine = wave_level_counts(c, L);
+    if (lane < TREE_ROWS) wcnt[w][lane] = mine;
+    __syncthreads();
+    if (threadIdx.x < TREE_ROWS) {
+        int t = base[threadIdx.x];
+        for (int k = 0; k < TB / 64; ++k) {
+            const int v = wcnt[k][threadIdx.x];
+            wcnt[k][threadIdx.x] = t;
+            t += v;
+        }
+    }
+    __syncthreads();
+    int prev = -1;
+    for (int l = 0; l <= MAX_LEVEL; ++l) {
+        const bool in = c < l && l <= L;
+        const u64 bal = __ballot(in);
+        if (!in) continue;
+        const int idx = wcnt[w][l] + __popcll(bal & lt);
+        if (idx < node_cap) {
+            node_level[idx] = (unsigned char)l;
+            node_start[idx] = i;
+        }
+        if (prev >= 0 && prev < node_cap) node_first[prev] = idx;
+        prev = idx;
+    }
+    const u64 bal = __ballot(L > c);
+    if (L > c) {
+        const int lf = wcnt[w][MAX_LEVEL + 1] + __popcll(bal & lt);
+        if (prev < node_cap) node_first[prev] = ~lf;
+        leaf_start[lf] = i;
+        leaf_node[lf] = prev;
     }
 }
 
 // Group cells: the largest nodes holding at most gcap particles (at or below min_level),
 // plus leaves that hold more (runs of equal keys).  They partition the sorted particles.
-// Each is cut into target groups of at most gsz consecutive particles: the first position
-// of every group is flagged and the group's size recorded there.
+// Each is cut into target groups of at most gsz consecutive particles: the group's size is
+// recorded at its first position, and the groups of each tile of positions are counted.
 __global__ void k_group_starts(const DevCtl* __restrict__ ctl, int gcap, int gsz, int min_level,
                                const int4* __restrict__ topo, const int* __restrict__ parent,
-                               const int2* __restrict__ range, u32* gflag, u32* gsize) {
+                               const int2* __restrict__ range, u32* gsize, int* gcount) {
     const int nn = ctl->n_nodes;
     for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < nn; b += gridDim.x * blockDim.x) {
         const int4 tp = topo[b];
-        const bool fits = range[b].y <= gcap && tp.z >= min_level;
-        if (!(fits || tp.w)) continue;
+        const int2 r = range[b];
         const int p = parent[b];
+        const bool fits = r.y <= gcap && tp.z >= min_level;
+        if (!(fits || tp.w)) continue;
         bool pfits = false;
         if (p >= 0) pfits = range[p].y <= gcap && topo[p].z >= min_level;
         if (pfits) continue;
-        const int2 r = range[b];
         const int e = r.x + r.y;
         for (int k = r.x; k < e; k += gsz) {
-            gflag[k] = 1u;
             gsize[k] = (u32)min(gsz, e - k);
+            atomicAdd(&gcount[k / GROUP_TILE], 1);
         }
     }
 }
 
-// Target groups in sorted order: group gscan[i] starts at each flagged position i.
-__global__ void k_emit_groups(int n, int batched, DevCtl* ctl, const u32* __restrict__ gflag,
-                              const u32* __restrict__ gscan, const u32* __restrict__ gsize,
-                              const u64* __restrict__ key, const int* __restrict__ seg_root_rank, int4* group) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) ctl->n_groups = (int)gscan[n];
-    if (i < n && gflag[i]) {
+// Target groups in sorted order; a tile's first group follows those of the tiles before it, which
+// the workgroup adds up itself.
+__global__ void __launch_bounds__(GROUP_TILE) k_emit_groups(int n, int batched, DevCtl* ctl,
+                                                            const u32* __restrict__ gsize,
+                                                            const int* __restrict__ gcount,
+                                                            const u64* __restrict__ key,
+                                                            const int* __restrict__ seg_root_rank, int4* group) {
+    const int i = blockIdx.x * GROUP_TILE + threadIdx.x;
+    const u32 sz = i < n ? gsize[i] : 0u;
+    int before = 0;
+    for (int t = threadIdx.x; t < (int)blockIdx.x; t += GROUP_TILE) before += gcount[t];
+    int first, own;
+    block_scan(before, first);
+    const int at = first + block_scan(sz ? 1 : 0, own);
+    if (sz) {
         const int rank = batched ? seg_root_rank[(int)((key[i] >> 54) & 511ull)] : -1;
-        group[gscan[i]] = make_int4(i, (int)gsize[i], rank, 0);
+        group[at] = make_int4(i, (int)sz, rank, 0);
     }
-}
-
-// Pre-order node records, leaf table and per-level node counts.  A grid-stride loop over
-// positions; the level counts are wave-aggregated into LDS and added to the global counts
-// once per workgroup, so the 24 global counters see few atomics.
-__global__ void __launch_bounds__(256) k_emit_nodes(int n, const signed char* __restrict__ lcp,
-                                                     const unsigned char* __restrict__ lvl,
-                                                     const u64* __restrict__ scan, unsigned char* pre_level,
-                                                     unsigned char* pre_leaf, int* pre_start, int* leaf_start,
-                                                     int* leaf_pre, DevCtl* ctl, int node_cap) {
-    __shared__ int hist[24];
-    if (threadIdx.x < 24) hist[threadIdx.x] = 0;
-    __syncthreads();
-    const u64 tot = scan[n];
-    const int n_nodes = (int)(tot >> 32), n_leaves = (int)(tot & 0xffffffffu);
-    const int stride = gridDim.x * blockDim.x;
-    for (int i0 = blockIdx.x * blockDim.x; i0 < n; i0 += stride) {
-        const int i = i0 + threadIdx.x;
-        int c = MAX_LEVEL, L = -1;
-        if (i < n) {
-            c = lcp[i];
-            L = lvl[i];
-        }
-        if (L > c) {
-            const u64 sv = scan[i];
-            const int base = (int)(sv >> 32), lf = (int)(sv & 0xffffffffu);
-            for (int l = c + 1; l <= L; ++l) {
-                const int idx = base + (l - c - 1);
-                if (idx < node_cap) {
-                    pre_level[idx] = (unsigned char)l;
-                    pre_leaf[idx] = (unsigned char)(l == L);
-                    pre_start[idx] = i;
-                }
-            }
-            leaf_start[lf] = i;
-            leaf_pre[lf] = base + (L - c - 1);
-        }
-        // nodes per level: position i starts one node at each level c+1 .. L
-        const u64 any = __ballot(L > c);
-        if (any) {
-            for (int l = 0; l <= MAX_LEVEL; ++l) {
-                const int k = __popcll(__ballot(c < l && l <= L));
-                if (k && lane_id() == 0) atomicAdd(&hist[l], k);
-            }
-        }
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        ctl->n_nodes = n_nodes < node_cap ? n_nodes : node_cap;
-        ctl->n_leaves = n_leaves;
-        leaf_start[n_leaves] = n;
-        if (n_nodes > node_cap) set_err(ctl, ERR_NODE_CAP);
-    }
-    __syncthreads();
-    if (threadIdx.x < 24 && hist[threadIdx.x]) atomicAdd(&ctl->level_count[threadIdx.x], hist[threadIdx.x]);
-}
-
-
-// Stable counting sort of pre-order nodes by level (2048-node tiles, 5-bit digit).
-constexpr int LS_THREADS = 256, LS_ITEMS = 8, LS_TILE = LS_THREADS * LS_ITEMS, LS_WAVES = LS_THREADS / 64;
-
-__global__ void __launch_bounds__(LS_THREADS) k_lsort_hist(const DevCtl* __restrict__ ctl,
-                                                          const unsigned char* __restrict__ pre_level, int* hist) {
-    __shared__ int h[24];
-    const int nn = ctl->n_nodes;
-    const int ntiles = (nn + LS_TILE - 1) / LS_TILE;
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        if (threadIdx.x < 24) h[threadIdx.x] = 0;
-        __syncthreads();
-        for (int r = 0; r < LS_ITEMS; ++r) {
-            const int i = tile * LS_TILE + r * LS_THREADS + threadIdx.x;
-            if (i < nn) atomicAdd(&h[pre_level[i]], 1);
-        }
-        __syncthreads();
-        if (threadIdx.x < 24) hist[tile * 24 + threadIdx.x] = h[threadIdx.x];
-        __syncthreads();
-    }
-}
-
-// One wave per level (24): the level's first breadth-first index (level_off, the prefix of
-// the level counts; written here for every later kernel), then the exclusive scan of that
-// level's tile counts offset by it.
-__global__ void __launch_bounds__(64) k_lsort_scan(DevCtl* ctl, int* hist) {
-    const int l = blockIdx.x;
-    const int nn = ctl->n_nodes;
-    const int ntiles = (nn + LS_TILE - 1) / LS_TILE;
-    int carry = 0;
-    for (int k = 0; k < l; ++k) carry += ctl->level_count[k];
-    if (lane_id() == 0) ctl->level_off[l] = carry;
-    for (int t0 = 0; t0 < ntiles; t0 += 64) {
-        const int t = t0 + lane_id();
-        const int v = t < ntiles ? hist[t * 24 + l] : 0;
-        const int inc = wave_incl_scan(v);
-        if (t < ntiles) hist[t * 24 + l] = carry + inc - v;
-        carry += wave_last(inc);
-    }
-}
-
-__global__ void __launch_bounds__(LS_THREADS) k_lsort_scatter(const DevCtl* __restrict__ ctl,
-                                                             const unsigned char* __restrict__ pre_level,
-                                                             const int* __restrict__ hist, int* pre_to_bfs,
-                                                             int* bfs_to_pre) {
-    __shared__ int wcnt[LS_WAVES][24];
-    __shared__ int woff[LS_WAVES][24];
-    const int nn = ctl->n_nodes;
-    const int ntiles = (nn + LS_TILE - 1) / LS_TILE;
-    const int w = threadIdx.x >> 6, lane = lane_id();
-    const u64 lt = lanemask_lt();
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        for (int j = threadIdx.x; j < LS_WAVES * 24; j += LS_THREADS) (&wcnt[0][0])[j] = 0;
-        __syncthreads();
-        const int base = tile * LS_TILE + w * (64 * LS_ITEMS) + lane;
-        int rank[LS_ITEMS], lev[LS_ITEMS];
-        for (int r = 0; r < LS_ITEMS; ++r) {
-            const int i = base + r * 64;
-            const bool ok = i < nn;
-            const int dg = ok ? pre_level[i] : 0;
-            lev[r] = dg;
-            u64 peers = __ballot(ok);
-#pragma unroll
-            for (int b = 0; b < 5; ++b) {
-                const bool bit = (dg >> b) & 1;
-                const u64 bb = __ballot(bit);
-                peers &= bit ? bb : ~bb;
-            }
-            const int before = ok ? wcnt[w][dg] : 0;
-            rank[r] = before + __popcll(peers & lt);
-            __builtin_amdgcn_wave_barrier();  // every lane has read its count before a leader updates it
-            if (ok && (peers & lt) == 0ull) wcnt[w][dg] = before + __popcll(peers);
-        }
-        __syncthreads();
-        if (threadIdx.x < 24) {
-            int acc = hist[tile * 24 + threadIdx.x];
-            for (int q = 0; q < LS_WAVES; ++q) {
-                woff[q][threadIdx.x] = acc;
-                acc += wcnt[q][threadIdx.x];
-            }
-        }
-        __syncthreads();
-        for (int r = 0; r < LS_ITEMS; ++r) {
-            const int i = base + r * 64;
-            if (i < nn) {
-                const int bfs = woff[w][lev[r]] + rank[r];
-                pre_to_bfs[i] = bfs;
-                bfs_to_pre[bfs] = i;
-            }
-        }
-        __syncthreads();
-    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) ctl->n_groups = first + own;
 }
 
 // ---- nodes in breadth-first order: eight lanes per node
@@ -461,42 +466,38 @@ __device__ __forceinline__ void internal_node(const NodeArgs& A, NodeSums& S, in
 // Topology of every node (leaf -> particle range; internal -> children range) and the leaves'
 // geometry and moments, whatever their level: the bottom-up kernels below then only combine
 // children.
-__global__ void __launch_bounds__(256) k_finalize(NodeArgs A, const unsigned char* __restrict__ pre_level,
-                                                   const unsigned char* __restrict__ pre_leaf,
-                                                   const int* __restrict__ pre_start, const int* __restrict__ pre_to_bfs,
-                                                   const int* __restrict__ bfs_to_pre, const signed char* __restrict__ lcp,
-                                                   const u64* __restrict__ scan, const int* __restrict__ leaf_start) {
+__global__ void __launch_bounds__(256) k_finalize(NodeArgs A, const unsigned char* __restrict__ node_level,
+                                                   const int* __restrict__ node_start, const int* __restrict__ node_first,
+                                                   const signed char* __restrict__ lcp,
+                                                   const int* __restrict__ leaf_start) {
     __shared__ NodeSums sums[256 / NODE_LANES];
     NodeSums& S = sums[threadIdx.x / NODE_LANES];
     const int nn = A.ctl->n_nodes;
     const int j = threadIdx.x & (NODE_LANES - 1);
     const int stride = gridDim.x * (blockDim.x / NODE_LANES);
     for (int b = blockIdx.x * (blockDim.x / NODE_LANES) + threadIdx.x / NODE_LANES; b < nn; b += stride) {
-        const int pre = bfs_to_pre[b];
-        const int l = pre_level[pre], s = pre_start[pre];
+        const int l = node_level[b], s = node_start[b], f = node_first[b];
         if (b == 0 && j == 0) A.parent[0] = -1;
-        if (pre_leaf[pre]) {
-            const int lf = (int)(scan[s] & 0xffffffffu);
-            const int cnt = leaf_start[lf + 1] - s;
+        if (f < 0) {
+            const int cnt = leaf_start[~f + 1] - s;
             if (j == 0) {
                 A.topo[b] = make_int4(s, cnt, l, 1);
                 A.range[b] = make_int2(s, cnt);
             }
             leaf_node(A, S, b, s, cnt, node_side(A, s, l), j);
-        } else if (pre + 1 >= nn) {  // only with a truncated (over-capacity) tree
+        } else if (f >= nn) {  // only with a truncated (over-capacity) tree
             if (j == 0) {
                 A.topo[b] = make_int4(s, 0, l, 1);
                 A.range[b] = make_int2(s, 0);
             }
             leaf_node(A, S, b, s, 0, node_side(A, s, l), j);
         } else {
-            const int fc = pre_to_bfs[pre + 1];
-            const int end = A.ctl->level_off[l + 1] + A.ctl->level_count[l + 1];
-            const bool child = j == 0 || (fc + j < end && lcp[pre_start[bfs_to_pre[fc + j]]] >= l);
+            const int end = min(nn, A.ctl->level_off[l + 1] + A.ctl->level_count[l + 1]);
+            const bool child = j == 0 || (f + j < end && lcp[node_start[f + j]] >= l);
             const u32 mask = (u32)(__ballot(child) >> (lane_id() & ~(NODE_LANES - 1))) & 0xffu;
             const int nc = __ffs((int)~mask) - 1;  // children are the leading run (1 .. 8)
-            if (j < nc) A.parent[fc + j] = b;
-            if (j == 0) A.topo[b] = make_int4(fc, nc, l, 0);
+            if (j < nc) A.parent[f + j] = b;
+            if (j == 0) A.topo[b] = make_int4(f, nc, l, 0);
         }
     }
 }
@@ -601,43 +602,45 @@ static int grid_cap(int n, int bs, int cap) {
 void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     const int n = dm.n;
     if (n <= 0) return;
-    auto levels = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((n + TB - 1) / TB), dim3(TB), 0, s, d.key_a, n, dm.leaf_size, dm.min_level, d.lcp,
-                           d.lvl, d.scan_in, d.ctl, d.gflag);
+    const int tb = tree_tile(n), ntiles = (n + tb - 1) / tb;
+    auto run = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(ntiles), dim3(tb), 0, s, d.key_a, n, dm.leaf_size, dm.min_level, d.lcp, d.lvl,
+                           d.tree_hist, ntiles, d.gsize, d.gcount);
+    };
+    auto levels = [&](auto w) {
+        if (tb == TB_SMALL) run(k_leaf_levels<decltype(w)::value, TB_SMALL>);
+        else run(k_leaf_levels<decltype(w)::value, TB_LARGE>);
     };
     switch (dm.leaf_size) {  // the autotuner's leaf sizes and the node-node scheme's 64
-        case 8: levels(k_leaf_levels<8>); break;
-        case 12: levels(k_leaf_levels<12>); break;
-        case 16: levels(k_leaf_levels<16>); break;
-        case 24: levels(k_leaf_levels<24>); break;
-        case 32: levels(k_leaf_levels<32>); break;
-        case 64: levels(k_leaf_levels<64>); break;
-        default: levels(k_leaf_levels<0>); break;
+        case 8: levels(std::integral_constant<int, 8>()); break;
+        case 12: levels(std::integral_constant<int, 12>()); break;
+        case 16: levels(std::integral_constant<int, 16>()); break;
+        case 24: levels(std::integral_constant<int, 24>()); break;
+        case 32: levels(std::integral_constant<int, 32>()); break;
+        case 64: levels(std::integral_constant<int, 64>()); break;
+        default: levels(std::integral_constant<int, 0>()); break;
     }
-    scan_u64(s, d.scan_in, d.scan_out, n, d.scan_tmp);
-    hipLaunchKernelGGL(k_emit_nodes, dim3(grid_cap(n, 256, 512)), dim3(256), 0, s, n, d.lcp, d.lvl, d.scan_out,
-                       d.pre_level, d.pre_leaf, d.pre_start, d.leaf_start, d.leaf_pre, d.ctl, dm.node_cap);
-    const int tiles_cap = grid_cap(dm.node_cap, LS_TILE, 1024);
-    hipLaunchKernelGGL(k_lsort_hist, dim3(tiles_cap), dim3(LS_THREADS), 0, s, d.ctl, d.pre_level, d.lsort_hist);
-    hipLaunchKernelGGL(k_lsort_scan, dim3(24), dim3(64), 0, s, d.ctl, d.lsort_hist);
-    hipLaunchKernelGGL(k_lsort_scatter, dim3(tiles_cap), dim3(LS_THREADS), 0, s, d.ctl, d.pre_level, d.lsort_hist,
-                       d.pre_to_bfs, d.bfs_to_pre);
+    hipLaunchKernelGGL(k_level_scan, dim3(TREE_ROWS), dim3(ntiles <= 1024 ? 256 : 1024), 0, s, d.tree_hist, ntiles);
+    auto emit = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(ntiles), dim3(tb), 0, s, n, d.lcp, d.lvl, d.tree_hist, ntiles, d.node_level,
+                           d.node_start, d.node_first, d.leaf_start, d.leaf_node, d.ctl, dm.node_cap);
+    };
+    if (tb == TB_SMALL) emit(k_emit_nodes<TB_SMALL>);
+    else emit(k_emit_nodes<TB_LARGE>);
     const NodeArgs A{d.ctl, dm.batched, dm.mass_moments, d.key_a, d.topo, d.parent, d.pos4, d.m,
                      d.nbox_lo, d.nbox_hi, d.mom0, d.mom1, d.mom2, d.range};
     // about 4 n / leaf_size nodes of eight lanes; the kernel loops over any beyond that
     hipLaunchKernelGGL(k_finalize, dim3(grid_cap(4 * (n / dm.leaf_size) + 64, 256 / NODE_LANES, 8192)), dim3(256), 0, s,
-                       A, d.pre_level, d.pre_leaf, d.pre_start, d.pre_to_bfs, d.bfs_to_pre, d.lcp, d.scan_out,
-                       d.leaf_start);
+                       A, d.node_level, d.node_start, d.node_first, d.lcp, d.leaf_start);
     hipLaunchKernelGGL(k_subtree_moments, dim3(grid_cap(n, 16, 2048)), dim3(SUB_THREADS), 0, s, A);
     hipLaunchKernelGGL(k_top_moments, dim3(1), dim3(1024), 0, s, A);
     // target groups: cells of at most 4 * group_size particles, cut into runs of group_size
     const int gcap = 4 * dm.group_size;
     const int g = grid_cap(dm.node_cap, 256, 2048);
     hipLaunchKernelGGL(k_group_starts, dim3(g), dim3(256), 0, s, d.ctl, gcap, dm.group_size, dm.min_level, d.topo,
-                       d.parent, d.range, d.gflag, d.gsize);
-    scan_u32_total(s, d.gflag, d.gscan, n, d.scan_tmp);
-    hipLaunchKernelGGL(k_emit_groups, dim3((n + 255) / 256), dim3(256), 0, s, n, dm.batched, d.ctl, d.gflag, d.gscan,
-                       d.gsize, d.key_a, d.seg_root_rank, d.group);
+                       d.parent, d.range, d.gsize, d.gcount);
+    hipLaunchKernelGGL(k_emit_groups, dim3((n + GROUP_TILE - 1) / GROUP_TILE), dim3(GROUP_TILE), 0, s, n, dm.batched,
+                       d.ctl, d.gsize, d.gcount, d.key_a, d.seg_root_rank, d.group);
 }
 
 // Export (test path): node keys etc. in breadth-first order.

@@ -4,7 +4,7 @@ import pytest
 
 from workloads import polytrope_n1, uniform_random
 
-from gpu_helpers import gpu_gravity, gpu_keys_order, gpu_neighbors, make_ctx, parts, to_np
+from gpu_helpers import gpu_gravity, gpu_keys_order, gpu_neighbors, gpu_tree, make_ctx, parts, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -124,3 +124,29 @@ def test_csr_lists_of_any_length(orc, n, h, group):
     assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
     longest = np.diff(off).max()
     assert longest == n if h == 0.9 else longest > 64
+
+
+# ---------------------------------------------------------------------------- octree numbering
+@pytest.mark.parametrize("n,leaf", [(255, 1), (256, 8), (257, 16), (1023, 13), (1024, 32), (1025, 64), (4097, 5),
+                                    (262144, 24), (262145, 13), (264193, 32)])   # tiles of 256 and of 1,024 positions
+def test_octree_at_tile_edges(orc, n, leaf):
+    ps = uniform_random(n, seed=71)
+    ps.x[: n // 3] *= 0.01     # deep and shallow parts
+    ctx = make_ctx(n, leaf_size=leaf)
+    k, o = gpu_keys_order(ctx, parts(ps))
+    t, g = orc.octree(k[o], leaf), gpu_tree(ctx)
+    for f in ("key", "level", "leaf", "start", "count"):
+        a = np.lexsort((t["start"], t["level"]))
+        assert np.array_equal(np.asarray(t[f])[a], g[f]), f   # breadth-first: by level, then position
+
+
+@pytest.mark.parametrize("n", [1023, 1025, 2049])
+def test_groups_at_tile_edges(orc, n):
+    """Target groups that start and end around the group tiles: every particle in one group."""
+    ps = uniform_random(n, seed=72, h=(0.02, 0.06))
+    for group in (8, 64):
+        ctx = make_ctx(n, group_size=group, nbr_capacity=512)
+        gpu_keys_order(ctx, parts(ps))
+        off, idx = gpu_neighbors(ctx, n)
+        ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+        assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
