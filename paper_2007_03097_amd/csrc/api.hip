@@ -367,9 +367,8 @@ static sph_status build_from_caller(sph_ctx* c, const sph_particles* p, const do
         launch_set_box(c->stream, d, dm, 0);
     }
     launch_keys(c->stream, d, dm, p->x, p->y, p->z, p->vx, p->vy, p->vz, p->m, p->h, p->u, (u64*)keys_out, 1);
-    sort_keys(c->stream, d, dm.n, nullptr);  // equal keys by caller index
-    launch_gather_input(c->stream, d, dm, p->u, order_out);
-    build_octree(c->stream, d, dm);
+    sort_caller_keys(c->stream, d, dm.n);
+    build_input_tree(c->stream, d, dm, p->u, order_out);
     HIPCHK(c, hipGetLastError());
     c->tree_ok = true;
     return SPH_OK;
@@ -629,13 +628,10 @@ static void accel_pass(sph_ctx* c, hipStream_t s, const DevPtrs& d, const double
 static void step_launches(sph_ctx* c, hipStream_t s, int p, bool later) {
     const DevPtrs& a = c->d[p];
     const DevPtrs& b = c->d[1 - p];
-    const int n = c->dm.n;
-    if (!later) launch_box_init(s, a, c->dm);  // later steps: the previous permute reset the box
+    if (!later) launch_box_init(s, a, c->dm);  // later steps: the previous move reset the box
     launch_kick_drift(s, a, c->dm, later, c->cfg.adaptive_h);  // also merges the new box
-    launch_step_keys(s, a, c->dm);        // also derives L and S
-    sort_keys(s, a, n, a.id);             // equal keys by particle ID
-    launch_step_permute(s, a, n);         // also writes the pair records
-    build_octree(s, b, c->dm);
+    sort_step_keys(s, a, c->dm);          // also derives L and S
+    build_step_tree(s, a, b, c->dm);      // moves the state and writes the pair records on the way
     accel_pass(c, s, b, b.up, c->cfg.energy_form == SPH_ENERGY_THERMOKINETIC);
 }
 

@@ -394,12 +394,15 @@ void launch_set_box(hipStream_t s, const DevPtrs& d, const Dims& dm, int from_ho
 void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
                  const double* z, const double* vx, const double* vy, const double* vz, const double* m,
                  const double* h, const double* u, u64* keys_out_caller, int caller_order);
-void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie);
-void launch_gather_input(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out);
+void sort_caller_keys(hipStream_t s, const DevPtrs& d, int n);
+void sort_step_keys(hipStream_t s, const DevPtrs& d, const Dims& dm);
 // k_tree.hip
 int64_t tree_hist_words(int64_t n);
 int64_t group_hist_words(int64_t n);
-void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm);
+// after sort_caller_keys: snapshot of the caller's particles in key order, octree and groups
+void build_input_tree(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out);
+// after sort_step_keys: the resident state moves from set a to set b = swapped(a), octree and groups
+void build_step_tree(hipStream_t s, const DevPtrs& a, const DevPtrs& b, const Dims& dm);
 void launch_tree_export(hipStream_t s, const DevPtrs& d, const Dims& dm, u64* key, int32_t* level,
                         int32_t* leaf, int64_t* start, int64_t* count);
 // k_walk.hip
@@ -430,8 +433,6 @@ void launch_fill_zero(hipStream_t s, int n, double* dst);
 void launch_gather_caller(hipStream_t s, const DevPtrs& d, int n, const double* src_caller, double* dst);
 void launch_box_init(hipStream_t s, const DevPtrs& d, const Dims& dm);
 void launch_kick_drift(hipStream_t s, const DevPtrs& d, const Dims& dm, bool pre_kick, int adaptive_h);
-void launch_step_keys(hipStream_t s, const DevPtrs& d, const Dims& dm);
-void launch_step_permute(hipStream_t s, const DevPtrs& d, int n);
 void launch_kick(hipStream_t s, const DevPtrs& d, const Dims& dm, int adaptive_h);
 void launch_set_hnext(hipStream_t s, const DevPtrs& d, int n);
 void launch_diag(hipStream_t s, const DevPtrs& d, const Dims& dm, int with_phi, int kinetic_in_u, double eps_grav);

@@ -5,7 +5,6 @@
 //                Hilbert index, sentinel bit 63, segment number in bits 54..62 for
 //                segmented sets
 //  * merge sort  (key, value) with ties by particle ID: the (key, ID) order of the paper
-//  * gather      caller-order input -> key-ordered SoA + AoS records
 #include <utility>
 
 #include "common.h"
@@ -175,8 +174,8 @@ __device__ __forceinline__ u64 make_key(double x, double y, double z, const doub
 }
 
 // Caller-order keys + input validation.  Each particle is also written as one 64-byte record
-// (x, y, z, h), (vx, vy, vz, m) in caller order, from which k_gather_input reads it: a gather of
-// one line per particle and u instead of nine (see there).
+// (x, y, z, h), (vx, vy, vz, m) in caller order, from which the gather into key order reads it: one
+// line per particle and u instead of nine (InputMove in k_tree.hip).
 __global__ void __launch_bounds__(256) k_keys(DevCtl* ctl, const int4* chunk, int batched, int curve,
                                                const double* __restrict__ x, const double* __restrict__ y,
                                                const double* __restrict__ z, const double* __restrict__ vx,
@@ -211,9 +210,9 @@ void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* 
 }
 
 // Step-loop keys, in the previous key order, which the sort takes as it is (it orders equal
-// keys by ID itself): nearly sorted input, and no scatter to the caller's order.
-// (the positions, velocities and energies it keys were checked for non-finite values by the
-// kick-drift that wrote them)
+// keys by ID itself): nearly sorted input, and no scatter to the caller's order.  The positions
+// were checked for non-finite values by the kick-drift that wrote them.  (Made in the sort's tile
+// kernel instead, the keys of 4,096 particles keep one CU busy for 7 us, against 3 us for this launch.)
 __global__ void __launch_bounds__(256) k_step_keys(DevCtl* ctl, const int4* chunk, int batched, int curve,
                                                     const double* __restrict__ x, const double* __restrict__ y,
                                                     const double* __restrict__ z, u64* key) {
@@ -236,16 +235,14 @@ __global__ void __launch_bounds__(256) k_step_keys(DevCtl* ctl, const int4* chun
             ctl->side[ch.z] = L;
         }
     }
-    for (int p = ch.x + threadIdx.x; p < ch.y; p += blockDim.x) {
-        const double px = x[p], py = y[p], pz = z[p];
-        key[p] = make_key(px, py, pz, box, S, ch.z, batched, curve);
-    }
+    for (int p = ch.x + threadIdx.x; p < ch.y; p += blockDim.x)
+        key[p] = make_key(x[p], y[p], z[p], box, S, ch.z, batched, curve);
 }
 
-void launch_step_keys(hipStream_t s, const DevPtrs& d, const Dims& dm) {
+static void launch_step_keys(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     if (dm.n_chunks > 0)
-        hipLaunchKernelGGL(k_step_keys, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, dm.curve, d.x, d.y,
-                           d.z, d.key_a);
+        hipLaunchKernelGGL(k_step_keys, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, dm.curve, d.x,
+                           d.y, d.z, d.key_a);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -392,7 +389,7 @@ void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
 
 // ---------------------------------------------------------------------------------------
 // Merge sort of (u64 key, u32 value), value = the input index: tiles of MS_TILE keys sorted in
-// LDS by one workgroup each (three resident per CU), then 2-way merge passes over runs that double (merge path: every
+// LDS by one workgroup each (two resident per CU), then 2-way merge passes over runs that double (merge path: every
 // workgroup finds where its MS_OUT outputs start in both runs and merges them in LDS).
 //
 // Equal keys are ordered by `tie[value]` (the particle ID; tie == nullptr: the value itself), in
@@ -402,11 +399,12 @@ void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
 //
 // What bounds it: launches for small sets; LDS reads in the tiles, memory in the passes for
 // large ones.  Measured per sort against an LSD radix sort of 8-bit digits (8 passes of three
-// kernels at any size, for 63 key bits): 4,096 keys 134 -> 16-22 us, 123K 144 -> 69 us, 1M 183 ->
-// 116 us (a pass 10 us, 2.3 TB/s; the tiles 34 us), 4M 400 -> 375 us (a pass 29 us, 3.5 TB/s).
-// Tiles of 8,192 keys (one resident workgroup) save a pass and lose as much: 47 us at 1M.
-constexpr int MS_ITEMS = 8, MS_THREADS = 512, MS_TILE = MS_THREADS * MS_ITEMS;
-constexpr int MM_THREADS = 256, MS_OUT = MM_THREADS * MS_ITEMS;
+// kernels at any size, for 63 key bits): 4,096 keys 134 -> 15-21 us, 123K 144 -> 59 us, 1M 183 ->
+// 101 us (a pass 8.9 us, 2.7 TB/s; the tiles 30 us), 4M 400 -> 365 us (a pass 28 us, 3.6 TB/s).
+// Tiles of 8,192 keys save a pass and lose as much (47 us at 1M); 8 keys a thread instead of 4
+// leave fewer waves to hide the LDS latency (tiles 34 us, a pass 10.3 us at 1M).
+constexpr int MS_ITEMS = 4, MS_THREADS = 1024, MS_TILE = MS_THREADS * MS_ITEMS;
+constexpr int MM_ITEMS = 4, MM_THREADS = 512, MS_OUT = MM_THREADS * MM_ITEMS;
 constexpr u32 MS_PAD = 0xffffffffu;  // value of a filler entry past the end of the last tile
 
 // Slot of item i in LDS: one spare slot after every 8 items, so that the lanes of a wave, whose
@@ -421,16 +419,16 @@ __device__ __forceinline__ bool ms_tie_less(u32 va, u32 vb, const u32* __restric
     else return va < vb;
 }
 
-// Merges MS_ITEMS outputs of the sorted runs A = [a, ae) and B = [b, be) of LDS items, from the
+// Merges ITEMS outputs of the sorted runs A = [a, ae) and B = [b, be) of LDS items, from the
 // split (a, b) on.  One LDS read per output and no branch on which run it comes from; the read
 // past a run's end is in bounds (the arrays have a spare slot) and unused.
-template <bool TIE>
+template <int ITEMS, bool TIE>
 __device__ __forceinline__ void ms_merge_items(const u64* sk, const u32* sv, int a, int ae, int b, int be,
                                                const u32* __restrict__ tie, u64* k, u32* v) {
     u64 ka = sk[ms_slot(a)], kb = sk[ms_slot(b)];
     u32 va = sv[ms_slot(a)], vb = sv[ms_slot(b)];
 #pragma unroll
-    for (int r = 0; r < MS_ITEMS; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         bool b_less = kb < ka;
         if (kb == ka && a < ae && b < be) b_less = ms_tie_less<TIE>(vb, va, tie);
         const bool from_a = a < ae && (b >= be || !b_less);
@@ -466,23 +464,30 @@ __device__ __forceinline__ int ms_split(const u64* sk, const u32* sv, int a0, in
     return lo;
 }
 
-// One tile: every thread sorts 8 keys in registers, then runs of 8, 16, ... merge in LDS.
+// One tile: every thread sorts MS_ITEMS keys in registers, then runs of that size merge in LDS.
 template <bool TIE>
-__global__ void __launch_bounds__(MS_THREADS) k_ms_tile(const u64* kin, u64* kout, u32* vout, int n,
+__global__ void __launch_bounds__(MS_THREADS) k_ms_tile(const u64* key, u64* kout, u32* vout, int n,
                                                         const u32* __restrict__ tie) {
     __shared__ u64 sk[MS_TILE + MS_TILE / 8 + 1];
     __shared__ u32 sv[MS_TILE + MS_TILE / 8 + 1];
     const int t0 = blockIdx.x * MS_TILE;
     const int cnt = n - t0 < MS_TILE ? n - t0 : MS_TILE;
     const int i0 = threadIdx.x * MS_ITEMS;
+#pragma unroll
+    for (int r = 0; r < MS_ITEMS; ++r) {  // consecutive lanes read consecutive keys
+        const int i = r * MS_THREADS + threadIdx.x;
+        if (i < cnt) sk[ms_slot(i)] = key[t0 + i];
+    }
+    __syncthreads();
     u64 k[MS_ITEMS];
     u32 v[MS_ITEMS];
 #pragma unroll
     for (int r = 0; r < MS_ITEMS; ++r) {
         const bool ok = i0 + r < cnt;
-        k[r] = ok ? kin[t0 + i0 + r] : ~0ull;
+        k[r] = ok ? sk[ms_slot(i0 + r)] : ~0ull;
         v[r] = ok ? (u32)(t0 + i0 + r) : MS_PAD;
     }
+    __syncthreads();
     if (i0 < cnt) {
 #pragma unroll
         for (int s = 0; s < MS_ITEMS; ++s) {  // odd-even transposition network
@@ -519,7 +524,7 @@ __global__ void __launch_bounds__(MS_THREADS) k_ms_tile(const u64* kin, u64* kou
             const bool stays = b0 == e || (in_a ? k[MS_ITEMS - 1] < sk[ms_slot(b0)] : sk[ms_slot(b0 - 1)] < k[0]);
             if (!stays) {
                 const int a = ms_split<TIE>(sk, sv, a0, b0 - a0, b0, e - b0, d, tie);
-                ms_merge_items<TIE>(sk, sv, a0 + a, b0, b0 + d - a, e, tie, k, v);
+                ms_merge_items<MS_ITEMS, TIE>(sk, sv, a0 + a, b0, b0 + d - a, e, tie, k, v);
             }
         }
         __syncthreads();
@@ -603,17 +608,17 @@ __global__ void __launch_bounds__(MM_THREADS) k_ms_merge(const u64* __restrict__
         sv[ms_slot(i)] = A ? va[i] : vb[i - ca];
     }
     __syncthreads();
-    const int i0 = threadIdx.x * MS_ITEMS;
-    u64 k[MS_ITEMS];
-    u32 v[MS_ITEMS];
+    const int i0 = threadIdx.x * MM_ITEMS;
+    u64 k[MM_ITEMS];
+    u32 v[MM_ITEMS];
     if (i0 < on) {
         const int a = ms_split<TIE>(sk, sv, 0, ca, ca, cb, i0, tie);
-        ms_merge_items<TIE>(sk, sv, a, ca, ca + i0 - a, on, tie, k, v);
+        ms_merge_items<MM_ITEMS, TIE>(sk, sv, a, ca, ca + i0 - a, on, tie, k, v);
     }
     __syncthreads();
     if (i0 < on) {
 #pragma unroll
-        for (int r = 0; r < MS_ITEMS; ++r) {
+        for (int r = 0; r < MM_ITEMS; ++r) {
             if (i0 + r < on) {
                 sk[ms_slot(i0 + r)] = k[r];
                 sv[ms_slot(i0 + r)] = v[r];
@@ -629,7 +634,8 @@ __global__ void __launch_bounds__(MM_THREADS) k_ms_merge(const u64* __restrict__
 
 // Sorts key_a (any order) into key_a, with the input index of each sorted key in val_a.
 template <bool TIE>
-static void sort_keys_impl(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
+static void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
+    if (n <= 0) return;
     int passes = 0;
     for (long long run = MS_TILE; run < n; run *= 2) ++passes;
     // the tile sort starts in the buffer from which the passes end in _a
@@ -646,37 +652,11 @@ static void sort_keys_impl(hipStream_t s, const DevPtrs& d, int n, const u32* ti
     }
 }
 
-void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
-    if (n <= 0) return;
-    if (tie) sort_keys_impl<true>(s, d, n, tie);
-    else sort_keys_impl<false>(s, d, n, nullptr);
-}
+// The keys in key_a, in caller order: equal keys by index.
+void sort_caller_keys(hipStream_t s, const DevPtrs& d, int n) { sort_keys<false>(s, d, n, nullptr); }
 
-// ---------------------------------------------------------------------------------------
-// Caller-order input -> key-ordered snapshot.  The caller's order is arbitrary: gathered array by
-// array, every 8-byte read costs a line, and the records of k_keys cost one line for eight of
-// the nine fields.
-// 4M particles in random order: the gather 784 -> 245 us and the keys, which write the records,
-// 83 -> 150 us; 1M: 179 -> 57 us and 18 -> 38 us.
-__global__ void __launch_bounds__(256) k_gather_input(int n, const u32* __restrict__ perm,
-                                                       const double4* __restrict__ rec, const double* __restrict__ u,
-                                                       DevPtrs d, int64_t* order_out) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const u32 i = perm[q];
-    const double4 p = rec[2 * (size_t)i], v = rec[2 * (size_t)i + 1];
-    const double pu = u[i];
-    d.id[q] = i;
-    d.x[q] = p.x; d.y[q] = p.y; d.z[q] = p.z;
-    d.vx[q] = v.x; d.vy[q] = v.y; d.vz[q] = v.z;
-    d.m[q] = v.w; d.h[q] = p.w; d.u[q] = pu;
-    d.pos4[q] = p;
-    d.vel4[q] = v;
-    if (order_out) order_out[q] = (int64_t)i;
-}
-
-void launch_gather_input(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out) {
-    if (dm.n > 0)
-        hipLaunchKernelGGL(k_gather_input, dim3((dm.n + 255) / 256), dim3(256), 0, s, dm.n, d.val_a, d.rec, u, d,
-                           order_out);
+// The keys of the step's new positions, in the previous key order: equal keys by particle ID.
+void sort_step_keys(hipStream_t s, const DevPtrs& d, const Dims& dm) {
+    launch_step_keys(s, d, dm);
+    sort_keys<true>(s, d, dm.n, d.id);
 }

@@ -104,34 +104,6 @@ void launch_kick_drift(hipStream_t s, const DevPtrs& d, const Dims& dm, bool pre
     else go(k_kick_drift<false>);
 }
 
-// New key order: q <- old position val[q] (the sort carried the positions); the second
-// buffer set receives the data, and the pair kernels' records pos4 = (x, h),
-// vel4 = (predicted v, m) are written too.  The predicted velocities enter vel4 only: the
-// next kick-drift writes them anew before anything reads them.  The step's keys are made, so
-// block 0 also resets the box accumulators of every set for the next step's kick-drift (a run's
-// first step resets them itself: other calls may use them in between).
-__global__ void k_step_permute(int n, const u32* __restrict__ val, DevPtrs d) {
-    if (blockIdx.x == 0) {
-        constexpr int NB = (int)(sizeof(d.ctl->box_enc) / sizeof(u64));
-        for (int i = threadIdx.x; i < NB; i += blockDim.x) d.ctl->box_enc[i] = (i % 6) < 3 ? ~0ull : 0ull;
-    }
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n) return;
-    const u32 p = val[q];
-    d.id2[q] = d.id[p];
-    const double px = d.x[p], py = d.y[p], pz = d.z[p], hh = d.h[p], mm = d.m[p];
-    const double wx = d.vpx[p], wy = d.vpy[p], wz = d.vpz[p];
-    d.x2[q] = px; d.y2[q] = py; d.z2[q] = pz;
-    d.vx2[q] = d.vx[p]; d.vy2[q] = d.vy[p]; d.vz2[q] = d.vz[p];
-    d.u2[q] = d.u[p]; d.m2[q] = mm; d.h2[q] = hh;
-    d.up2[q] = d.up[p];
-    d.pos4[q] = make_double4(px, py, pz, hh);
-    d.vel4[q] = make_double4(wx, wy, wz, mm);
-}
-void launch_step_permute(hipStream_t s, const DevPtrs& d, int n) {
-    if (n > 0) hipLaunchKernelGGL(k_step_permute, g256(n), dim3(256), 0, s, n, d.val_a, d);
-}
-
 // v = v' + dt/2 a_new;  u = u' + dt/2 du_new;  optional lagged h update.  One block per
 // chunk, dt the segment's step size.
 __global__ void __launch_bounds__(256) k_kick(const DevCtl* __restrict__ ctl, const int4* __restrict__ chunk,

@@ -107,18 +107,74 @@ __device__ __forceinline__ int wave_level_counts(int c, int L) {
     return lane == MAX_LEVEL + 1 ? k : mine;
 }
 
-// Per sorted position: lcp and leaf level (leaf capacity win); per tile: nodes per level and
-// leaves, hist[row * (ntiles + 1) + tile].  Also clears what later kernels of the build count
-// into: the group sizes of every position and the group counts.  W > 0: the leaf capacity is
-// W (= win) and the window runs in registers; W = 0: any win, through LDS.
-template <int W, int TB>
-__global__ void __launch_bounds__(TB) k_leaf_levels(const u64* __restrict__ key, int n, int win, int min_level,
-                                                    signed char* lcp, unsigned char* lvl, int* hist, int ntiles,
-                                                    u32* gsize, int* gcount) {
+// What a sort is followed by: the data of sorted position q fetched from where the sort found it.
+//
+// Caller-order input -> key-ordered snapshot.  The caller's order is arbitrary: gathered array by
+// array, every 8-byte read costs a line, and the records of k_keys cost one line for eight of
+// the nine fields.  4M particles in random order: the gather 784 -> 245 us and the keys, which
+// write the records, 83 -> 150 us; 1M: 179 -> 57 us and 18 -> 38 us.
+struct InputMove {
+    DevPtrs d;
+    const double* u;
+    int64_t* order_out;
+    __device__ __forceinline__ void begin() const {}
+    __device__ __forceinline__ void move(int q) const {
+        const u32 i = d.val_a[q];
+        const double4 p = d.rec[2 * (size_t)i], v = d.rec[2 * (size_t)i + 1];
+        const double pu = u[i];
+        d.id[q] = i;
+        d.x[q] = p.x; d.y[q] = p.y; d.z[q] = p.z;
+        d.vx[q] = v.x; d.vy[q] = v.y; d.vz[q] = v.z;
+        d.m[q] = v.w; d.h[q] = p.w; d.u[q] = pu;
+        d.pos4[q] = p;
+        d.vel4[q] = v;
+        if (order_out) order_out[q] = (int64_t)i;
+    }
+};
+// New key order of a step: q <- old position val[q] (the sort carried the positions); the second
+// buffer set receives the data, and the pair kernels' records pos4 = (x, h),
+// vel4 = (predicted v, m) are written too.  The predicted velocities enter vel4 only: the
+// next kick-drift writes them anew before anything reads them.  The step's keys are made, so
+// the first workgroup also resets the box accumulators of every set for the next step's kick-drift
+// (a run's first step resets them itself: other calls may use them in between).
+struct StepMove {
+    DevPtrs d;
+    __device__ __forceinline__ void begin() const {
+        if (blockIdx.x != 0) return;
+        constexpr int NB = (int)(sizeof(d.ctl->box_enc) / sizeof(u64));
+        for (int i = threadIdx.x; i < NB; i += blockDim.x) d.ctl->box_enc[i] = (i % 6) < 3 ? ~0ull : 0ull;
+    }
+    __device__ __forceinline__ void move(int q) const {
+        const u32 p = d.val_a[q];
+        d.id2[q] = d.id[p];
+        const double px = d.x[p], py = d.y[p], pz = d.z[p], hh = d.h[p], mm = d.m[p];
+        const double wx = d.vpx[p], wy = d.vpy[p], wz = d.vpz[p];
+        d.x2[q] = px; d.y2[q] = py; d.z2[q] = pz;
+        d.vx2[q] = d.vx[p]; d.vy2[q] = d.vy[p]; d.vz2[q] = d.vz[p];
+        d.u2[q] = d.u[p]; d.m2[q] = mm; d.h2[q] = hh;
+        d.up2[q] = d.up[p];
+        d.pos4[q] = make_double4(px, py, pz, hh);
+        d.vel4[q] = make_double4(wx, wy, wz, mm);
+    }
+};
+
+// Per sorted position: its data moved into place, lcp and leaf level (leaf capacity win); per
+// tile: nodes per level and leaves, hist[row * (ntiles + 1) + tile].  Also clears what later kernels
+// of the build count into: the group sizes of every position and the group counts.  W > 0: the
+// leaf capacity is W (= win) and the window runs in registers; W = 0: any win, through LDS.  The
+// move (memory) and the window (vector ALU) share a launch:
+// 62 us for 987,840 particles in a step where two kernels took 55 + 16 us, and one launch fewer.
+template <int W, int TB, typename Move>
+__global__ void __launch_bounds__(TB) k_order_levels(Move mv, const u64* __restrict__ key, int n, int win, int min_level,
+                                                     signed char* lcp, unsigned char* lvl, int* hist, int ntiles,
+                                                     u32* gsize, int* gcount) {
     __shared__ signed char c[TB + 2 * MAX_WIN + 2];
     __shared__ signed char mrow[W > 0 ? 1 : TB * MAX_WIN];
     __shared__ int wcnt[TB / 64][TREE_ROWS];
     const int b0 = blockIdx.x * TB;
+    const int i = b0 + threadIdx.x;
+    mv.begin();
+    if (i < n) mv.move(i);
     if (threadIdx.x == 0 && b0 % GROUP_TILE == 0) gcount[b0 / GROUP_TILE] = 0;
     const int lo = b0 - win;                      // c[j] holds position lo + j
     const int cnt = TB + 2 * win + 1;
@@ -129,7 +185,6 @@ __global__ void __launch_bounds__(TB) k_leaf_levels(const u64* __restrict__ key,
         c[j] = (signed char)v;
     }
     __syncthreads();
-    const int i = b0 + threadIdx.x;
     const int ci = i - lo;
     int L = -1, cc = MAX_LEVEL;
     if (i < n) {
@@ -599,17 +654,18 @@ static int grid_cap(int n, int bs, int cap) {
     return g < 1 ? 1 : (g > cap ? cap : g);
 }
 
-void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm) {
+template <typename Move>
+static void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm, const Move& mv) {
     const int n = dm.n;
     if (n <= 0) return;
     const int tb = tree_tile(n), ntiles = (n + tb - 1) / tb;
     auto run = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(ntiles), dim3(tb), 0, s, d.key_a, n, dm.leaf_size, dm.min_level, d.lcp, d.lvl,
+        hipLaunchKernelGGL(kern, dim3(ntiles), dim3(tb), 0, s, mv, d.key_a, n, dm.leaf_size, dm.min_level, d.lcp, d.lvl,
                            d.tree_hist, ntiles, d.gsize, d.gcount);
     };
     auto levels = [&](auto w) {
-        if (tb == TB_SMALL) run(k_leaf_levels<decltype(w)::value, TB_SMALL>);
-        else run(k_leaf_levels<decltype(w)::value, TB_LARGE>);
+        if (tb == TB_SMALL) run(k_order_levels<decltype(w)::value, TB_SMALL, Move>);
+        else run(k_order_levels<decltype(w)::value, TB_LARGE, Move>);
     };
     switch (dm.leaf_size) {  // the autotuner's leaf sizes and the node-node scheme's 64
         case 8: levels(std::integral_constant<int, 8>()); break;
@@ -641,6 +697,13 @@ void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm) {
                        d.parent, d.range, d.gsize, d.gcount);
     hipLaunchKernelGGL(k_emit_groups, dim3((n + GROUP_TILE - 1) / GROUP_TILE), dim3(GROUP_TILE), 0, s, n, dm.batched,
                        d.ctl, d.gsize, d.gcount, d.key_a, d.seg_root_rank, d.group);
+}
+
+void build_input_tree(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out) {
+    build_octree(s, d, dm, InputMove{d, u, order_out});
+}
+void build_step_tree(hipStream_t s, const DevPtrs& a, const DevPtrs& b, const Dims& dm) {
+    build_octree(s, b, dm, StepMove{a});
 }
 
 // Export (test path): node keys etc. in breadth-first order.
