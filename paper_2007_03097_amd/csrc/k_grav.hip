@@ -36,7 +36,7 @@ template <>
 struct GravStage<false> {
     union {
         struct {
-            double4 c0[64], c1[64], c2[64];  // the record of cell_term
+            double4 c0[32], c1[32], c2[32];  // the record of cell_term
         } cell;
         struct {
             double4 pm[64];  // (x, y, z, m)
@@ -203,7 +203,7 @@ __device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C>& St, co
                            double e2, bool phi, TargetSums& A, TargetSums& B) {
     const int lane = lane_id();
     const bool any = T.va || T.vb;
-    constexpr int CS = 64;  // cells staged per round
+    constexpr int CS = FP32C ? 64 : 32;  // cells staged per round
     for (int k0 = 0; k0 < ncell; k0 += CS) {
         __syncthreads();
         if (lane < CS && k0 + lane < ncell) {
@@ -250,34 +250,24 @@ __device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C>& St, co
     }
 }
 
-// Particles of the listed leaves, concatenated and staged through LDS 64 at a time (one
-// load per lane per round): put(lane, position, mass, index) writes the staged record,
-// tile(tn) evaluates each staged tile of tn particles.  leaves[] is overwritten with the
-// leaves' first particles.  Returns the number of particles.
+// Particles of the listed leaves (first particles in leaves[], counts in St.loff[], which become
+// offsets), concatenated and staged through LDS 64 at a time (one load per lane per round):
+// put(lane, position, mass, index) writes the staged record, tile(tn) evaluates each staged tile of
+// tn particles.  Returns the number of particles.
 template <typename Stage, typename Tile, typename Put>
-__device__ int stage_leaves_put(int nleaf, int* leaves, Stage& St, const int4* __restrict__ topo,
-                                 const double4* __restrict__ pos4, const double* __restrict__ m, Tile&& tile,
+__device__ int stage_leaves_put(int nleaf, int* leaves, Stage& St, const double4* __restrict__ pos4,
+                                const double* __restrict__ m, Tile&& tile,
                                  Put&& put) {
     const int lane = lane_id();
-    int carry = 0;
-    for (int j0 = 0; j0 < nleaf; j0 += 64) {  // particle offsets of the leaves
+    int total = 0;
+    for (int j0 = 0; j0 < nleaf; j0 += 64) {  // particle counts of the leaves -> offsets
         const int j = j0 + lane;
-        int c = 0, st = 0;
-        if (j < nleaf) {
-            const int4 tp = topo[leaves[j]];
-            st = tp.x;
-            c = tp.y;
-        }
+        const int c = j < nleaf ? St.loff[j] : 0;
         const int incl = wave_incl_scan(c);
-        __syncthreads();
-        if (j < nleaf) {
-            leaves[j] = st;
-            St.loff[j] = carry + incl - c;
-        }
-        carry += wave_last(incl);
+        if (j < nleaf) St.loff[j] = total + incl - c;
+        total += wave_last(incl);
     }
     __syncthreads();
-    const int total = carry;
     int last = -1;
     for (int p0 = 0; p0 < total; p0 += 64) {
         const int p = p0 + lane;
@@ -295,9 +285,9 @@ __device__ int stage_leaves_put(int nleaf, int* leaves, Stage& St, const int4* _
 
 // stage_leaves_put with (x, y, z, m) records in FP64.
 template <typename Stage, typename Tile>
-__device__ int stage_leaves(int nleaf, int* leaves, Stage& St, const int4* __restrict__ topo,
-                             const double4* __restrict__ pos4, const double* __restrict__ m, Tile&& tile) {
-    return stage_leaves_put(nleaf, leaves, St, topo, pos4, m, tile, [&](int lane, const double4& ps, double mass, int src) {
+__device__ int stage_leaves(int nleaf, int* leaves, Stage& St, const double4* __restrict__ pos4,
+                                const double* __restrict__ m, Tile&& tile) {
+    return stage_leaves_put(nleaf, leaves, St, pos4, m, tile, [&](int lane, const double4& ps, double mass, int src) {
         St.part.pm[lane] = make_double4(ps.x, ps.y, ps.z, mass);
         St.part.src[lane] = src;
     });
@@ -307,8 +297,8 @@ __device__ int stage_leaves(int nleaf, int* leaves, Stage& St, const int4* __res
 // With softening the self pair is evaluated like any other (it adds no force) and its
 // potential term -m_q/eps is taken out by the caller.  Returns the number of sources.
 template <bool FP32C>
-__device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const int4* __restrict__ topo,
-                            const double4* __restrict__ pos4, const double* __restrict__ m, const GravTargets& T,
+__device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const double4* __restrict__ pos4,
+                                const double* __restrict__ m, const GravTargets& T,
                             double e2, bool phi, TargetSums& A, TargetSums& B) {
     const bool any = T.va || T.vb;
     const bool soft = e2 > 0.0;
@@ -332,7 +322,7 @@ __device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const i
             }
         };
         return stage_leaves_put(
-            nleaf, leaves, St, topo, pos4, m,
+            nleaf, leaves, St, pos4, m,
             [&](int tn) {
                 if (!any) return;
                 if (phi) run(tn, BoolC<true>());
@@ -363,7 +353,7 @@ __device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const i
             }
         }
     };
-    return stage_leaves(nleaf, leaves, St, topo, pos4, m, [&](int tn) {
+    return stage_leaves(nleaf, leaves, St, pos4, m, [&](int tn) {
         if (!any) return;
         if (phi) run(tn, BoolC<true>());
         else run(tn, BoolC<false>());
@@ -380,8 +370,8 @@ struct LaneTarget {
 };
 
 template <bool FP32C, typename Stage>
-__device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const int4* __restrict__ topo,
-                             const double4* __restrict__ pos4, const double* __restrict__ m, const LaneTarget& T,
+__device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const double4* __restrict__ pos4,
+                                const double* __restrict__ m, const LaneTarget& T,
                              double e2, bool phi, TargetSums& A) {
     const bool soft = e2 > 0.0;
     auto run = [&](int tn, auto ph) {
@@ -393,7 +383,7 @@ __device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const int4* __re
                 if (St.part.src[j] != T.q) part_term<FP32C, PH>(T.a, St.part.pm[j], e2, A);
         }
     };
-    stage_leaves(nleaf, leaves, St, topo, pos4, m, [&](int tn) {
+    stage_leaves(nleaf, leaves, St, pos4, m, [&](int tn) {
         if (!T.v) return;
         if (phi) run(tn, BoolC<true>());
         else run(tn, BoolC<false>());
@@ -416,17 +406,17 @@ __global__ void k_zero_grav_counts(DevCtl* ctl) {
 // grid cost ~12% of the 4M-particle pass.
 template <bool FP32C>
 __device__ void eval_lists(int ncell, int nleaf, const int* cells, int* leaves, GravStage<FP32C>& St,
-                           const int4* __restrict__ topo, const double4* __restrict__ mom0,
+                           const double4* __restrict__ mom0,
                            const double4* __restrict__ mom1, const double4* __restrict__ mom2,
                            const double4* __restrict__ pos4, const double* __restrict__ m, const GravTargets& T,
                            double eps, bool phi, TargetSums& A, TargetSums& B, int ng, u64& n_cells, u64& n_pairs) {
     eval_cells<FP32C>(ncell, cells, St, mom0, mom1, mom2, T, eps * eps, phi, A, B);
     n_cells += (u64)ncell * (u64)ng;
-    n_pairs += (u64)eval_leaves<FP32C>(nleaf, leaves, St, topo, pos4, m, T, eps * eps, phi, A, B) * (u64)ng;
+    n_pairs += (u64)eval_leaves<FP32C>(nleaf, leaves, St, pos4, m, T, eps * eps, phi, A, B) * (u64)ng;
 }
 
 template <bool FP32C>
-__global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restrict__ group, int gsz,
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ? 1 : 4))) k_gravity(DevCtl* ctl, const int4* __restrict__ group, int gsz,
                                                 const int4* __restrict__ topo, const double4* __restrict__ nbox_lo,
                                                 const double4* __restrict__ nbox_hi, const double4* __restrict__ mom0,
                                                 const double4* __restrict__ mom1, const double4* __restrict__ mom2,
@@ -497,7 +487,7 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
                 break;
             }
             if (nc + 64 > GW_CELLS || nl + 64 > GW_LEAVES) {
-                eval_lists<FP32C>(nc, nl, cells, leaves, St, topo, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B,
+                eval_lists<FP32C>(nc, nl, cells, leaves, St, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B,
                                   g.y, n_cells, n_pairs);
                 nc = nl = 0;
                 __syncthreads();
@@ -532,7 +522,10 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
             }
             const u64 bc = __ballot(kind == 1), bl = __ballot(kind == 2);
             if (kind == 1) cells[nc + __popcll(bc & lt)] = node;
-            if (kind == 2) leaves[nl + __popcll(bl & lt)] = node;
+            if (kind == 2) {
+                leaves[nl + __popcll(bl & lt)] = tp.x;
+                St.loff[nl + __popcll(bl & lt)] = tp.y;
+            }
             nc += __popcll(bc);
             nl += __popcll(bl);
             const int nch = kind == 3 ? tp.y : 0;
@@ -547,7 +540,7 @@ __global__ void __launch_bounds__(64) k_gravity(DevCtl* ctl, const int4* __restr
             __syncthreads();
         }
         __syncthreads();
-        eval_lists<FP32C>(nc, nl, cells, leaves, St, topo, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B,
+        eval_lists<FP32C>(nc, nl, cells, leaves, St, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B,
                                   g.y, n_cells, n_pairs);
         // per target: lanes tp + TP*phi combine in a fixed order
         double r[8];
@@ -814,7 +807,10 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
                     }
                 }
             }
-            if (lane == 0) leaves[0] = L;  // the leaf's own particle pairs
+            if (lane == 0) {  // the leaf's own particle pairs
+                leaves[0] = tl.x;
+                St.loff[0] = tl.y;
+            }
             int nt = 0, nl = 1, iters = 0;
             TargetSums A;
             double fgx = 0.0, fgy = 0.0, fgz = 0.0, fc = 0.0;
@@ -831,7 +827,7 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
                     __syncthreads();
                 }
                 if (nl + 64 > FM_LEAVES) {
-                    eval_leaves1<FP32C>(nl, leaves, St, topo, pos4, m, T, e2, phi, A);
+                    eval_leaves1<FP32C>(nl, leaves, St, pos4, m, T, e2, phi, A);
                     nl = 0;
                     __syncthreads();
                 }
@@ -869,7 +865,10 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
                     tnode[o] = Y;
                     tdep[o] = (unsigned char)e;
                 }
-                if (kind == 2) leaves[nl + __popcll(bl & lt)] = Y;
+                if (kind == 2) {
+                    leaves[nl + __popcll(bl & lt)] = ty.x;
+                    St.loff[nl + __popcll(bl & lt)] = ty.y;
+                }
                 nt += __popcll(bt);
                 nl += __popcll(bl);
                 const int np = kind == 3 ? 1 : (kind == 4 ? ty.y : 0);
@@ -894,7 +893,7 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
             __syncthreads();
             if (phi) fmm_eval_terms<true>(nt, tnode, tdep, Pth, D, mom0, e2, fgx, fgy, fgz, fc);
             else fmm_eval_terms<false>(nt, tnode, tdep, Pth, D, mom0, e2, fgx, fgy, fgz, fc);
-            eval_leaves1<FP32C>(nl, leaves, St, topo, pos4, m, T, e2, phi, A);
+            eval_leaves1<FP32C>(nl, leaves, St, pos4, m, T, e2, phi, A);
             fgx = lanes_sum_d(fgx, 1);
             fgy = lanes_sum_d(fgy, 1);
             fgz = lanes_sum_d(fgz, 1);
