@@ -32,6 +32,11 @@ constexpr double M_1_PI_D = 0.318309886183790671537767526745028724;
 // them, and k_set_box merges them (a segmented set has one per segment).
 constexpr int BOX_SLOTS = 64;
 
+// Nodes of the starting level of the neighbour walks: as many as one round of a walk pops (it keeps
+// room for eight children of each on its 512-entry stack), so that starting there visits the same
+// nodes in the same order as starting at the root.
+constexpr int WALK_START = 56;
+
 // Counter slots of the gravity pass's term counts, one 128-byte line each.
 constexpr int GRAV_SLOTS = 64;
 
@@ -44,6 +49,7 @@ struct DevCtl {
     int n_groups;                 // target groups
     int level_count[24];          // nodes per level
     int level_off[24];            // exclusive prefix of level_count
+    int walk_level;               // level at which a single set's neighbour walks start (k_top_moments)
     u64 box_enc[512 * 6];         // per segment: ordered-integer min x,y,z then max x,y,z
     double box[512 * 6];          // decoded per-segment box lo.xyz, hi.xyz
     double scale[512];            // 2^B / L per segment (0 when L == 0)

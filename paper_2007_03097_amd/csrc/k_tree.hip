@@ -636,9 +636,20 @@ __global__ void __launch_bounds__(SUB_THREADS) k_subtree_moments(NodeArgs A) {
 }
 
 // Internal nodes of the levels above the cut in one workgroup, a barrier between levels.
-__global__ void __launch_bounds__(1024) k_top_moments(NodeArgs A) {
+// Also finds the level at which the neighbour walks start: the last one with at most WALK_START nodes
+// and no leaf above it.
+__global__ void __launch_bounds__(1024) k_top_moments(NodeArgs A, DevCtl* ctl) {
     __shared__ NodeSums S[1024 / NODE_LANES];
     const int j = threadIdx.x & (NODE_LANES - 1);
+    if (threadIdx.x < 64) {
+        int l = 0;
+        while (l < MAX_LEVEL && A.ctl->level_count[l + 1] > 0 && A.ctl->level_count[l + 1] <= WALK_START) {
+            const int b0 = A.ctl->level_off[l], nb = A.ctl->level_count[l];  // at most WALK_START nodes
+            if (__ballot(lane_id() < nb && A.topo[b0 + min(lane_id(), nb - 1)].w)) break;
+            ++l;
+        }
+        if (threadIdx.x == 0) ctl->walk_level = l;
+    }
     for (int level = subtree_cut(A.ctl) - 1; level >= 0; --level) {
         const int b0 = A.ctl->level_off[level], nb = A.ctl->level_count[level];
         for (int k = threadIdx.x / NODE_LANES; k < nb; k += 1024 / NODE_LANES) {
@@ -689,7 +700,7 @@ static void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm, const 
     hipLaunchKernelGGL(k_finalize, dim3(grid_cap(4 * (n / dm.leaf_size) + 64, 256 / NODE_LANES, 8192)), dim3(256), 0, s,
                        A, d.node_level, d.node_start, d.node_first, d.lcp, d.leaf_start);
     hipLaunchKernelGGL(k_subtree_moments, dim3(grid_cap(n, 16, 2048)), dim3(SUB_THREADS), 0, s, A);
-    hipLaunchKernelGGL(k_top_moments, dim3(1), dim3(1024), 0, s, A);
+    hipLaunchKernelGGL(k_top_moments, dim3(1), dim3(1024), 0, s, A, d.ctl);
     // target groups: cells of at most 4 * group_size particles, cut into runs of group_size
     const int gcap = 4 * dm.group_size;
     const int g = grid_cap(dm.node_cap, 256, 2048);

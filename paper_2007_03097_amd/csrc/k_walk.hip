@@ -14,17 +14,14 @@
 //     candidate list is matched (step 3) whenever it fills, so any number of candidates
 //     is handled with fixed LDS.
 //  3. Each candidate particle is tested against the group box (conservatively, as the
-//     nodes are); survivors are staged in an LDS ring and matched 64 at a time: lane
-//     (tp, phi) tests the block of sources phi*T .. phi*T + T - 1 (T = group_size/2) against
-//     its two targets tp and tp + T with the exact predicate
-//     fl(fl(fl(dx dx) + fl(dy dy)) + fl(dz dz)) < fl(t t), recording hits as bits (two
-//     targets per lane halve the LDS reads per pair test).  The predicate is screened in FP32
-//     (fp32_screen below): the screen decides every pair outside a proven error margin, the
-//     few pairs inside it take the FP64 expression, so the lists are those of the FP64
-//     predicate bit for bit.  The OR of all lanes' bits is the tile's part of the group's
-//     source union U (sources that are a neighbour of at least one target), appended to
-//     U in staging order.  The 64/T lanes of a target then take consecutive slot ranges
-//     and write, for each hit, the source's index in U.
+//     nodes are); survivors are staged in an LDS ring and matched 64 at a time with the exact
+//     predicate fl(fl(fl(dx dx) + fl(dy dy)) + fl(dz dz)) < fl(t t).  The predicate is screened
+//     on the matrix cores (see Screen below): the screen decides every pair outside a proven
+//     error margin, the few pairs inside it take the FP64 expression, so the lists are those of
+//     the FP64 predicate bit for bit.  The OR of all targets' hits is the tile's part of the
+//     group's source union U (sources that are a neighbour of at least one target), appended to
+//     U in staging order.  The 64 / group_size lanes of a target then take consecutive source
+//     ranges of the tile and write, for each hit, the source's index in U.
 // Outputs per group (n_g targets starting at sorted position s):
 //   uni[s*cap + i], i < ucnt[group]: particle index of the i-th member of U;
 //   nbr[s*cap + k*n_g + t]: slot k of target t, a 16-bit index into U (|U| <= UNION_MAX),
@@ -43,207 +40,251 @@ struct GroupBox {
     double lo[3], hi[3], hg;
 };
 
-// FP32 screen of the exact predicate.  Coordinates are offsets from the group origin o (the
-// group's first target), each formed in FP64 and rounded to FP32; h is rounded to FP32.
-// With u = 2^-24 and E the largest per-axis offset of a target from o, the screen values
-//   r2' = fma(dx', dx', fma(dy', dy', dz' dz')),  t' = fl(h_a' + h_b')
-// (dx' = fl(x_a' - x_b') ...) give r2' and t'^2 within 3.6u E^2 + 10.7u r^2 and 4.1u t^2 of the
-// exact r^2 and t^2 = (h_a + h_b)^2 (offset errors grow with |x - o| <= E + |dx|), and the
-// FP64 expressions differ from them by O(2^-53).  The screen value d' = fma(t', t', -r2')
-// rounds once, so with t2' = fl(t'^2) and
-//   M = 2^-21 E^2 + 2^-19 t2' + 2^-100   (about twice the bound; the last term covers FP32
-//                                          underflow)
-// the FP64 predicate holds when d' > M and fails when d' < -M.  Pairs with
-// |d'| <= M, and any NaN or overflow, are undecided and take the FP64 expression.  FP32
-// arithmetic issues at twice the FP64 rate on this GPU and the staged records halve.
+// Screen of the exact predicate: the signed margin t^2 - r^2 (t = h_a + h_b) of 32 targets against 32
+// sources is a contraction over six terms,
+//   t^2 - r^2 = a . 2b + h_a 2h_b + c_a + c_b,   c = h^2 - |x|^2,
+// of offsets a, b from the centre of the group's box, and runs on the matrix cores in FP32
+// (v_mfma_f32_32x32x2_f32, three per 1,024 pairs: K = 6).  Error of the computed value D: with
+// u = 2^-24 and S = (|a| + |b|)^2 + (h_a + h_b)^2, which bounds the sum of the terms' magnitudes, the
+// rounded inputs give at most 4u S (offsets and h are formed in FP64 and rounded once, c likewise)
+// and six accumulations, taken at 2u each so that any order or truncation is covered, 12u S; FP32
+// underflow less than 2^-100.  The margin
+//   M = 2^-19 S' + 2^-100,   S' >= S for every pair of the tile,
+// is twice that.  It is added to c_a, so that D' = D + M: D' < 0 means t^2 - r^2 < 0 and D' > 2M
+// means t^2 - r^2 > 0, each by more than the FP64 expression's own rounding (O(2^-53) S), and a
+// D' between is undecided.  S' takes the half diagonal R of the group box, the largest h of the
+// group hg and of the tile's sources hm: |a| <= R, and a source that passed the group-box filter
+// has |b| <= R + hg + hm.  Where M is not below 2^100 (or NaN) every pair is undecided; below,
+// nothing overflows.
+//
+// The former screen ran on the vector ALUs, 12 instructions a pair test, and bound the kernel
+// (about 780 of some 1,400 vector instructions per tile of 64 sources and 64 targets); a D'
+// costs 1.5 of them here, its sign shifted into the hit mask and its bits into the running
+// minimum that finds undecided pairs.  SCREENFIG
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int TILE_COMP = 5;  // staged per source: 2 b (three), 2 h, c
+struct Tile {
+    float v[TILE_COMP][TILE_RING];
+    int src[TILE_RING];
+};
+
 struct Screen {
-    double o[3];   // group origin
-    float me;      // 2^-21 E^2 + 2^-100, rounded up
+    double o[3];   // centre of the group's box
+    float reach;   // 2 R + hg, rounded up
+    float hg;      // rounded up
 };
 
-// Each lane serves two targets of the group, tp and tp + TP (TP = group_size / 2), and a
-// block of B = TP staged sources; the P = 64 / TP lanes with the same tp cover the tile.
-// One LDS read of a source feeds two pair tests.
-template <int TP_>
+__device__ __forceinline__ float next_up(double v) { return (float)(v * (1.0 + 0x1p-20)); }
+
+// Stages source b at ring slot r.
+__device__ __forceinline__ void stage_source(Tile& tile, int r, const double4& b, int src, const Screen& S) {
+    const double x = b.x - S.o[0], y = b.y - S.o[1], z = b.z - S.o[2];
+    tile.v[0][r] = 2.0f * (float)x;
+    tile.v[1][r] = 2.0f * (float)y;
+    tile.v[2][r] = 2.0f * (float)z;
+    tile.v[3][r] = 2.0f * (float)b.w;
+    tile.v[4][r] = (float)(b.w * b.w - ((x * x + y * y) + z * z));
+    tile.src[r] = src;
+}
+
+// Targets of a group of at most T.  Matrix columns: the lane's column of block k is target
+// 32 k + lane % 32, of which it supplies the terms 2q + lane / 32 (q = 0 .. 2).  Lists: the lane writes
+// for target lane % T, with the P = 64 / T lanes of a target splitting the tile's sources.
+template <int T>
 struct LaneTargets {
-    static constexpr int TP = TP_, P = 64 / TP_;
-    float4 a, b;    // targets tp and tp + TP: FP32 offsets from the origin, h
-    bool va, vb;    // they exist
-    int tp, phi;
-    int cnt_a, cnt_b;
+    static constexpr int P = 64 / T, NC = T == 64 ? 2 : 1;
+    float b0[NC], b1[NC], b2[NC];
+    int t, p, cnt;
 };
 
-__device__ __forceinline__ float4 offset_rec(const double4& p, const Screen& S) {
-    return make_float4((float)(p.x - S.o[0]), (float)(p.y - S.o[1]), (float)(p.z - S.o[2]), (float)p.w);
-}
-
-// Margin of the screen for target a against a tile whose sources have |h| <= hm:
-// M' = fma(fl(fl(|h_a| + hm)^2), 2^-19, me) is at least the margin fma(t2', 2^-19, me) of
-// each of those pairs (t2' = fl(fl(h_a + h_b)^2), every operation monotone), so deciding
-// with M' keeps the screen's guarantee and only leaves a few more pairs undecided.  A NaN
-// h makes M' NaN and every pair of the target undecided.
-__device__ __forceinline__ float tile_margin(float ha, float hm, float me) {
-    const float tt = fabsf(ha) + hm;
-    return fmaf(tt * tt, 0x1p-19f, me);
-}
-
-// d' = fma(t', t', -r2') of one pair (the screen value; see fp32_screen above).
-__device__ __forceinline__ float screen_d(const float4& a, const float4& s) {
-    const float dx = a.x - s.x, dy = a.y - s.y, dz = a.z - s.z;
-    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    const float tt = a.w + s.w;
-    return fmaf(tt, tt, -r2);
-}
-
-// Largest |h| of the tn (>= 1) sources of the tile at ring positions head .., over the wave:
-// the bits of a non-negative float order as unsigned integers (a NaN above every number).
-__device__ __forceinline__ float tile_hmax(const float4* tile, int head, int tn) {
+template <int T>
+__device__ __forceinline__ void load_targets(LaneTargets<T>& L, const double4* __restrict__ pos4, int gx, int gy,
+                                             const Screen& S) {
     const int lane = lane_id();
-    const u32 v = lane < tn ? __float_as_uint(fabsf(tile[(head + lane) & (TILE_RING - 1)].w)) : 0u;
-    return __uint_as_float(wave_reduce_u32(v, [](u32 a, u32 b) { return max(a, b); }));
+    const bool odd = lane >= 32;
+#pragma unroll
+    for (int k = 0; k < L.NC; ++k) {
+        const int col = 32 * k + (lane & 31);
+        const double4 A = pos4[gx + (col < gy ? col : 0)];  // columns past the group repeat its first target
+        const double x = A.x - S.o[0], y = A.y - S.o[1], z = A.z - S.o[2];
+        L.b0[k] = odd ? (float)y : (float)x;
+        L.b1[k] = odd ? (float)A.w : (float)z;
+        L.b2[k] = odd ? (float)(A.w * A.w - ((x * x + y * y) + z * z)) : 1.0f;
+    }
 }
 
-// The exact FP64 predicate for the pairs the screen left undecided (bit i = tile source i).
-__device__ void resolve_exact(u32 q, const double4& A, int head, int j0, const int* tsrc,
-                              const double4* __restrict__ pos4, u32& hits) {
-    while (q) {
-        const int it = __ffs(q) - 1;
-        q &= q - 1;
-        const double4 s = pos4[tsrc[(head + j0 + it) & (TILE_RING - 1)]];
+// The exact predicate for undecided elements of a 32 x 32 block (bit i of und = element i, matrix row
+// (i & 3) + 8 (i >> 2) + 4 half); rows from `rows` on are stale.
+__device__ u32 resolve_exact(u32 und, u32 hits, const double4 A, int half, int rows, int slot0, const Tile& tile,
+                             const double4* __restrict__ pos4) {
+    while (und) {
+        const int i = __ffs(und) - 1;
+        und &= und - 1;
+        const int m = (i & 3) + 8 * (i >> 2) + 4 * half;
+        if (m >= rows) continue;
+        const double4 s = pos4[tile.src[(slot0 + m) & (TILE_RING - 1)]];
         const double dx = A.x - s.x, dy = A.y - s.y, dz = A.z - s.z;
         double r2 = dx * dx + dy * dy;
         r2 = r2 + dz * dz;
         const double tt = A.w + s.w;
-        if (r2 < tt * tt) hits |= 1u << it;
+        hits = r2 < tt * tt ? hits | (1u << i) : hits & ~(1u << i);
     }
+    return hits;
 }
 
-// Slots for one target's hits: the P lanes of the target take consecutive slot ranges in
-// phi order, each in ascending source order; the entry is the source's index in the union.
-template <int TP>
-__device__ __forceinline__ void append_hits(u32 bits, int t, int& cnt, const LaneTargets<TP>& L, u64 ub, int ucnt,
-                                            int gy, int cap, u16* mylist) {
-    const int lane = lane_id();
-    const int mine = __popc(bits);
-    int incl = mine;
-    for (int d = L.TP; d < 64; d <<= 1) {
-        const int v = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += v;
+// Matches the tn (1 .. 64) sources at ring positions head .. against the group's targets: hits go to
+// the group's union and to the targets' lists.
+template <int T>
+__device__ __forceinline__ void test_tile(int head, int tn, const Tile& tile, LaneTargets<T>& L, const Screen& S,
+                                          const double4* __restrict__ pos4, int gx, int gy, int cap, u16* mylist,
+                                          int* myuni, int ulim, int& ucnt) {
+    const int lane = lane_id(), col = lane & 31, half = lane >> 5;
+    // largest |h| of the tile: non-negative floats order as unsigned integers, a NaN above them
+    const u32 hv = lane < tn ? __float_as_uint(fabsf(tile.v[3][(head + lane) & (TILE_RING - 1)])) : 0u;
+    const float hm = 0.5f * __uint_as_float(wave_reduce_u32(hv, [](u32 a, u32 b) { return max(a, b); }));
+    const float R = S.reach + hm, tt = S.hg + hm;
+    const float M = fmaf(fmaf(R, R, tt * tt), 0x1p-19f * (1.0f + 0x1p-18f), 0x1p-100f);
+    const bool all = !(M < 0x1p100f);
+    const u32 lim = __float_as_uint(2.0f * M * (1.0f + 0x1p-18f));
+    // matrix rows: the terms 2q + half of source 32 r + lane % 32 (head is a multiple of 64)
+    float a0[2], a1[2], a2[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int j = (head + 32 * r + col) & (TILE_RING - 1);
+        a0[r] = tile.v[half][j];
+        a1[r] = tile.v[2 + half][j];
+        a2[r] = half ? 1.0f : tile.v[4][j];
     }
-    const int tot = __shfl(incl, L.tp + L.TP * (L.P - 1), 64);
-    int slot = cnt + incl - mine;
-    const int j0 = L.phi * L.TP;
-    while (bits) {
-        const int it = __ffs(bits) - 1;
-        bits &= bits - 1;
-        const int j = j0 + it;
-        // past UNION_MAX (an overflow the kernel reports) entries stay at the last index, in bounds
-        if (slot < cap) mylist[slot * gy + t] = (u16)min(ucnt + __popcll(ub & ((1ull << j) - 1ull)), UNION_MAX - 1);
-        ++slot;
-    }
-    cnt += tot;
-}
-
-// Exact predicate fl(fl(fl(dx dx) + fl(dy dy)) + fl(dz dz)) < fl(t t), t = fl(h_a + h_b),
-// for the 64 (or, at the end, fewer) filtered sources at ring positions head .. head+tn-1
-// (FP32 screen, FP64 for the undecided pairs); hits go to the group's union and to the
-// targets' lists.
-template <int TP>
-__device__ __forceinline__ void test_tile(int head, int tn, const float4* tile, const int* tsrc, LaneTargets<TP>& L,
-                                          float me, const double4* __restrict__ pos4, int gx, int gy, int cap,
-                                          u16* mylist, int* myuni, int ulim, int& ucnt) {
-    const int lane = lane_id();
-    const int j0 = L.phi * TP;
-    const int je = min(max(tn - j0, 0), TP);  // sources of this lane's block
-    const u32 valid = je >= 32 ? 0xffffffffu : (1u << je) - 1u;
-    const float hm = tile_hmax(tile, head, tn);
-    const float Ma = tile_margin(L.a.w, hm, me), Mb = tile_margin(L.b.w, hm, me);
-    // head is a multiple of 64, so the block's TP ring entries are contiguous; entries past
-    // the block's end are stale records whose bits are masked off below
-    const float4* blk = tile + ((head + j0) & (TILE_RING - 1));
-    u32 ba = 0, bb = 0;
-    u64 und = 0;  // lanes with an undecided pair
-    // sources in descending order, each decision shifted in at bit 0, so that bit it ends up
-    // holding source it; one ballot per comparison keeps the undecided masks in scalar registers
-#pragma unroll 4
-    for (int it = TP - 1; it >= 0; --it) {
-        const float4 s = blk[it];
-        const float da = screen_d(L.a, s), db = screen_d(L.b, s);
-        ba = ba + ba + (da > Ma ? 1u : 0u);
-        bb = bb + bb + (db > Mb ? 1u : 0u);
-        und |= __builtin_amdgcn_ballot_w64(!(fabsf(da) > Ma)) | __builtin_amdgcn_ballot_w64(!(fabsf(db) > Mb));
-    }
-    ba &= L.va ? valid : 0u;
-    bb &= L.vb ? valid : 0u;
-    if (und) {  // rare: the lanes concerned redo their block's undecided pairs in FP64
-        u32 qa = 0, qb = 0;
-        if ((und >> lane) & 1ull) {
-            for (int it = 0; it < je; ++it) {
-                const float4 s = blk[it];
-                if (!(fabsf(screen_d(L.a, s)) > Ma)) qa |= 1u << it;
-                if (!(fabsf(screen_d(L.b, s)) > Mb)) qb |= 1u << it;
+    u32 w[LaneTargets<T>::NC][2];  // the column's hits, source 32 r + bit (the same in both halves)
+#pragma unroll
+    for (int k = 0; k < LaneTargets<T>::NC; ++k) {
+        w[k][0] = w[k][1] = 0u;
+        if (32 * k >= gy) continue;
+        const bool exists = 32 * k + col < gy;
+        const float b2 = L.b2[k] + (half ? M : 0.0f);
+        f32x16 D[2] = {};
+        D[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[0], L.b0[k], D[0], 0, 0, 0);
+        D[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[1], L.b0[k], D[1], 0, 0, 0);
+        D[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[0], L.b1[k], D[0], 0, 0, 0);
+        D[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[1], L.b1[k], D[1], 0, 0, 0);
+        D[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[0], b2, D[0], 0, 0, 0);
+        D[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a2[1], b2, D[1], 0, 0, 0);
+        u32 hits[2], low = 0xffffffffu;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            u32 miss = 0u;
+#pragma unroll
+            for (int i = 15; i >= 0; --i) {
+                const u32 v = __float_as_uint(D[r][i]);
+                miss = __builtin_amdgcn_alignbit(miss, v, 31);  // miss << 1 | sign
+                low = min(low, v);                              // negative values lie above all others
             }
-            if (!L.va) qa = 0u;
-            if (!L.vb) qb = 0u;
+            hits[r] = ~miss & 0xffffu;
         }
-        if (qa) resolve_exact(qa, pos4[gx + L.tp], head, j0, tsrc, pos4, ba);
-        if (qb) resolve_exact(qb, pos4[gx + L.tp + TP], head, j0, tsrc, pos4, bb);
+        if (__ballot(low <= lim) || all) {  // rare: undecided pairs take the FP64 expression
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                u32 und = 0u;
+#pragma unroll
+                for (int i = 15; i >= 0; --i) und = und + und + (__float_as_uint(D[r][i]) <= lim || all ? 1u : 0u);
+                if (exists && und)
+                    hits[r] = resolve_exact(und, hits[r], pos4[gx + 32 * k + col], half, tn - 32 * r, head + 32 * r,
+                                            tile, pos4);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            // nibble n of the half's hits holds rows 8 n + 4 half ..; both halves' rows together
+            u32 h = hits[r];
+            h = (h | (h << 8)) & 0x00ff00ffu;
+            h = (h | (h << 4)) & 0x0f0f0f0fu;
+            const auto both = __builtin_amdgcn_permlane32_swap(h << (4 * half), h << (4 * half), false, false);
+            const int rows = tn - 32 * r;
+            const u32 valid = rows >= 32 ? 0xffffffffu : (rows > 0 ? (1u << rows) - 1u : 0u);
+            w[k][r] = exists ? (both[0] | both[1]) & valid : 0u;
+        }
     }
-    // union of the tile, bit j = ring entry head + j
-    const u64 mine = (u64)(ba | bb) << j0;
+    u32 w0 = w[0][0], w1 = w[0][1];  // hits of the lane's list target
+    if constexpr (T == 64) {
+        w0 = half ? w[1][0] : w0;
+        w1 = half ? w[1][1] : w1;
+    } else if constexpr (T < 32) {
+        w0 = (u32)__shfl((int)w0, L.t, 64);
+        w1 = (u32)__shfl((int)w1, L.t, 64);
+    }
     auto either = [](u32 a, u32 b) { return a | b; };
-    const u64 ub = (u64)wave_reduce_u32((u32)mine, either) | ((u64)wave_reduce_u32((u32)(mine >> 32), either) << 32);
+    const u32 u0 = wave_reduce_u32(w0, either), u1 = wave_reduce_u32(w1, either);  // union of the tile
+    const u64 ub = (u64)u0 | ((u64)u1 << 32);
     if ((ub >> lane) & 1ull) {
         const int r = ucnt + __popcll(ub & lanemask_lt());
-        if (r < ulim) myuni[r] = tsrc[(head + lane) & (TILE_RING - 1)];
+        if (r < ulim) myuni[r] = tile.src[(head + lane) & (TILE_RING - 1)];
     }
-    append_hits(ba, L.tp, L.cnt_a, L, ub, ucnt, gy, cap, mylist);
-    append_hits(bb, L.tp + L.TP, L.cnt_b, L, ub, ucnt, gy, cap, mylist);
+    // the lane's share of its target's hits: sources p T .. p T + T - 1, after those before them
+    u32 m0 = w0, m1 = w1;
+    int slot = L.cnt;
+    if constexpr (T < 64) {
+        const int j0 = L.p * T;
+        const u32 below = (1u << (j0 & 31)) - 1u, range = T == 32 ? 0xffffffffu : ((1u << (T & 31)) - 1u) << (j0 & 31);
+        if (j0 < 32) {
+            slot += __popc(w0 & below);
+            m0 &= range;
+            m1 = 0u;
+        } else {
+            slot += __popc(w0) + __popc(w1 & below);
+            m0 = 0u;
+            m1 &= range;
+        }
+    }
+    L.cnt += __popc(w0) + __popc(w1);
+    auto append = [&](u32 bits, u32 uw, int first) {
+        while (bits) {
+            const int j = __ffs(bits) - 1;
+            bits &= bits - 1;
+            // past UNION_MAX (an overflow the kernel reports) entries stay at the last index, in bounds
+            if (slot < cap) mylist[slot * gy + L.t] = (u16)min(first + __popc(uw & ((1u << j) - 1u)), UNION_MAX - 1);
+            ++slot;
+        }
+    };
+    append(m0, u0, ucnt);
+    append(m1, u1, ucnt + __popc(u0));
     ucnt += __popcll(ub);
 }
 
-// Matching of the group's targets against the particles of the nc candidate leaves in
-// cand[] (node ids; reused for the leaves' first particles).  Each candidate particle is
-// first tested against the group box, in the same monotone operation order as the node
+// Matching of the group's targets against the particles of the nc candidate leaves, whose first
+// particles are in cand[] and particle counts in coff[] (which become offsets).  Each candidate
+// particle is first tested against the group box, in the same monotone operation order as the node
 // test (gap^2 < (hmax_group + h_b)^2), so no true neighbour is dropped; survivors enter an
 // LDS ring and are matched 64 at a time.  Sources left in the ring (< 64) are matched by
-// the caller's final flush.
-template <int TP>
-__device__ void match_candidates(int nc, int* cand, int* coff, float4* tile, int* tsrc, int& head, int& tail,
-                                 const GroupBox& gb, const Screen& S, const int4* __restrict__ topo,
-                                 const double4* __restrict__ pos4, LaneTargets<TP>& L, int gx, int gy, int cap,
-                                 u16* mylist, int* myuni, int ulim, int& ucnt) {
+// the caller's final flush.  The next 64 candidates are loaded before a tile is matched.
+template <int T>
+__device__ void match_candidates(int nc, int* cand, int* coff, Tile& tile, int& head, int& tail, const GroupBox& gb,
+                                 const Screen& S, const double4* __restrict__ pos4, LaneTargets<T>& L, int gx, int gy,
+                                 int cap, u16* mylist, int* myuni, int ulim, int& ucnt) {
     const int lane = lane_id();
     const u64 lt = lanemask_lt();
-    int carry = 0;
+    int total = 0;
     for (int j0 = 0; j0 < nc; j0 += 64) {
         const int j = j0 + lane;
-        int c = 0, st = 0;
-        if (j < nc) {
-            const int4 tp = topo[cand[j]];
-            st = tp.x;
-            c = tp.y;
-        }
+        const int c = j < nc ? coff[j] : 0;
         const int incl = wave_incl_scan(c);
-        __syncthreads();
-        if (j < nc) {
-            cand[j] = st;
-            coff[j] = carry + incl - c;
-        }
-        carry += wave_last(incl);
+        if (j < nc) coff[j] = total + incl - c;
+        total += wave_last(incl);
     }
     __syncthreads();
-    const int total = carry;
-    int last = -1;
-    for (int p0 = 0; p0 < total; p0 += 64) {
-        const int p = p0 + lane;
-        bool pass = false;
-        int src = 0;
-        double4 b = make_double4(0, 0, 0, 0);
+    int last = -1, src = 0;
+    double4 b;
+    auto fetch = [&](int p0) {
         const int a = tile_owner(coff, nc, p0, last);
-        if (p < total) {
-            src = cand[a] + (p - coff[a]);
+        if (p0 + lane < total) {
+            src = cand[a] + (p0 + lane - coff[a]);
             b = pos4[src];
+        }
+    };
+    if (total > 0) fetch(0);
+    for (int p0 = 0; p0 < total; p0 += 64) {
+        bool pass = false;
+        if (p0 + lane < total) {
             const double gx = fmax(0.0, fmax(b.x - gb.hi[0], gb.lo[0] - b.x));
             const double gy2 = fmax(0.0, fmax(b.y - gb.hi[1], gb.lo[1] - b.y));
             const double gz = fmax(0.0, fmax(b.z - gb.hi[2], gb.lo[2] - b.z));
@@ -253,25 +294,20 @@ __device__ void match_candidates(int nc, int* cand, int* coff, float4* tile, int
             pass = r2 < tt * tt;
         }
         const u64 bal = __ballot(pass);
-        if (pass) {
-            const int r = (tail + __popcll(bal & lt)) & (TILE_RING - 1);
-            tile[r] = offset_rec(b, S);
-            tsrc[r] = src;
-        }
+        if (pass) stage_source(tile, (tail + __popcll(bal & lt)) & (TILE_RING - 1), b, src, S);
         tail += __popcll(bal);
         __syncthreads();
+        if (p0 + 64 < total) fetch(p0 + 64);
         if (tail - head >= 64) {
-            test_tile(head, 64, tile, tsrc, L, S.me, pos4, gx, gy, cap, mylist, myuni, ulim, ucnt);
+            test_tile(head, 64, tile, L, S, pos4, gx, gy, cap, mylist, myuni, ulim, ucnt);
             head += 64;
         }
         __syncthreads();
     }
 }
 
-// 96 VGPRs (five waves per SIMD, no spills) against 110 (four) unconstrained: the walk's
-// dependent loads need the extra wave more than the screen needs the registers.
-template <int TP>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_nbr_lists(DevCtl* ctl, const int4* __restrict__ group, int gsz, int cap,
+template <int T>
+__global__ void __launch_bounds__(64) k_nbr_lists(DevCtl* ctl, const int4* __restrict__ group, int cap,
                                                   const int4* __restrict__ topo, const double4* __restrict__ nbox_lo,
                                                   const double4* __restrict__ nbox_hi, const double4* __restrict__ pos4,
                                                   u16* __restrict__ nbr, int* __restrict__ nbr_cnt,
@@ -280,42 +316,40 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
     __shared__ int stack[WALK_STACK];
     __shared__ int cand[WALK_CAND];
     __shared__ int coff[WALK_CAND];
-    __shared__ float4 tile[TILE_RING];
-    __shared__ int tsrc[TILE_RING];
+    __shared__ Tile tile;
     const int lane = lane_id();
     const u64 lt = lanemask_lt();
-    LaneTargets<TP> L;
-    L.tp = lane & (L.TP - 1);
-    L.phi = lane / L.TP;
+    LaneTargets<T> L;
+    L.t = lane % T;
+    L.p = lane / T;
     int g0, g1, gstep;
     group_range(ctl->n_groups, g0, g1, gstep);
     for (int gi = g0; gi < g1; gi += gstep) {
         const int4 g = group[gi];
-        L.va = L.tp < g.y;
-        L.vb = L.tp + L.TP < g.y;
-        const double4 A = L.va ? pos4[g.x + L.tp] : make_double4(0, 0, 0, 0);
-        const double4 B = L.vb ? pos4[g.x + L.tp + L.TP] : make_double4(0, 0, 0, 0);
-        L.cnt_a = L.cnt_b = 0;
         GroupBox gb;
-        gb.lo[0] = wave_min(fmin(L.va ? A.x : INFINITY, L.vb ? B.x : INFINITY));
-        gb.lo[1] = wave_min(fmin(L.va ? A.y : INFINITY, L.vb ? B.y : INFINITY));
-        gb.lo[2] = wave_min(fmin(L.va ? A.z : INFINITY, L.vb ? B.z : INFINITY));
-        gb.hi[0] = wave_max(fmax(L.va ? A.x : -INFINITY, L.vb ? B.x : -INFINITY));
-        gb.hi[1] = wave_max(fmax(L.va ? A.y : -INFINITY, L.vb ? B.y : -INFINITY));
-        gb.hi[2] = wave_max(fmax(L.va ? A.z : -INFINITY, L.vb ? B.z : -INFINITY));
-        gb.hg = wave_max(fmax(L.va ? A.w : 0.0, L.vb ? B.w : 0.0));
+        {
+            const double4 A = pos4[g.x + (L.t < g.y ? L.t : 0)];  // lanes past the group repeat its first target
+            gb.lo[0] = wave_min(A.x);
+            gb.lo[1] = wave_min(A.y);
+            gb.lo[2] = wave_min(A.z);
+            gb.hi[0] = wave_max(A.x);
+            gb.hi[1] = wave_max(A.y);
+            gb.hi[2] = wave_max(A.z);
+            gb.hg = wave_max(A.w);
+        }
         Screen S;
         {
-            const double4 o = pos4[g.x];
-            S.o[0] = o.x;
-            S.o[1] = o.y;
-            S.o[2] = o.z;
-            double E = 0.0;
-            for (int c = 0; c < 3; ++c) E = fmax(E, fmax(gb.hi[c] - S.o[c], S.o[c] - gb.lo[c]));
-            S.me = (float)((ldexp(E * E, -21) + 0x1p-100) * (1.0 + 0x1p-20));  // rounded up
+            double d2 = 0.0;
+            for (int c = 0; c < 3; ++c) {
+                S.o[c] = 0.5 * (gb.lo[c] + gb.hi[c]);
+                const double e = fmax(gb.hi[c] - S.o[c], S.o[c] - gb.lo[c]);
+                d2 += e * e;
+            }
+            S.reach = next_up(2.0 * sqrt(d2) + gb.hg);
+            S.hg = next_up(gb.hg);
         }
-        L.a = offset_rec(A, S);
-        L.b = offset_rec(B, S);
+        load_targets(L, pos4, g.x, g.y, S);
+        L.cnt = 0;
         const double* lo = gb.lo;
         const double* hi = gb.hi;
         const double hg = gb.hg;
@@ -323,11 +357,15 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
         int* myuni = uni + (size_t)g.x * (size_t)cap;
         const int ulim = min(g.y * cap, UNION_MAX);
         int ucnt = 0, head = 0, tail = 0;
-        const int root = g.z < 0 ? 0 : ctl->level_off[3] + g.z;
-        __syncthreads();
-        if (lane == 0) stack[0] = root;
-        int sp = 1, nc = 0, iters = 0;
+        // a segment's walk starts at its root, a single set's at the nodes of walk_level (those
+        // above it would all be opened, or their whole subtrees pruned)
+        const bool single = g.z < 0;
+        const int wl = ctl->walk_level;
+        const int first = single ? ctl->level_off[wl] : ctl->level_off[3] + g.z;
+        int sp = single ? ctl->level_count[wl] : 1, nc = 0, iters = 0;
         bool overflow = false;
+        __syncthreads();
+        if (lane < sp) stack[lane] = first + lane;
         __syncthreads();
         while (sp > 0) {
             if (++iters > (1 << 20)) {  // bounded: every wave leaves the loop
@@ -335,8 +373,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
                 break;
             }
             if (nc + 64 > WALK_CAND) {
-                match_candidates(nc, cand, coff, tile, tsrc, head, tail, gb, S, topo, pos4, L, g.x, g.y, cap, mylist,
-                                 myuni, ulim, ucnt);
+                match_candidates(nc, cand, coff, tile, head, tail, gb, S, pos4, L, g.x, g.y, cap, mylist, myuni,
+                                 ulim, ucnt);
                 nc = 0;
             }
             // pop at most as many nodes as the free stack can take the children of (8 each)
@@ -361,7 +399,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
             }
             const bool isleaf = hit && tp.w;
             const u64 bl = __ballot(isleaf);
-            if (isleaf) cand[nc + __popcll(bl & lt)] = node;
+            if (isleaf) {
+                cand[nc + __popcll(bl & lt)] = tp.x;
+                coff[nc + __popcll(bl & lt)] = tp.y;
+            }
             nc += __popcll(bl);
             const int nch = (hit && !tp.w) ? tp.y : 0;
             const int incl = wave_incl_scan(nch);
@@ -376,10 +417,10 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
         }
         __syncthreads();
         if (!overflow) {
-            match_candidates(nc, cand, coff, tile, tsrc, head, tail, gb, S, topo, pos4, L, g.x, g.y, cap, mylist,
-                             myuni, ulim, ucnt);
+            match_candidates(nc, cand, coff, tile, head, tail, gb, S, pos4, L, g.x, g.y, cap, mylist, myuni, ulim,
+                             ucnt);
             if (tail > head)
-                test_tile(head, tail - head, tile, tsrc, L, S.me, pos4, g.x, g.y, cap, mylist, myuni, ulim, ucnt);
+                test_tile(head, tail - head, tile, L, S, pos4, g.x, g.y, cap, mylist, myuni, ulim, ucnt);
             __syncthreads();
         } else if (lane == 0)
             set_err(ctl, ERR_WALK_STACK);
@@ -387,17 +428,13 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
             ucnt_out[gi] = overflow ? 0 : (ucnt < ulim ? ucnt : ulim);
             if (ucnt > UNION_MAX) set_err(ctl, ERR_UNION_CAP);
         }
-        if (L.phi == 0) {
-            for (int s = 0; s < 2; ++s) {
-                if (!(s ? L.vb : L.va)) continue;
-                const int q = g.x + L.tp + s * L.TP;
-                const int cnt = s ? L.cnt_b : L.cnt_a;
-                nbr_cnt[q] = overflow ? 0 : (cnt < cap ? cnt : cap);
-                list_base[q] = overflow ? -1 : gi;
-                if (cnt > cap) {
-                    set_err(ctl, ERR_NBR_CAP);
-                    atomicMax(&ctl->nbr_max, cnt);
-                }
+        if (L.p == 0 && L.t < g.y) {
+            const int q = g.x + L.t;
+            nbr_cnt[q] = overflow ? 0 : (L.cnt < cap ? L.cnt : cap);
+            list_base[q] = overflow ? -1 : gi;
+            if (L.cnt > cap) {
+                set_err(ctl, ERR_NBR_CAP);
+                atomicMax(&ctl->nbr_max, L.cnt);
             }
         }
     }
@@ -406,14 +443,14 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) k_
 void launch_nbr_lists(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     if (dm.n <= 0) return;
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.group, dm.group_size, dm.nbr_cap,
+        hipLaunchKernelGGL(kern, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.group, dm.nbr_cap,
                            d.topo, d.nbox_lo, d.nbox_hi, d.pos4, d.nbr, d.nbr_cnt, d.nbr_base, d.uni, d.ucnt);
     };
     switch (dm.group_size) {  // validated at context creation: 8, 16, 32 or 64
-        case 8: go(k_nbr_lists<4>); break;
-        case 16: go(k_nbr_lists<8>); break;
-        case 32: go(k_nbr_lists<16>); break;
-        default: go(k_nbr_lists<32>); break;
+        case 8: go(k_nbr_lists<8>); break;
+        case 16: go(k_nbr_lists<16>); break;
+        case 32: go(k_nbr_lists<32>); break;
+        default: go(k_nbr_lists<64>); break;
     }
 }
 

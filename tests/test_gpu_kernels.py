@@ -150,3 +150,20 @@ def test_groups_at_tile_edges(orc, n):
         off, idx = gpu_neighbors(ctx, n)
         ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
         assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
+
+
+# ---------------------------------------------------------------------------- neighbour screen
+@pytest.mark.parametrize("group", [8, 16, 32, 64])
+@pytest.mark.parametrize("scale,shift", [(1.0, 0.0), (1e-25, 0.0), (1e-11, 0.0), (1e11, 0.0), (1e25, 0.0), (1.0, 1e7)])
+def test_neighbors_at_any_scale(orc, scale, shift, group):
+    """The screen's margin, its underflow term, the overflow rule (every pair exact) and offsets from a
+    distant origin; h spread by 20, odd counts (part-filled groups and tiles)."""
+    ps = uniform_random(1231, seed=83, h=(0.01, 0.2))
+    for f in ("x", "y", "z"):
+        setattr(ps, f, getattr(ps, f) * scale + shift)
+    ps.h = ps.h * scale
+    ctx = make_ctx(ps.n, group_size=group, nbr_capacity=1024)
+    gpu_keys_order(ctx, parts(ps))
+    off, idx = gpu_neighbors(ctx, ps.n)
+    ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+    assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
