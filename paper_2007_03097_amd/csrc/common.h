@@ -68,7 +68,7 @@ struct DevCtl {
 struct DevPtrs {
     DevCtl* ctl;
     // sort
-    u64 *key_a, *key_b;           // n_cap
+    u64 *key_a, *key_b;           // n_cap: sorted keys; keys to sort (and scratch of the sort)
     u32 *val_a, *val_b;           // n_cap
     void* scan_tmp;               // 8 * scan_blocks_cap (u64)
     // Morton-ordered particle data (SoA FP64)

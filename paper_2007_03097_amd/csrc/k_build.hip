@@ -206,7 +206,7 @@ void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* 
                  const double* h, const double* u, u64* keys_out_caller, int) {
     if (dm.n_chunks > 0)
         hipLaunchKernelGGL(k_keys, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, dm.curve, x, y, z, vx, vy,
-                           vz, m, h, u, d.key_a, keys_out_caller, d.rec);
+                           vz, m, h, u, d.key_b, keys_out_caller, d.rec);
 }
 
 // Step-loop keys, in the previous key order, which the sort takes as it is (it orders equal
@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(256) k_step_keys(DevCtl* ctl, const int4* chun
 static void launch_step_keys(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     if (dm.n_chunks > 0)
         hipLaunchKernelGGL(k_step_keys, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, dm.curve, d.x,
-                           d.y, d.z, d.key_a);
+                           d.y, d.z, d.key_b);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -399,7 +399,7 @@ void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
 //
 // What bounds it: launches for small sets; LDS reads in the tiles, memory in the passes for
 // large ones.  Measured per sort against an LSD radix sort of 8-bit digits (8 passes of three
-// kernels at any size, for 63 key bits): 4,096 keys 134 -> 15-21 us, 123K 144 -> 59 us, 1M 183 ->
+// kernels at any size, for 63 key bits): 4,096 keys 134 -> 15-21 us (6.5 us by rank, below), 123K 144 -> 59 us, 1M 183 ->
 // 101 us (a pass 8.9 us, 2.7 TB/s; the tiles 30 us), 4M 400 -> 365 us (a pass 28 us, 3.6 TB/s).
 // Tiles of 8,192 keys save a pass and lose as much (47 us at 1M); 8 keys a thread instead of 4
 // leave fewer waves to hide the LDS latency (tiles 34 us, a pass 10.3 us at 1M).
@@ -569,6 +569,50 @@ __device__ __forceinline__ int ms_split_global(const u64* __restrict__ key, cons
     return lo;
 }
 
+// Small sets: the place of a key is the number of keys before it.  A workgroup holds RANK_KEYS keys
+// in RANK_PARTS lanes each, every lane counting over its part of all keys, staged in LDS RANK_STAGE at
+// a time; equal keys (rare) are told apart by a second pass over the lanes concerned.  n^2 work on
+// the whole chip against the tile sort's n log^2 n on one or two CUs: 4,096 keys 15-21 -> 6.5 us, 8,192
+// (a tile sort and a merge) 34 -> 16 us; at 16,384 it would take 64 us against 40.
+constexpr int RANK_THREADS = 1024, RANK_KEYS = 16, RANK_PARTS = RANK_THREADS / RANK_KEYS, RANK_STAGE = 8192;
+constexpr int RANK_MAX = 8192;
+
+template <bool TIE>
+__global__ void __launch_bounds__(RANK_THREADS) k_rank_sort(const u64* __restrict__ key, u64* __restrict__ kout,
+                                                            u32* __restrict__ vout, int n,
+                                                            const u32* __restrict__ tie) {
+    __shared__ u64 sk[RANK_STAGE];
+    __shared__ int part[RANK_THREADS / 64][RANK_KEYS];
+    // lanes l and l + 16 m of a wave hold key l % 16; wave w, lane group m: part 4 w + m
+    const int kk = threadIdx.x % RANK_KEYS, p = threadIdx.x / RANK_KEYS;
+    const int i = blockIdx.x * RANK_KEYS + kk;
+    for (int j = threadIdx.x; j < n; j += RANK_THREADS) sk[j] = key[j];
+    __syncthreads();
+    const u64 mine = i < n ? sk[i] : 0ull;
+    int less = 0, same = 0;
+#pragma unroll 4
+    for (int j = p; j < n; j += RANK_PARTS) {
+        const u64 k = sk[j];
+        less += k < mine ? 1 : 0;
+        same += k == mine ? 1 : 0;
+    }
+    if (i < n && same > (i % RANK_PARTS == p ? 1 : 0)) {  // other keys equal to this one
+        for (int j = p; j < n; j += RANK_PARTS)
+            if (sk[j] == mine && j != i && (TIE ? tie[j] < tie[i] : j < i)) ++less;
+    }
+    less += __shfl_xor(less, 16, 64);
+    less += __shfl_xor(less, 32, 64);
+    if (lane_id() < RANK_KEYS) part[threadIdx.x >> 6][kk] = less;
+    __syncthreads();
+    if (threadIdx.x < RANK_KEYS && i < n) {
+        int r = 0;
+#pragma unroll
+        for (int w = 0; w < RANK_THREADS / 64; ++w) r += part[w][kk];
+        kout[r] = mine;
+        vout[r] = (u32)i;
+    }
+}
+
 // One merge pass: pairs of runs of `run` keys.
 template <bool TIE>
 __global__ void __launch_bounds__(MM_THREADS) k_ms_merge(const u64* __restrict__ kin, const u32* __restrict__ vin,
@@ -632,16 +676,21 @@ __global__ void __launch_bounds__(MM_THREADS) k_ms_merge(const u64* __restrict__
     }
 }
 
-// Sorts key_a (any order) into key_a, with the input index of each sorted key in val_a.
+// Sorts the keys in key_b (any order) into key_a, with the input index of each in val_a.
 template <bool TIE>
 static void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
     if (n <= 0) return;
+    if (n <= RANK_MAX) {
+        hipLaunchKernelGGL(k_rank_sort<TIE>, dim3((n + RANK_KEYS - 1) / RANK_KEYS), dim3(RANK_THREADS), 0, s, d.key_b,
+                           d.key_a, d.val_a, n, tie);
+        return;
+    }
     int passes = 0;
     for (long long run = MS_TILE; run < n; run *= 2) ++passes;
     // the tile sort starts in the buffer from which the passes end in _a
     u64 *ki = (passes & 1) ? d.key_b : d.key_a, *ko = (passes & 1) ? d.key_a : d.key_b;
     u32 *vi = (passes & 1) ? d.val_b : d.val_a, *vo = (passes & 1) ? d.val_a : d.val_b;
-    hipLaunchKernelGGL(k_ms_tile<TIE>, dim3((n + MS_TILE - 1) / MS_TILE), dim3(MS_THREADS), 0, s, d.key_a, ki, vi, n,
+    hipLaunchKernelGGL(k_ms_tile<TIE>, dim3((n + MS_TILE - 1) / MS_TILE), dim3(MS_THREADS), 0, s, d.key_b, ki, vi, n,
                        tie);
     int run = MS_TILE;
     for (int p = 0; p < passes; ++p, run *= 2) {
@@ -652,7 +701,7 @@ static void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
     }
 }
 
-// The keys in key_a, in caller order: equal keys by index.
+// The keys in key_b, in caller order: equal keys by index.
 void sort_caller_keys(hipStream_t s, const DevPtrs& d, int n) { sort_keys<false>(s, d, n, nullptr); }
 
 // The keys of the step's new positions, in the previous key order: equal keys by particle ID.
