@@ -236,18 +236,28 @@ __device__ __forceinline__ void test_tile(int head, int tn, const Tile& tile, La
             m1 &= range;
         }
     }
-    L.cnt += __popc(w0) + __popc(w1);
-    auto append = [&](u32 bits, u32 uw, int first) {
+    const int end = slot + (int)__popc(m0) + (int)__popc(m1);
+    if (__ballot(end > cap)) {  // an overflow the kernel reports: only the slots below cap are written
+        while (slot + (int)__popc(m0) + (int)__popc(m1) > cap && (m0 | m1)) {
+            if (m1) m1 &= ~(1u << (31 - __clz((int)m1)));
+            else m0 &= ~(1u << (31 - __clz((int)m0)));
+        }
+    }
+    L.cnt += (int)(__popc(w0) + __popc(w1));
+    // entries past UNION_MAX (likewise reported) stay at the last index, in bounds
+    const u32 last = UNION_MAX - 1, stride = 2u * (u32)gy;
+    u32 at = 2u * ((u32)slot * (u32)gy + (u32)L.t);  // byte offset in the group's block, below 2 x 64 x 4,096
+    auto append = [&](u32 bits, u32 uw, u32 first) {
         while (bits) {
-            const int j = __ffs(bits) - 1;
+            const u32 before = __builtin_amdgcn_ubfe(uw, 0u, (u32)__builtin_ctz(bits));
             bits &= bits - 1;
-            // past UNION_MAX (an overflow the kernel reports) entries stay at the last index, in bounds
-            if (slot < cap) mylist[slot * gy + L.t] = (u16)min(first + __popc(uw & ((1u << j) - 1u)), UNION_MAX - 1);
-            ++slot;
+            const u32 e = first + __popc(before);
+            *reinterpret_cast<u16*>(reinterpret_cast<char*>(mylist) + at) = (u16)(e < last ? e : last);
+            at += stride;
         }
     };
-    append(m0, u0, ucnt);
-    append(m1, u1, ucnt + __popc(u0));
+    append(m0, u0, (u32)ucnt);
+    append(m1, u1, (u32)ucnt + __popc(u0));
     ucnt += __popcll(ub);
 }
 
