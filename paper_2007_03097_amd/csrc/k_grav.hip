@@ -95,7 +95,7 @@ struct TargetSums {
 // sum for free.  Record: a = (M, com), b = (Qxx, Qyy, Qzz, -tr(I) eps^2), d = (Qxy, Qxz, Qyz, -).
 // The kernel is bound by its FP64 instructions (at 4M particles it runs at what the FMA probe
 // sustains of the issue rate): 36 per term, 38 with the potential, against 39 and 44 with the
-// trace carried along; TRACEFIG
+// trace carried along: 15.7 -> 14.2 ms.
 template <bool PH = true>
 __device__ __forceinline__ void cell_term(const double4 me, const double4 a, const double4 b, const double4 d,
                                           double e2, TargetSums& S) {
@@ -360,31 +360,42 @@ __device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const d
     });
 }
 
-// One target per lane: target t of c (lanes t + c ph, ph < P = 64 / c, split the staged
-// sources), for targets that fill a wave poorly (the particles of one octree leaf).
+// The targets of one octree leaf: lane tp + TP ph serves target tp and (FP64, TWO) target tp + TP, the
+// P = 64 / TP lanes of a target splitting the staged sources.  Two targets a lane halve the LDS reads
+// and fill more lane slots (18 targets: 126 of 128, one a lane: 54 of 64; 40 targets: 120 of 128 and
+// 40 of 64): 262,144 particles 2.45 -> 2.20 ms with the register bound that keeps four waves per SIMD
+// (2.42 ms without it).  The FP32C sums, whose last bits depend on the split, keep one target.
 struct LaneTarget {
-    double4 a;
-    int q;
-    bool v;
-    int ph, P;
+    double4 a, b;
+    int qa, qb;
+    bool va, vb;
+    int ph, P, TP;
 };
 
-template <bool FP32C, typename Stage>
+template <bool FP32C, bool TWO, typename Stage>
 __device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const double4* __restrict__ pos4,
-                                const double* __restrict__ m, const LaneTarget& T,
-                             double e2, bool phi, TargetSums& A) {
+                             const double* __restrict__ m, const LaneTarget& T, double e2, bool phi, TargetSums& A,
+                             TargetSums& B) {
     const bool soft = e2 > 0.0;
     auto run = [&](int tn, auto ph) {
         constexpr bool PH = decltype(ph)::value;
         if (soft) {
-            for (int j = T.ph; j < tn; j += T.P) part_term<FP32C, PH>(T.a, St.part.pm[j], e2, A);
+            for (int j = T.ph; j < tn; j += T.P) {
+                const double4 s = St.part.pm[j];
+                part_term<FP32C, PH>(T.a, s, e2, A);
+                if constexpr (TWO) part_term<FP32C, PH>(T.b, s, e2, B);
+            }
         } else {
-            for (int j = T.ph; j < tn; j += T.P)
-                if (St.part.src[j] != T.q) part_term<FP32C, PH>(T.a, St.part.pm[j], e2, A);
+            for (int j = T.ph; j < tn; j += T.P) {
+                const int src = St.part.src[j];
+                if (src != T.qa) part_term<FP32C, PH>(T.a, St.part.pm[j], e2, A);
+                if constexpr (TWO)
+                    if (src != T.qb) part_term<FP32C, PH>(T.b, St.part.pm[j], e2, B);
+            }
         }
     };
     stage_leaves(nleaf, leaves, St, pos4, m, [&](int tn) {
-        if (!T.v) return;
+        if (!T.va) return;
         if (phi) run(tn, BoolC<true>());
         else run(tn, BoolC<false>());
         if (FP32C) A.flush_tile();
@@ -648,13 +659,13 @@ void launch_gravity(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
 // over Y's children.  Every node-node term of an ancestor is evaluated once per leaf below
 // it -- no scatter, no atomics, a fixed summation order.  The lanes evaluate 64 accepted
 // pairs at a time (one each) and sum the constant fields across the wave at the end;
-// the particle pairs of unaccepted leaf pairs go through eval_leaves1, one target per lane
-// (a leaf fills a wave poorly; 64 / c lanes share each of its c targets).  The
+// the particle pairs of unaccepted leaf pairs go through eval_leaves1 (a leaf fills a wave
+// poorly, so several lanes share each of its targets).  The
 // potential's linear part is referred to the leaf's centre of mass.
 constexpr int FM_STACK = 672;
 constexpr int FM_TERMS = 192;
 constexpr int FM_LEAVES = 192;
-constexpr int FM_TARGETS = 64;    // targets per pass over a leaf (one per lane)
+constexpr int FM_TARGETS = 64;    // targets per pass over a leaf
 static_assert(7 * MAX_LEVEL + DFS_HEADROOM <= FM_STACK, "the initial pairs of a path and the headroom fit");
 
 // LDS staging of the particle sums (the node-node walk has no cell tiles).
@@ -699,16 +710,19 @@ __device__ __forceinline__ void fmm_unpack(u64 c, int* v) {
     v[2] = (int)(c >> 42);
 }
 
+// 3 T^2 < 4 theta^2 |D|^2: coordinates and sides are below 2^23, so their differences are exact in 32 bits
+// and the squares and sums (below 2^48) exact in FP64, at a fraction of 64-bit integer products.
 __device__ __forceinline__ bool fmm_accept(int la, const int* ca, int lb, const int* cb, double th4) {
-    const long long T = (1ll << (MAX_LEVEL - la + 1)) + (1ll << (MAX_LEVEL - lb + 1));
-    long long D2 = 0;
+    const double T = (double)((1 << (MAX_LEVEL - la + 1)) + (1 << (MAX_LEVEL - lb + 1)));
+    double D2 = 0.0;
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        const long long a = (2ll * ca[d] + 1) << (MAX_LEVEL - la);
-        const long long b = (2ll * cb[d] + 1) << (MAX_LEVEL - lb);
-        D2 += (a - b) * (a - b);
+        const int a = (2 * ca[d] + 1) << (MAX_LEVEL - la);
+        const int b = (2 * cb[d] + 1) << (MAX_LEVEL - lb);
+        const double e = (double)(a - b);
+        D2 = fma(e, e, D2);
     }
-    return 3.0 * (double)(T * T) < th4 * (double)D2;
+    return 3.0 * (T * T) < th4 * D2;
 }
 
 // Accepted pairs (tnode[k], depth tdep[k]): lane k evaluates pair k, k + 64, ... and keeps
@@ -736,7 +750,7 @@ __device__ __forceinline__ void fmm_eval_terms(int nt, const int* tnode, const u
 }
 
 template <bool FP32C>
-__global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__ leaf_node,
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ? 1 : 4))) k_fmm(DevCtl* ctl, const int* __restrict__ leaf_node,
                                             const int* __restrict__ parent,
                                             const int4* __restrict__ topo, const int2* __restrict__ range,
                                             const double4* __restrict__ mom0, const double* __restrict__ ncell,
@@ -784,12 +798,18 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
         const double4 cl = Pth.com[D];
         for (int t0 = 0; t0 < tl.y; t0 += FM_TARGETS) {
             const int cc = min(FM_TARGETS, tl.y - t0);
+            constexpr bool TWO = !FP32C;
             LaneTarget T;
-            T.P = 64 / cc;
-            T.ph = lane / cc;
-            T.q = tl.x + t0 + (lane - T.ph * cc);
-            T.v = T.ph < T.P;
-            T.a = T.v ? pos4[T.q] : make_double4(0, 0, 0, 0);
+            T.TP = TWO ? (cc + 1) >> 1 : cc;
+            T.P = 64 / T.TP;
+            T.ph = lane / T.TP;
+            const int tp = lane - T.ph * T.TP;
+            T.qa = tl.x + t0 + tp;
+            T.qb = T.qa + T.TP;
+            T.va = T.ph < T.P;
+            T.vb = TWO && T.va && tp + T.TP < cc;
+            T.a = T.va ? pos4[T.qa] : make_double4(0, 0, 0, 0);
+            T.b = T.vb ? pos4[T.qb] : T.a;
             // initial pairs: (X_e+1, C) for every other child C of every ancestor X_e
             const int n0 = lane < D ? Pth.topo[lane].y - 1 : 0;
             const int incl = wave_incl_scan(n0);
@@ -812,7 +832,7 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
                 St.loff[0] = tl.y;
             }
             int nt = 0, nl = 1, iters = 0;
-            TargetSums A;
+            TargetSums A, B;
             double fgx = 0.0, fgy = 0.0, fgz = 0.0, fc = 0.0;
             __syncthreads();
             while (sp > 0) {
@@ -827,7 +847,7 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
                     __syncthreads();
                 }
                 if (nl + 64 > FM_LEAVES) {
-                    eval_leaves1<FP32C>(nl, leaves, St, pos4, m, T, e2, phi, A);
+                    eval_leaves1<FP32C, TWO>(nl, leaves, St, pos4, m, T, e2, phi, A, B);
                     nl = 0;
                     __syncthreads();
                 }
@@ -893,50 +913,49 @@ __global__ void __launch_bounds__(64) k_fmm(DevCtl* ctl, const int* __restrict__
             __syncthreads();
             if (phi) fmm_eval_terms<true>(nt, tnode, tdep, Pth, D, mom0, e2, fgx, fgy, fgz, fc);
             else fmm_eval_terms<false>(nt, tnode, tdep, Pth, D, mom0, e2, fgx, fgy, fgz, fc);
-            eval_leaves1<FP32C>(nl, leaves, St, pos4, m, T, e2, phi, A);
+            eval_leaves1<FP32C, TWO>(nl, leaves, St, pos4, m, T, e2, phi, A, B);
             fgx = lanes_sum_d(fgx, 1);
             fgy = lanes_sum_d(fgy, 1);
             fgz = lanes_sum_d(fgz, 1);
             fc = lanes_sum_d(fc, 1);
-            // each target's P partial sums (lanes t + cc ph) combined in phase order
-            __syncthreads();
-            St.part.pm[lane] = FP32C ? make_double4(A.kx.value(), A.ky.value(), A.kz.value(), A.kp.value())
-                                     : make_double4(A.gx, A.gy, A.gz, A.ph);
-            __syncthreads();
-            if (T.v && T.ph == 0) {
+            // each target's P partial sums (lanes tp + TP ph) combined in phase order
+            for (int h = 0; h < (TWO ? 2 : 1); ++h) {
+                __syncthreads();
+                if (FP32C) St.part.pm[lane] = make_double4(A.kx.value(), A.ky.value(), A.kz.value(), A.kp.value());
+                else St.part.pm[lane] = h ? make_double4(B.gx, B.gy, B.gz, B.ph) : make_double4(A.gx, A.gy, A.gz, A.ph);
+                __syncthreads();
+                if (!(h ? T.vb : T.va) || T.ph != 0) continue;
                 double4 r = St.part.pm[lane];
                 for (int k = 1; k < T.P; ++k) {
-                    const double4 o = St.part.pm[lane + k * cc];
+                    const double4 o = St.part.pm[lane + k * T.TP];
                     r.x += o.x;
                     r.y += o.y;
                     r.z += o.z;
                     r.w += o.w;
                 }
-                {
-                    const int q = T.q;
-                    const double4 me = T.a;
-                    const double lin = fma(fgx, me.x - cl.y, fma(fgy, me.y - cl.z, fgz * (me.z - cl.w)));
-                    const double gx = G * (r.x + fgx), gy = G * (r.y + fgy), gz = G * (r.z + fgz);
-                    double ph = G * (r.w + (fc - lin));
-                    if (eps > 0.0) {  // take out the self pair's potential term (see eval_leaves1)
-                        const double is = FP32C ? (double)__builtin_amdgcn_rsqf((float)e2) : rsq_nr1(e2);
-                        ph += G * (m[q] * is);
-                    }
-                    if (accumulate) {
-                        gxo[q] += gx;
-                        gyo[q] += gy;
-                        gzo[q] += gz;
-                        if (deo) {  // thermokinetic form: the work of gravity on e = u + v^2/2
-                            const double4 v = vel4[q];
-                            deo[q] += fma(v.x, gx, fma(v.y, gy, v.z * gz));
-                        }
-                    } else {
-                        gxo[q] = gx;
-                        gyo[q] = gy;
-                        gzo[q] = gz;
-                    }
-                    if (phi) pho[q] = ph;
+                const int q = h ? T.qb : T.qa;
+                const double4 me = h ? T.b : T.a;
+                const double lin = fma(fgx, me.x - cl.y, fma(fgy, me.y - cl.z, fgz * (me.z - cl.w)));
+                const double gx = G * (r.x + fgx), gy = G * (r.y + fgy), gz = G * (r.z + fgz);
+                double ph = G * (r.w + (fc - lin));
+                if (eps > 0.0) {  // take out the self pair's potential term (see eval_leaves1)
+                    const double is = FP32C ? (double)__builtin_amdgcn_rsqf((float)e2) : rsq_nr1(e2);
+                    ph += G * (m[q] * is);
                 }
+                if (accumulate) {
+                    gxo[q] += gx;
+                    gyo[q] += gy;
+                    gzo[q] += gz;
+                    if (deo) {  // thermokinetic form: the work of gravity on e = u + v^2/2
+                        const double4 v = vel4[q];
+                        deo[q] += fma(v.x, gx, fma(v.y, gy, v.z * gz));
+                    }
+                } else {
+                    gxo[q] = gx;
+                    gyo[q] = gy;
+                    gzo[q] = gz;
+                }
+                if (phi) pho[q] = ph;
             }
         }
     }
