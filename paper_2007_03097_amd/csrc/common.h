@@ -297,81 +297,35 @@ __device__ __forceinline__ int lcp_digits(u64 a, u64 b) {
 
 // ---------------------------------------------------------------------------------------
 // M4 cubic spline (support 2h): W = w(q) / (pi h^3), grad_a W_ab = r_ab g(q) / (pi h^5),
-// g = w'(q) / q; and compensated FP32 accumulators.  Both pieces are evaluated and one is
+// g = w'(q) / q; and compensated FP32 accumulators.  Both pieces of w are evaluated and one is
 // selected, so a wavefront never splits on q.
 
-__device__ __forceinline__ double m4_w(double q) {
-    const double t = fmax(2.0 - q, 0.0);
-    const double wo = 0.25 * (t * t * t);
-    const double wi = fma(q * q, fma(0.75, q, -1.5), 1.0);
-    return q < 1.0 ? wi : wo;
-}
 // g(q) given 1/q (unused, and may be inf or NaN, for q < 1)
-__device__ __forceinline__ double m4_g(double q, double inv_q) {
-    const double t = fmax(2.0 - q, 0.0);
-    const double go = -0.75 * (t * t) * inv_q;
-    const double gi = fma(2.25, q, -3.0);
-    return q < 1.0 ? gi : go;
-}
 __device__ __forceinline__ float m4_wf(float q) {
     const float t = fmaxf(2.0f - q, 0.0f);
     const float wo = 0.25f * (t * t * t);
     const float wi = fmaf(q * q, fmaf(0.75f, q, -1.5f), 1.0f);
     return q < 1.0f ? wi : wo;
 }
-__device__ __forceinline__ float m4_gf(float q, float inv_q) {
-    const float t = fmaxf(2.0f - q, 0.0f);
-    const float go = -0.75f * (t * t) * inv_q;
-    const float gi = fmaf(2.25f, q, -3.0f);
-    return q < 1.0f ? gi : go;
-}
 
-// FP64 reciprocal and square root for the pair sums, from the hardware estimates refined
-// by Newton-Raphson steps (reciprocal: r <- r + r (1 - x r), twice) and by one Goldschmidt
-// step plus one Newton correction (square root); a few ulp, not correctly rounded.
-// rcp_nr: x positive and normal.  sqrt_nr: a >= 0 (0 gives 0).
-__device__ __forceinline__ double rcp_nr(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
+// FP64 reciprocal and reciprocal square root of positive, normal arguments for the pair sums: the
+// hardware estimates refined by one third-order step, r (1 + e + e^2) and y (1 + e/2 + 3 e^2/8) with e the
+// estimate's residual (about 1e-7); within 1 ulp, not correctly rounded.
+__device__ __forceinline__ double rcp_nr3(double x) {
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(fma(e, e, e), r, r);
 }
-// 1/sqrt(a) for a positive and normal: two Newton steps y <- y (3/2 - a y^2 / 2).
-__device__ __forceinline__ double rsq_nr(double a) {
-    double y = __builtin_amdgcn_rsq(a);
-    const double h = 0.5 * a;
-    y = y * fma(-h * y, y, 1.5);
-    return y * fma(-h * y, y, 1.5);
+__device__ __forceinline__ double rsq_nr3(double a) {
+    const double y = __builtin_amdgcn_rsq(a);
+    const double e = fma(-a * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 // One Newton step only: the hardware estimate (~5e-8 relative) refined to ~4e-15, for sums
 // whose own approximation error is far larger (tree gravity).
 __device__ __forceinline__ double rsq_nr1(double a) {
     const double y = __builtin_amdgcn_rsq(a);
     return y * fma(-0.5 * a * y, y, 1.5);
-}
-__device__ __forceinline__ double sqrt_nr(double a) {
-    const double y = __builtin_amdgcn_rsq(a);
-    double r = a * y, h = 0.5 * y;
-    const double e = fma(-r, h, 0.5);
-    r = fma(r, e, r);
-    h = fma(h, e, h);
-    const double d = fma(-r, r, a);
-    r = fma(d, h, r);
-    return a > 0.0 ? r : 0.0;
-}
-// sqrt(a) and 1/sqrt(a) together, a >= 0: the Goldschmidt step of sqrt_nr refines both;
-// the inverse to about 1e-14 relative (a == 0 gives sqrt 0 and a non-finite inverse).
-__device__ __forceinline__ double sqrt_rsq_nr(double a, double& inv) {
-    const double y = __builtin_amdgcn_rsq(a);
-    double r = a * y, h = 0.5 * y;
-    const double e = fma(-r, h, 0.5);
-    r = fma(r, e, r);
-    h = fma(h, e, h);
-    const double d = fma(-r, r, a);
-    r = fma(d, h, r);
-    inv = 2.0 * h;
-    return a > 0.0 ? r : 0.0;
 }
 
 // Kahan accumulator (explicit operation order; the library is built without floating-point

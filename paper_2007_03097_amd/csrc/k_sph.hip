@@ -56,26 +56,96 @@ void launch_thermo_from_caller(hipStream_t s, const DevPtrs& d, const Dims& dm, 
 
 constexpr int PAIR_THREADS = 256;
 constexpr int DENS_CHUNK = 512;
-// Union sources staged per round of the force pass: FP64 records are 96 bytes, so 256 keep six
-// workgroups per CU; the 48-byte FP32C records take 512, which covers most groups' union in one
-// round (a wave runs each round as long as its busiest target, so fewer rounds waste fewer lanes).
-constexpr int FORCE_CHUNK = 256;
+// Union sources staged per round of the force pass: the largest counts that leave four workgroups a CU
+// (88-byte records in FP64, 80-byte ones in FP32C).  A wave runs each round as long as its busiest
+// target, so a union in one round wastes fewer lanes: at 987,840 particles in groups of 64 FP64 takes
+// 239 us at 256 a round (seven workgroups a CU), 232 at 384 and 204 at 464; at 131,101 in groups of 32,
+// with smaller unions, 42 and 44 us.  512 threads a workgroup: 288 us (half the entries a thread).
+constexpr int FORCE_CHUNK = 464;
 constexpr int FORCE_CHUNK_F = 512;
 
-// Density term of one pair: FP64, or FP32 on group-origin offsets with Kahan
-// compensation.  One term is m_b w(r/h_ab) / h_ab^3 (1/pi applied at the end).
+// A thread's entries of its target's list: slots phi, phi + PL, ... of a list whose slots lie n_g entries
+// apart, as byte offsets from the group's (uniform) base.
+struct Entries {
+    const char* base;
+    u32 off, step, end, last;
+    int a0, a1, a2, a3;  // the entries of the next four slots
+    __device__ __forceinline__ Entries(const u16* b, int ng, int t, int phi, int PL, int cnt)
+        : base(reinterpret_cast<const char*>(b)) {
+        off = 2u * (u32)(phi * ng + t);
+        step = 2u * (u32)(PL * ng);
+        end = 2u * (u32)(cnt * ng + t);
+        last = cnt > 0 ? end - 2u * (u32)ng : 2u * (u32)t;  // slot 0 of an empty list exists too
+        load();
+    }
+    __device__ __forceinline__ int at(u32 o) const { return *reinterpret_cast<const u16*>(base + min(o, last)); }
+    __device__ __forceinline__ void load() {
+        a0 = at(off);
+        a1 = at(off + step);
+        a2 = at(off + 2 * step);
+        a3 = at(off + 3 * step);
+    }
+    // Hands the entries below ce (those of the staged round; entries ascend) to add, in batches of four
+    // that are read one batch ahead.  Slots are clamped into the list; off < end decides.  A batch that
+    // ends early ends the round too: the next batch's entries are beyond ce or the list's end as well.
+    // The next batch is carried by the loop, or the compiler sinks each load to the test that uses it.
+    template <typename Add>
+    __device__ __forceinline__ void round(int ce, Add&& add) {
+        auto take = [&](int r) {
+            if (!(off < end && r < ce)) return false;
+            add(r);
+            off += step;
+            return true;
+        };
+        while (off < end && a0 < ce) {
+            const int b0 = at(off + 4 * step), b1 = at(off + 5 * step), b2 = at(off + 6 * step), b3 = at(off + 7 * step);
+            add(a0);
+            off += step;
+            if (take(a1))
+                if (take(a2)) take(a3);
+            a0 = b0;
+            a1 = b1;
+            a2 = b2;
+            a3 = b3;
+        }
+    }
+};
+
+// Both passes are bound by VALU issue (FP64 at 987,840 particles: 65-70% of the issue slots, the rest waits
+// for list entries and at the group's ends), so the pair term is written for few instructions: density
+// 145 -> 119 us, forces 279 -> 204 us with PairGeo, the byte offsets and batches of Entries and the
+// force pass's one round.
+//
+// Geometry of one pair in FP64 from one reciprocal square root: with T = h_a + h_b = 2 h_ab,
+// y = 1/(r T) gives r/T = r^2 y and 1/T^2 = (r^2 y) y, without a square root or a reciprocal of its own.
+// r^2 is held above 1e-180 (a pair at the same place: r/T then vanishes beside 1 and the direction is 0).
+struct PairGeo {
+    double T, s, r2, y, qh, iT2;  // s = T^2, qh = r/T = q/2, iT2 = 1/T^2
+    __device__ __forceinline__ PairGeo(double dx, double dy, double dz, double ha, double hb) {
+        T = ha + hb;
+        s = T * T;
+        r2 = fmax(fma(dx, dx, fma(dy, dy, dz * dz)), 1e-180);
+        y = rsq_nr3(r2 * s);
+        qh = r2 * y;
+        iT2 = qh * y;
+    }
+};
+
+// Density term of one pair: FP64, or FP32 on group-origin offsets with Kahan compensation.  One term is
+// m_b w(r/h_ab) / h_ab^3 (1/pi applied at the end); in FP64 m_b (u^3 - v^3/2) / T^3 with u = 1 - r/T and
+// v = max(1 - 2 r/T, 0), that is 1/16 of it (w = (2-q)^3/4 - (1-q)^3, the second part for q < 1 only).
 template <bool FP32C>
 struct DensAcc;
 template <>
 struct DensAcc<false> {
     double s = 0.0;
     __device__ __forceinline__ void add(const double4 me, const double4 b, double mb) {
-        const double dx = me.x - b.x, dy = me.y - b.y, dz = me.z - b.z;
-        const double r = sqrt_nr(fma(dx, dx, fma(dy, dy, dz * dz)));
-        const double ih = rcp_nr(0.5 * (me.w + b.w));
-        s = fma(mb * m4_w(r * ih), ih * ih * ih, s);
+        const PairGeo g(me.x - b.x, me.y - b.y, me.z - b.z, me.w, b.w);
+        const double u = 1.0 - g.qh, v = fmax(fma(-2.0, g.qh, 1.0), 0.0);
+        const double w = fma(u * u, u, -(v * v) * (0.5 * v));
+        s = fma(mb * w, g.iT2 * (g.iT2 * g.T), s);
     }
-    __device__ __forceinline__ double value() const { return s; }
+    __device__ __forceinline__ double value() const { return 16.0 * s; }
 };
 template <>
 struct DensAcc<true> {
@@ -168,70 +238,21 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_density(
         const double4 mp = tv ? pos4[q] : make_double4(org.x, org.y, org.z, 1);
         const typename DensSrc<FP32C>::Rec me = DensSrc<FP32C>::target(mp, org);
         const int cnt = tv ? nbr_cnt[q] : 0;
-        const u16* lst = nbr + (size_t)g.x * cap + t;
+        Entries E(nbr + (size_t)g.x * cap, g.y, t, phi, PL, cnt);
         const int* un = uni + (size_t)g.x * cap;
         const int nu = ucnt[gi];
+        const double mq = m[q], uq = u_eos[q];  // for the end: in flight during the sums
         DensAcc<FP32C> acc;
-        auto stage = [&](int c0, int cn) {  // union members c0 .. c0 + cn - 1 into LDS
+        for (int c0 = 0; c0 < nu; c0 += DENS_CHUNK) {  // union members c0 .. c0 + cn - 1 through LDS
+            const int cn = nu - c0 < DENS_CHUNK ? nu - c0 : DENS_CHUNK;
             __syncthreads();
             for (int i = tid; i < cn; i += PAIR_THREADS) {
                 const int b = un[c0 + i];
                 S.put(i, pos4[b], m[b], org);
             }
+            if (c0) E.load();
             __syncthreads();
-        };
-        if constexpr (FP32C) {
-            // The thread's entries k = phi, phi + PL, ... are read in batches of four, one batch
-            // ahead of the batch being summed; every load goes to a register that is consumed only
-            // after the next batch's loads are issued, and leaving a staged round keeps no loaded
-            // value (the next round reloads from its slot), so no load is waited for early.  Slots
-            // are clamped into the list (slot 0 of an empty list exists too); k < cnt decides.
-            const int kmax = cnt > 0 ? cnt - 1 : 0;
-            auto entry = [&](int kk) -> int { return lst[min(kk, kmax) * g.y]; };
-            int k = phi;
-            for (int c0 = 0; c0 < nu; c0 += DENS_CHUNK) {
-                const int cn = nu - c0 < DENS_CHUNK ? nu - c0 : DENS_CHUNK;
-                stage(c0, cn);
-                const int ce = c0 + cn;
-                auto take = [&](int r) {  // sums entry r if it is in the list and in this round
-                    if (!(k < cnt && r < ce)) return false;
-                    acc.add(me, S.rec(r - c0), S.mass[r - c0]);
-                    k += PL;
-                    return true;
-                };
-                int a0 = entry(k), a1 = entry(k + PL), a2 = entry(k + 2 * PL), a3 = entry(k + 3 * PL);
-                while (true) {
-                    const int b0 = entry(k + 4 * PL), b1 = entry(k + 5 * PL), b2 = entry(k + 6 * PL),
-                              b3 = entry(k + 7 * PL);
-                    if (!take(a0) || !take(a1) || !take(a2) || !take(a3)) break;
-                    a0 = entry(k + 4 * PL);
-                    a1 = entry(k + 5 * PL);
-                    a2 = entry(k + 6 * PL);
-                    a3 = entry(k + 7 * PL);
-                    if (!take(b0) || !take(b1) || !take(b2) || !take(b3)) break;
-                }
-            }
-        } else {  // the longer FP64 term hides a four-deep rotation's waits (batches measured slower)
-            int k = phi;
-            int e = k < cnt ? lst[k * g.y] : INT_MAX;
-            int e1 = k + PL < cnt ? lst[(k + PL) * g.y] : INT_MAX;
-            int e2 = k + 2 * PL < cnt ? lst[(k + 2 * PL) * g.y] : INT_MAX;
-            int e3 = k + 3 * PL < cnt ? lst[(k + 3 * PL) * g.y] : INT_MAX;
-            for (int c0 = 0; c0 < nu; c0 += DENS_CHUNK) {
-                const int cn = nu - c0 < DENS_CHUNK ? nu - c0 : DENS_CHUNK;
-                stage(c0, cn);
-                const int ce = c0 + cn;
-                while (e < ce) {
-                    const int kn = k + 4 * PL;
-                    const int en = kn < cnt ? lst[kn * g.y] : INT_MAX;
-                    acc.add(me, S.rec(e - c0), S.mass[e - c0]);
-                    k += PL;
-                    e = e1;
-                    e1 = e2;
-                    e2 = e3;
-                    e3 = en;
-                }
-            }
+            E.round(c0 + cn, [&](int r) { acc.add(me, S.rec(r - c0), S.mass[r - c0]); });
         }
         __syncthreads();
         double* red = reinterpret_cast<double*>(&S);
@@ -241,7 +262,7 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_density(
             double sum = red[t];
             for (int f = 1; f < PL; ++f) sum += red[t + g.y * f];
             const double r_ = sum * M_1_PI_D;
-            double ue = u_eos[q];
+            double ue = uq;
             const double4 mpos = mp;
             if (kin) {  // u_eos holds the total energy e = u + v^2/2 (thermokinetic form)
                 const double4 v = vel4[q];
@@ -253,7 +274,7 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_density(
             rho[q] = r_;
             P[q] = p_;
             cs[q] = c_;
-            hnext[q] = h_coeff * cbrt(m[q] / r_);
+            hnext[q] = h_coeff * cbrt(mq / r_);
             thr4[q] = make_double4(r_, pr2, c_, ue);
             thrf[q] = make_float4((float)r_, (float)pr2, (float)c_, (float)mpos.w);
         }
@@ -279,7 +300,9 @@ template <bool FP32C>
 struct ForceSrc;
 template <>
 struct ForceSrc<false> {
-    Split4<FORCE_CHUNK> pos, vel, thr;
+    Split4<FORCE_CHUNK> pos, vel;
+    double2 rp[FORCE_CHUNK];  // rho, P/rho^2
+    double c[FORCE_CHUNK];    // -(alpha/2) c
 };
 template <>
 struct ForceSrc<true> {
@@ -310,15 +333,15 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_forces(
         const int q = g.x + t;
         const double4 me = tv ? pos4[q] : make_double4(0, 0, 0, 1);
         const int cnt = tv ? nbr_cnt[q] : 0;
-        const u16* lst = nbr + (size_t)g.x * cap + t;
+        Entries E(nbr + (size_t)g.x * cap, g.y, t, phi, PL, cnt);
         const int* un = uni + (size_t)g.x * cap;
         const int nu = ucnt[gi];
-        int k = phi;
         double fx, fy, fz, fu;
         if constexpr (!FP32C) {
-            int e = k < cnt ? lst[k * g.y] : INT_MAX;
             const double4 mv = tv ? vel4[q] : make_double4(0, 0, 0, 0);
             const double4 mt = tv ? thr4[q] : make_double4(1, 0, 0, 0);
+            const double al2 = -0.5 * alpha, be2 = 0.5 * beta, ep4 = 0.25 * eps_av;
+            const double mc = al2 * mt.z;
             double sx = 0, sy = 0, sz = 0, su = 0;
             for (int c0 = 0; c0 < nu; c0 += FORCE_CHUNK) {
                 const int cn = nu - c0 < FORCE_CHUNK ? nu - c0 : FORCE_CHUNK;
@@ -327,61 +350,54 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_forces(
                     const int b = un[c0 + i];
                     S.pos.put(i, pos4[b]);
                     S.vel.put(i, vel4[b]);
-                    S.thr.put(i, thr4[b]);
+                    const double4 tb = thr4[b];
+                    S.rp[i] = make_double2(tb.x, tb.y);
+                    S.c[i] = al2 * tb.z;
                 }
+                if (c0) E.load();
                 __syncthreads();
-                const int ce = c0 + cn;
-                while (e < ce) {
-                    const int kn = k + PL;
-                    const int en = kn < cnt ? lst[kn * g.y] : INT_MAX;
+                E.round(c0 + cn, [&](int e) {
                     const int j = e - c0;
                     const double4 sb = S.pos.get(j);
                     const double4 vb = S.vel.get(j);
-                    const double4 tb = S.thr.get(j);
+                    const double2 tb = S.rp[j];
                     const double dx = me.x - sb.x, dy = me.y - sb.y, dz = me.z - sb.z;
-                    const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-                    double ir;
-                    const double r = sqrt_rsq_nr(r2, ir);
-                    const double hab = 0.5 * (me.w + sb.w);
-                    const double ih = rcp_nr(hab);
-                    const double ih2 = ih * ih;
-                    const double qq = r * ih;
-                    const double gw = m4_g(qq, hab * ir) * (ih2 * ih2 * ih) * M_1_PI_D;
+                    const PairGeo p(dx, dy, dz, me.w, sb.w);
+                    // g(q)/h_ab^5 = -48 G/T^5: G = 2 - 3 r/T for q < 1, else u^2/(r/T) with u = 1 - r/T
+                    const double u = 1.0 - p.qh;
+                    const double G = p.qh < 0.5 ? fma(-3.0, p.qh, 2.0) : (u * u) * (p.s * p.y);
+                    const double F = (vb.w * G) * ((p.iT2 * p.iT2) * (p.iT2 * p.T));
                     const double wx = mv.x - vb.x, wy = mv.y - vb.y, wz = mv.z - vb.z;
                     const double vr = fma(wx, dx, fma(wy, dy, wz * dz));
                     double Pi = 0.0;
-                    if (vr < 0.0) {  // one reciprocal of den * rhobar gives 1/den and 1/rhobar
-                        const double den = fma(eps_av * hab, hab, r2);
-                        const double rb = 0.5 * (mt.x + tb.x);
-                        const double inv = rcp_nr(den * rb);
-                        const double mu = hab * vr * (rb * inv);
-                        Pi = fma(-alpha * 0.5 * (mt.z + tb.z), mu, beta * mu * mu) * (den * inv);
+                    if (vr < 0.0) {  // one reciprocal of den (rho_a + rho_b) gives 1/den and 1/(rho_a + rho_b)
+                        const double den = fma(ep4, p.s, p.r2);
+                        const double rs = mt.x + tb.x;
+                        const double inv = rcp_nr3(den * rs);
+                        const double mu2 = (p.T * vr) * (rs * inv);  // 2 mu
+                        Pi = (fma(be2, mu2, mc + S.c[j]) * mu2) * (den * inv);
                     }
-                    const double term = vb.w * ((mt.y + tb.y) + Pi) * gw;
-                    sx = fma(-term, dx, sx);
-                    sy = fma(-term, dy, sy);
-                    sz = fma(-term, dz, sz);
+                    const double c = F * ((mt.y + tb.y) + Pi);
+                    sx = fma(c, dx, sx);
+                    sy = fma(c, dy, sy);
+                    sz = fma(c, dz, sz);
                     if (THERMO) {  // eq. (8): P_a v_b/rho_a^2 + P_b v_a/rho_b^2 + (v_a + v_b)/2 Pi
                         const double var = fma(mv.x, dx, fma(mv.y, dy, mv.z * dz));
                         const double vbr = fma(vb.x, dx, fma(vb.y, dy, vb.z * dz));
-                        su = fma(-vb.w * gw, fma(mt.y, vbr, fma(tb.y, var, 0.5 * Pi * (var + vbr))), su);
+                        su = fma(F, fma(mt.y, vbr, fma(tb.y, var, 0.5 * Pi * (var + vbr))), su);
                     } else {
-                        su = fma(vb.w * fma(0.5, Pi, mt.y) * gw, vr, su);
+                        su = fma(-F * fma(0.5, Pi, mt.y), vr, su);
                     }
-                    k = kn;
-                    e = en;
-                }
+                });
             }
-            fx = sx; fy = sy; fz = sz; fu = su;
+            constexpr double K = 48.0 * M_1_PI_D;
+            fx = K * sx; fy = K * sy; fz = K * sz; fu = K * su;
         } else {
             const double4 mv = tv ? vel4[q] : make_double4(0, 0, 0, 0);
             const float4 mt = tv ? thrf[q] : make_float4(1, 0, 0, 1);
             const float alf = (float)alpha, bef = (float)beta, epf = (float)eps_av;
             const float ipi = (float)M_1_PI_D;
             Kahan sx, sy, sz, su;
-            // entries read in batches of four, one batch ahead (as in the FP32C density pass)
-            const int kmax = cnt > 0 ? cnt - 1 : 0;
-            auto entry = [&](int kk) -> int { return lst[min(kk, kmax) * g.y]; };
             for (int c0 = 0; c0 < nu; c0 += FORCE_CHUNK_F) {
                 const int cn = nu - c0 < FORCE_CHUNK_F ? nu - c0 : FORCE_CHUNK_F;
                 __syncthreads();
@@ -391,11 +407,10 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_forces(
                     S.vel.put(i, vel4[b]);
                     S.thr[i] = thrf[b];
                 }
+                if (c0) E.load();
                 __syncthreads();
-                const int ce = c0 + cn;
-                auto take = [&](int ent) {
-                    if (!(k < cnt && ent < ce)) return false;
-                    const int j = ent - c0;
+                E.round(c0 + cn, [&](int e) {
+                    const int j = e - c0;
                     const double4 sb = S.pos.get(j);
                     const double4 vb = S.vel.get(j);
                     const float4 tb = S.thr[j];
@@ -440,20 +455,7 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_forces(
                     } else {
                         su.add(mb * fmaf(0.5f, Pi, mt.y) * gw * vr);
                     }
-                    k += PL;
-                    return true;
-                };
-                int a0 = entry(k), a1 = entry(k + PL), a2 = entry(k + 2 * PL), a3 = entry(k + 3 * PL);
-                while (true) {
-                    const int b0 = entry(k + 4 * PL), b1 = entry(k + 5 * PL), b2 = entry(k + 6 * PL),
-                              b3 = entry(k + 7 * PL);
-                    if (!take(a0) || !take(a1) || !take(a2) || !take(a3)) break;
-                    a0 = entry(k + 4 * PL);
-                    a1 = entry(k + 5 * PL);
-                    a2 = entry(k + 6 * PL);
-                    a3 = entry(k + 7 * PL);
-                    if (!take(b0) || !take(b1) || !take(b2) || !take(b3)) break;
-                }
+                });
             }
             fx = sx.value(); fy = sy.value(); fz = sz.value(); fu = su.value();
         }

@@ -4,7 +4,8 @@ import pytest
 
 from workloads import polytrope_n1, uniform_random
 
-from gpu_helpers import gpu_gravity, gpu_keys_order, gpu_neighbors, gpu_tree, make_ctx, parts, to_np
+from gpu_helpers import (gpu_density, gpu_forces, gpu_gravity, gpu_keys_order, gpu_neighbors, gpu_tree, make_ctx, parts,
+                         to_np)
 
 pytestmark = pytest.mark.gpu
 
@@ -167,3 +168,51 @@ def test_neighbors_at_any_scale(orc, scale, shift, group):
     off, idx = gpu_neighbors(ctx, ps.n)
     ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
     assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
+
+
+# ---------------------------------------------------------------------------- pair sums
+@pytest.mark.parametrize("group", [8, 64])
+@pytest.mark.parametrize("scale", [1e-30, 1.0, 1e25])
+def test_pair_sums_at_any_scale(orc, scale, group):
+    """FP64 density and forces where r/h runs from 0 (coincident particles) over 1e-9 to the support's
+    edge, lists from one entry to several batches, unions over several staged rounds.  Every operation
+    of a term is within a few ulp, and u = 1 - r/2h loses no more than an ulp of 1 at the edge, where
+    the term itself is that small beside the sum: 1e-12 of the sum of the terms' magnitudes."""
+    ps = uniform_random(1503, seed=91, h=(0.01, 0.2))
+    for f in ("x", "y", "z"):
+        a = getattr(ps, f)
+        a[1:40:2] = a[0:39:2]              # coincident pairs
+        a[41:80:2] = a[40:79:2] + 1e-11    # pairs at about 1e-9 h
+    for f in ("x", "y", "z", "h"):
+        setattr(ps, f, getattr(ps, f) * scale)
+    ctx = make_ctx(ps.n, group_size=group, nbr_capacity=2048)
+    gpu_keys_order(ctx, parts(ps))
+    got = gpu_density(ctx, ps.n)
+    csr = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+    ref = orc.density(ps.fields(), csr)
+    for a, b in zip(got, ref):
+        assert np.max(np.abs(a - b) / np.abs(b)) <= 1e-12
+    ax, ay, az, du = gpu_forces(ctx, ps.n)
+    r_ax, r_ay, r_az, r_du, Sa, Su = orc.forces(ps.fields(), ref[0], ref[1], ref[2], csr)
+    assert np.all(np.sqrt((ax - r_ax) ** 2 + (ay - r_ay) ** 2 + (az - r_az) ** 2) <= 1e-12 * Sa)
+    assert np.all(np.abs(du - r_du) <= 1e-12 * Su)
+
+
+# ---------------------------------------------------------------------------- node-node gravity
+@pytest.mark.parametrize("eps", [0.0, 0.02])
+@pytest.mark.parametrize("leaf", [1, 2, 3, 31, 32, 33, 63, 64])
+def test_fmm_leaf_populations(orc, leaf, eps):
+    """Leaves of one to 64 targets (two a lane, odd counts) and, past 64, several passes over a leaf:
+    within 1e-12 of each particle's absolute-sum scale."""
+    import paper_2007_03097_amd as sph
+    ps = uniform_random(1999, seed=92)
+    if eps > 0.0:
+        for f in ("x", "y", "z"):
+            getattr(ps, f)[:131] = getattr(ps, f)[0]    # one leaf of 131: 64 + 64 + 3
+    ctx = make_ctx(ps.n, theta=0.6, G=1.0, soft_eps=eps, leaf_size=leaf, gravity_scheme=sph.SPH_GRAVITY_FMM)
+    k, o = gpu_keys_order(ctx, parts(ps))
+    gx, gy, gz, phi = gpu_gravity(ctx, ps.n)
+    box = orc.bbox(ps.x, ps.y, ps.z)
+    r = orc.fmm_gravity(ps.x[o], ps.y[o], ps.z[o], ps.m[o], orc.octree(k[o], leaf), box, orc.scale(box, 21), 0.6, 1.0, eps)
+    d = np.sqrt((gx[o] - r["gx"]) ** 2 + (gy[o] - r["gy"]) ** 2 + (gz[o] - r["gz"]) ** 2)
+    assert np.max(d / r["sg"]) <= 1e-12 and np.max(np.abs(phi[o] - r["phi"]) / r["sp"]) <= 1e-12
