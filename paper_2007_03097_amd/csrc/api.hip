@@ -280,6 +280,7 @@ static sph_status prepare(sph_ctx* c, const sph_particles* p) {
         }
         dm.group_grid = (int)(8 * u1);
         dm.pair_grid = (int)(8 * u4);
+        dm.wave_cap = c->waves > 0 ? c->waves * 256 : INT_MAX;
     }
     if (!same) {
         if (!chunks.empty())

@@ -50,6 +50,7 @@ struct DevCtl {
     int level_count[24];          // nodes per level
     int level_off[24];            // exclusive prefix of level_count
     int walk_level;               // level at which a single set's neighbour walks start (k_top_moments)
+    int fmm_heavy[8];             // leaves of an XCD's share that a whole workgroup takes (node-node gravity)
     u64 box_enc[512 * 6];         // per segment: ordered-integer min x,y,z then max x,y,z
     double box[512 * 6];          // decoded per-segment box lo.xyz, hi.xyz
     double scale[512];            // 2^B / L per segment (0 when L == 0)
@@ -130,6 +131,7 @@ struct Dims {
     int nbr_cap;
     int group_grid;   // grid (multiple of 8) of the one-wave per-group kernels
     int pair_grid;    // the same for the four-wave pair kernels (density, forces)
+    int wave_cap;     // wavefronts that a per-group grid may hold
     int n_chunks;
     int node_cap;
     int min_level;    // 3 when batched, else 0
@@ -212,6 +214,13 @@ __device__ __forceinline__ double wave_min(double v) {
 }
 __device__ __forceinline__ double wave_max(double v) {
     return wave_reduce_d(v, [](double a, double b) { return fmax(a, b); });
+}
+
+// Orders LDS accesses of one wave (its lanes run in step and LDS serves them in order).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Owner of each of 64 consecutive items p0 + lane of a concatenation whose parts start at the

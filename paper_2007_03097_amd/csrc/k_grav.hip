@@ -1,8 +1,8 @@
 // Octree self-gravity (Sec. 2.2.2 of arXiv:2007.03097, eq. (10), with Plummer softening
 // and quadrupole moments).
 //
-// One wavefront per target group, two targets per lane.  The wide walk tests up to 64 nodes at once against the
-// group's box: a cell B is accepted for the whole group when its particle box does not touch
+// One, two or four wavefronts per target group, two targets per lane.  The wide walk (by the first of them)
+// tests up to 64 nodes at once against the group's box: a cell B is accepted for the whole group when its particle box does not touch
 // the group box and b_B < theta d, b_B being the distance from B's centre of mass to the
 // farthest corner of its particle box (B's radius about the centre of mass) and d the
 // distance from the centre of mass to the group box (theta = 0 opens everything: the exact
@@ -14,8 +14,8 @@
 // with R = r_a - R_B, s^2 = |R|^2 + eps^2, I = sum m y y^T about R_B.  Unaccepted leaves
 // contribute softened particle sums with the target itself skipped.  Cell and leaf lists
 // live in LDS and are evaluated whenever they fill, so the walk needs no global scratch;
-// the evaluation stages cell moments (32 at a time in FP64, 64 in FP32C) and leaf particles
-// (64 at a time) through LDS.
+// the evaluation stages cell moments (32 a wavefront at a time in FP64, 64 in FP32C) and leaf
+// particles (64 a wavefront at a time) through LDS.
 #include "common.h"
 
 constexpr int GW_STACK = 768;
@@ -27,39 +27,47 @@ constexpr int GW_LEAVES = 256;
 constexpr int DFS_HEADROOM = 7 * MAX_LEVEL + 8;
 static_assert(GW_STACK > 2 * DFS_HEADROOM, "room for wide rounds above the headroom");
 
-// LDS staging of one evaluation: cell moments in the cell phase, particles in the leaf phase.
-// FP32C stages FP32 records, 64 cells per round; FP64 stages 32 cells of 96 bytes per round.
-// Either way the walk's LDS stays near 10 KB per workgroup (16 workgroups per CU).
-template <bool FP32C>
+// W wavefronts work on one unit: the thread's index among them, and their barrier (one wavefront alone
+// needs none, only its LDS accesses in order).
+template <int W>
+__device__ __forceinline__ int unit_thread() {
+    return W == 1 ? lane_id() : (int)threadIdx.x;
+}
+template <int W>
+__device__ __forceinline__ void unit_sync() {
+    if constexpr (W == 1) wave_lds_fence();
+    else __syncthreads();
+}
+
+// LDS staging of one evaluation by W wavefronts: cell moments in the cell phase, particles in the leaf
+// phase.  FP32C stages FP32 records, 64 W cells per round; FP64 stages 32 W cells of 96 bytes per round.
+// With one wavefront the walk's LDS stays near 10 KB per workgroup (16 workgroups per CU).
+template <bool FP32C, int W>
 struct GravStage;
-template <>
-struct GravStage<false> {
+template <int W>
+struct GravStage<false, W> {
     union {
         struct {
-            double4 c0[32], c1[32], c2[32];  // the record of cell_term
+            double4 c0[32 * W], c1[32 * W], c2[32 * W];  // the record of cell_term
         } cell;
         struct {
-            double4 pm[64];  // (x, y, z, m)
-            int src[64];     // particle index (self test without softening)
+            double4 pm[64 * W];  // (x, y, z, m)
+            int src[64 * W];     // particle index (self test without softening)
         } part;
-        double red[4][64];   // a target's partial sums
+        double red[4][64 * W];   // a target's partial sums
     };
     int loff[GW_LEAVES + 1];  // particle offsets of the staged leaves
 };
-template <>
-struct GravStage<true> {
+template <int W>
+struct GravStage<true, W> {
     union {
         struct {             // positions as offsets from the group origin
-            float4 c0[64], c1[64], c2[64];
+            float4 c0[64 * W], c1[64 * W], c2[64 * W];
         } cellf;
         struct {
-            float4 pm[64];
-            int src[64];
+            float4 pm[64 * W];
+            int src[64 * W];
         } partf;
-        struct {
-            double4 pm[64];
-            int src[64];
-        } part;
     };
     int loff[GW_LEAVES + 1];
 };
@@ -176,10 +184,11 @@ __device__ __forceinline__ void part_term_f(const float4 me, const float4 sb, fl
     if constexpr (PH) S.tph = fmaf(-sb.w, i1, S.tph);
 }
 
-// Two targets per lane: tp and tp + TP; the P = 64 / TP lanes with the same tp split every
-// staged tile, so each LDS read of a cell or particle feeds two evaluations.  FP64: TP is half
-// the group's targets, rounded up (lanes past P TP idle); FP32C, whose sums depend in their last
-// bits on how the tiles are split: the fewest power of two that holds them.
+// Two targets per lane: tp and tp + TP; the P lanes with the same tp split every staged tile, so each LDS
+// read of a cell or particle feeds two evaluations.  FP64: TP is half the group's targets, rounded up,
+// and P = 64 W / TP over all W wavefronts (lanes past P TP idle).  FP32C, whose sums depend in their last
+// bits on how the tiles are split: TP the fewest power of two that holds the targets, P = 64 / TP, and
+// with W = 2 each wavefront serves one of the lane's two targets.
 struct GravTargets {
     double4 a, b;
     float4 fa, fb;  // FP32C: offsets from the group origin o
@@ -197,46 +206,50 @@ struct BoolC {
     static constexpr bool value = B;
 };
 
-template <bool FP32C>
-__device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C>& St, const double4* __restrict__ mom0,
+template <bool FP32C, int W>
+__device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C, W>& St, const double4* __restrict__ mom0,
                            const double4* __restrict__ mom1, const double4* __restrict__ mom2, const GravTargets& T,
                            double e2, bool phi, TargetSums& A, TargetSums& B) {
-    const int lane = lane_id();
+    const int tid = unit_thread<W>();
     const bool any = T.va || T.vb;
-    constexpr int CS = FP32C ? 64 : 32;  // cells staged per round
+    constexpr bool TWO = !(FP32C && W > 1);
+    constexpr int CS = (FP32C ? 64 : 32) * W;  // cells staged per round
     for (int k0 = 0; k0 < ncell; k0 += CS) {
-        __syncthreads();
-        if (lane < CS && k0 + lane < ncell) {
-            const int c = cells[k0 + lane];
+        unit_sync<W>();
+        if (tid < CS && k0 + tid < ncell) {
+            const int c = cells[k0 + tid];
             const double4 c0 = mom0[c], c1 = mom1[c], c2 = mom2[c];
             if constexpr (FP32C) {
-                St.cellf.c0[lane] = make_float4((float)c0.x, (float)(c0.y - T.o[0]), (float)(c0.z - T.o[1]),
-                                                (float)(c0.w - T.o[2]));
-                St.cellf.c1[lane] = make_float4((float)(3.0 * c1.x), (float)(3.0 * c1.y), (float)(3.0 * c1.z),
-                                                (float)(1.5 * c1.w));
-                St.cellf.c2[lane] = make_float4((float)(3.0 * c2.x), (float)(3.0 * c2.y), (float)(3.0 * c2.z),
-                                                (float)(0.5 * c1.w));
+                St.cellf.c0[tid] = make_float4((float)c0.x, (float)(c0.y - T.o[0]), (float)(c0.z - T.o[1]),
+                                               (float)(c0.w - T.o[2]));
+                St.cellf.c1[tid] = make_float4((float)(3.0 * c1.x), (float)(3.0 * c1.y), (float)(3.0 * c1.z),
+                                               (float)(1.5 * c1.w));
+                St.cellf.c2[tid] = make_float4((float)(3.0 * c2.x), (float)(3.0 * c2.y), (float)(3.0 * c2.z),
+                                               (float)(0.5 * c1.w));
             } else {  // see cell_term
-                St.cell.c0[lane] = c0;
-                St.cell.c1[lane] = make_double4(fma(3.0, c1.x, -c1.w), fma(3.0, c1.y, -c1.w), fma(3.0, c1.z, -c1.w),
-                                                -e2 * c1.w);
-                St.cell.c2[lane] = make_double4(3.0 * c2.x, 3.0 * c2.y, 3.0 * c2.z, 0.0);
+                St.cell.c0[tid] = c0;
+                St.cell.c1[tid] = make_double4(fma(3.0, c1.x, -c1.w), fma(3.0, c1.y, -c1.w), fma(3.0, c1.z, -c1.w),
+                                               -e2 * c1.w);
+                St.cell.c2[tid] = make_double4(3.0 * c2.x, 3.0 * c2.y, 3.0 * c2.z, 0.0);
             }
         }
-        __syncthreads();
+        unit_sync<W>();
         const int cn = ncell - k0 < CS ? ncell - k0 : CS;
-        if (!any) continue;
         auto run = [&](auto ph) {
             constexpr bool PH = decltype(ph)::value;
             if constexpr (FP32C) {
                 const float e2f = (float)e2;
-                for (int k = T.phi; k < cn; k += T.P) {
-                    const float4 a = St.cellf.c0[k], b = St.cellf.c1[k], d = St.cellf.c2[k];
-                    cell_term_f<PH>(T.fa, a, b, d, e2f, A);
-                    cell_term_f<PH>(T.fb, a, b, d, e2f, B);
+                for (int s = 0; s < cn; s += 64) {  // tile by tile, whatever W
+                    const int e = min(s + 64, cn);
+#pragma unroll TWO ? 1 : 4
+                    for (int k = s + T.phi; k < e; k += T.P) {
+                        const float4 a = St.cellf.c0[k], b = St.cellf.c1[k], d = St.cellf.c2[k];
+                        cell_term_f<PH>(T.fa, a, b, d, e2f, A);
+                        if constexpr (TWO) cell_term_f<PH>(T.fb, a, b, d, e2f, B);
+                    }
+                    A.flush_tile();
+                    if constexpr (TWO) B.flush_tile();
                 }
-                A.flush_tile();
-                B.flush_tile();
             } else {
                 for (int k = T.phi; k < cn; k += T.P) {
                     const double4 a = St.cell.c0[k], b = St.cell.c1[k], d = St.cell.c2[k];
@@ -245,119 +258,135 @@ __device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C>& St, co
                 }
             }
         };
-        if (phi) run(BoolC<true>());
-        else run(BoolC<false>());
+        if (any) {
+            if (phi) run(BoolC<true>());
+            else run(BoolC<false>());
+        }
     }
 }
 
 // Particles of the listed leaves (first particles in leaves[], counts in St.loff[], which become
-// offsets), concatenated and staged through LDS 64 at a time (one load per lane per round):
-// put(lane, position, mass, index) writes the staged record, tile(tn) evaluates each staged tile of
+// offsets), concatenated and staged through LDS 64 W at a time (one load per lane per round):
+// put(slot, position, mass, index) writes the staged record, tile(tn) evaluates each staged tile of
 // tn particles.  Returns the number of particles.
-template <typename Stage, typename Tile, typename Put>
+template <int W, typename Stage, typename Tile, typename Put>
 __device__ int stage_leaves_put(int nleaf, int* leaves, Stage& St, const double4* __restrict__ pos4,
-                                const double* __restrict__ m, Tile&& tile,
-                                 Put&& put) {
-    const int lane = lane_id();
+                                const double* __restrict__ m, Tile&& tile, Put&& put) {
+    const int lane = lane_id(), wave = W > 1 ? threadIdx.x >> 6 : 0;
     int total = 0;
-    for (int j0 = 0; j0 < nleaf; j0 += 64) {  // particle counts of the leaves -> offsets
-        const int j = j0 + lane;
-        const int c = j < nleaf ? St.loff[j] : 0;
-        const int incl = wave_incl_scan(c);
-        if (j < nleaf) St.loff[j] = total + incl - c;
-        total += wave_last(incl);
+    if (W == 1 || wave == 0) {
+        for (int j0 = 0; j0 < nleaf; j0 += 64) {  // particle counts of the leaves -> offsets
+            const int j = j0 + lane;
+            const int c = j < nleaf ? St.loff[j] : 0;
+            const int incl = wave_incl_scan(c);
+            if (j < nleaf) St.loff[j] = total + incl - c;
+            total += wave_last(incl);
+        }
+        if (W > 1 && lane == 0) St.loff[nleaf] = total;
     }
-    __syncthreads();
+    unit_sync<W>();
+    if (W > 1) total = St.loff[nleaf];
     int last = -1;
-    for (int p0 = 0; p0 < total; p0 += 64) {
-        const int p = p0 + lane;
-        __syncthreads();
-        const int a = tile_owner(St.loff, nleaf, p0, last);
+    for (int p0 = 0; p0 < total; p0 += 64 * W) {
+        unit_sync<W>();
+        int a = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const int own = tile_owner(St.loff, nleaf, p0 + 64 * w, last);
+            if (w == wave) a = own;
+        }
+        const int p = p0 + unit_thread<W>();
         if (p < total) {
             const int src = leaves[a] + (p - St.loff[a]);
-            put(lane, pos4[src], m[src], src);
+            put(unit_thread<W>(), pos4[src], m[src], src);
         }
-        __syncthreads();
-        tile(total - p0 < 64 ? total - p0 : 64);
+        unit_sync<W>();
+        tile(total - p0 < 64 * W ? total - p0 : 64 * W);
     }
     return total;
 }
 
 // stage_leaves_put with (x, y, z, m) records in FP64.
-template <typename Stage, typename Tile>
+template <int W, typename Stage, typename Tile>
 __device__ int stage_leaves(int nleaf, int* leaves, Stage& St, const double4* __restrict__ pos4,
-                                const double* __restrict__ m, Tile&& tile) {
-    return stage_leaves_put(nleaf, leaves, St, pos4, m, tile, [&](int lane, const double4& ps, double mass, int src) {
-        St.part.pm[lane] = make_double4(ps.x, ps.y, ps.z, mass);
-        St.part.src[lane] = src;
+                            const double* __restrict__ m, Tile&& tile) {
+    return stage_leaves_put<W>(nleaf, leaves, St, pos4, m, tile, [&](int i, const double4& ps, double mass, int src) {
+        St.part.pm[i] = make_double4(ps.x, ps.y, ps.z, mass);
+        St.part.src[i] = src;
     });
 }
 
 // Leaves evaluated by softened particle sums (self excluded) for the lane's two targets.
 // With softening the self pair is evaluated like any other (it adds no force) and its
 // potential term -m_q/eps is taken out by the caller.  Returns the number of sources.
-template <bool FP32C>
-__device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C>& St, const double4* __restrict__ pos4,
-                                const double* __restrict__ m, const GravTargets& T,
-                            double e2, bool phi, TargetSums& A, TargetSums& B) {
+template <bool FP32C, int W>
+__device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C, W>& St, const double4* __restrict__ pos4,
+                           const double* __restrict__ m, const GravTargets& T, double e2, bool phi, TargetSums& A,
+                           TargetSums& B) {
     const bool any = T.va || T.vb;
+    constexpr bool TWO = !(FP32C && W > 1);
     const bool soft = e2 > 0.0;
     if constexpr (FP32C) {
         const float e2f = (float)e2;
+        auto run = [&](int j0, int j1, auto ph) {
+            constexpr bool PH = decltype(ph)::value;
+            if (soft) {
+#pragma unroll TWO ? 1 : 4
+                for (int j = j0 + T.phi; j < j1; j += T.P) {
+                    const float4 sb = St.partf.pm[j];
+                    part_term_f<PH>(T.fa, sb, e2f, A);
+                    if constexpr (TWO) part_term_f<PH>(T.fb, sb, e2f, B);
+                }
+            } else {
+                for (int j = j0 + T.phi; j < j1; j += T.P) {
+                    const float4 sb = St.partf.pm[j];
+                    const int s = St.partf.src[j];
+                    if (s != T.qa) part_term_f<PH>(T.fa, sb, e2f, A);
+                    if constexpr (TWO)
+                        if (s != T.qb) part_term_f<PH>(T.fb, sb, e2f, B);
+                }
+            }
+        };
+        return stage_leaves_put<W>(
+            nleaf, leaves, St, pos4, m,
+            [&](int tn) {
+                if (!any) return;
+                for (int s = 0; s < tn; s += 64) {  // tile by tile, whatever W
+                    if (phi) run(s, min(s + 64, tn), BoolC<true>());
+                    else run(s, min(s + 64, tn), BoolC<false>());
+                    A.flush_tile();
+                    if constexpr (TWO) B.flush_tile();
+                }
+            },
+            [&](int i, const double4& ps, double mass, int src) {
+                St.partf.pm[i] = make_float4((float)(ps.x - T.o[0]), (float)(ps.y - T.o[1]), (float)(ps.z - T.o[2]),
+                                             (float)mass);
+                St.partf.src[i] = src;
+            });
+    } else {
         auto run = [&](int tn, auto ph) {
             constexpr bool PH = decltype(ph)::value;
             if (soft) {
                 for (int j = T.phi; j < tn; j += T.P) {
-                    const float4 sb = St.partf.pm[j];
-                    part_term_f<PH>(T.fa, sb, e2f, A);
-                    part_term_f<PH>(T.fb, sb, e2f, B);
+                    const double4 sb = St.part.pm[j];
+                    part_term<false, PH>(T.a, sb, e2, A);
+                    part_term<false, PH>(T.b, sb, e2, B);
                 }
             } else {
                 for (int j = T.phi; j < tn; j += T.P) {
-                    const float4 sb = St.partf.pm[j];
-                    const int s = St.partf.src[j];
-                    if (s != T.qa) part_term_f<PH>(T.fa, sb, e2f, A);
-                    if (s != T.qb) part_term_f<PH>(T.fb, sb, e2f, B);
+                    const double4 sb = St.part.pm[j];
+                    const int s = St.part.src[j];
+                    if (s != T.qa) part_term<false, PH>(T.a, sb, e2, A);
+                    if (s != T.qb) part_term<false, PH>(T.b, sb, e2, B);
                 }
             }
         };
-        return stage_leaves_put(
-            nleaf, leaves, St, pos4, m,
-            [&](int tn) {
-                if (!any) return;
-                if (phi) run(tn, BoolC<true>());
-                else run(tn, BoolC<false>());
-                A.flush_tile();
-                B.flush_tile();
-            },
-            [&](int lane, const double4& ps, double mass, int src) {
-                St.partf.pm[lane] = make_float4((float)(ps.x - T.o[0]), (float)(ps.y - T.o[1]), (float)(ps.z - T.o[2]),
-                                                (float)mass);
-                St.partf.src[lane] = src;
-            });
+        return stage_leaves<W>(nleaf, leaves, St, pos4, m, [&](int tn) {
+            if (!any) return;
+            if (phi) run(tn, BoolC<true>());
+            else run(tn, BoolC<false>());
+        });
     }
-    auto run = [&](int tn, auto ph) {
-        constexpr bool PH = decltype(ph)::value;
-        if (soft) {
-            for (int j = T.phi; j < tn; j += T.P) {
-                const double4 sb = St.part.pm[j];
-                part_term<false, PH>(T.a, sb, e2, A);
-                part_term<false, PH>(T.b, sb, e2, B);
-            }
-        } else {
-            for (int j = T.phi; j < tn; j += T.P) {
-                const double4 sb = St.part.pm[j];
-                const int s = St.part.src[j];
-                if (s != T.qa) part_term<false, PH>(T.a, sb, e2, A);
-                if (s != T.qb) part_term<false, PH>(T.b, sb, e2, B);
-            }
-        }
-    };
-    return stage_leaves(nleaf, leaves, St, pos4, m, [&](int tn) {
-        if (!any) return;
-        if (phi) run(tn, BoolC<true>());
-        else run(tn, BoolC<false>());
-    });
 }
 
 // The targets of one octree leaf: lane tp + TP ph serves target tp and (FP64, TWO) target tp + TP, the
@@ -372,7 +401,7 @@ struct LaneTarget {
     int ph, P, TP;
 };
 
-template <bool FP32C, bool TWO, typename Stage>
+template <bool FP32C, bool TWO, int W, typename Stage>
 __device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const double4* __restrict__ pos4,
                              const double* __restrict__ m, const LaneTarget& T, double e2, bool phi, TargetSums& A,
                              TargetSums& B) {
@@ -394,7 +423,7 @@ __device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const double4* _
             }
         }
     };
-    stage_leaves(nleaf, leaves, St, pos4, m, [&](int tn) {
+    stage_leaves<W>(nleaf, leaves, St, pos4, m, [&](int tn) {
         if (!T.va) return;
         if (phi) run(tn, BoolC<true>());
         else run(tn, BoolC<false>());
@@ -402,11 +431,63 @@ __device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const double4* _
     });
 }
 
-__global__ void k_zero_grav_counts(DevCtl* ctl) {
-    const int s = threadIdx.x;
-    if (s < GRAV_SLOTS) {
-        ctl->grav_cnt[s][0] = 0;
-        ctl->grav_cnt[s][1] = 0;
+// Order in which the workgroups take their units (target groups, or leaves for leaf_node): within each
+// XCD's contiguous share, the units of most targets first, so that what is left at the end is short (a
+// unit takes 100 to 400 us whatever the set's size).  Before them the heavy leaves: the at most 16
+// coarsest ones that lie two levels or more above the share's average.  One workgroup per share counts
+// and places its units; the first also clears the pass's term counters.  1,000,003 particles in groups
+// of 64, FP32C: 1.96 -> 1.80 ms; 131,101 in groups of 32, FP64: 0.451 -> 0.370 ms; 4,194,304: 12.78 -> 12.61.
+__global__ void __launch_bounds__(1024) k_unit_order(DevCtl* ctl, const int4* __restrict__ group,
+                                                     const int* __restrict__ leaf_node, const int4* __restrict__ topo,
+                                                     int* __restrict__ order) {
+    __shared__ int at[65], lev[MAX_LEVEL + 1], heavy_at, cut;
+    const int tid = threadIdx.x;
+    if (blockIdx.x == 0 && tid < GRAV_SLOTS) {
+        ctl->grav_cnt[tid][0] = 0;
+        ctl->grav_cnt[tid][1] = 0;
+    }
+    if (tid < 65) at[tid] = 0;
+    if (tid <= MAX_LEVEL) lev[tid] = 0;
+    int u0, u1, step;  // (eight workgroups: step 1 from the share's first unit)
+    group_range(leaf_node ? ctl->n_leaves : ctl->n_groups, u0, u1, step);
+    __syncthreads();
+    if (leaf_node) {
+        for (int u = u0 + tid; u < u1; u += 1024) atomicAdd(&lev[topo[leaf_node[u]].z], 1);
+        __syncthreads();
+    }
+    if (tid == 0) {
+        cut = -1;
+        heavy_at = 0;
+        if (leaf_node) {
+            long long sum = 0, n = u1 - u0;
+            for (int l = 0; l <= MAX_LEVEL; ++l) sum += (long long)l * lev[l];
+            int k = 0;
+            for (int l = 0; l <= MAX_LEVEL && (l + 2) * n <= sum; ++l) {
+                k += lev[l];
+                if (k > 16) break;
+                cut = l;
+            }
+        }
+    }
+    __syncthreads();
+    const int c = cut;
+    const int wide = leaf_node && ctl->n_leaves <= 4096 ? 16 : INT_MAX;
+    auto size = [&](int u) {  // 0: heavy
+        const int4 t = leaf_node ? topo[leaf_node[u]] : group[u];
+        return leaf_node && (t.z <= c || t.y >= wide) ? 0 : min(t.y, 64);
+    };
+    for (int u = u0 + tid; u < u1; u += 1024) atomicAdd(&at[size(u)], 1);
+    __syncthreads();
+    if (tid == 0 && leaf_node) ctl->fmm_heavy[blockIdx.x] = at[0];
+    if (tid < 64) {  // first place of size 64 - tid
+        const int k = at[64 - tid];
+        const int incl = wave_incl_scan(k);
+        at[64 - tid] = at[0] + incl - k;
+    }
+    __syncthreads();
+    for (int u = u0 + tid; u < u1; u += 1024) {
+        const int z = size(u);
+        order[u0 + atomicAdd(z ? &at[z] : &heavy_at, 1)] = u;
     }
 }
 
@@ -415,40 +496,41 @@ __global__ void k_zero_grav_counts(DevCtl* ctl) {
 // lane).  A group adds them to the pass's counters once, at its end: a returnless atomic still
 // holds the wave's next memory wait, and one per flush on two addresses shared by the whole
 // grid cost ~12% of the 4M-particle pass.
-template <bool FP32C>
-__device__ void eval_lists(int ncell, int nleaf, const int* cells, int* leaves, GravStage<FP32C>& St,
+template <bool FP32C, int W>
+__device__ void eval_lists(int ncell, int nleaf, const int* cells, int* leaves, GravStage<FP32C, W>& St,
                            const double4* __restrict__ mom0,
                            const double4* __restrict__ mom1, const double4* __restrict__ mom2,
                            const double4* __restrict__ pos4, const double* __restrict__ m, const GravTargets& T,
                            double eps, bool phi, TargetSums& A, TargetSums& B, int ng, u64& n_cells, u64& n_pairs) {
-    eval_cells<FP32C>(ncell, cells, St, mom0, mom1, mom2, T, eps * eps, phi, A, B);
+    eval_cells<FP32C, W>(ncell, cells, St, mom0, mom1, mom2, T, eps * eps, phi, A, B);
     n_cells += (u64)ncell * (u64)ng;
-    n_pairs += (u64)eval_leaves<FP32C>(nleaf, leaves, St, pos4, m, T, eps * eps, phi, A, B) * (u64)ng;
+    n_pairs += (u64)eval_leaves<FP32C, W>(nleaf, leaves, St, pos4, m, T, eps * eps, phi, A, B) * (u64)ng;
 }
 
-template <bool FP32C>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ? 1 : 4))) k_gravity(DevCtl* ctl, const int4* __restrict__ group, int gsz,
-                                                const int4* __restrict__ topo, const double4* __restrict__ nbox_lo,
-                                                const double4* __restrict__ nbox_hi, const double4* __restrict__ mom0,
-                                                const double4* __restrict__ mom1, const double4* __restrict__ mom2,
-                                                const double4* __restrict__ pos4, const double* __restrict__ m,
-                                                double G, double eps, double theta, int accumulate,
-                                                double* __restrict__ gxo, double* __restrict__ gyo,
-                                                double* __restrict__ gzo, double* __restrict__ pho,
-                                                const double4* __restrict__ vel4, double* __restrict__ deo) {
+// W wavefronts per target group: the first one walks the tree and fills the lists, all of them evaluate.
+template <bool FP32C, int W>
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(FP32C ? 1 : 4))) k_gravity(
+    DevCtl* ctl, const int* __restrict__ order, const int4* __restrict__ group, int gsz, const int4* __restrict__ topo,
+    const double4* __restrict__ nbox_lo, const double4* __restrict__ nbox_hi, const double4* __restrict__ mom0,
+    const double4* __restrict__ mom1, const double4* __restrict__ mom2, const double4* __restrict__ pos4,
+    const double* __restrict__ m, double G, double eps, double theta, int accumulate, double* __restrict__ gxo,
+    double* __restrict__ gyo, double* __restrict__ gzo, double* __restrict__ pho, const double4* __restrict__ vel4,
+    double* __restrict__ deo) {
+    constexpr bool TWO = !(FP32C && W > 1);
     __shared__ int stack[GW_STACK];
     __shared__ int cells[GW_CELLS];
     __shared__ int leaves[GW_LEAVES];
-    __shared__ GravStage<FP32C> St;
-    const int lane = lane_id();
+    __shared__ GravStage<FP32C, W> St;
+    __shared__ int walked[3];  // cells and leaves listed, nodes left on the stack
+    const int lane = lane_id(), wave = W > 1 ? threadIdx.x >> 6 : 0;
     GravTargets T;
     // the potential is evaluated (and written) unless the step sequence has switched it off:
     // inside a run of steps only the last step's value is read (by the energy diagnostic)
     const bool phi = pho != nullptr && ctl->skip_phi == 0;
     int g0, g1, gstep;
     group_range(ctl->n_groups, g0, g1, gstep);
-    for (int gi = g0; gi < g1; gi += gstep) {
-        const int4 g = group[gi];
+    for (int ui = g0; ui < g1; ui += gstep) {
+        const int4 g = group[order[ui]];
         // TP target pairs per wave: with few targets, more lanes split the tiles.  Halving the
         // targets fills 92-94% of the lane slots (groups of at most 32, 23 on average at 4M),
         // powers of two 87%.
@@ -458,14 +540,16 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ?
         } else {
             T.TP = (g.y + 1) >> 1;
         }
-        T.P = 64 / T.TP;
-        T.tp = lane % T.TP;
-        T.phi = lane / T.TP;
+        const int slot = FP32C ? lane : (int)threadIdx.x;
+        T.P = (FP32C ? 64 : 64 * W) / T.TP;
+        T.tp = slot % T.TP;
+        T.phi = slot / T.TP;
         const bool works = T.phi < T.P;
-        T.qa = g.x + T.tp;
+        const int ta = TWO ? T.tp : T.tp + wave * T.TP;
+        T.qa = g.x + ta;
         T.qb = g.x + T.tp + T.TP;
-        T.va = works && T.tp < g.y;
-        T.vb = works && T.tp + T.TP < g.y;
+        T.va = works && ta < g.y;
+        T.vb = TWO && works && T.tp + T.TP < g.y;
         T.a = T.va ? pos4[T.qa] : make_double4(0, 0, 0, 0);
         T.b = T.vb ? pos4[T.qb] : make_double4(0, 0, 0, 0);
         if (FP32C) {
@@ -476,102 +560,117 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ?
             T.fa = make_float4((float)(T.a.x - o.x), (float)(T.a.y - o.y), (float)(T.a.z - o.z), 0.0f);
             T.fb = make_float4((float)(T.b.x - o.x), (float)(T.b.y - o.y), (float)(T.b.z - o.z), 0.0f);
         }
-        double lo[3], hi[3];
-        lo[0] = wave_min(fmin(T.va ? T.a.x : INFINITY, T.vb ? T.b.x : INFINITY));
-        lo[1] = wave_min(fmin(T.va ? T.a.y : INFINITY, T.vb ? T.b.y : INFINITY));
-        lo[2] = wave_min(fmin(T.va ? T.a.z : INFINITY, T.vb ? T.b.z : INFINITY));
-        hi[0] = wave_max(fmax(T.va ? T.a.x : -INFINITY, T.vb ? T.b.x : -INFINITY));
-        hi[1] = wave_max(fmax(T.va ? T.a.y : -INFINITY, T.vb ? T.b.y : -INFINITY));
-        hi[2] = wave_max(fmax(T.va ? T.a.z : -INFINITY, T.vb ? T.b.z : -INFINITY));
+        double lo[3], hi[3];  // the group's box, for the walking wavefront
+        if (W == 1 || wave == 0) {
+            const double4 p = pos4[g.x + min(lane, g.y - 1)];
+            lo[0] = wave_min(p.x);
+            lo[1] = wave_min(p.y);
+            lo[2] = wave_min(p.z);
+            hi[0] = wave_max(p.x);
+            hi[1] = wave_max(p.y);
+            hi[2] = wave_max(p.z);
+        }
         const double th2 = theta * theta;
         const u64 lt = lanemask_lt();
         TargetSums A, B;
         const int root = g.z < 0 ? 0 : ctl->level_off[3] + g.z;
         __syncthreads();
-        if (lane == 0) stack[0] = root;
-        int sp = 1, nc = 0, nl = 0, iters = 0;
+        if (threadIdx.x == 0) stack[0] = root;
+        int sp = 1, iters = 0;
         u64 n_cells = 0, n_pairs = 0;
-        __syncthreads();
-        while (sp > 0) {
-            if (++iters > (1 << 22)) {  // bounded: every wave leaves the loop
-                if (lane == 0) set_err(ctl, ERR_GRAV_LIST);
-                break;
-            }
-            if (nc + 64 > GW_CELLS || nl + 64 > GW_LEAVES) {
-                eval_lists<FP32C>(nc, nl, cells, leaves, St, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B,
-                                  g.y, n_cells, n_pairs);
-                nc = nl = 0;
-                __syncthreads();
-            }
-            // pop as many nodes as the stack can take the children of (8 each) while keeping
-            // the depth-first headroom; past it, one node per round
-            int k = sp < 64 ? sp : 64;
-            const int room = (GW_STACK - DFS_HEADROOM - sp) / 8;
-            if (k > room) k = room > 1 ? room : 1;
-            const int node = lane < k ? stack[sp - k + lane] : -1;
-            __syncthreads();
-            sp -= k;
-            int kind = 0;  // 1 = accepted cell, 2 = leaf to open, 3 = open children
-            int4 tp = make_int4(0, 0, 0, 0);
-            if (node >= 0) {
-                tp = topo[node];
-                const double4 a = nbox_lo[node], b = nbox_hi[node], m0 = mom0[node];
-                const double com[3] = {m0.y, m0.z, m0.w};
-                double d2 = 0.0;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const double gp = com[c] < lo[c] ? lo[c] - com[c] : (com[c] > hi[c] ? com[c] - hi[c] : 0.0);
-                    d2 += gp * gp;
+        wave_lds_fence();
+        while (true) {
+            int nc = 0, nl = 0;
+            // until the lists may not hold another round or the walk has ended
+            while ((W == 1 || wave == 0) && sp > 0 && nc + 64 <= GW_CELLS && nl + 64 <= GW_LEAVES) {
+                if (++iters > (1 << 22)) {  // bounded: every wave leaves the loop
+                    if (lane == 0) set_err(ctl, ERR_GRAV_LIST);
+                    sp = 0;
+                    break;
                 }
-                const bool apart =
-                    a.x > hi[0] || b.x < lo[0] || a.y > hi[1] || b.y < lo[1] || a.z > hi[2] || b.z < lo[2];
-                const double ux = fmax(com[0] - a.x, b.x - com[0]), uy = fmax(com[1] - a.y, b.y - com[1]),
-                             uz = fmax(com[2] - a.z, b.z - com[2]);
-                const double b2 = (ux * ux + uy * uy) + uz * uz;  // radius^2 about the centre of mass
-                if (apart && b2 < th2 * d2) kind = 1;
-                else kind = tp.w ? 2 : 3;
+                // pop as many nodes as the stack can take the children of (8 each) while keeping
+                // the depth-first headroom; past it, one node per round
+                int k = sp < 64 ? sp : 64;
+                const int room = (GW_STACK - DFS_HEADROOM - sp) / 8;
+                if (k > room) k = room > 1 ? room : 1;
+                const int node = lane < k ? stack[sp - k + lane] : -1;
+                wave_lds_fence();
+                sp -= k;
+                int kind = 0;  // 1 = accepted cell, 2 = leaf to open, 3 = open children
+                int4 tp = make_int4(0, 0, 0, 0);
+                if (node >= 0) {
+                    tp = topo[node];
+                    const double4 a = nbox_lo[node], b = nbox_hi[node], m0 = mom0[node];
+                    const double com[3] = {m0.y, m0.z, m0.w};
+                    double d2 = 0.0;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const double gp = com[c] < lo[c] ? lo[c] - com[c] : (com[c] > hi[c] ? com[c] - hi[c] : 0.0);
+                        d2 += gp * gp;
+                    }
+                    const bool apart =
+                        a.x > hi[0] || b.x < lo[0] || a.y > hi[1] || b.y < lo[1] || a.z > hi[2] || b.z < lo[2];
+                    const double ux = fmax(com[0] - a.x, b.x - com[0]), uy = fmax(com[1] - a.y, b.y - com[1]),
+                                 uz = fmax(com[2] - a.z, b.z - com[2]);
+                    const double b2 = (ux * ux + uy * uy) + uz * uz;  // radius^2 about the centre of mass
+                    if (apart && b2 < th2 * d2) kind = 1;
+                    else kind = tp.w ? 2 : 3;
+                }
+                const u64 bc = __ballot(kind == 1), bl = __ballot(kind == 2);
+                if (kind == 1) cells[nc + __popcll(bc & lt)] = node;
+                if (kind == 2) {
+                    leaves[nl + __popcll(bl & lt)] = tp.x;
+                    St.loff[nl + __popcll(bl & lt)] = tp.y;
+                }
+                nc += __popcll(bc);
+                nl += __popcll(bl);
+                const int nch = kind == 3 ? tp.y : 0;
+                const int incl = wave_incl_scan(nch);
+                const int tot = wave_last(incl);
+                if (sp + tot > GW_STACK) {
+                    if (lane == 0) set_err(ctl, ERR_GRAV_LIST);
+                    sp = 0;
+                    break;
+                }
+                for (int j = 0; j < nch; ++j) stack[sp + incl - nch + j] = tp.x + j;
+                sp += tot;
+                wave_lds_fence();
             }
-            const u64 bc = __ballot(kind == 1), bl = __ballot(kind == 2);
-            if (kind == 1) cells[nc + __popcll(bc & lt)] = node;
-            if (kind == 2) {
-                leaves[nl + __popcll(bl & lt)] = tp.x;
-                St.loff[nl + __popcll(bl & lt)] = tp.y;
+            if (W > 1) {
+                if (threadIdx.x == 0) {
+                    walked[0] = nc;
+                    walked[1] = nl;
+                    walked[2] = sp;
+                }
+                __syncthreads();
+                nc = walked[0];
+                nl = walked[1];
+                sp = walked[2];
             }
-            nc += __popcll(bc);
-            nl += __popcll(bl);
-            const int nch = kind == 3 ? tp.y : 0;
-            const int incl = wave_incl_scan(nch);
-            const int tot = wave_last(incl);
-            if (sp + tot > GW_STACK) {
-                if (lane == 0) set_err(ctl, ERR_GRAV_LIST);
-                break;
-            }
-            for (int j = 0; j < nch; ++j) stack[sp + incl - nch + j] = tp.x + j;
-            sp += tot;
+            eval_lists<FP32C, W>(nc, nl, cells, leaves, St, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B, g.y, n_cells,
+                                 n_pairs);
             __syncthreads();
+            if (sp <= 0) break;
         }
-        __syncthreads();
-        eval_lists<FP32C>(nc, nl, cells, leaves, St, mom0, mom1, mom2, pos4, m, T, eps, phi, A, B,
-                                  g.y, n_cells, n_pairs);
         // per target: lanes tp + TP*phi combine in a fixed order
         double r[8];
         if constexpr (FP32C) {
             r[0] = A.kx.value(); r[1] = A.ky.value(); r[2] = A.kz.value(); r[3] = A.kp.value();
             r[4] = B.kx.value(); r[5] = B.ky.value(); r[6] = B.kz.value(); r[7] = B.kp.value();
 #pragma unroll
-            for (int i = 0; i < 8; ++i) r[i] = G * lanes_sum_d(r[i], T.TP);
+            for (int i = 0; i < 8; ++i) r[i] = G * lanes_sum_d(r[i], T.TP);  // (B: zero if !TWO)
         } else {
             const double v[8] = {A.gx, A.gy, A.gz, A.ph, B.gx, B.gy, B.gz, B.ph};
 #pragma unroll
             for (int h = 0; h < 8; h += 4) {
                 __syncthreads();
 #pragma unroll
-                for (int i = 0; i < 4; ++i) St.red[i][lane] = v[h + i];
+                for (int i = 0; i < 4; ++i) St.red[i][threadIdx.x] = v[h + i];
                 __syncthreads();
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     double t = v[h + i];  // the lanes with phi = 0 use it
-                    for (int k = 1; k < T.P; ++k) t += St.red[i][min(lane + k * T.TP, 63)];
+                    for (int k = 1; k < T.P; ++k) t += St.red[i][min((int)threadIdx.x + k * T.TP, 64 * W - 1)];
                     r[h + i] = G * t;
                 }
             }
@@ -602,8 +701,8 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ?
                 if (phi) pho[q] = ph;
             }
         }
-        if (lane == 0) {  // last, so that no later memory wait of the group holds for it
-            u64* slot = ctl->grav_cnt[gi & (GRAV_SLOTS - 1)];
+        if (threadIdx.x == 0) {  // last, so that no later memory wait of the group holds for it
+            u64* slot = ctl->grav_cnt[ui & (GRAV_SLOTS - 1)];
             atomicAdd(&slot[0], n_cells);
             atomicAdd(&slot[1], n_pairs);
         }
@@ -617,15 +716,29 @@ void launch_gravity(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
     double* gy = accumulate ? d.ay : d.gy;
     double* gz = accumulate ? d.az : d.gz;
     double* de = (accumulate && thermo) ? d.du : nullptr;
-    hipLaunchKernelGGL(k_zero_grav_counts, dim3(1), dim3(64), 0, s, d.ctl);
-    if (fp32c)
-        hipLaunchKernelGGL(k_gravity<true>, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.group, dm.group_size, d.topo,
+    int* order = reinterpret_cast<int*>(d.gsize);  // free once the groups are emitted
+    hipLaunchKernelGGL(k_unit_order, dim3(8), dim3(1024), 0, s, d.ctl, d.group, nullptr, d.topo, order);
+    auto go = [&](auto kern, int waves) {
+        const int grid = std::min(dm.group_grid, 8 * std::max(1, dm.wave_cap / (8 * waves)));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), 0, s, d.ctl, order, d.group, dm.group_size, d.topo,
                            d.nbox_lo, d.nbox_hi, d.mom0, d.mom1, d.mom2, d.pos4, d.m, G, eps, theta, accumulate, gx, gy,
                            gz, d.phi, d.vel4, de);
-    else
-        hipLaunchKernelGGL(k_gravity<false>, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.group, dm.group_size, d.topo,
-                           d.nbox_lo, d.nbox_hi, d.mom0, d.mom1, d.mom2, d.pos4, d.m, G, eps, theta, accumulate, gx, gy,
-                           gz, d.phi, d.vel4, de);
+    };
+    // Wavefronts a group: with few groups the chip is not full of single wavefronts.  With the tree, us,
+    // for 1 / 2 / 4 (FP32C 1 / 2): 20,011 particles in groups of 32, FP64 254 / 229 / 210, FP32C 240 / 209;
+    // 50,000 in groups of 32, 331 / 304 / 341 and 290 / 270; 262,144 in groups of 64, 1197 / 1078 / 1132 and
+    // 875 / 816; 131,101 in groups of 32, 534 / 538 and 445 / 456; 500,000 in groups of 64, 1638 / 1639 and
+    // 1114 / 1217.  Groups of 16 lack the targets for four (8,000 particles: 153 / 146 / 155).
+    const int64_t units = dm.n / std::max(1, dm.group_size);
+    const int W = units > 4096 ? 1 : (units > 1024 || dm.group_size <= 16 || fp32c ? 2 : 4);
+    if (fp32c) {
+        if (W > 1) go(k_gravity<true, 2>, 2);
+        else go(k_gravity<true, 1>, 1);
+    } else {
+        if (W > 2) go(k_gravity<false, 4>, 4);
+        else if (W > 1) go(k_gravity<false, 2>, 2);
+        else go(k_gravity<false, 1>, 1);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -652,7 +765,7 @@ void launch_gravity(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
 // pair, so the forces two nodes exert on each other are opposite and central: linear and
 // angular momentum are conserved up to rounding.
 //
-// GPU form: every leaf of the tree is a target of one wavefront, which replays the part of
+// GPU form: every leaf of the tree is a target of one wavefront (or four), which replays the part of
 // the recursion that involves the leaf's ancestors X_0 (root) .. X_D (the leaf): each self
 // pair (X_e, X_e) yields the pairs (X_e+1, C) for the other children C of X_e, and a pair
 // (X_e, Y) either ends (term or particle pairs), moves down the path (X split) or fans out
@@ -669,10 +782,11 @@ constexpr int FM_TARGETS = 64;    // targets per pass over a leaf
 static_assert(7 * MAX_LEVEL + DFS_HEADROOM <= FM_STACK, "the initial pairs of a path and the headroom fit");
 
 // LDS staging of the particle sums (the node-node walk has no cell tiles).
+template <int W>
 struct FmmStage {
     struct {
-        double4 pm[64];  // (x, y, z, m)
-        int src[64];     // particle index (self test without softening)
+        double4 pm[64 * W];  // (x, y, z, m)
+        int src[64 * W];     // particle index (self test without softening)
     } part;
     int loff[FM_LEAVES + 1];  // particle offsets of the staged leaves
 };
@@ -728,12 +842,12 @@ __device__ __forceinline__ bool fmm_accept(int la, const int* ca, int lb, const 
 // Accepted pairs (tnode[k], depth tdep[k]): lane k evaluates pair k, k + 64, ... and keeps
 // its own partial sums of the field (fg) and of the potential referred to the leaf's
 // centre of mass (fc); the caller sums them across the wave.
-template <bool PH>
+template <bool PH, int W>
 __device__ __forceinline__ void fmm_eval_terms(int nt, const int* tnode, const unsigned char* tdep, const FmmPath& P,
                                                int D, const double4* __restrict__ mom0, double e2, double& fgx,
                                                double& fgy, double& fgz, double& fc) {
     const double4 cl = P.com[D];
-    for (int k = lane_id(); k < nt; k += 64) {
+    for (int k = unit_thread<W>(); k < nt; k += 64 * W) {
         const double4 cx = P.com[tdep[k]];
         const double4 cy = mom0[tnode[k]];
         const double Rx = cx.y - cy.y, Ry = cx.z - cy.z, Rz = cx.w - cy.w;
@@ -749,117 +863,129 @@ __device__ __forceinline__ void fmm_eval_terms(int nt, const int* tnode, const u
     }
 }
 
-template <bool FP32C>
-__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ? 1 : 4))) k_fmm(DevCtl* ctl, const int* __restrict__ leaf_node,
-                                            const int* __restrict__ parent,
-                                            const int4* __restrict__ topo, const int2* __restrict__ range,
-                                            const double4* __restrict__ mom0, const double* __restrict__ ncell,
-                                            const double4* __restrict__ pos4, const double* __restrict__ m, double G,
-                                            double eps, double th4,
-                                            int accumulate, double* __restrict__ gxo, double* __restrict__ gyo,
-                                            double* __restrict__ gzo, double* __restrict__ pho,
-                                            const double4* __restrict__ vel4, double* __restrict__ deo) {
-    __shared__ int stk[FM_STACK];
-    __shared__ unsigned char sdep[FM_STACK];
-    const bool phi = pho != nullptr && ctl->skip_phi == 0;  // as in k_gravity
-    __shared__ int tnode[FM_TERMS];
-    __shared__ unsigned char tdep[FM_TERMS];
-    __shared__ int leaves[FM_LEAVES];
-    __shared__ FmmStage St;
-    __shared__ FmmPath Pth;
-    const int lane = lane_id();
-    const double e2 = eps * eps;
+// LDS of W wavefronts that work on one leaf.
+template <int W>
+struct FmmLds {
+    int stk[FM_STACK];
+    int tnode[FM_TERMS];
+    int leaves[FM_LEAVES];
+    unsigned char sdep[FM_STACK], tdep[FM_TERMS];
+    int walked[3];   // pairs and leaves listed, pairs left on the stack
+    double4 far[W];  // the waves' constant fields
+    FmmStage<W> St;
+    FmmPath Pth;
+};
+
+struct FmmArgs {
+    DevCtl* ctl;
+    const int* order;
+    const int* leaf_node;
+    const int* parent;
+    const int4* topo;
+    const int2* range;
+    const double4* mom0;
+    const double* ncell;
+    const double4* pos4;
+    const double* m;
+    double G, eps, th4;
+    int accumulate;
+    double *gxo, *gyo, *gzo, *pho;
+    const double4* vel4;
+    double* deo;
+};
+
+// Leaf L by W wavefronts: the first one replays the recursion and fills the lists, all of them evaluate.
+template <bool FP32C, int W>
+__device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, bool phi) {
+    DevCtl* ctl = K.ctl;
+    const int* __restrict__ parent = K.parent;
+    const int4* __restrict__ topo = K.topo;
+    const int2* __restrict__ range = K.range;
+    const double4* __restrict__ mom0 = K.mom0;
+    const double* __restrict__ ncell = K.ncell;
+    const double4* __restrict__ pos4 = K.pos4;
+    const double* __restrict__ m = K.m;
+    const double G = K.G, eps = K.eps, th4 = K.th4, e2 = eps * eps;
+    const int lane = lane_id(), tid = unit_thread<W>(), wave = W > 1 ? threadIdx.x >> 6 : 0;
     const u64 lt = lanemask_lt();
-    int l0, l1, lstep;
-    group_range(ctl->n_leaves, l0, l1, lstep);
-    for (int li = l0; li < l1; li += lstep) {
-        const int L = leaf_node[li];
-        const int4 tl = topo[L];
-        const int D = tl.z;  // one set: the root is at level 0
-        __syncthreads();
-        if (lane == 0) {
-            int b = L;
-            for (int e = D; e >= 0; --e) {
-                Pth.node[e] = b;
-                b = e > 0 ? parent[b] : -1;
-            }
+    const int4 tl = topo[L];
+    const int D = tl.z;  // one set: the root is at level 0
+    unit_sync<W>();
+    if (tid == 0) {
+        int b = L;
+        for (int e = D; e >= 0; --e) {
+            S.Pth.node[e] = b;
+            b = e > 0 ? parent[b] : -1;
         }
-        __syncthreads();
-        if (lane <= D) {
-            const int b = Pth.node[lane];
-            const int4 t = topo[b];
-            const int st = range[b].x;
-            Pth.topo[lane] = t;
-            Pth.start[lane] = st;
-            Pth.com[lane] = mom0[b];
-            fmm_unpack((u64)__double_as_longlong(ncell[4 * b]), Pth.cell[lane]);
-        }
-        __syncthreads();
-        const double4 cl = Pth.com[D];
-        for (int t0 = 0; t0 < tl.y; t0 += FM_TARGETS) {
-            const int cc = min(FM_TARGETS, tl.y - t0);
-            constexpr bool TWO = !FP32C;
-            LaneTarget T;
-            T.TP = TWO ? (cc + 1) >> 1 : cc;
-            T.P = 64 / T.TP;
-            T.ph = lane / T.TP;
-            const int tp = lane - T.ph * T.TP;
-            T.qa = tl.x + t0 + tp;
-            T.qb = T.qa + T.TP;
-            T.va = T.ph < T.P;
-            T.vb = TWO && T.va && tp + T.TP < cc;
-            T.a = T.va ? pos4[T.qa] : make_double4(0, 0, 0, 0);
-            T.b = T.vb ? pos4[T.qb] : T.a;
-            // initial pairs: (X_e+1, C) for every other child C of every ancestor X_e
-            const int n0 = lane < D ? Pth.topo[lane].y - 1 : 0;
-            const int incl = wave_incl_scan(n0);
-            int sp = wave_last(incl);
-            if (lane < D) {
-                const int4 t = Pth.topo[lane];
-                const int nxt = Pth.node[lane + 1];
-                int o = incl - n0;
-                for (int j = 0; j < t.y; ++j) {
-                    const int ch = t.x + j;
-                    if (ch != nxt) {
-                        stk[o] = ch;
-                        sdep[o] = (unsigned char)(lane + 1);
-                        ++o;
-                    }
+    }
+    unit_sync<W>();
+    if ((W == 1 || wave == 0) && lane <= D) {
+        const int b = S.Pth.node[lane];
+        const int4 t = topo[b];
+        const int st = range[b].x;
+        S.Pth.topo[lane] = t;
+        S.Pth.start[lane] = st;
+        S.Pth.com[lane] = mom0[b];
+        fmm_unpack((u64)__double_as_longlong(ncell[4 * b]), S.Pth.cell[lane]);
+    }
+    unit_sync<W>();
+    const double4 cl = S.Pth.com[D];
+    for (int t0 = 0; t0 < tl.y; t0 += FM_TARGETS) {
+        const int cc = min(FM_TARGETS, tl.y - t0);
+        constexpr bool TWO = !FP32C;
+        LaneTarget T;
+        T.TP = TWO ? (cc + 1) >> 1 : cc;
+        T.P = 64 * W / T.TP;
+        T.ph = tid / T.TP;
+        const int tp = tid - T.ph * T.TP;
+        T.qa = tl.x + t0 + tp;
+        T.qb = T.qa + T.TP;
+        T.va = T.ph < T.P;
+        T.vb = TWO && T.va && tp + T.TP < cc;
+        T.a = T.va ? pos4[T.qa] : make_double4(0, 0, 0, 0);
+        T.b = T.vb ? pos4[T.qb] : T.a;
+        // initial pairs: (X_e+1, C) for every other child C of every ancestor X_e
+        const int n0 = lane < D ? S.Pth.topo[lane].y - 1 : 0;
+        const int incl = wave_incl_scan(n0);
+        int sp = wave_last(incl);
+        if ((W == 1 || wave == 0) && lane < D) {
+            const int4 t = S.Pth.topo[lane];
+            const int nxt = S.Pth.node[lane + 1];
+            int o = incl - n0;
+            for (int j = 0; j < t.y; ++j) {
+                const int ch = t.x + j;
+                if (ch != nxt) {
+                    S.stk[o] = ch;
+                    S.sdep[o] = (unsigned char)(lane + 1);
+                    ++o;
                 }
             }
-            if (lane == 0) {  // the leaf's own particle pairs
-                leaves[0] = tl.x;
-                St.loff[0] = tl.y;
-            }
-            int nt = 0, nl = 1, iters = 0;
-            TargetSums A, B;
-            double fgx = 0.0, fgy = 0.0, fgz = 0.0, fc = 0.0;
-            __syncthreads();
-            while (sp > 0) {
+        }
+        if (tid == 0) {  // the leaf's own particle pairs
+            S.leaves[0] = tl.x;
+            S.St.loff[0] = tl.y;
+        }
+        int nt = 0, nl = 1, iters = 0;
+        TargetSums A, B;
+        double fgx = 0.0, fgy = 0.0, fgz = 0.0, fc = 0.0;
+        unit_sync<W>();
+        while (true) {
+            // until a list may not hold another round or the walk has ended
+            while ((W == 1 || wave == 0) && sp > 0 && nt + 64 <= FM_TERMS && nl + 64 <= FM_LEAVES) {
                 if (++iters > (1 << 22)) {  // bounded: every wave leaves the loop
                     if (lane == 0) set_err(ctl, ERR_GRAV_LIST);
+                    sp = 0;
                     break;
-                }
-                if (nt + 64 > FM_TERMS) {
-                    if (phi) fmm_eval_terms<true>(nt, tnode, tdep, Pth, D, mom0, e2, fgx, fgy, fgz, fc);
-                    else fmm_eval_terms<false>(nt, tnode, tdep, Pth, D, mom0, e2, fgx, fgy, fgz, fc);
-                    nt = 0;
-                    __syncthreads();
-                }
-                if (nl + 64 > FM_LEAVES) {
-                    eval_leaves1<FP32C, TWO>(nl, leaves, St, pos4, m, T, e2, phi, A, B);
-                    nl = 0;
-                    __syncthreads();
                 }
                 int k = sp < 64 ? sp : 64;  // wide rounds only above the depth-first headroom
                 const int room = (FM_STACK - DFS_HEADROOM - sp) / 8;
                 if (k > room) k = room > 1 ? room : 1;
                 int Y = -1, e = 0;
                 if (lane < k) {
-                    Y = stk[sp - k + lane];
-                    e = sdep[sp - k + lane];
+                    Y = S.stk[sp - k + lane];
+                    e = S.sdep[sp - k + lane];
                 }
-                __syncthreads();
+                wave_lds_fence();
                 sp -= k;
                 int kind = 0;  // 1 = node-node term, 2 = leaf pair, 3 = split X, 4 = split Y
                 int4 ty = make_int4(0, 0, 0, 0);
@@ -868,13 +994,13 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ?
                     const int sy = range[Y].x;
                     int cy[3];
                     fmm_unpack((u64)__double_as_longlong(ncell[4 * Y]), cy);
-                    const int4 tx = Pth.topo[e];
-                    if (fmm_accept(tx.z, Pth.cell[e], ty.z, cy, th4)) {
+                    const int4 tx = S.Pth.topo[e];
+                    if (fmm_accept(tx.z, S.Pth.cell[e], ty.z, cy, th4)) {
                         kind = 1;
                     } else if (tx.w && ty.w) {
                         kind = 2;
                     } else {
-                        bool split_x = tx.z < ty.z || (tx.z == ty.z && Pth.start[e] < sy);
+                        bool split_x = tx.z < ty.z || (tx.z == ty.z && S.Pth.start[e] < sy);
                         if (split_x ? tx.w : ty.w) split_x = !split_x;
                         kind = split_x ? 3 : 4;
                     }
@@ -882,12 +1008,12 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ?
                 const u64 bt = __ballot(kind == 1), bl = __ballot(kind == 2);
                 if (kind == 1) {
                     const int o = nt + __popcll(bt & lt);
-                    tnode[o] = Y;
-                    tdep[o] = (unsigned char)e;
+                    S.tnode[o] = Y;
+                    S.tdep[o] = (unsigned char)e;
                 }
                 if (kind == 2) {
-                    leaves[nl + __popcll(bl & lt)] = ty.x;
-                    St.loff[nl + __popcll(bl & lt)] = ty.y;
+                    S.leaves[nl + __popcll(bl & lt)] = ty.x;
+                    S.St.loff[nl + __popcll(bl & lt)] = ty.y;
                 }
                 nt += __popcll(bt);
                 nl += __popcll(bl);
@@ -896,68 +1022,134 @@ __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FP32C ?
                 const int tot = wave_last(pin);
                 if (sp + tot > FM_STACK) {
                     if (lane == 0) set_err(ctl, ERR_GRAV_LIST);
+                    sp = 0;
                     break;
                 }
                 if (kind == 3) {
-                    stk[sp + pin - 1] = Y;
-                    sdep[sp + pin - 1] = (unsigned char)(e + 1);
+                    S.stk[sp + pin - 1] = Y;
+                    S.sdep[sp + pin - 1] = (unsigned char)(e + 1);
                 } else if (kind == 4) {
                     for (int j = 0; j < np; ++j) {
-                        stk[sp + pin - np + j] = ty.x + j;
-                        sdep[sp + pin - np + j] = (unsigned char)e;
+                        S.stk[sp + pin - np + j] = ty.x + j;
+                        S.sdep[sp + pin - np + j] = (unsigned char)e;
                     }
                 }
                 sp += tot;
-                __syncthreads();
+                wave_lds_fence();
             }
-            __syncthreads();
-            if (phi) fmm_eval_terms<true>(nt, tnode, tdep, Pth, D, mom0, e2, fgx, fgy, fgz, fc);
-            else fmm_eval_terms<false>(nt, tnode, tdep, Pth, D, mom0, e2, fgx, fgy, fgz, fc);
-            eval_leaves1<FP32C, TWO>(nl, leaves, St, pos4, m, T, e2, phi, A, B);
-            fgx = lanes_sum_d(fgx, 1);
-            fgy = lanes_sum_d(fgy, 1);
-            fgz = lanes_sum_d(fgz, 1);
-            fc = lanes_sum_d(fc, 1);
-            // each target's P partial sums (lanes tp + TP ph) combined in phase order
-            for (int h = 0; h < (TWO ? 2 : 1); ++h) {
-                __syncthreads();
-                if (FP32C) St.part.pm[lane] = make_double4(A.kx.value(), A.ky.value(), A.kz.value(), A.kp.value());
-                else St.part.pm[lane] = h ? make_double4(B.gx, B.gy, B.gz, B.ph) : make_double4(A.gx, A.gy, A.gz, A.ph);
-                __syncthreads();
-                if (!(h ? T.vb : T.va) || T.ph != 0) continue;
-                double4 r = St.part.pm[lane];
-                for (int k = 1; k < T.P; ++k) {
-                    const double4 o = St.part.pm[lane + k * T.TP];
-                    r.x += o.x;
-                    r.y += o.y;
-                    r.z += o.z;
-                    r.w += o.w;
+            if (W > 1) {
+                if (tid == 0) {
+                    S.walked[0] = nt;
+                    S.walked[1] = nl;
+                    S.walked[2] = sp;
                 }
-                const int q = h ? T.qb : T.qa;
-                const double4 me = h ? T.b : T.a;
-                const double lin = fma(fgx, me.x - cl.y, fma(fgy, me.y - cl.z, fgz * (me.z - cl.w)));
-                const double gx = G * (r.x + fgx), gy = G * (r.y + fgy), gz = G * (r.z + fgz);
-                double ph = G * (r.w + (fc - lin));
-                if (eps > 0.0) {  // take out the self pair's potential term (see eval_leaves1)
-                    const double is = FP32C ? (double)__builtin_amdgcn_rsqf((float)e2) : rsq_nr1(e2);
-                    ph += G * (m[q] * is);
-                }
-                if (accumulate) {
-                    gxo[q] += gx;
-                    gyo[q] += gy;
-                    gzo[q] += gz;
-                    if (deo) {  // thermokinetic form: the work of gravity on e = u + v^2/2
-                        const double4 v = vel4[q];
-                        deo[q] += fma(v.x, gx, fma(v.y, gy, v.z * gz));
-                    }
-                } else {
-                    gxo[q] = gx;
-                    gyo[q] = gy;
-                    gzo[q] = gz;
-                }
-                if (phi) pho[q] = ph;
+                unit_sync<W>();
+                nt = S.walked[0];
+                nl = S.walked[1];
+                sp = S.walked[2];
             }
+            // each list by itself, when it is full: FP32C sums depend on how a list's tiles are cut
+            if (nt + 64 > FM_TERMS || sp <= 0) {
+                if (phi) fmm_eval_terms<true, W>(nt, S.tnode, S.tdep, S.Pth, D, mom0, e2, fgx, fgy, fgz, fc);
+                else fmm_eval_terms<false, W>(nt, S.tnode, S.tdep, S.Pth, D, mom0, e2, fgx, fgy, fgz, fc);
+                nt = 0;
+            }
+            if (nl + 64 > FM_LEAVES || sp <= 0) {
+                eval_leaves1<FP32C, TWO, W>(nl, S.leaves, S.St, pos4, m, T, e2, phi, A, B);
+                nl = 0;
+            }
+            unit_sync<W>();
+            if (sp <= 0) break;
         }
+        fgx = lanes_sum_d(fgx, 1);
+        fgy = lanes_sum_d(fgy, 1);
+        fgz = lanes_sum_d(fgz, 1);
+        fc = lanes_sum_d(fc, 1);
+        if (W > 1) {
+            if (lane == 0) S.far[wave] = make_double4(fgx, fgy, fgz, fc);
+            unit_sync<W>();
+            double4 f = S.far[0];
+            for (int w = 1; w < W; ++w) {
+                f.x += S.far[w].x;
+                f.y += S.far[w].y;
+                f.z += S.far[w].z;
+                f.w += S.far[w].w;
+            }
+            fgx = f.x; fgy = f.y; fgz = f.z; fc = f.w;
+        }
+        // each target's P partial sums (lanes tp + TP ph) combined in phase order
+        for (int h = 0; h < (TWO ? 2 : 1); ++h) {
+            unit_sync<W>();
+            if (FP32C) S.St.part.pm[tid] = make_double4(A.kx.value(), A.ky.value(), A.kz.value(), A.kp.value());
+            else S.St.part.pm[tid] = h ? make_double4(B.gx, B.gy, B.gz, B.ph) : make_double4(A.gx, A.gy, A.gz, A.ph);
+            unit_sync<W>();
+            if (!(h ? T.vb : T.va) || T.ph != 0) continue;
+            double4 r = S.St.part.pm[tid];
+            for (int k = 1; k < T.P; ++k) {
+                const double4 o = S.St.part.pm[tid + k * T.TP];
+                r.x += o.x;
+                r.y += o.y;
+                r.z += o.z;
+                r.w += o.w;
+            }
+            const int q = h ? T.qb : T.qa;
+            const double4 me = h ? T.b : T.a;
+            const double lin = fma(fgx, me.x - cl.y, fma(fgy, me.y - cl.z, fgz * (me.z - cl.w)));
+            const double gx = G * (r.x + fgx), gy = G * (r.y + fgy), gz = G * (r.z + fgz);
+            double ph = G * (r.w + (fc - lin));
+            if (eps > 0.0) {  // take out the self pair's potential term (see eval_leaves1)
+                const double is = FP32C ? (double)__builtin_amdgcn_rsqf((float)e2) : rsq_nr1(e2);
+                ph += G * (m[q] * is);
+            }
+            if (K.accumulate) {
+                K.gxo[q] += gx;
+                K.gyo[q] += gy;
+                K.gzo[q] += gz;
+                if (K.deo) {  // thermokinetic form: the work of gravity on e = u + v^2/2
+                    const double4 v = K.vel4[q];
+                    K.deo[q] += fma(v.x, gx, fma(v.y, gy, v.z * gz));
+                }
+            } else {
+                K.gxo[q] = gx;
+                K.gyo[q] = gy;
+                K.gzo[q] = gz;
+            }
+            if (phi) K.pho[q] = ph;
+        }
+    }
+}
+
+// One workgroup of four wavefronts takes one heavy leaf, or four others, one each.  A leaf that is far larger
+// than its neighbours' (few particles at the edge of a set, next to many small cells) opens everything
+// around it down to the particles: eight such leaves of the 262,144-particle polytrope ran 0.7 ms longer
+// than all other work in one wavefront each.  With at most 4,096 leaves (four
+// workgroups a CU hold 1,024 at once) leaves of 16 targets and more count as heavy too; smaller ones are
+// bound by the walk, which one wavefront does.  With the tree, us, for limits of 0 / 1,024 / 4,096 leaves:
+// 3,000 particles in leaves of 48 264 / 206 / 212, 20,011 in leaves of 32 448 / 442 / 362, 35,000 in leaves
+// of 64 1000 / 1010 / 583, 50,000 in leaves of 64 850 / 847 / 721; no difference past that.  Four leaves a
+// workgroup, sizes in order and the heavy leaves together: 262,144 particles 2.18 -> 1.56 ms.
+// The FP32C sums, whose last bits depend on the split, keep one wavefront a leaf.
+template <bool FP32C>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FP32C ? 1 : 4))) k_fmm(const FmmArgs K) {
+    __shared__ __align__(32) char lds[4 * sizeof(FmmLds<1>)];
+    static_assert(sizeof(FmmLds<4>) <= sizeof(lds), "the workgroup's form fits the four wavefronts' areas");
+    const bool phi = K.pho != nullptr && K.ctl->skip_phi == 0;  // as in k_gravity
+    int l0, l1, step;
+    group_range(K.ctl->n_leaves, l0, l1, step);
+    const int first = l0 - (int)(blockIdx.x / 8);  // the share's first leaf
+    const int heavy = FP32C ? 0 : K.ctl->fmm_heavy[blockIdx.x & 7];
+    for (int j = blockIdx.x / 8;; j += step) {
+        if (j < heavy) {
+            if constexpr (!FP32C)
+                fmm_leaf<FP32C, 4>(K, *reinterpret_cast<FmmLds<4>*>(lds), K.leaf_node[K.order[first + j]], phi);
+            __syncthreads();
+            continue;
+        }
+        const int u = first + heavy + 4 * (j - heavy);
+        if (u >= l1) break;
+        const int w = u + (int)(threadIdx.x >> 6);
+        if (w < l1)
+            fmm_leaf<FP32C, 1>(K, reinterpret_cast<FmmLds<1>*>(lds)[threadIdx.x >> 6], K.leaf_node[K.order[w]], phi);
     }
 }
 
@@ -973,12 +1165,12 @@ void launch_fmm(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, doub
     const int cg = std::min(2048, (dm.node_cap + 255) / 256);
     hipLaunchKernelGGL(k_fmm_cells, dim3(cg), dim3(256), 0, s, d.ctl, d.topo, d.range,
                        d.pos4, d.mom2);
-    if (fp32c)
-        hipLaunchKernelGGL(k_fmm<true>, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.leaf_node, d.parent,
-                           d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4, accumulate, gx, gy, gz, d.phi,
-                           d.vel4, de);
-    else
-        hipLaunchKernelGGL(k_fmm<false>, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.leaf_node, d.parent,
-                           d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4, accumulate, gx, gy, gz,
-                           d.phi, d.vel4, de);
+    int* order = reinterpret_cast<int*>(d.gsize);  // free once the groups are emitted
+    hipLaunchKernelGGL(k_unit_order, dim3(8), dim3(1024), 0, s, d.ctl, d.group, d.leaf_node, d.topo, order);
+    // four leaves a workgroup, about 3 n / leaf_size of them; the kernel loops over any beyond that
+    const int grid = std::min(8 * (int)((dm.n / std::max(1, dm.leaf_size) + 23) / 8), 8 * std::max(1, dm.wave_cap / 32));
+    const FmmArgs K{d.ctl, order, d.leaf_node, d.parent, d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4,
+                    accumulate, gx, gy, gz, d.phi, d.vel4, de};
+    if (fp32c) hipLaunchKernelGGL(k_fmm<true>, dim3(grid), dim3(256), 0, s, K);
+    else hipLaunchKernelGGL(k_fmm<false>, dim3(grid), dim3(256), 0, s, K);
 }

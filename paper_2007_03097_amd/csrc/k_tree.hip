@@ -392,13 +392,6 @@ struct NodeSums {
     double v[NODE_SUMS][NODE_LANES + 1];  // (a spare column against bank conflicts)
 };
 
-// Orders LDS accesses of one wave (its lanes run in step and LDS serves them in order).
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // acc (of lane q < Q) plus the eight lanes' terms t[q], in lane order.
 template <int Q>
 __device__ __forceinline__ void add_in_order(NodeSums& S, int j, const double (&t)[Q], double& acc) {

@@ -216,3 +216,45 @@ def test_fmm_leaf_populations(orc, leaf, eps):
     r = orc.fmm_gravity(ps.x[o], ps.y[o], ps.z[o], ps.m[o], orc.octree(k[o], leaf), box, orc.scale(box, 21), 0.6, 1.0, eps)
     d = np.sqrt((gx[o] - r["gx"]) ** 2 + (gy[o] - r["gy"]) ** 2 + (gz[o] - r["gz"]) ** 2)
     assert np.max(d / r["sg"]) <= 1e-12 and np.max(np.abs(phi[o] - r["phi"]) / r["sp"]) <= 1e-12
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,group", [(1, 8), (501, 16), (3001, 64), (33001, 32), (70001, 16)])
+def test_gravity_wavefronts_a_group(orc, n, group, prec):
+    """One, two and four wavefronts a group (by the number of groups), odd populations, and a grid of one
+    wavefront per compute unit that loops over the groups: the direct sum's field at theta = 0 for the
+    small sets, and the same bits from both grids."""
+    ps = uniform_random(n, seed=93)
+    out = []
+    for waves in (0, 1):
+        ctx = make_ctx(n, theta=0.0 if n < 4000 else 0.6, G=1.0, soft_eps=0.01, group_size=group, leaf_size=16,
+                       precision=prec, waves_per_cu=waves)
+        gpu_keys_order(ctx, parts(ps))
+        out.append(np.stack(gpu_gravity(ctx, n)))
+    assert np.array_equal(out[0], out[1])
+    if n < 4000:
+        gx, gy, gz, phi, sg = orc.gravity_direct(ps.x, ps.y, ps.z, ps.m, 1.0, 0.01, scale=True)
+        d = np.sqrt(((out[0][:3] - np.stack([gx, gy, gz])) ** 2).sum(0))
+        assert np.all(d <= (1e-12, 1e-6)[prec] * sg + 1e-300)
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_fmm_heavy_leaf(orc, prec):
+    """Few particles in a cell far larger than its neighbours' (heavy leaves), and a grid of one wavefront
+    per compute unit that loops over heavy and other leaves."""
+    import paper_2007_03097_amd as sph
+    ps = uniform_random(90001, seed=94)
+    ps.x[7:] *= 0.11
+    ps.y[7:] *= 0.11
+    ps.z[7:] *= 0.11      # seven particles of the unit box, the others near a corner of it
+    out = []
+    for waves in (0, 1):
+        ctx = make_ctx(ps.n, theta=0.6, G=1.0, soft_eps=0.01, leaf_size=16, precision=prec, waves_per_cu=waves,
+                       gravity_scheme=sph.SPH_GRAVITY_FMM)
+        k, o = gpu_keys_order(ctx, parts(ps))
+        out.append(np.stack(gpu_gravity(ctx, ps.n)))
+    assert np.array_equal(out[0], out[1])
+    box = orc.bbox(ps.x, ps.y, ps.z)
+    r = orc.fmm_gravity(ps.x[o], ps.y[o], ps.z[o], ps.m[o], orc.octree(k[o], 16), box, orc.scale(box, 21), 0.6, 1.0, 0.01)
+    d = np.sqrt(((out[0][:3][:, o] - np.stack([r["gx"], r["gy"], r["gz"]])) ** 2).sum(0))
+    assert np.all(d <= (1e-12, 1e-6)[prec] * r["sg"])
