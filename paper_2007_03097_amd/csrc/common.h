@@ -223,6 +223,18 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// W wavefronts work on one unit: the thread's index among them, and their barrier (one wavefront alone
+// needs none, only its LDS accesses in order).
+template <int W>
+__device__ __forceinline__ int unit_thread() {
+    return W == 1 ? lane_id() : (int)threadIdx.x;
+}
+template <int W>
+__device__ __forceinline__ void unit_sync() {
+    if constexpr (W == 1) wave_lds_fence();
+    else __syncthreads();
+}
+
 // Owner of each of 64 consecutive items p0 + lane of a concatenation whose parts start at the
 // ascending LDS offsets off[0 .. n): the last part that starts at or before the item.  `last` is the
 // owner of item p0 - 1 (-1 at the start; updated): no part is empty, so at most 64 parts start among

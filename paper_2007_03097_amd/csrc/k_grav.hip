@@ -27,18 +27,6 @@ constexpr int GW_LEAVES = 256;
 constexpr int DFS_HEADROOM = 7 * MAX_LEVEL + 8;
 static_assert(GW_STACK > 2 * DFS_HEADROOM, "room for wide rounds above the headroom");
 
-// W wavefronts work on one unit: the thread's index among them, and their barrier (one wavefront alone
-// needs none, only its LDS accesses in order).
-template <int W>
-__device__ __forceinline__ int unit_thread() {
-    return W == 1 ? lane_id() : (int)threadIdx.x;
-}
-template <int W>
-__device__ __forceinline__ void unit_sync() {
-    if constexpr (W == 1) wave_lds_fence();
-    else __syncthreads();
-}
-
 // LDS staging of one evaluation by W wavefronts: cell moments in the cell phase, particles in the leaf
 // phase.  FP32C stages FP32 records, 64 W cells per round; FP64 stages 32 W cells of 96 bytes per round.
 // With one wavefront the walk's LDS stays near 10 KB per workgroup (16 workgroups per CU).

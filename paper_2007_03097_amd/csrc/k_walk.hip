@@ -3,8 +3,8 @@
 // particle).
 //
 // One wavefront per target group (at most group_size consecutive particles of one compact
-// octree cell), in an XCD-aware loop over the groups (one group per workgroup at the
-// default grid, which holds a workgroup per expected group).
+// octree cell), or two or four where groups are few, in an XCD-aware loop over the groups (one group
+// per workgroup at the default grid, which holds a workgroup per expected group).
 //  1. Group box and largest h by wave reductions.
 //  2. Wide tree walk: up to 64 nodes are tested at once, one per lane, against the group
 //     box.  A node survives when the squared gap between the boxes, summed in the same
@@ -68,9 +68,20 @@ struct GroupBox {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int TILE_COMP = 5;  // staged per source: 2 b (three), 2 h, c
+template <int W>
 struct Tile {
-    float v[TILE_COMP][TILE_RING];
-    int src[TILE_RING];
+    static constexpr int RING = TILE_RING * W;
+    float v[TILE_COMP][RING];
+    int src[RING];
+};
+
+// What W wavefronts that match a tile each tell one another.
+template <int W>
+struct Exchange {
+    int pass[W];      // candidates that passed the box filter
+    int uni[W];       // union members of the wavefront's tile
+    int hits[W][64];  // hits of a target in it
+    int walked[3];    // candidates listed, nodes left on the stack, overflow
 };
 
 struct Screen {
@@ -82,7 +93,8 @@ struct Screen {
 __device__ __forceinline__ float next_up(double v) { return (float)(v * (1.0 + 0x1p-20)); }
 
 // Stages source b at ring slot r.
-__device__ __forceinline__ void stage_source(Tile& tile, int r, const double4& b, int src, const Screen& S) {
+template <int W>
+__device__ __forceinline__ void stage_source(Tile<W>& tile, int r, const double4& b, int src, const Screen& S) {
     const double x = b.x - S.o[0], y = b.y - S.o[1], z = b.z - S.o[2];
     tile.v[0][r] = 2.0f * (float)x;
     tile.v[1][r] = 2.0f * (float)y;
@@ -120,14 +132,15 @@ __device__ __forceinline__ void load_targets(LaneTargets<T>& L, const double4* _
 
 // The exact predicate for undecided elements of a 32 x 32 block (bit i of und = element i, matrix row
 // (i & 3) + 8 (i >> 2) + 4 half); rows from `rows` on are stale.
-__device__ u32 resolve_exact(u32 und, u32 hits, const double4 A, int half, int rows, int slot0, const Tile& tile,
+template <int W>
+__device__ u32 resolve_exact(u32 und, u32 hits, const double4 A, int half, int rows, int slot0, const Tile<W>& tile,
                              const double4* __restrict__ pos4) {
     while (und) {
         const int i = __ffs(und) - 1;
         und &= und - 1;
         const int m = (i & 3) + 8 * (i >> 2) + 4 * half;
         if (m >= rows) continue;
-        const double4 s = pos4[tile.src[(slot0 + m) & (TILE_RING - 1)]];
+        const double4 s = pos4[tile.src[(slot0 + m) & (Tile<W>::RING - 1)]];
         const double dx = A.x - s.x, dy = A.y - s.y, dz = A.z - s.z;
         double r2 = dx * dx + dy * dy;
         r2 = r2 + dz * dz;
@@ -137,15 +150,16 @@ __device__ u32 resolve_exact(u32 und, u32 hits, const double4 A, int half, int r
     return hits;
 }
 
-// Matches the tn (1 .. 64) sources at ring positions head .. against the group's targets: hits go to
-// the group's union and to the targets' lists.
-template <int T>
-__device__ __forceinline__ void test_tile(int head, int tn, const Tile& tile, LaneTargets<T>& L, const Screen& S,
+// Matches the n sources (1 .. 64 W) at ring positions first .. against the group's targets, 64 per
+// wavefront: hits go to the group's union and to the targets' lists, in the order of the sources.
+template <int T, int W>
+__device__ __forceinline__ void test_tile(int first, int n, const Tile<W>& tile, LaneTargets<T>& L, const Screen& S,
                                           const double4* __restrict__ pos4, int gx, int gy, int cap, u16* mylist,
-                                          int* myuni, int ulim, int& ucnt) {
-    const int lane = lane_id(), col = lane & 31, half = lane >> 5;
+                                          int* myuni, int ulim, int& ucnt, Exchange<W>& X) {
+    const int lane = lane_id(), col = lane & 31, half = lane >> 5, wave = W > 1 ? threadIdx.x >> 6 : 0;
+    const int head = first + 64 * wave, tn = W > 1 ? min(n - 64 * wave, 64) : n;  // (none left: no hits)
     // largest |h| of the tile: non-negative floats order as unsigned integers, a NaN above them
-    const u32 hv = lane < tn ? __float_as_uint(fabsf(tile.v[3][(head + lane) & (TILE_RING - 1)])) : 0u;
+    const u32 hv = lane < tn ? __float_as_uint(fabsf(tile.v[3][(head + lane) & (Tile<W>::RING - 1)])) : 0u;
     const float hm = 0.5f * __uint_as_float(wave_reduce_u32(hv, [](u32 a, u32 b) { return max(a, b); }));
     const float R = S.reach + hm, tt = S.hg + hm;
     const float M = fmaf(fmaf(R, R, tt * tt), 0x1p-19f * (1.0f + 0x1p-18f), 0x1p-100f);
@@ -155,7 +169,7 @@ __device__ __forceinline__ void test_tile(int head, int tn, const Tile& tile, La
     float a0[2], a1[2], a2[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
-        const int j = (head + 32 * r + col) & (TILE_RING - 1);
+        const int j = (head + 32 * r + col) & (Tile<W>::RING - 1);
         a0[r] = tile.v[half][j];
         a1[r] = tile.v[2 + half][j];
         a2[r] = half ? 1.0f : tile.v[4][j];
@@ -220,13 +234,31 @@ __device__ __forceinline__ void test_tile(int head, int tn, const Tile& tile, La
     auto either = [](u32 a, u32 b) { return a | b; };
     const u32 u0 = wave_reduce_u32(w0, either), u1 = wave_reduce_u32(w1, either);  // union of the tile
     const u64 ub = (u64)u0 | ((u64)u1 << 32);
+    int ufirst = ucnt, slot = L.cnt;  // after those of the wavefronts before this one
+    if constexpr (W > 1) {
+        if (L.p == 0) X.hits[wave][L.t] = (int)(__popc(w0) + __popc(w1));
+        if (lane == 0) X.uni[wave] = (int)__popcll(ub);
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < W; ++v) {
+            const int h = X.hits[v][L.t], u = X.uni[v];
+            L.cnt += h;
+            ucnt += u;
+            if (v < wave) {
+                slot += h;
+                ufirst += u;
+            }
+        }
+    } else {
+        L.cnt += (int)(__popc(w0) + __popc(w1));
+        ucnt += (int)__popcll(ub);
+    }
     if ((ub >> lane) & 1ull) {
-        const int r = ucnt + __popcll(ub & lanemask_lt());
-        if (r < ulim) myuni[r] = tile.src[(head + lane) & (TILE_RING - 1)];
+        const int r = ufirst + __popcll(ub & lanemask_lt());
+        if (r < ulim) myuni[r] = tile.src[(head + lane) & (Tile<W>::RING - 1)];
     }
     // the lane's share of its target's hits: sources p T .. p T + T - 1, after those before them
     u32 m0 = w0, m1 = w1;
-    int slot = L.cnt;
     if constexpr (T < 64) {
         const int j0 = L.p * T;
         const u32 below = (1u << (j0 & 31)) - 1u, range = T == 32 ? 0xffffffffu : ((1u << (T & 31)) - 1u) << (j0 & 31);
@@ -247,7 +279,6 @@ __device__ __forceinline__ void test_tile(int head, int tn, const Tile& tile, La
             else m0 &= ~(1u << (31 - __clz((int)m0)));
         }
     }
-    L.cnt += (int)(__popc(w0) + __popc(w1));
     // entries past UNION_MAX (likewise reported) stay at the last index, in bounds
     const u32 last = UNION_MAX - 1, stride = 2u * (u32)gy;
     u32 at = 2u * ((u32)slot * (u32)gy + (u32)L.t);  // byte offset in the group's block, below 2 x 64 x 4,096
@@ -260,9 +291,8 @@ __device__ __forceinline__ void test_tile(int head, int tn, const Tile& tile, La
             at += stride;
         }
     };
-    append(m0, u0, (u32)ucnt);
-    append(m1, u1, (u32)ucnt + __popc(u0));
-    ucnt += __popcll(ub);
+    append(m0, u0, (u32)ufirst);
+    append(m1, u1, (u32)ufirst + __popc(u0));
 }
 
 // Matching of the group's targets against the particles of the nc candidate leaves, whose first
@@ -271,34 +301,44 @@ __device__ __forceinline__ void test_tile(int head, int tn, const Tile& tile, La
 // test (gap^2 < (hmax_group + h_b)^2), so no true neighbour is dropped; survivors enter an
 // LDS ring and are matched 64 at a time.  Sources left in the ring (< 64) are matched by
 // the caller's final flush.  The next 64 candidates are loaded before a tile is matched.
-template <int T>
-__device__ void match_candidates(int nc, int* cand, int* coff, Tile& tile, int& head, int& tail, const GroupBox& gb,
+template <int T, int W>
+__device__ void match_candidates(int nc, int* cand, int* coff, Tile<W>& tile, int& head, int& tail, const GroupBox& gb,
                                  const Screen& S, const double4* __restrict__ pos4, LaneTargets<T>& L, int gx, int gy,
-                                 int cap, u16* mylist, int* myuni, int ulim, int& ucnt) {
-    const int lane = lane_id();
+                                 int cap, u16* mylist, int* myuni, int ulim, int& ucnt, Exchange<W>& X) {
+    const int lane = lane_id(), wave = W > 1 ? threadIdx.x >> 6 : 0;
     const u64 lt = lanemask_lt();
     int total = 0;
-    for (int j0 = 0; j0 < nc; j0 += 64) {
-        const int j = j0 + lane;
-        const int c = j < nc ? coff[j] : 0;
-        const int incl = wave_incl_scan(c);
-        if (j < nc) coff[j] = total + incl - c;
-        total += wave_last(incl);
+    if (W == 1 || wave == 0) {
+        for (int j0 = 0; j0 < nc; j0 += 64) {
+            const int j = j0 + lane;
+            const int c = j < nc ? coff[j] : 0;
+            const int incl = wave_incl_scan(c);
+            if (j < nc) coff[j] = total + incl - c;
+            total += wave_last(incl);
+        }
+        if (W > 1 && lane == 0) coff[nc] = total;
     }
-    __syncthreads();
+    unit_sync<W>();
+    if (W > 1) total = coff[nc];
     int last = -1, src = 0;
     double4 b;
     auto fetch = [&](int p0) {
-        const int a = tile_owner(coff, nc, p0, last);
-        if (p0 + lane < total) {
-            src = cand[a] + (p0 + lane - coff[a]);
+        int a = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const int own = tile_owner(coff, nc, p0 + 64 * w, last);
+            if (w == wave) a = own;
+        }
+        const int p = p0 + 64 * wave + lane;
+        if (p < total) {
+            src = cand[a] + (p - coff[a]);
             b = pos4[src];
         }
     };
     if (total > 0) fetch(0);
-    for (int p0 = 0; p0 < total; p0 += 64) {
+    for (int p0 = 0; p0 < total; p0 += 64 * W) {
         bool pass = false;
-        if (p0 + lane < total) {
+        if (p0 + 64 * wave + lane < total) {
             const double gx = fmax(0.0, fmax(b.x - gb.hi[0], gb.lo[0] - b.x));
             const double gy2 = fmax(0.0, fmax(b.y - gb.hi[1], gb.lo[1] - b.y));
             const double gz = fmax(0.0, fmax(b.z - gb.hi[2], gb.lo[2] - b.z));
@@ -308,30 +348,45 @@ __device__ void match_candidates(int nc, int* cand, int* coff, Tile& tile, int& 
             pass = r2 < tt * tt;
         }
         const u64 bal = __ballot(pass);
-        if (pass) stage_source(tile, (tail + __popcll(bal & lt)) & (TILE_RING - 1), b, src, S);
-        tail += __popcll(bal);
-        __syncthreads();
-        if (p0 + 64 < total) fetch(p0 + 64);
-        if (tail - head >= 64) {
-            test_tile(head, 64, tile, L, S, pos4, gx, gy, cap, mylist, myuni, ulim, ucnt);
-            head += 64;
+        int at = tail;
+        if constexpr (W > 1) {
+            if (lane == 0) X.pass[wave] = (int)__popcll(bal);
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < W; ++v) {
+                const int c = X.pass[v];
+                if (v < wave) at += c;
+                tail += c;
+            }
+        } else {
+            tail += __popcll(bal);
         }
-        __syncthreads();
+        if (pass) stage_source(tile, (at + __popcll(bal & lt)) & (Tile<W>::RING - 1), b, src, S);
+        unit_sync<W>();
+        if (p0 + 64 * W < total) fetch(p0 + 64 * W);
+        if (tail - head >= 64 * W) {
+            test_tile(head, 64 * W, tile, L, S, pos4, gx, gy, cap, mylist, myuni, ulim, ucnt, X);
+            head += 64 * W;
+        }
+        unit_sync<W>();
     }
 }
 
-template <int T>
-__global__ void __launch_bounds__(64) k_nbr_lists(DevCtl* ctl, const int4* __restrict__ group, int cap,
-                                                  const int4* __restrict__ topo, const double4* __restrict__ nbox_lo,
-                                                  const double4* __restrict__ nbox_hi, const double4* __restrict__ pos4,
-                                                  u16* __restrict__ nbr, int* __restrict__ nbr_cnt,
-                                                  int* __restrict__ list_base, int* __restrict__ uni,
-                                                  int* __restrict__ ucnt_out) {
+// W wavefronts per group: the first one walks the tree, all of them match the candidates, a tile each.
+template <int T, int W>
+__global__ void __launch_bounds__(64 * W) k_nbr_lists(DevCtl* ctl, const int4* __restrict__ group, int cap,
+                                                      const int4* __restrict__ topo,
+                                                      const double4* __restrict__ nbox_lo,
+                                                      const double4* __restrict__ nbox_hi,
+                                                      const double4* __restrict__ pos4, u16* __restrict__ nbr,
+                                                      int* __restrict__ nbr_cnt, int* __restrict__ list_base,
+                                                      int* __restrict__ uni, int* __restrict__ ucnt_out) {
     __shared__ int stack[WALK_STACK];
     __shared__ int cand[WALK_CAND];
-    __shared__ int coff[WALK_CAND];
-    __shared__ Tile tile;
-    const int lane = lane_id();
+    __shared__ int coff[WALK_CAND + 1];
+    __shared__ Tile<W> tile;
+    __shared__ Exchange<W> X;
+    const int lane = lane_id(), wave = W > 1 ? threadIdx.x >> 6 : 0;
     const u64 lt = lanemask_lt();
     LaneTargets<T> L;
     L.t = lane % T;
@@ -376,73 +431,86 @@ __global__ void __launch_bounds__(64) k_nbr_lists(DevCtl* ctl, const int4* __res
         const bool single = g.z < 0;
         const int wl = ctl->walk_level;
         const int first = single ? ctl->level_off[wl] : ctl->level_off[3] + g.z;
-        int sp = single ? ctl->level_count[wl] : 1, nc = 0, iters = 0;
+        int sp = single ? ctl->level_count[wl] : 1, iters = 0;
         bool overflow = false;
-        __syncthreads();
-        if (lane < sp) stack[lane] = first + lane;
-        __syncthreads();
-        while (sp > 0) {
-            if (++iters > (1 << 20)) {  // bounded: every wave leaves the loop
-                overflow = true;
-                break;
+        unit_sync<W>();
+        if ((int)threadIdx.x < sp && (W == 1 || wave == 0)) stack[lane] = first + lane;
+        wave_lds_fence();
+        while (true) {
+            int nc = 0;
+            // until the list may not hold another round or the walk has ended
+            while ((W == 1 || wave == 0) && sp > 0 && nc + 64 <= WALK_CAND) {
+                if (++iters > (1 << 20)) {  // bounded: every wave leaves the loop
+                    overflow = true;
+                    break;
+                }
+                // pop at most as many nodes as the free stack can take the children of (8 each)
+                int k = sp < 64 ? sp : 64;
+                const int room = (WALK_STACK - sp) / 8;
+                if (k > room) k = room > 1 ? room : 1;
+                const int node = lane < k ? stack[sp - k + lane] : -1;
+                wave_lds_fence();
+                sp -= k;
+                bool hit = false;
+                int4 tp = make_int4(0, 0, 0, 0);
+                if (node >= 0) {
+                    tp = topo[node];
+                    const double4 a = nbox_lo[node], b = nbox_hi[node];
+                    const double gx = fmax(0.0, fmax(a.x - hi[0], lo[0] - b.x));
+                    const double gy = fmax(0.0, fmax(a.y - hi[1], lo[1] - b.y));
+                    const double gz = fmax(0.0, fmax(a.z - hi[2], lo[2] - b.z));
+                    double r2 = gx * gx + gy * gy;
+                    r2 = r2 + gz * gz;
+                    const double tt = hg + a.w;
+                    hit = r2 < tt * tt;
+                }
+                const bool isleaf = hit && tp.w;
+                const u64 bl = __ballot(isleaf);
+                if (isleaf) {
+                    cand[nc + __popcll(bl & lt)] = tp.x;
+                    coff[nc + __popcll(bl & lt)] = tp.y;
+                }
+                nc += __popcll(bl);
+                const int nch = (hit && !tp.w) ? tp.y : 0;
+                const int incl = wave_incl_scan(nch);
+                const int tot = wave_last(incl);
+                if (sp + tot > WALK_STACK) {
+                    overflow = true;
+                    break;
+                }
+                for (int j = 0; j < nch; ++j) stack[sp + incl - nch + j] = tp.x + j;
+                sp += tot;
+                wave_lds_fence();
             }
-            if (nc + 64 > WALK_CAND) {
-                match_candidates(nc, cand, coff, tile, head, tail, gb, S, pos4, L, g.x, g.y, cap, mylist, myuni,
-                                 ulim, ucnt);
-                nc = 0;
+            if (W > 1) {
+                if (threadIdx.x == 0) {
+                    X.walked[0] = nc;
+                    X.walked[1] = sp;
+                    X.walked[2] = overflow;
+                }
+                __syncthreads();
+                nc = X.walked[0];
+                sp = X.walked[1];
+                overflow = X.walked[2];
             }
-            // pop at most as many nodes as the free stack can take the children of (8 each)
-            int k = sp < 64 ? sp : 64;
-            const int room = (WALK_STACK - sp) / 8;
-            if (k > room) k = room > 1 ? room : 1;
-            const int node = lane < k ? stack[sp - k + lane] : -1;
-            __syncthreads();
-            sp -= k;
-            bool hit = false;
-            int4 tp = make_int4(0, 0, 0, 0);
-            if (node >= 0) {
-                tp = topo[node];
-                const double4 a = nbox_lo[node], b = nbox_hi[node];
-                const double gx = fmax(0.0, fmax(a.x - hi[0], lo[0] - b.x));
-                const double gy = fmax(0.0, fmax(a.y - hi[1], lo[1] - b.y));
-                const double gz = fmax(0.0, fmax(a.z - hi[2], lo[2] - b.z));
-                double r2 = gx * gx + gy * gy;
-                r2 = r2 + gz * gz;
-                const double tt = hg + a.w;
-                hit = r2 < tt * tt;
-            }
-            const bool isleaf = hit && tp.w;
-            const u64 bl = __ballot(isleaf);
-            if (isleaf) {
-                cand[nc + __popcll(bl & lt)] = tp.x;
-                coff[nc + __popcll(bl & lt)] = tp.y;
-            }
-            nc += __popcll(bl);
-            const int nch = (hit && !tp.w) ? tp.y : 0;
-            const int incl = wave_incl_scan(nch);
-            const int tot = wave_last(incl);
-            if (sp + tot > WALK_STACK) {
-                overflow = true;
-                break;
-            }
-            for (int j = 0; j < nch; ++j) stack[sp + incl - nch + j] = tp.x + j;
-            sp += tot;
-            __syncthreads();
-        }
-        __syncthreads();
-        if (!overflow) {
+            if (overflow) break;
+            unit_sync<W>();
             match_candidates(nc, cand, coff, tile, head, tail, gb, S, pos4, L, g.x, g.y, cap, mylist, myuni, ulim,
-                             ucnt);
+                             ucnt, X);
+            unit_sync<W>();
+            if (sp <= 0) break;
+        }
+        if (!overflow) {
             if (tail > head)
-                test_tile(head, tail - head, tile, L, S, pos4, g.x, g.y, cap, mylist, myuni, ulim, ucnt);
-            __syncthreads();
-        } else if (lane == 0)
+                test_tile(head, tail - head, tile, L, S, pos4, g.x, g.y, cap, mylist, myuni, ulim, ucnt, X);
+            unit_sync<W>();
+        } else if (threadIdx.x == 0)
             set_err(ctl, ERR_WALK_STACK);
-        if (lane == 0) {
+        if (threadIdx.x == 0) {
             ucnt_out[gi] = overflow ? 0 : (ucnt < ulim ? ucnt : ulim);
             if (ucnt > UNION_MAX) set_err(ctl, ERR_UNION_CAP);
         }
-        if (L.p == 0 && L.t < g.y) {
+        if (L.p == 0 && L.t < g.y && (W == 1 || wave == 0)) {
             const int q = g.x + L.t;
             nbr_cnt[q] = overflow ? 0 : (L.cnt < cap ? L.cnt : cap);
             list_base[q] = overflow ? -1 : gi;
@@ -456,15 +524,29 @@ __global__ void __launch_bounds__(64) k_nbr_lists(DevCtl* ctl, const int4* __res
 
 void launch_nbr_lists(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     if (dm.n <= 0) return;
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(dm.group_grid), dim3(64), 0, s, d.ctl, d.group, dm.nbr_cap,
+    auto go = [&](auto kern, int waves) {
+        const int grid = std::min(dm.group_grid, 8 * std::max(1, dm.wave_cap / (8 * waves)));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), 0, s, d.ctl, d.group, dm.nbr_cap,
                            d.topo, d.nbox_lo, d.nbox_hi, d.pos4, d.nbr, d.nbr_cnt, d.nbr_base, d.uni, d.ucnt);
     };
+    // Wavefronts a group: with few groups a wavefront's own latencies (25 us at 4,096 particles) are the
+    // kernel's time, and the matching, though not the walk, is shared.  Lists alone, us, for 1 / 2 / 4: 4,096
+    // particles in groups of 32 25.9 / 20.7 / 19.0; 50,021 in groups of 32 47 / 43 / 55; 123,480 in groups of
+    // 64 65 / 69 / 78; with build, density and forces 20,011 in groups of 64 178 / 168 / 163, 100,003 in groups
+    // of 64 266 / 256 / 268, 50,021 in groups of 16 240 / 258 / 276.
+    const int64_t units = dm.n / std::max(1, dm.group_size);
+    const int W = units > 1600 ? 1 : (units > 512 ? 2 : 4);
+    auto size = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        if (W == 4) go(k_nbr_lists<T, 4>, 4);
+        else if (W == 2) go(k_nbr_lists<T, 2>, 2);
+        else go(k_nbr_lists<T, 1>, 1);
+    };
     switch (dm.group_size) {  // validated at context creation: 8, 16, 32 or 64
-        case 8: go(k_nbr_lists<8>); break;
-        case 16: go(k_nbr_lists<16>); break;
-        case 32: go(k_nbr_lists<32>); break;
-        default: go(k_nbr_lists<64>); break;
+        case 8: size(std::integral_constant<int, 8>()); break;
+        case 16: size(std::integral_constant<int, 16>()); break;
+        case 32: size(std::integral_constant<int, 32>()); break;
+        default: size(std::integral_constant<int, 64>()); break;
     }
 }
 

@@ -258,3 +258,16 @@ def test_fmm_heavy_leaf(orc, prec):
     r = orc.fmm_gravity(ps.x[o], ps.y[o], ps.z[o], ps.m[o], orc.octree(k[o], 16), box, orc.scale(box, 21), 0.6, 1.0, 0.01)
     d = np.sqrt(((out[0][:3][:, o] - np.stack([r["gx"], r["gy"], r["gz"]])) ** 2).sum(0))
     assert np.all(d <= (1e-12, 1e-6)[prec] * r["sg"])
+
+
+@pytest.mark.parametrize("waves", [0, 1])
+@pytest.mark.parametrize("n,group", [(4103, 8), (4105, 8), (12807, 8), (12809, 8), (32769, 64), (32833, 64), (3, 64)])
+def test_neighbors_wavefronts_a_group(orc, n, group, waves):
+    """Both sides of the numbers of groups at which one, two or four wavefronts share a group's matching;
+    tiles that only some of them have; and a grid that loops over the groups."""
+    ps = uniform_random(n, seed=95, h=(0.5 * n ** (-1.0 / 3), 2.0 * n ** (-1.0 / 3)))
+    ctx = make_ctx(n, group_size=group, nbr_capacity=1024, waves_per_cu=waves)
+    gpu_keys_order(ctx, parts(ps))
+    off, idx = gpu_neighbors(ctx, n)
+    ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+    assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
