@@ -336,24 +336,41 @@ __global__ void __launch_bounds__(TB) k_emit_nodes(int n, const signed char* __r
 // Group cells: the largest nodes holding at most gcap particles (at or below min_level),
 // plus leaves that hold more (runs of equal keys).  They partition the sorted particles.
 // Each is cut into target groups of at most gsz consecutive particles: the group's size is
-// recorded at its first position, and the groups of each tile of positions are counted.
+// recorded at its first position, and the groups of each tile of positions are counted: one atomic
+// for the lanes of a wave whose cells start in the same tile (nodes are in breadth-first order, so
+// these are neighbours; one atomic a group took 36 us for 100,000 groups of 16, 5.5 so).
 __global__ void k_group_starts(const DevCtl* __restrict__ ctl, int gcap, int gsz, int min_level,
                                const int4* __restrict__ topo, const int* __restrict__ parent,
                                const int2* __restrict__ range, u32* gsize, int* gcount) {
     const int nn = ctl->n_nodes;
-    for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < nn; b += gridDim.x * blockDim.x) {
-        const int4 tp = topo[b];
-        const int2 r = range[b];
-        const int p = parent[b];
-        const bool fits = r.y <= gcap && tp.z >= min_level;
-        if (!(fits || tp.w)) continue;
-        bool pfits = false;
-        if (p >= 0) pfits = range[p].y <= gcap && topo[p].z >= min_level;
-        if (pfits) continue;
-        const int e = r.x + r.y;
-        for (int k = r.x; k < e; k += gsz) {
-            gsize[k] = (u32)min(gsz, e - k);
-            atomicAdd(&gcount[k / GROUP_TILE], 1);
+    for (int b0 = blockIdx.x * blockDim.x; b0 < nn; b0 += gridDim.x * blockDim.x) {
+        const int b = b0 + threadIdx.x;
+        int tile = -1, count = 0;
+        if (b < nn) {
+            const int4 tp = topo[b];
+            const int2 r = range[b];
+            const int p = parent[b];
+            const bool fits = r.y <= gcap && tp.z >= min_level;
+            bool pfits = false;
+            if (p >= 0) pfits = range[p].y <= gcap && topo[p].z >= min_level;
+            if ((fits || tp.w) && !pfits) {
+                const int e = r.x + r.y;
+                tile = r.x / GROUP_TILE;
+                for (int k = r.x; k < e; k += gsz) {
+                    gsize[k] = (u32)min(gsz, e - k);
+                    if (k / GROUP_TILE == tile) ++count;
+                    else atomicAdd(&gcount[k / GROUP_TILE], 1);
+                }
+            }
+        }
+        u64 todo = __ballot(count > 0);
+        while (todo) {
+            const int t = __builtin_amdgcn_readlane(tile, __builtin_ctzll(todo));
+            const bool same = count > 0 && tile == t;
+            const u64 m = __ballot(same);
+            const int sum = wave_last(wave_incl_scan(same ? count : 0));
+            if (lane_id() == 0) atomicAdd(&gcount[t], sum);
+            todo &= ~m;
         }
     }
 }
