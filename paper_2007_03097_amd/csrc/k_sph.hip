@@ -10,9 +10,10 @@
 //                       mu = h_ab v_ab . r_ab / (r^2 + eps h_ab^2)
 // with the M4 cubic spline, W = w(q)/(pi h^3), grad_a W_ab = r_ab g(q)/(pi h^5), g = w'(q)/q.
 //
-// One 256-thread workgroup per target group, in an XCD-aware loop over the groups.  The group's
+// One workgroup of NT = 256 threads (128 for small groups in FP64) per target group, in an XCD-aware loop
+// over the groups.  The group's
 // source union (built with the lists) is staged in LDS in chunks; each of the group's n_g
-// targets is served by PL = 256/n_g threads that take every PL-th entry of its list --
+// targets is served by PL = NT/n_g threads that take every PL-th entry of its list --
 // entries are ascending union indices, so each thread walks its entries once across the
 // chunks --
 // and read the source records from LDS.  The partial sums of a target are added in a
@@ -54,16 +55,6 @@ void launch_thermo_from_caller(hipStream_t s, const DevPtrs& d, const Dims& dm, 
                            cs, d.rho, d.P, d.cs, d.thr4, d.thrf);
 }
 
-constexpr int PAIR_THREADS = 256;
-constexpr int DENS_CHUNK = 512;
-// Union sources staged per round of the force pass: the largest counts that leave four workgroups a CU
-// (88-byte records in FP64, 80-byte ones in FP32C).  A wave runs each round as long as its busiest
-// target, so a union in one round wastes fewer lanes: at 987,840 particles in groups of 64 FP64 takes
-// 239 us at 256 a round (seven workgroups a CU), 232 at 384 and 204 at 464; at 131,101 in groups of 32,
-// with smaller unions, 42 and 44 us.  512 threads a workgroup: 288 us (half the entries a thread).
-constexpr int FORCE_CHUNK = 464;
-constexpr int FORCE_CHUNK_F = 512;
-
 // A thread's entries of its target's list: slots phi, phi + PL, ... of a list whose slots lie n_g entries
 // apart, as byte offsets from the group's (uniform) base.
 struct Entries {
@@ -86,9 +77,9 @@ struct Entries {
         a3 = at(off + 3 * step);
     }
     // Hands the entries below ce (those of the staged round; entries ascend) to add, in batches of four
-    // that are read one batch ahead.  Slots are clamped into the list; off < end decides.  A batch that
-    // ends early ends the round too: the next batch's entries are beyond ce or the list's end as well.
-    // The next batch is carried by the loop, or the compiler sinks each load to the test that uses it.
+    // that are read one batch ahead.  A batch that ends early ends the round too: the next batch's
+    // entries are beyond ce as well, or INT_MAX.  The next batch is carried by the loop, or the
+    // compiler sinks each load to the test that uses it.
     template <typename Add>
     __device__ __forceinline__ void round(int ce, Add&& add) {
         auto take = [&](int r) {
@@ -98,7 +89,13 @@ struct Entries {
             return true;
         };
         while (off < end && a0 < ce) {
-            const int b0 = at(off + 4 * step), b1 = at(off + 5 * step), b2 = at(off + 6 * step), b3 = at(off + 7 * step);
+            int b0 = INT_MAX, b1 = INT_MAX, b2 = INT_MAX, b3 = INT_MAX;
+            if (off + 4 * step < end) {
+                b0 = at(off + 4 * step);
+                b1 = at(off + 5 * step);
+                b2 = at(off + 6 * step);
+                b3 = at(off + 7 * step);
+            }
             add(a0);
             off += step;
             if (take(a1))
@@ -184,12 +181,12 @@ struct Split4 {
 };
 
 // Density sources staged in LDS: FP64 (x, y, z, h) and m, or FP32 offset records and m.
-template <bool FP32C>
+template <bool FP32C, int CH>
 struct DensSrc;
-template <>
-struct DensSrc<false> {
-    Split4<DENS_CHUNK> pos;
-    double mass[DENS_CHUNK];
+template <int CH>
+struct DensSrc<false, CH> {
+    Split4<CH> pos;
+    double mass[CH];
     using Rec = double4;
     using Mass = double;
     __device__ __forceinline__ void put(int i, const double4 p, double mb, const double4&) {
@@ -199,10 +196,10 @@ struct DensSrc<false> {
     __device__ __forceinline__ double4 rec(int i) const { return pos.get(i); }
     __device__ __forceinline__ static double4 target(const double4 p, const double4&) { return p; }
 };
-template <>
-struct DensSrc<true> {
-    float4 pos[DENS_CHUNK];
-    float mass[DENS_CHUNK];
+template <int CH>
+struct DensSrc<true, CH> {
+    float4 pos[CH];
+    float mass[CH];
     using Rec = float4;
     using Mass = float;
     __device__ __forceinline__ void put(int i, const double4 p, double mb, const double4& o) {
@@ -212,41 +209,49 @@ struct DensSrc<true> {
     __device__ __forceinline__ float4 rec(int i) const { return pos[i]; }
     __device__ __forceinline__ static float4 target(const double4 p, const double4& o) { return offset_rec(p, o); }
 };
-static_assert(sizeof(DensSrc<true>) >= PAIR_THREADS * sizeof(double), "the reduction reuses the staging");
+// Sets whose workgroups (256 threads, 40 KB) are resident at once.
+static bool few_groups(const Dims& dm) { return dm.n <= 512 * (int64_t)dm.group_size; }
+// FP64 sums over small groups take 128 threads: with 256 a thread would have three or four entries of its
+// target's list, too few beside what it does once.  1.0M particles in 56 boxes, groups of 16: density 216
+// -> 171 us, forces 363 -> 300 us; 123,480 of the tube 33 -> 27 and 52 -> 40 us; groups of 32 keep 256
+// (density 148 and 143, forces 248 and 297 us).  The FP32C sums, whose last bits depend on the
+// split, keep 256.
+static bool narrow_groups(const Dims& dm) { return dm.group_size <= 16 && !few_groups(dm); }
 
-template <bool FP32C>
-__global__ void __launch_bounds__(PAIR_THREADS) k_density(
+template <bool FP32C, int NT, int CH>
+__global__ void __launch_bounds__(NT) k_density(
     const DevCtl* __restrict__ ctl, const int4* __restrict__ group, int gsz, int cap, const u16* __restrict__ nbr,
     const int* __restrict__ nbr_cnt, const int* __restrict__ uni, const int* __restrict__ ucnt,
     const double4* __restrict__ pos4, const double4* __restrict__ vel4, const double* __restrict__ m,
     const double* __restrict__ u_eos, int kin, double gamma, double h_coeff, double* __restrict__ rho,
     double* __restrict__ P, double* __restrict__ cs, double* __restrict__ hnext, double4* __restrict__ thr4,
     float4* __restrict__ thrf) {
-    __shared__ DensSrc<FP32C> S;
+    __shared__ DensSrc<FP32C, CH> S;  // CH union members a round
+    static_assert(sizeof(S) >= NT * sizeof(double), "the reduction reuses the staging");
     const int tid = threadIdx.x;
     int g0, g1, gstep;
     group_range(ctl->n_groups, g0, g1, gstep);
     for (int gi = g0; gi < g1; gi += gstep) {
         const int4 g = group[gi];
-        // PL = 256 / n_g threads per target, so a group with few targets still fills the
-        // workgroup; thread tid serves target tid mod n_g (the last 256 mod n_g threads idle)
-        const int PL = PAIR_THREADS / g.y;
+        // PL = NT / n_g threads per target, so a group with few targets still fills the
+        // workgroup; thread tid serves target tid mod n_g (the last NT mod n_g threads idle)
+        const int PL = NT / g.y;
         const int t = tid % g.y, phi = tid / g.y;
         const bool tv = phi < PL;
         const int q = g.x + t;
         const double4 org = pos4[g.x];  // group origin (FP32C offsets)
         const double4 mp = tv ? pos4[q] : make_double4(org.x, org.y, org.z, 1);
-        const typename DensSrc<FP32C>::Rec me = DensSrc<FP32C>::target(mp, org);
+        const typename DensSrc<FP32C, CH>::Rec me = DensSrc<FP32C, CH>::target(mp, org);
         const int cnt = tv ? nbr_cnt[q] : 0;
         Entries E(nbr + (size_t)g.x * cap, g.y, t, phi, PL, cnt);
         const int* un = uni + (size_t)g.x * cap;
         const int nu = ucnt[gi];
         const double mq = m[q], uq = u_eos[q];  // for the end: in flight during the sums
         DensAcc<FP32C> acc;
-        for (int c0 = 0; c0 < nu; c0 += DENS_CHUNK) {  // union members c0 .. c0 + cn - 1 through LDS
-            const int cn = nu - c0 < DENS_CHUNK ? nu - c0 : DENS_CHUNK;
+        for (int c0 = 0; c0 < nu; c0 += CH) {  // union members c0 .. c0 + cn - 1 through LDS
+            const int cn = nu - c0 < CH ? nu - c0 : CH;
             __syncthreads();
-            for (int i = tid; i < cn; i += PAIR_THREADS) {
+            for (int i = tid; i < cn; i += NT) {
                 const int b = un[c0 + i];
                 S.put(i, pos4[b], m[b], org);
             }
@@ -284,50 +289,48 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_density(
 void launch_density(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, double gamma, double h_coeff,
                     const double* u_eos, int kin) {
     if (dm.n <= 0) return;
-    if (fp32c)
-        hipLaunchKernelGGL(k_density<true>, dim3(dm.pair_grid), dim3(PAIR_THREADS), 0, s, d.ctl, d.group,
-                           dm.group_size, dm.nbr_cap, d.nbr, d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.m, u_eos,
-                           kin, gamma, h_coeff, d.rho, d.P, d.cs, d.hnext, d.thr4, d.thrf);
-    else
-        hipLaunchKernelGGL(k_density<false>, dim3(dm.pair_grid), dim3(PAIR_THREADS), 0, s, d.ctl, d.group,
-                           dm.group_size, dm.nbr_cap, d.nbr, d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.m, u_eos,
-                           kin, gamma, h_coeff, d.rho, d.P, d.cs, d.hnext, d.thr4, d.thrf);
+    auto go = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, d.group, dm.group_size, dm.nbr_cap, d.nbr,
+                           d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.m, u_eos, kin, gamma, h_coeff, d.rho, d.P,
+                           d.cs, d.hnext, d.thr4, d.thrf);
+    };
+    if (fp32c) go(k_density<true, 256, 512>, 256);
+    else if (narrow_groups(dm)) go(k_density<false, 128, 256>, 128);
+    else go(k_density<false, 256, 512>, 256);
 }
 
 // Source records in LDS for the force sums: FP64 (x, h), (v, m), (rho, P/rho^2, c), or
 // FP32C (x, h) and (v, m) in FP64 and (rho, P/rho^2, c, h) in FP32.
-template <bool FP32C>
+template <bool FP32C, int CH>
 struct ForceSrc;
-template <>
-struct ForceSrc<false> {
-    Split4<FORCE_CHUNK> pos, vel;
-    double2 rp[FORCE_CHUNK];  // rho, P/rho^2
-    double c[FORCE_CHUNK];    // -(alpha/2) c
+template <int CH>
+struct ForceSrc<false, CH> {
+    Split4<CH> pos, vel;
+    double2 rp[CH];  // rho, P/rho^2
+    double c[CH];    // -(alpha/2) c
 };
-template <>
-struct ForceSrc<true> {
-    Split4<FORCE_CHUNK_F> pos, vel;  // x, y, z, h and predicted v, m in FP64: the pair's differences
-    float4 thr[FORCE_CHUNK_F];       // and its support-edge margin are formed in FP64
+template <int CH>
+struct ForceSrc<true, CH> {
+    Split4<CH> pos, vel;  // x, y, z, h and predicted v, m in FP64: the pair's differences
+    float4 thr[CH];       // and its support-edge margin are formed in FP64
 };
-static_assert(sizeof(ForceSrc<false>) >= 4 * PAIR_THREADS * sizeof(double), "the reduction reuses the staging");
-static_assert(sizeof(ForceSrc<true>) >= 4 * PAIR_THREADS * sizeof(double), "the reduction reuses the staging");
-
-template <bool FP32C, bool THERMO>
-__global__ void __launch_bounds__(PAIR_THREADS) k_forces(
+template <bool FP32C, bool THERMO, int NT, int CH>
+__global__ void __launch_bounds__(NT) k_forces(
     const DevCtl* __restrict__ ctl, const int4* __restrict__ group, int gsz, int cap, const u16* __restrict__ nbr,
     const int* __restrict__ nbr_cnt, const int* __restrict__ uni, const int* __restrict__ ucnt,
     const double4* __restrict__ pos4, const double4* __restrict__ vel4, const double4* __restrict__ thr4,
     const float4* __restrict__ thrf, double alpha, double beta, double eps_av,
     double* __restrict__ ax, double* __restrict__ ay, double* __restrict__ az, double* __restrict__ du) {
-    __shared__ ForceSrc<FP32C> S;
+    __shared__ ForceSrc<FP32C, CH> S;  // CH union members a round
+    static_assert(sizeof(S) >= 4 * NT * sizeof(double), "the reduction reuses the staging");
     const int tid = threadIdx.x;
     int g0, g1, gstep;
     group_range(ctl->n_groups, g0, g1, gstep);
     for (int gi = g0; gi < g1; gi += gstep) {
         const int4 g = group[gi];
-        // PL = 256 / n_g threads per target, so a group with few targets still fills the
-        // workgroup; thread tid serves target tid mod n_g (the last 256 mod n_g threads idle)
-        const int PL = PAIR_THREADS / g.y;
+        // PL = NT / n_g threads per target, so a group with few targets still fills the
+        // workgroup; thread tid serves target tid mod n_g (the last NT mod n_g threads idle)
+        const int PL = NT / g.y;
         const int t = tid % g.y, phi = tid / g.y;
         const bool tv = phi < PL;
         const int q = g.x + t;
@@ -343,10 +346,10 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_forces(
             const double al2 = -0.5 * alpha, be2 = 0.5 * beta, ep4 = 0.25 * eps_av;
             const double mc = al2 * mt.z;
             double sx = 0, sy = 0, sz = 0, su = 0;
-            for (int c0 = 0; c0 < nu; c0 += FORCE_CHUNK) {
-                const int cn = nu - c0 < FORCE_CHUNK ? nu - c0 : FORCE_CHUNK;
+            for (int c0 = 0; c0 < nu; c0 += CH) {
+                const int cn = nu - c0 < CH ? nu - c0 : CH;
                 __syncthreads();
-                for (int i = tid; i < cn; i += PAIR_THREADS) {
+                for (int i = tid; i < cn; i += NT) {
                     const int b = un[c0 + i];
                     S.pos.put(i, pos4[b]);
                     S.vel.put(i, vel4[b]);
@@ -398,10 +401,10 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_forces(
             const float alf = (float)alpha, bef = (float)beta, epf = (float)eps_av;
             const float ipi = (float)M_1_PI_D;
             Kahan sx, sy, sz, su;
-            for (int c0 = 0; c0 < nu; c0 += FORCE_CHUNK_F) {
-                const int cn = nu - c0 < FORCE_CHUNK_F ? nu - c0 : FORCE_CHUNK_F;
+            for (int c0 = 0; c0 < nu; c0 += CH) {
+                const int cn = nu - c0 < CH ? nu - c0 : CH;
                 __syncthreads();
-                for (int i = tid; i < cn; i += PAIR_THREADS) {
+                for (int i = tid; i < cn; i += NT) {
                     const int b = un[c0 + i];
                     S.pos.put(i, pos4[b]);
                     S.vel.put(i, vel4[b]);
@@ -462,18 +465,18 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_forces(
         __syncthreads();
         double* red = reinterpret_cast<double*>(&S);  // 4 x 256 doubles
         red[tid] = fx;
-        red[PAIR_THREADS + tid] = fy;
-        red[2 * PAIR_THREADS + tid] = fz;
-        red[3 * PAIR_THREADS + tid] = fu;
+        red[NT + tid] = fy;
+        red[2 * NT + tid] = fz;
+        red[3 * NT + tid] = fu;
         __syncthreads();
         if (tv && phi == 0) {
-            double s0 = red[t], s1 = red[PAIR_THREADS + t], s2 = red[2 * PAIR_THREADS + t], s3 = red[3 * PAIR_THREADS + t];
+            double s0 = red[t], s1 = red[NT + t], s2 = red[2 * NT + t], s3 = red[3 * NT + t];
             for (int f = 1; f < PL; ++f) {
                 const int i = t + g.y * f;
                 s0 += red[i];
-                s1 += red[PAIR_THREADS + i];
-                s2 += red[2 * PAIR_THREADS + i];
-                s3 += red[3 * PAIR_THREADS + i];
+                s1 += red[NT + i];
+                s2 += red[2 * NT + i];
+                s3 += red[3 * NT + i];
             }
             ax[q] = s0;
             ay[q] = s1;
@@ -486,16 +489,29 @@ __global__ void __launch_bounds__(PAIR_THREADS) k_forces(
 void launch_forces(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, double alpha, double beta,
                    double eps_av, int thermo) {
     if (dm.n <= 0) return;
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(PAIR_THREADS), 0, s, d.ctl, d.group, dm.group_size,
+    auto go = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, d.group, dm.group_size,
                            dm.nbr_cap, d.nbr, d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.thr4, d.thrf, alpha,
                            beta, eps_av, d.ax, d.ay, d.az, d.du);
     };
+    // Union members staged a round.  A wave runs each round as long as its busiest target, so a union in one
+    // round wastes fewer lanes, but the records (88 bytes, 80 in FP32C) bound the workgroups a CU holds.
+    // Forces alone, us, at 256 / 320 / 464 (FP32C 512): 987,840 particles in groups of 64, FP64 239 / - / 204;
+    // 1.2M in 64 boxes, groups of 64, FP32C 306 / 289 / 276; 1.0M in 56 boxes, groups of 32, FP64 269 / 249 /
+    // 269; the same in groups of 16, FP32C 316 / 338 / 441, FP64 365 / 391 / 451 and with 128 threads 326 (192:
+    // 300).  Few groups take the largest: 3,375 in groups of 32, FP32C 9.0 / 8.2 / 7.2.
+    auto pick = [&](auto f, auto th) {
+        constexpr bool F = decltype(f)::value, TH = decltype(th)::value;
+        if (dm.group_size > 32 || few_groups(dm)) go(k_forces<F, TH, 256, F ? 512 : 464>, 256);
+        else if (dm.group_size > 16) go(k_forces<F, TH, 256, 320>, 256);
+        else if constexpr (F) go(k_forces<F, TH, 256, 256>, 256);
+        else go(k_forces<F, TH, 128, 192>, 128);
+    };
     if (fp32c) {
-        if (thermo) go(k_forces<true, true>);
-        else go(k_forces<true, false>);
+        if (thermo) pick(std::true_type(), std::true_type());
+        else pick(std::true_type(), std::false_type());
     } else {
-        if (thermo) go(k_forces<false, true>);
-        else go(k_forces<false, false>);
+        if (thermo) pick(std::false_type(), std::true_type());
+        else pick(std::false_type(), std::false_type());
     }
 }

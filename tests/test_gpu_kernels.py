@@ -198,6 +198,28 @@ def test_pair_sums_at_any_scale(orc, scale, group):
     assert np.all(np.abs(du - r_du) <= 1e-12 * Su)
 
 
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,group", [(4096, 8), (4097, 8), (8193, 16), (16384, 32), (16385, 32), (32769, 64)])
+def test_pair_sums_of_every_workgroup_form(orc, n, group, prec):
+    """Both sides of the set sizes at which the pair kernels take other workgroups and staging rounds;
+    lists from a few to over 200 entries (h spread by four), unions of one to several rounds: 1e-12 (FP32C
+    1e-6) of the sum of the terms' magnitudes."""
+    h0 = (40.0 / (n * 32.0 / 3.0 * np.pi)) ** (1.0 / 3.0)
+    ps = uniform_random(n, seed=96, h=(0.5 * h0, 2.0 * h0))
+    tol = (1e-12, 1e-6)[prec]
+    ctx = make_ctx(n, group_size=group, nbr_capacity=2048, precision=prec)
+    gpu_keys_order(ctx, parts(ps))
+    rho, P, c, hn = gpu_density(ctx, n)
+    csr = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+    ref = orc.density(ps.fields(), csr)
+    for a, b in zip((rho, P, c, hn), ref):
+        assert np.max(np.abs(a - b) / np.abs(b)) <= tol
+    ax, ay, az, du = gpu_forces(ctx, n)
+    r_ax, r_ay, r_az, r_du, Sa, Su = orc.forces(ps.fields(), rho, P, c, csr)
+    assert np.all(np.sqrt((ax - r_ax) ** 2 + (ay - r_ay) ** 2 + (az - r_az) ** 2) <= tol * Sa)
+    assert np.all(np.abs(du - r_du) <= tol * Su)
+
+
 # ---------------------------------------------------------------------------- node-node gravity
 @pytest.mark.parametrize("eps", [0.0, 0.02])
 @pytest.mark.parametrize("leaf", [1, 2, 3, 31, 32, 33, 63, 64])
