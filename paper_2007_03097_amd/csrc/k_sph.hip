@@ -110,7 +110,7 @@ struct Entries {
 
 // Both passes are bound by VALU issue (FP64 at 987,840 particles: 65-70% of the issue slots, the rest waits
 // for list entries and at the group's ends), so the pair term is written for few instructions: density
-// 145 -> 119 us, forces 279 -> 204 us with PairGeo, the byte offsets and batches of Entries and the
+// 145 -> 119 us, forces 279 -> 214 us with PairGeo, the byte offsets and batches of Entries and the
 // force pass's one round.
 //
 // Geometry of one pair in FP64 from one reciprocal square root: with T = h_a + h_b = 2 h_ab,
@@ -369,7 +369,8 @@ __global__ void __launch_bounds__(NT) k_forces(
                     // g(q)/h_ab^5 = -48 G/T^5: G = 2 - 3 r/T for q < 1, else u^2/(r/T) with u = 1 - r/T
                     const double u = 1.0 - p.qh;
                     const double G = p.qh < 0.5 ? fma(-3.0, p.qh, 2.0) : (u * u) * (p.s * p.y);
-                    const double F = (vb.w * G) * ((p.iT2 * p.iT2) * (p.iT2 * p.T));
+                    const double i2 = fma(p.iT2, fma(-p.s, p.iT2, 1.0), p.iT2);  // its third power counts
+                    const double F = (vb.w * G) * ((i2 * i2) * (i2 * p.T));
                     const double wx = mv.x - vb.x, wy = mv.y - vb.y, wz = mv.z - vb.z;
                     const double vr = fma(wx, dx, fma(wy, dy, wz * dz));
                     double Pi = 0.0;
@@ -496,7 +497,7 @@ void launch_forces(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, d
     };
     // Union members staged a round.  A wave runs each round as long as its busiest target, so a union in one
     // round wastes fewer lanes, but the records (88 bytes, 80 in FP32C) bound the workgroups a CU holds.
-    // Forces alone, us, at 256 / 320 / 464 (FP32C 512): 987,840 particles in groups of 64, FP64 239 / - / 204;
+    // Forces alone, us, at 256 / 320 / 464 (FP32C 512): 987,840 particles in groups of 64, FP64 239 / - / 204 (214 with the correction of 1/T^2);
     // 1.2M in 64 boxes, groups of 64, FP32C 306 / 289 / 276; 1.0M in 56 boxes, groups of 32, FP64 269 / 249 /
     // 269; the same in groups of 16, FP32C 316 / 338 / 441, FP64 365 / 391 / 451 and with 128 threads 326 (192:
     // 300).  Few groups take the largest: 3,375 in groups of 32, FP32C 9.0 / 8.2 / 7.2.
