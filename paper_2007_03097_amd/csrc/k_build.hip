@@ -389,8 +389,9 @@ void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
 
 // ---------------------------------------------------------------------------------------
 // Merge sort of (u64 key, u32 value), value = the input index: tiles of MS_TILE keys sorted in
-// LDS by one workgroup each (two resident per CU), then 2-way merge passes over runs that double (merge path: every
-// workgroup finds where its MS_OUT outputs start in both runs and merges them in LDS).
+// LDS by one workgroup each (two resident per CU), then merge passes: 2-way over runs that double (merge path:
+// every workgroup finds where its MS_OUT outputs start in both runs and merges them in LDS), or by rank
+// over four or eight runs (k_ms_rank below).
 //
 // Equal keys are ordered by `tie[value]` (the particle ID; tie == nullptr: the value itself), in
 // the comparison, so the input may be in any order: the step sorts from the previous key order,
@@ -399,11 +400,11 @@ void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
 //
 // What bounds it: launches for small sets; LDS reads in the tiles, memory in the passes for
 // large ones.  Measured per sort against an LSD radix sort of 8-bit digits (8 passes of three
-// kernels at any size, for 63 key bits): 4,096 keys 134 -> 15-21 us (6.5 us by rank, below), 123K 144 -> 59 us, 1M 183 ->
+// kernels at any size, for 63 key bits): 4,096 keys 134 -> 15-21 us (6.5 us by rank, below), 123K 144 -> 59 us (43 by more ways), 1M 183 ->
 // 101 us (a pass 8.9 us, 2.7 TB/s; the tiles 30 us), 4M 400 -> 365 us (a pass 28 us, 3.6 TB/s).
 // Tiles of 8,192 keys save a pass and lose as much (47 us at 1M); 8 keys a thread instead of 4
 // leave fewer waves to hide the LDS latency (tiles 34 us, a pass 10.3 us at 1M).
-constexpr int MS_ITEMS = 4, MS_THREADS = 1024, MS_TILE = MS_THREADS * MS_ITEMS;
+constexpr int MS_ITEMS = 4, MS_TILE = 1024 * MS_ITEMS, MS_TILE_MID = 256 * MS_ITEMS;
 constexpr int MM_ITEMS = 4, MM_THREADS = 512, MS_OUT = MM_THREADS * MM_ITEMS;
 constexpr u32 MS_PAD = 0xffffffffu;  // value of a filler entry past the end of the last tile
 
@@ -465,17 +466,17 @@ __device__ __forceinline__ int ms_split(const u64* sk, const u32* sv, int a0, in
 }
 
 // One tile: every thread sorts MS_ITEMS keys in registers, then runs of that size merge in LDS.
-template <bool TIE>
-__global__ void __launch_bounds__(MS_THREADS) k_ms_tile(const u64* key, u64* kout, u32* vout, int n,
+template <bool TIE, int TILE>
+__global__ void __launch_bounds__(TILE / MS_ITEMS) k_ms_tile(const u64* key, u64* kout, u32* vout, int n,
                                                         const u32* __restrict__ tie) {
-    __shared__ u64 sk[MS_TILE + MS_TILE / 8 + 1];
-    __shared__ u32 sv[MS_TILE + MS_TILE / 8 + 1];
-    const int t0 = blockIdx.x * MS_TILE;
-    const int cnt = n - t0 < MS_TILE ? n - t0 : MS_TILE;
+    __shared__ u64 sk[TILE + TILE / 8 + 1];
+    __shared__ u32 sv[TILE + TILE / 8 + 1];
+    const int t0 = blockIdx.x * TILE;
+    const int cnt = n - t0 < TILE ? n - t0 : TILE;
     const int i0 = threadIdx.x * MS_ITEMS;
 #pragma unroll
     for (int r = 0; r < MS_ITEMS; ++r) {  // consecutive lanes read consecutive keys
-        const int i = r * MS_THREADS + threadIdx.x;
+        const int i = r * (TILE / MS_ITEMS) + threadIdx.x;
         if (i < cnt) sk[ms_slot(i)] = key[t0 + i];
     }
     __syncthreads();
@@ -676,6 +677,123 @@ __global__ void __launch_bounds__(MM_THREADS) k_ms_merge(const u64* __restrict__
     }
 }
 
+// One K-way merge pass over runs of `run` (a power of two, at least MR_THREADS) keys.  A workgroup takes
+// MR_THREADS consecutive keys of a run.  Where its first and last key belong in the other K - 1 runs is found
+// by half waves, 32 probes a round; the keys between go to LDS, where every thread finds the places of its
+// own key by K - 1 binary searches side by side.  Its place is the sum.  Keys that crowd in few places of
+// other runs (more than MR_STAGE of them) are searched in memory.
+constexpr int MR_THREADS = 512, MR_STAGE = 4608;  // (one spare item: a run without items reads there)
+
+template <bool TIE, int K>
+__global__ void __launch_bounds__(MR_THREADS) k_ms_rank(const u64* __restrict__ kin, const u32* __restrict__ vin,
+                                                        u64* __restrict__ kout, u32* __restrict__ vout, int n, int run,
+                                                        const u32* __restrict__ tie) {
+    __shared__ u64 sk[MR_STAGE + 1];
+    __shared__ int bound[2][K - 1];
+    const int i0 = blockIdx.x * MR_THREADS, i = i0 + threadIdx.x;
+    const int p0 = (int)((long long)i0 / ((long long)K * run) * ((long long)K * run));  // first key of the K runs
+    const int own = (i0 - p0) / run;
+    auto start = [&](int r) { return (int)min(p0 + (long long)(r < own ? r : r + 1) * run, (long long)n); };
+    u64 mine = 0;
+    u32 v = 0;
+    if (i < n) {
+        mine = kin[i];
+        v = vin[i];
+    }
+    {
+        const int half = lane_id() >> 5, j = lane_id() & 31;
+        const int e = half ? min(i0 + MR_THREADS, n) - 1 : i0;  // the last or the first key
+        const u64 ke = kin[e];
+        const u32 ve = vin[e];
+        for (int r = threadIdx.x >> 6; r < K - 1; r += MR_THREADS / 64) {
+            const int at = start(r);
+            int lo = 0, hi = min(run, n - at);
+            while (__ballot(lo < hi)) {  // both halves take part until both are done
+                const int step = (hi - lo + 31) / 32;
+                const int c = lo + (j + 1) * step - 1;
+                bool past = false;  // item c does not precede the key
+                if (lo < hi && c < hi) {
+                    const u64 k = kin[at + c];
+                    past = ke < k;
+                    if (k == ke) past = ms_tie_less<TIE>(ve, vin[at + c], tie);
+                }
+                const u32 m = (u32)(__ballot(past) >> (32 * half));
+                if (lo < hi) {
+                    if (m) {
+                        const int f = __ffs((int)m) - 1;
+                        hi = lo + (f + 1) * step - 1;
+                        lo = lo + f * step;
+                    } else {
+                        lo = min(hi, lo + ((hi - lo) / step) * step);
+                    }
+                }
+            }
+            if (j == 0) bound[half][r] = lo;
+        }
+    }
+    __syncthreads();
+    int at[K - 1], len[K - 1], off[K - 1], total = 0, longest = 1;
+    int o = p0 + (i - p0) % run;
+#pragma unroll
+    for (int r = 0; r < K - 1; ++r) {
+        const int lo = __builtin_amdgcn_readfirstlane(bound[0][r]);
+        at[r] = start(r) + lo;
+        len[r] = __builtin_amdgcn_readfirstlane(bound[1][r]) - lo;
+        off[r] = total;
+        total += len[r];
+        longest = max(longest, len[r]);
+        o += lo;
+    }
+    const bool staged = total <= MR_STAGE;
+    if (staged) {
+        constexpr int U = 4;  // loads in flight
+        for (int x0 = threadIdx.x; x0 < total; x0 += U * MR_THREADS) {
+            u64 k[U];
+#pragma unroll
+            for (int q = 0; q < U; ++q) {
+                const int x = min(x0 + q * MR_THREADS, total - 1);
+                int from = at[0];
+#pragma unroll
+                for (int r = 1; r < K - 1; ++r) from = x >= off[r] ? at[r] - off[r] : from;
+                k[q] = kin[from + x];
+            }
+#pragma unroll
+            for (int q = 0; q < U; ++q)
+                if (x0 + q * MR_THREADS < total) sk[x0 + q * MR_THREADS] = k[q];
+        }
+    }
+    __syncthreads();
+    if (i >= n) return;
+    auto search = [&](auto&& item) {
+        int pos[K - 1];
+#pragma unroll
+        for (int r = 0; r < K - 1; ++r) pos[r] = 0;
+        for (int step = 1 << (31 - __clz(longest)); step > 0; step >>= 1) {
+            u64 k[K - 1];
+            u32 same = 0;
+#pragma unroll
+            for (int r = 0; r < K - 1; ++r) k[r] = item(r, max(min(pos[r] + step, len[r]) - 1, 0));
+#pragma unroll
+            for (int r = 0; r < K - 1; ++r) {
+                const int c = pos[r] + step;
+                same |= c <= len[r] && k[r] == mine ? 1u << r : 0u;
+                pos[r] = c <= len[r] && k[r] < mine ? c : pos[r];
+            }
+            if (same) {  // rare
+#pragma unroll
+                for (int r = 0; r < K - 1; ++r)
+                    if (((same >> r) & 1u) && ms_tie_less<TIE>(vin[at[r] + pos[r] + step - 1], v, tie)) pos[r] += step;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < K - 1; ++r) o += pos[r];
+    };
+    if (staged) search([&](int r, int c) { return sk[off[r] + c]; });
+    else search([&](int r, int c) { return kin[min(at[r] + c, n - 1)]; });
+    kout[o] = mine;
+    vout[o] = v;
+}
+
 // Sorts the keys in key_b (any order) into key_a, with the input index of each in val_a.
 template <bool TIE>
 static void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
@@ -685,17 +803,44 @@ static void sort_keys(hipStream_t s, const DevPtrs& d, int n, const u32* tie) {
                            d.key_a, d.val_a, n, tie);
         return;
     }
-    int passes = 0;
-    for (long long run = MS_TILE; run < n; run *= 2) ++passes;
+    // Middling sets do not fill the chip with tiles of 4,096 keys, and the 7 us that a pass takes there are
+    // latency: tiles of 1,024 (16 us against 28) and passes of up to eight ways (8: 10-14 us, 4: 7-12 us).  Sorts,
+    // us, before and so: 20,011 keys 48 -> 32, 50,021 56 -> 38, 123,480 (a step's) 58 -> 43, 200,003 75 ->
+    // 57; up to 2^19 keys.  Then memory counts: four-way passes of 16 us at 1M for two of 9 up to 2^21 keys
+    // (4M: 68 us for two of 28).
+    const bool mid = n <= (1 << 19);
+    const int tile = mid ? MS_TILE_MID : MS_TILE, most = mid ? 8 : n <= (1 << 21) ? 4 : 2;
+    // the fewest passes of at most `most` ways, each with no more ways than these need
+    int passes = 0, ways[32];
+    for (long long run = tile; run < n; ++passes) {
+        int left = 1, w = 2;
+        for (long long r = most * run; r < n; r *= most) ++left;
+        auto reach = [&] {
+            long long r = run;
+            for (int p = 0; p < left; ++p) r *= w;
+            return r;
+        };
+        while (reach() < n) w *= 2;
+        ways[passes] = w;
+        run *= w;
+    }
     // the tile sort starts in the buffer from which the passes end in _a
     u64 *ki = (passes & 1) ? d.key_b : d.key_a, *ko = (passes & 1) ? d.key_a : d.key_b;
     u32 *vi = (passes & 1) ? d.val_b : d.val_a, *vo = (passes & 1) ? d.val_a : d.val_b;
-    hipLaunchKernelGGL(k_ms_tile<TIE>, dim3((n + MS_TILE - 1) / MS_TILE), dim3(MS_THREADS), 0, s, d.key_b, ki, vi, n,
-                       tie);
-    int run = MS_TILE;
-    for (int p = 0; p < passes; ++p, run *= 2) {
-        hipLaunchKernelGGL(k_ms_merge<TIE>, dim3((n + MS_OUT - 1) / MS_OUT), dim3(MM_THREADS), 0, s, ki, vi, ko, vo, n,
-                           run, tie);
+    auto sort_tiles = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((n + tile - 1) / tile), dim3(tile / MS_ITEMS), 0, s, d.key_b, ki, vi, n, tie);
+    };
+    if (mid) sort_tiles(k_ms_tile<TIE, MS_TILE_MID>);
+    else sort_tiles(k_ms_tile<TIE, MS_TILE>);
+    int run = tile;
+    for (int p = 0; p < passes; ++p) {
+        auto pass = [&](auto kern, int threads, int keys) {
+            hipLaunchKernelGGL(kern, dim3((n + keys - 1) / keys), dim3(threads), 0, s, ki, vi, ko, vo, n, run, tie);
+        };
+        if (ways[p] == 8) pass(k_ms_rank<TIE, 8>, MR_THREADS, MR_THREADS);
+        else if (ways[p] == 4) pass(k_ms_rank<TIE, 4>, MR_THREADS, MR_THREADS);
+        else pass(k_ms_merge<TIE>, MM_THREADS, MS_OUT);
+        run *= ways[p];
         std::swap(ki, ko);
         std::swap(vi, vo);
     }

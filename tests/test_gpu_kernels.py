@@ -170,6 +170,23 @@ def test_neighbors_at_any_scale(orc, scale, shift, group):
     assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
 
 
+# ---------------------------------------------------------------------------- merge passes by rank
+@pytest.mark.parametrize("family", ["random", "duplicates", "crowded"])
+@pytest.mark.parametrize("n", [8193, 9217, 16385, 65536, 65537, 73729, 131073, 524288, 524289, 1048577])
+def test_rank_merge(orc, n, family):
+    """Passes of two, four and eight ways around the sizes where their number changes, last runs of one key
+    and of a few, equal keys in every run, and keys that crowd in few places of the other runs (searched
+    in memory, not in LDS)."""
+    ps = _sort_set(n, family if family == "duplicates" else "random")
+    if family == "crowded":
+        for f in ("x", "y", "z"):
+            a = getattr(ps, f)
+            a[8192:] = 0.4 + 0.01 * a[8192:]
+    ctx = make_ctx(n)
+    k, o = gpu_keys_order(ctx, parts(ps))
+    assert np.array_equal(k, orc.keys(ps.x, ps.y, ps.z)) and np.array_equal(o, orc.order(k))
+
+
 # ---------------------------------------------------------------------------- pair sums
 @pytest.mark.parametrize("group", [8, 64])
 @pytest.mark.parametrize("scale", [1e-30, 1.0, 1e25])
