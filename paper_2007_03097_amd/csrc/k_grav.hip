@@ -88,10 +88,11 @@ struct TargetSums {
 // of the expansion cancel but for the softening's share: with u = R.Q.R - tr(I) eps^2,
 //   g += -R (M/s^3 + (5/2) u/s^7) + Q.R/s^5,   phi -= M/s + (1/2) u/s^5
 // (3 R.I.R = R.Q.R + tr(I) (s^2 - eps^2)), so u takes its constant from the record and starts the
-// sum for free.  Record: a = (M, com), b = (Qxx, Qyy, Qzz, -tr(I) eps^2), d = (Qxy, Qxz, Qyz, -).
+// sum for free.  With 2/s for 1/s (an operation less) the powers of two go into the record,
+// a = (M/8, com), b = (Qxx, Qyy, Qzz, -tr(I) eps^2)/32, d = (Qxy, Qxz, Qyz, -)/32, and the sum holds phi/4.
 // The kernel is bound by its FP64 instructions (at 4M particles it runs at what the FMA probe
-// sustains of the issue rate): 36 per term, 38 with the potential, against 39 and 44 with the
-// trace carried along: 15.7 -> 14.2 ms.
+// sustains of the issue rate): 35 per term, 37 with the potential, against 39 and 44 with the
+// trace carried along (15.7 -> 14.2 ms) and 1/s itself (node-node gravity of 262,144 particles 1.61 -> 1.58 ms, the walk of 4M unchanged).
 template <bool PH = true>
 __device__ __forceinline__ void cell_term(const double4 me, const double4 a, const double4 b, const double4 d,
                                           double e2, TargetSums& S) {
@@ -101,27 +102,27 @@ __device__ __forceinline__ void cell_term(const double4 me, const double4 a, con
     const double QRz = fma(d.y, Rx, fma(d.z, Ry, b.z * Rz));
     const double u = fma(Rx, QRx, fma(Ry, QRy, fma(Rz, QRz, b.w)));
     const double s2 = fma(Rx, Rx, fma(Ry, Ry, fma(Rz, Rz, e2)));
-    const double i1 = rsq_nr1(s2);
+    const double i1 = rsq2_nr1(s2);  // 2/s
     const double i2 = i1 * i1, i3 = i1 * i2, i5 = i3 * i2, u5 = u * i5;
-    const double cR = fma(-2.5, u5 * i2, -a.x * i3);
+    const double cR = fma(-0.625, u5 * i2, -a.x * i3);
     S.gx = fma(cR, Rx, fma(i5, QRx, S.gx));
     S.gy = fma(cR, Ry, fma(i5, QRy, S.gy));
     S.gz = fma(cR, Rz, fma(i5, QRz, S.gz));
-    if constexpr (PH) S.ph = fma(-0.5, u5, fma(-a.x, i1, S.ph));
+    if constexpr (PH) S.ph = fma(-0.125, u5, fma(-a.x, i1, S.ph));
 }
 
-// Softened particle term of source sb = (x, y, z, m).
+// Softened particle term of source sb = (x, y, z, m), m/8 in FP64 (as in cell_term).
 template <bool FP32C, bool PH = true>
 __device__ __forceinline__ void part_term(const double4 me, const double4 sb, double e2, TargetSums& S) {
     if (!FP32C) {
         const double dx = me.x - sb.x, dy = me.y - sb.y, dz = me.z - sb.z;
         const double s2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, e2)));
-        const double i1 = rsq_nr1(s2);
-        const double mi3 = sb.w * i1 * i1 * i1;
+        const double i1 = rsq2_nr1(s2);  // 2/s
+        const double mi1 = sb.w * i1, mi3 = mi1 * (i1 * i1);
         S.gx = fma(-mi3, dx, S.gx);
         S.gy = fma(-mi3, dy, S.gy);
         S.gz = fma(-mi3, dz, S.gz);
-        if constexpr (PH) S.ph = fma(-sb.w, i1, S.ph);
+        if constexpr (PH) S.ph -= mi1;
     } else {
         const float dx = (float)(me.x - sb.x), dy = (float)(me.y - sb.y), dz = (float)(me.z - sb.z);
         const float s2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, (float)e2)));
@@ -215,10 +216,11 @@ __device__ void eval_cells(int ncell, const int* cells, GravStage<FP32C, W>& St,
                 St.cellf.c2[tid] = make_float4((float)(3.0 * c2.x), (float)(3.0 * c2.y), (float)(3.0 * c2.z),
                                                (float)(0.5 * c1.w));
             } else {  // see cell_term
-                St.cell.c0[tid] = c0;
-                St.cell.c1[tid] = make_double4(fma(3.0, c1.x, -c1.w), fma(3.0, c1.y, -c1.w), fma(3.0, c1.z, -c1.w),
-                                               -e2 * c1.w);
-                St.cell.c2[tid] = make_double4(3.0 * c2.x, 3.0 * c2.y, 3.0 * c2.z, 0.0);
+                constexpr double q = 3.0 / 32.0;
+                const double tr = c1.w / 32.0;
+                St.cell.c0[tid] = make_double4(0.125 * c0.x, c0.y, c0.z, c0.w);
+                St.cell.c1[tid] = make_double4(fma(q, c1.x, -tr), fma(q, c1.y, -tr), fma(q, c1.z, -tr), -e2 * tr);
+                St.cell.c2[tid] = make_double4(q * c2.x, q * c2.y, q * c2.z, 0.0);
             }
         }
         unit_sync<W>();
@@ -294,12 +296,12 @@ __device__ int stage_leaves_put(int nleaf, int* leaves, Stage& St, const double4
     return total;
 }
 
-// stage_leaves_put with (x, y, z, m) records in FP64.
-template <int W, typename Stage, typename Tile>
+// stage_leaves_put with (x, y, z, m) records in FP64, m/8 for FP64 sums.
+template <bool FP32C, int W, typename Stage, typename Tile>
 __device__ int stage_leaves(int nleaf, int* leaves, Stage& St, const double4* __restrict__ pos4,
                             const double* __restrict__ m, Tile&& tile) {
     return stage_leaves_put<W>(nleaf, leaves, St, pos4, m, tile, [&](int i, const double4& ps, double mass, int src) {
-        St.part.pm[i] = make_double4(ps.x, ps.y, ps.z, mass);
+        St.part.pm[i] = make_double4(ps.x, ps.y, ps.z, FP32C ? mass : 0.125 * mass);
         St.part.src[i] = src;
     });
 }
@@ -369,7 +371,7 @@ __device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C, W>& St, cons
                 }
             }
         };
-        return stage_leaves<W>(nleaf, leaves, St, pos4, m, [&](int tn) {
+        return stage_leaves<false, W>(nleaf, leaves, St, pos4, m, [&](int tn) {
             if (!any) return;
             if (phi) run(tn, BoolC<true>());
             else run(tn, BoolC<false>());
@@ -411,7 +413,7 @@ __device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const double4* _
             }
         }
     };
-    stage_leaves<W>(nleaf, leaves, St, pos4, m, [&](int tn) {
+    stage_leaves<FP32C, W>(nleaf, leaves, St, pos4, m, [&](int tn) {
         if (!T.va) return;
         if (phi) run(tn, BoolC<true>());
         else run(tn, BoolC<false>());
@@ -648,7 +650,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(FP3
 #pragma unroll
             for (int i = 0; i < 8; ++i) r[i] = G * lanes_sum_d(r[i], T.TP);  // (B: zero if !TWO)
         } else {
-            const double v[8] = {A.gx, A.gy, A.gz, A.ph, B.gx, B.gy, B.gz, B.ph};
+            const double v[8] = {A.gx, A.gy, A.gz, 4.0 * A.ph, B.gx, B.gy, B.gz, 4.0 * B.ph};
 #pragma unroll
             for (int h = 0; h < 8; h += 4) {
                 __syncthreads();
@@ -670,7 +672,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(FP3
                 double gx = r[4 * s], gy = r[4 * s + 1], gz = r[4 * s + 2], ph = r[4 * s + 3];
                 if (eps > 0.0) {  // take out the self pair's potential term (see eval_lists)
                     const double e2 = eps * eps;
-                    const double is = FP32C ? (double)__builtin_amdgcn_rsqf((float)e2) : rsq_nr1(e2);
+                    const double is = FP32C ? (double)__builtin_amdgcn_rsqf((float)e2) : 0.5 * rsq2_nr1(e2);
                     ph += G * (m[q] * is);
                 }
                 if (accumulate) {
@@ -1069,7 +1071,7 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
         for (int h = 0; h < (TWO ? 2 : 1); ++h) {
             unit_sync<W>();
             if (FP32C) S.St.part.pm[tid] = make_double4(A.kx.value(), A.ky.value(), A.kz.value(), A.kp.value());
-            else S.St.part.pm[tid] = h ? make_double4(B.gx, B.gy, B.gz, B.ph) : make_double4(A.gx, A.gy, A.gz, A.ph);
+            else S.St.part.pm[tid] = h ? make_double4(B.gx, B.gy, B.gz, 4.0 * B.ph) : make_double4(A.gx, A.gy, A.gz, 4.0 * A.ph);
             unit_sync<W>();
             if (!(h ? T.vb : T.va) || T.ph != 0) continue;
             double4 r = S.St.part.pm[tid];
@@ -1086,7 +1088,7 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
             const double gx = G * (r.x + fgx), gy = G * (r.y + fgy), gz = G * (r.z + fgz);
             double ph = G * (r.w + (fc - lin));
             if (eps > 0.0) {  // take out the self pair's potential term (see eval_leaves1)
-                const double is = FP32C ? (double)__builtin_amdgcn_rsqf((float)e2) : rsq_nr1(e2);
+                const double is = FP32C ? (double)__builtin_amdgcn_rsqf((float)e2) : 0.5 * rsq2_nr1(e2);
                 ph += G * (m[q] * is);
             }
             if (K.accumulate) {
