@@ -5,7 +5,7 @@ on one MI355X, FP64 and FP32-compensated, on the 3D Sod-type tube workload.
 Workload: 987,840 particles in [0,1] x [0,0.1]^2 (two lattices with spacing ratio 2:1:
 rho = 1, P = 1 left; rho = 0.125, P = 0.1 right), gamma = 5/3, adaptive h = 1.2 (m/rho)^(1/3),
 Monaghan viscosity alpha = 1, beta = 2, kick-drift-kick leapfrog at dt = 0.25 min(h/c).
-One benchmark step = one full leapfrog step: bounding box, keys, radix sort, reorder,
+One benchmark step = one full leapfrog step: bounding box, keys, sort, reorder,
 octree + moments, neighbour lists, density + EOS, forces, kicks.  Inputs are resident in
 HBM before the timed region.
 

@@ -106,7 +106,8 @@ struct DevPtrs {
     double4* mom2;                // node_cap: Ixy, Ixz, Iyz, cell (bits; node-node gravity only)
     // groups and neighbour lists
     int4* group;                  // group_cap: {start, count, segment root rank (-1 = root), 0}
-    u32* gsize;                   // n_cap: size of the target group starting at a position, else 0
+    u32* gsize;                   // n_cap: size of the target group starting at a position, else 0; after the groups'
+                                  // emission the gravity pass's order of units (k_unit_order)
     int* gcount;                  // group_hist_words(n_cap): groups starting in each tile of positions
     u16* nbr;                     // n_cap * nbr_cap: list slots, indices into the group's union
     int* nbr_cnt;                 // n_cap
@@ -129,8 +130,8 @@ struct Dims {
     int leaf_size;
     int group_size;
     int nbr_cap;
-    int group_grid;   // grid (multiple of 8) of the one-wave per-group kernels
-    int pair_grid;    // the same for the four-wave pair kernels (density, forces)
+    int group_grid;   // grid (multiple of 8) of the per-group kernels of one to four waves (lists, gravity)
+    int pair_grid;    // the same for the pair kernels (density, forces)
     int wave_cap;     // wavefronts that a per-group grid may hold
     int n_chunks;
     int node_cap;
