@@ -165,6 +165,7 @@ static size_t layout(const sph_ctx* c, char* base, DevPtrs* out) {
     d.mom2 = cv.take<double4>(NC);
     d.group = cv.take<int4>(GC);
     d.gsize = cv.take<u32>(N);
+    d.gorder = cv.take<int>(N);
     d.gcount = cv.take<int>((size_t)group_hist_words((int64_t)N));
     d.nbr = cv.take<u16>(NBR);
     d.nbr_cnt = cv.take<int>(N);

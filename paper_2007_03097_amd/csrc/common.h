@@ -107,7 +107,8 @@ struct DevPtrs {
     // groups and neighbour lists
     int4* group;                  // group_cap: {start, count, segment root rank (-1 = root), 0}
     u32* gsize;                   // n_cap: size of the target group starting at a position, else 0; after the groups'
-                                  // emission the gravity pass's order of units (k_unit_order)
+                                  // emission the order of the leaves in node-node gravity (k_unit_order)
+    int* gorder;                  // n_cap: order in which the group kernels take the groups (k_unit_order)
     int* gcount;                  // group_hist_words(n_cap): groups starting in each tile of positions
     u16* nbr;                     // n_cap * nbr_cap: list slots, indices into the group's union
     int* nbr_cnt;                 // n_cap
@@ -369,6 +370,16 @@ struct Kahan {
 };
 
 
+// Whether the group kernels take their groups in the order of k_unit_order: with gravity, whose kernel
+// gains from it at every size, and where the list kernel's tail counts for more than the order's 4-6 us.
+// Lists, us, in position order and by size: 200,003 particles in groups of 32 92 / 81, a 131,101-particle star
+// in groups of 32 88 / 74, 123,480 of the tube in groups of 64 65 / 60, 50,021 in groups of 32 43 / 42,
+// 987,840 in groups of 64 250 / 250 (forces 215 / 208).
+inline const int* group_order(const DevPtrs& d, const Dims& dm) {
+    const int64_t units = dm.n / std::max(1, dm.group_size);
+    return dm.mass_moments || (units > 2048 && units <= 8192) ? d.gorder : nullptr;
+}
+
 // ---------------------------------------------------------------------------------------
 // Launchers (defined in the .hip files)
 
@@ -390,6 +401,7 @@ int64_t group_hist_words(int64_t n);
 void build_input_tree(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out);
 // after sort_step_keys: the resident state moves from set a to set b = swapped(a), octree and groups
 void build_step_tree(hipStream_t s, const DevPtrs& a, const DevPtrs& b, const Dims& dm);
+void launch_unit_order(hipStream_t s, DevCtl* ctl, const int4* group, const int* leaf_node, const int4* topo, int* order);
 void launch_tree_export(hipStream_t s, const DevPtrs& d, const Dims& dm, u64* key, int32_t* level,
                         int32_t* leaf, int64_t* start, int64_t* count);
 // k_walk.hip

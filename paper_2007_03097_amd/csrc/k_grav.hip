@@ -421,63 +421,11 @@ __device__ void eval_leaves1(int nleaf, int* leaves, Stage& St, const double4* _
     });
 }
 
-// Order in which the workgroups take their units (target groups, or leaves for leaf_node): within each
-// XCD's contiguous share, the units of most targets first, so that what is left at the end is short (a
-// unit takes 100 to 400 us whatever the set's size).  Before them the heavy leaves: the at most 16
-// coarsest ones that lie two levels or more above the share's average.  One workgroup per share counts
-// and places its units; the first also clears the pass's term counters.  1,000,003 particles in groups
-// of 64, FP32C: 1.96 -> 1.80 ms; 131,101 in groups of 32, FP64: 0.451 -> 0.370 ms; 4,194,304: 12.78 -> 12.61.
-__global__ void __launch_bounds__(1024) k_unit_order(DevCtl* ctl, const int4* __restrict__ group,
-                                                     const int* __restrict__ leaf_node, const int4* __restrict__ topo,
-                                                     int* __restrict__ order) {
-    __shared__ int at[65], lev[MAX_LEVEL + 1], heavy_at, cut;
-    const int tid = threadIdx.x;
-    if (blockIdx.x == 0 && tid < GRAV_SLOTS) {
-        ctl->grav_cnt[tid][0] = 0;
-        ctl->grav_cnt[tid][1] = 0;
-    }
-    if (tid < 65) at[tid] = 0;
-    if (tid <= MAX_LEVEL) lev[tid] = 0;
-    int u0, u1, step;  // (eight workgroups: step 1 from the share's first unit)
-    group_range(leaf_node ? ctl->n_leaves : ctl->n_groups, u0, u1, step);
-    __syncthreads();
-    if (leaf_node) {
-        for (int u = u0 + tid; u < u1; u += 1024) atomicAdd(&lev[topo[leaf_node[u]].z], 1);
-        __syncthreads();
-    }
-    if (tid == 0) {
-        cut = -1;
-        heavy_at = 0;
-        if (leaf_node) {
-            long long sum = 0, n = u1 - u0;
-            for (int l = 0; l <= MAX_LEVEL; ++l) sum += (long long)l * lev[l];
-            int k = 0;
-            for (int l = 0; l <= MAX_LEVEL && (l + 2) * n <= sum; ++l) {
-                k += lev[l];
-                if (k > 16) break;
-                cut = l;
-            }
-        }
-    }
-    __syncthreads();
-    const int c = cut;
-    const int wide = leaf_node && ctl->n_leaves <= 4096 ? 16 : INT_MAX;
-    auto size = [&](int u) {  // 0: heavy
-        const int4 t = leaf_node ? topo[leaf_node[u]] : group[u];
-        return leaf_node && (t.z <= c || t.y >= wide) ? 0 : min(t.y, 64);
-    };
-    for (int u = u0 + tid; u < u1; u += 1024) atomicAdd(&at[size(u)], 1);
-    __syncthreads();
-    if (tid == 0 && leaf_node) ctl->fmm_heavy[blockIdx.x] = at[0];
-    if (tid < 64) {  // first place of size 64 - tid
-        const int k = at[64 - tid];
-        const int incl = wave_incl_scan(k);
-        at[64 - tid] = at[0] + incl - k;
-    }
-    __syncthreads();
-    for (int u = u0 + tid; u < u1; u += 1024) {
-        const int z = size(u);
-        order[u0 + atomicAdd(z ? &at[z] : &heavy_at, 1)] = u;
+__global__ void k_zero_grav_counts(DevCtl* ctl) {
+    const int s = threadIdx.x;
+    if (s < GRAV_SLOTS) {
+        ctl->grav_cnt[s][0] = 0;
+        ctl->grav_cnt[s][1] = 0;
     }
 }
 
@@ -706,11 +654,10 @@ void launch_gravity(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
     double* gy = accumulate ? d.ay : d.gy;
     double* gz = accumulate ? d.az : d.gz;
     double* de = (accumulate && thermo) ? d.du : nullptr;
-    int* order = reinterpret_cast<int*>(d.gsize);  // free once the groups are emitted
-    hipLaunchKernelGGL(k_unit_order, dim3(8), dim3(1024), 0, s, d.ctl, d.group, nullptr, d.topo, order);
+    hipLaunchKernelGGL(k_zero_grav_counts, dim3(1), dim3(64), 0, s, d.ctl);
     auto go = [&](auto kern, int waves) {
         const int grid = std::min(dm.group_grid, 8 * std::max(1, dm.wave_cap / (8 * waves)));
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), 0, s, d.ctl, order, d.group, dm.group_size, d.topo,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), 0, s, d.ctl, d.gorder, d.group, dm.group_size, d.topo,
                            d.nbox_lo, d.nbox_hi, d.mom0, d.mom1, d.mom2, d.pos4, d.m, G, eps, theta, accumulate, gx, gy,
                            gz, d.phi, d.vel4, de);
     };
@@ -1156,7 +1103,7 @@ void launch_fmm(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, doub
     hipLaunchKernelGGL(k_fmm_cells, dim3(cg), dim3(256), 0, s, d.ctl, d.topo, d.range,
                        d.pos4, d.mom2);
     int* order = reinterpret_cast<int*>(d.gsize);  // free once the groups are emitted
-    hipLaunchKernelGGL(k_unit_order, dim3(8), dim3(1024), 0, s, d.ctl, d.group, d.leaf_node, d.topo, order);
+    launch_unit_order(s, d.ctl, nullptr, d.leaf_node, d.topo, order);
     // four leaves a workgroup, about 3 n / leaf_size of them; the kernel loops over any beyond that
     const int grid = std::min(8 * (int)((dm.n / std::max(1, dm.leaf_size) + 23) / 8), 8 * std::max(1, dm.wave_cap / 32));
     const FmmArgs K{d.ctl, order, d.leaf_node, d.parent, d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4,

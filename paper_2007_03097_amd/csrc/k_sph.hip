@@ -220,7 +220,7 @@ static bool narrow_groups(const Dims& dm) { return dm.group_size <= 16 && !few_g
 
 template <bool FP32C, int NT, int CH>
 __global__ void __launch_bounds__(NT) k_density(
-    const DevCtl* __restrict__ ctl, const int4* __restrict__ group, int gsz, int cap, const u16* __restrict__ nbr,
+    const DevCtl* __restrict__ ctl, const int* __restrict__ order, const int4* __restrict__ group, int gsz, int cap, const u16* __restrict__ nbr,
     const int* __restrict__ nbr_cnt, const int* __restrict__ uni, const int* __restrict__ ucnt,
     const double4* __restrict__ pos4, const double4* __restrict__ vel4, const double* __restrict__ m,
     const double* __restrict__ u_eos, int kin, double gamma, double h_coeff, double* __restrict__ rho,
@@ -231,7 +231,8 @@ __global__ void __launch_bounds__(NT) k_density(
     const int tid = threadIdx.x;
     int g0, g1, gstep;
     group_range(ctl->n_groups, g0, g1, gstep);
-    for (int gi = g0; gi < g1; gi += gstep) {
+    for (int ui = g0; ui < g1; ui += gstep) {
+        const int gi = order ? order[ui] : ui;
         const int4 g = group[gi];
         // PL = NT / n_g threads per target, so a group with few targets still fills the
         // workgroup; thread tid serves target tid mod n_g (the last NT mod n_g threads idle)
@@ -290,7 +291,7 @@ void launch_density(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
                     const double* u_eos, int kin) {
     if (dm.n <= 0) return;
     auto go = [&](auto kern, int threads) {
-        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, d.group, dm.group_size, dm.nbr_cap, d.nbr,
+        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, group_order(d, dm), d.group, dm.group_size, dm.nbr_cap, d.nbr,
                            d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.m, u_eos, kin, gamma, h_coeff, d.rho, d.P,
                            d.cs, d.hnext, d.thr4, d.thrf);
     };
@@ -316,7 +317,7 @@ struct ForceSrc<true, CH> {
 };
 template <bool FP32C, bool THERMO, int NT, int CH>
 __global__ void __launch_bounds__(NT) k_forces(
-    const DevCtl* __restrict__ ctl, const int4* __restrict__ group, int gsz, int cap, const u16* __restrict__ nbr,
+    const DevCtl* __restrict__ ctl, const int* __restrict__ order, const int4* __restrict__ group, int gsz, int cap, const u16* __restrict__ nbr,
     const int* __restrict__ nbr_cnt, const int* __restrict__ uni, const int* __restrict__ ucnt,
     const double4* __restrict__ pos4, const double4* __restrict__ vel4, const double4* __restrict__ thr4,
     const float4* __restrict__ thrf, double alpha, double beta, double eps_av,
@@ -326,7 +327,8 @@ __global__ void __launch_bounds__(NT) k_forces(
     const int tid = threadIdx.x;
     int g0, g1, gstep;
     group_range(ctl->n_groups, g0, g1, gstep);
-    for (int gi = g0; gi < g1; gi += gstep) {
+    for (int ui = g0; ui < g1; ui += gstep) {
+        const int gi = order ? order[ui] : ui;
         const int4 g = group[gi];
         // PL = NT / n_g threads per target, so a group with few targets still fills the
         // workgroup; thread tid serves target tid mod n_g (the last NT mod n_g threads idle)
@@ -491,7 +493,7 @@ void launch_forces(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, d
                    double eps_av, int thermo) {
     if (dm.n <= 0) return;
     auto go = [&](auto kern, int threads) {
-        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, d.group, dm.group_size,
+        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, group_order(d, dm), d.group, dm.group_size,
                            dm.nbr_cap, d.nbr, d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.thr4, d.thrf, alpha,
                            beta, eps_av, d.ax, d.ay, d.az, d.du);
     };

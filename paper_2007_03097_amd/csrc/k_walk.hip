@@ -374,7 +374,8 @@ __device__ void match_candidates(int nc, int* cand, int* coff, Tile<W>& tile, in
 
 // W wavefronts per group: the first one walks the tree, all of them match the candidates, a tile each.
 template <int T, int W>
-__global__ void __launch_bounds__(64 * W) k_nbr_lists(DevCtl* ctl, const int4* __restrict__ group, int cap,
+__global__ void __launch_bounds__(64 * W) k_nbr_lists(DevCtl* ctl, const int* __restrict__ order,
+                                                      const int4* __restrict__ group, int cap,
                                                       const int4* __restrict__ topo,
                                                       const double4* __restrict__ nbox_lo,
                                                       const double4* __restrict__ nbox_hi,
@@ -393,7 +394,8 @@ __global__ void __launch_bounds__(64 * W) k_nbr_lists(DevCtl* ctl, const int4* _
     L.p = lane / T;
     int g0, g1, gstep;
     group_range(ctl->n_groups, g0, g1, gstep);
-    for (int gi = g0; gi < g1; gi += gstep) {
+    for (int ui = g0; ui < g1; ui += gstep) {
+        const int gi = order ? order[ui] : ui;
         const int4 g = group[gi];
         GroupBox gb;
         {
@@ -526,7 +528,7 @@ void launch_nbr_lists(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     if (dm.n <= 0) return;
     auto go = [&](auto kern, int waves) {
         const int grid = std::min(dm.group_grid, 8 * std::max(1, dm.wave_cap / (8 * waves)));
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), 0, s, d.ctl, d.group, dm.nbr_cap,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(64 * waves), 0, s, d.ctl, group_order(d, dm), d.group, dm.nbr_cap,
                            d.topo, d.nbox_lo, d.nbox_hi, d.pos4, d.nbr, d.nbr_cnt, d.nbr_base, d.uni, d.ucnt);
     };
     // Wavefronts a group: with few groups a wavefront's own latencies (25 us at 4,096 particles) are the
