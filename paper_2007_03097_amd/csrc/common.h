@@ -370,14 +370,14 @@ struct Kahan {
 };
 
 
-// Whether the group kernels take their groups in the order of k_unit_order: with gravity, whose kernel
-// gains from it at every size, and where the list kernel's tail counts for more than the order's 4-6 us.
-// Lists, us, in position order and by size: 200,003 particles in groups of 32 92 / 81, a 131,101-particle star
-// in groups of 32 88 / 74, 123,480 of the tube in groups of 64 65 / 60, 50,021 in groups of 32 43 / 42,
-// 987,840 in groups of 64 250 / 250 (forces 215 / 208).
+// The order of k_unit_order for the list and pair kernels, where the list kernel's tail counts for more than
+// the order's 4-6 us and the neighbours it parts (gravity takes it at every size).  Lists, us, in position
+// order and by size: 200,003 particles in groups of 32 92 / 81, a 131,101-particle star in groups of 32
+// 88 / 74, 123,480 of the tube in groups of 64 65 / 60, 50,021 in groups of 32 43 / 42, 987,840 in groups
+// of 64 250 / 250, a star of 4,194,304 in groups of 32 1600 / 1670.
 inline const int* group_order(const DevPtrs& d, const Dims& dm) {
     const int64_t units = dm.n / std::max(1, dm.group_size);
-    return dm.mass_moments || (units > 2048 && units <= 8192) ? d.gorder : nullptr;
+    return units > 2048 && units <= 8192 ? d.gorder : nullptr;
 }
 
 // ---------------------------------------------------------------------------------------

@@ -800,7 +800,7 @@ static void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm, const 
                        d.parent, d.range, d.gsize, d.gcount);
     hipLaunchKernelGGL(k_emit_groups, dim3((n + GROUP_TILE - 1) / GROUP_TILE), dim3(GROUP_TILE), 0, s, n, dm.batched,
                        d.ctl, d.gsize, d.gcount, d.key_a, d.seg_root_rank, d.group);
-    if (group_order(d, dm)) launch_unit_order(s, d.ctl, d.group, nullptr, d.topo, d.gorder);
+    if (dm.mass_moments || group_order(d, dm)) launch_unit_order(s, d.ctl, d.group, nullptr, d.topo, d.gorder);
 }
 
 void build_input_tree(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out) {

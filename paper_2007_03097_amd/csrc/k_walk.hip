@@ -374,7 +374,7 @@ __device__ void match_candidates(int nc, int* cand, int* coff, Tile<W>& tile, in
 
 // W wavefronts per group: the first one walks the tree, all of them match the candidates, a tile each.
 template <int T, int W>
-__global__ void __launch_bounds__(64 * W) k_nbr_lists(DevCtl* ctl, const int* __restrict__ order,
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ? 5 : 1))) k_nbr_lists(DevCtl* ctl, const int* __restrict__ order,
                                                       const int4* __restrict__ group, int cap,
                                                       const int4* __restrict__ topo,
                                                       const double4* __restrict__ nbox_lo,
