@@ -42,10 +42,12 @@ constexpr int GRAV_SLOTS = 64;
 
 // Control block living in device memory.
 struct DevCtl {
+    // read back in one copy at the end of a call (CtlHead)
     u32 err;
+    int nbr_max;                  // largest neighbour count seen (for overflow reports)
+    double diag[16];              // step diagnostics
     int n_nodes;
     int n_leaves;
-    int nbr_max;                  // largest neighbour count seen (for overflow reports)
     int n_groups;                 // target groups
     int level_count[24];          // nodes per level
     int level_off[24];            // exclusive prefix of level_count
@@ -55,7 +57,6 @@ struct DevCtl {
     double box[512 * 6];          // decoded per-segment box lo.xyz, hi.xyz
     double scale[512];            // 2^B / L per segment (0 when L == 0)
     double side[512];             // L (root cell side) per segment
-    double diag[16];              // step diagnostics
     double seg_dt[512];           // step size of each segment (read by the kick kernels)
     u64 dtb_enc[512];             // per segment: ordered-integer min of the time-step bound
     // last quadrupole gravity pass: particle-cell terms ([s][0]) and particle-particle terms
@@ -64,6 +65,16 @@ struct DevCtl {
     u64 grav_cnt[GRAV_SLOTS][16];
     int skip_phi;                 // nonzero: the gravity passes leave phi unevaluated
 };
+
+// The part of DevCtl that the host reads back, a prefix of it.
+struct CtlHead {
+    u32 err;
+    int nbr_max;
+    double diag[10];
+};
+static_assert(offsetof(DevCtl, err) == offsetof(CtlHead, err) && offsetof(DevCtl, nbr_max) == offsetof(CtlHead, nbr_max) &&
+                  offsetof(DevCtl, diag) == offsetof(CtlHead, diag),
+              "CtlHead is a prefix of DevCtl");
 
 // Device pointers of one context.  All arrays are carved out of the caller's workspace.
 struct DevPtrs {
