@@ -27,6 +27,7 @@ constexpr int UNION_MAX = 65536;
 
 constexpr int MAX_LEVEL = 21;   // 21 three-bit digits below the sentinel bit 63
 constexpr double M_1_PI_D = 0.318309886183790671537767526745028724;
+constexpr double M_1_PI_LO = -1.9678676675182486e-17;  // 1/pi - M_1_PI_D (6e-17 of it)
 
 // Accumulators of a single set's bounding box in k_bbox: workgroups spread their atomics over
 // them, and k_set_box merges them (a segmented set has one per segment).
