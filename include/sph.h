@@ -194,7 +194,9 @@ sph_status sph_find_neighbors(sph_ctx* ctx, int64_t* offsets_out, int32_t* idx_o
 
 /* Eq. (7) density with W_ab = W(r_ab, h_ab), h_ab = (h_a + h_b)/2, M4 cubic spline of
  * support 2h, self term included; ideal-gas EOS P = (gamma-1) rho u, c = sqrt(gamma P/rho);
- * eq. (9) h_next = h_coeff (m/rho)^(1/3).  Builds neighbour lists if needed.
+ * eq. (9) h_next = h_coeff (m/rho)^(1/3).  Builds neighbour lists if needed.  FP64 takes lengths in
+ * any unit in which h^-3 (here) and h^-5 (sph_compute_forces) are normal numbers: h from 1e-102 to
+ * 1e102 and from 1e-61 to 1e61.
  * Outputs: device double[n] in caller order; any may be NULL (the values stay in the
  * workspace for sph_compute_forces either way). */
 sph_status sph_compute_density(sph_ctx* ctx, double* rho, double* P, double* cs, double* h_next);

@@ -368,6 +368,12 @@ __device__ __forceinline__ double rsq2_nr1(double a) {
     return y * fma(-a, y * y, 3.0);
 }
 
+// The power of two k with k v in [1, 2) (v > 0; the nearest power there is at the ends of the range).
+__device__ __forceinline__ double inv_pow2(double v) {
+    const int e = (int)((u64)__double_as_longlong(v) >> 52) & 0x7ff;
+    return __longlong_as_double((long long)max(2046 - e, 1) << 52);
+}
+
 // Kahan accumulator (explicit operation order; the library is built without floating-point
 // contraction, so it is not fused).
 struct Kahan {

@@ -116,6 +116,9 @@ struct Entries {
 // Geometry of one pair in FP64 from one reciprocal square root: with T = h_a + h_b = 2 h_ab,
 // y = 1/(r T) gives r/T = r^2 y and 1/T^2 = (r^2 y) y, without a square root or a reciprocal of its own.
 // r^2 is held above 1e-180 (a pair at the same place: r/T then vanishes beside 1 and the direction is 0).
+// r^2 T^2 has to stay a normal number: T from 1.5e-64 to 1e77, more than the force terms' 1/T^5 leaves (1e-61
+// to 1e61).  The density, whose 1/T^3 reaches from 1e-102 to 1e102, takes lengths in units of the
+// group's own h (inv_pow2).
 struct PairGeo {
     double T, s, r2, y, qh, iT2;  // s = T^2, qh = r/T = q/2, iT2 = 1/T^2
     __device__ __forceinline__ PairGeo(double dx, double dy, double dz, double ha, double hb) {
@@ -186,7 +189,7 @@ struct Split4 {
     }
 };
 
-// Density sources staged in LDS: FP64 (x, y, z, h) and m, or FP32 offset records and m.
+// Density sources staged in LDS: FP64 (x, y, z, h), times the group's unit k, and m, or FP32 offset records and m.
 template <bool FP32C, int CH>
 struct DensSrc;
 template <int CH>
@@ -195,12 +198,14 @@ struct DensSrc<false, CH> {
     double mass[CH];
     using Rec = double4;
     using Mass = double;
-    __device__ __forceinline__ void put(int i, const double4 p, double mb, const double4&) {
-        pos.put(i, p);
+    __device__ __forceinline__ void put(int i, const double4 p, double mb, const double4&, double k) {
+        pos.put(i, target(p, p, k));
         mass[i] = mb;
     }
     __device__ __forceinline__ double4 rec(int i) const { return pos.get(i); }
-    __device__ __forceinline__ static double4 target(const double4 p, const double4&) { return p; }
+    __device__ __forceinline__ static double4 target(const double4 p, const double4&, double k) {
+        return make_double4(k * p.x, k * p.y, k * p.z, k * p.w);
+    }
 };
 template <int CH>
 struct DensSrc<true, CH> {
@@ -208,12 +213,12 @@ struct DensSrc<true, CH> {
     float mass[CH];
     using Rec = float4;
     using Mass = float;
-    __device__ __forceinline__ void put(int i, const double4 p, double mb, const double4& o) {
+    __device__ __forceinline__ void put(int i, const double4 p, double mb, const double4& o, double) {
         pos[i] = offset_rec(p, o);
         mass[i] = (float)mb;
     }
     __device__ __forceinline__ float4 rec(int i) const { return pos[i]; }
-    __device__ __forceinline__ static float4 target(const double4 p, const double4& o) { return offset_rec(p, o); }
+    __device__ __forceinline__ static float4 target(const double4 p, const double4& o, double) { return offset_rec(p, o); }
 };
 // Sets whose workgroups (256 threads, 40 KB) are resident at once.
 static bool few_groups(const Dims& dm) { return dm.n <= 512 * (int64_t)dm.group_size; }
@@ -247,8 +252,9 @@ __global__ void __launch_bounds__(NT) k_density(
         const bool tv = phi < PL;
         const int q = g.x + t;
         const double4 org = pos4[g.x];  // group origin (FP32C offsets)
+        const double k = FP32C ? 1.0 : inv_pow2(org.w);  // FP64: lengths in units of h (exact, a power of two)
         const double4 mp = tv ? pos4[q] : make_double4(org.x, org.y, org.z, 1);
-        const typename DensSrc<FP32C, CH>::Rec me = DensSrc<FP32C, CH>::target(mp, org);
+        const typename DensSrc<FP32C, CH>::Rec me = DensSrc<FP32C, CH>::target(mp, org, k);
         const int cnt = tv ? nbr_cnt[q] : 0;
         Entries E(nbr + (size_t)g.x * cap, g.y, t, phi, PL, cnt);
         const int* un = uni + (size_t)g.x * cap;
@@ -260,7 +266,7 @@ __global__ void __launch_bounds__(NT) k_density(
             __syncthreads();
             for (int i = tid; i < cn; i += NT) {
                 const int b = un[c0 + i];
-                S.put(i, pos4[b], m[b], org);
+                S.put(i, pos4[b], m[b], org, k);
             }
             if (c0) E.load();
             __syncthreads();
@@ -273,7 +279,7 @@ __global__ void __launch_bounds__(NT) k_density(
         if (tv && phi == 0) {
             double sum = red[t];
             for (int f = 1; f < PL; ++f) sum += red[t + g.y * f];
-            const double r_ = FP32C ? sum * M_1_PI_D : fma(sum, M_1_PI_D, sum * M_1_PI_LO);
+            const double r_ = FP32C ? sum * M_1_PI_D : fma(sum, M_1_PI_D, sum * M_1_PI_LO) * k * k * k;
             double ue = uq;
             const double4 mpos = mp;
             if (kin) {  // u_eos holds the total energy e = u + v^2/2 (thermokinetic form)

@@ -46,3 +46,23 @@ def test_density_rounding(orc, spread):
         ctx.close()
     rms = float(np.sqrt(np.mean(np.concatenate(err) ** 2)))
     assert rms <= 1.65e-16, rms
+
+
+# ---------------------------------------------------------------------------- units
+@pytest.mark.parametrize("group", [8, 32])
+@pytest.mark.parametrize("scale", [1e-95, 1e-75, 1e-66, 1e76, 1e90, 1e95])
+def test_density_in_any_unit(orc, scale, group):
+    """FP64 density where r^2 and h^2 are representable but their product is not, coincident pairs among
+    them: 1e-12 of the sum, every term being positive and within a few ulp."""
+    ps = uniform_random(1200, seed=97, h=(0.05, 0.2))
+    for f in ("x", "y", "z"):
+        a = getattr(ps, f)
+        a[1:40:2] = a[0:39:2]
+    for f in ("x", "y", "z", "h"):
+        setattr(ps, f, getattr(ps, f) * scale)
+    ctx = make_ctx(ps.n, group_size=group, nbr_capacity=1024)
+    gpu_keys_order(ctx, parts(ps))
+    rho, P, c, hn = gpu_density(ctx, ps.n)
+    ref = orc.density(ps.fields(), orc.neighbors(ps.x, ps.y, ps.z, ps.h))
+    for a, b in zip((rho, P, c, hn), ref):
+        assert np.all(np.abs(a / b - 1.0) <= 1e-12)
