@@ -54,8 +54,11 @@ struct GroupBox {
 // means t^2 - r^2 > 0, each by more than the FP64 expression's own rounding (O(2^-53) S), and a
 // D' between is undecided.  S' takes the half diagonal R of the group box, the largest h of the
 // group hg and of the tile's sources hm: |a| <= R, and a source that passed the group-box filter
-// has |b| <= R + hg + hm.  Where M is not below 2^100 (or NaN) every pair is undecided; below,
-// nothing overflows.
+// has |b| <= R + hg + hm.  Lengths are in units of the group's reach 2 R + hg, rounded to a power of two (exact),
+// so the screen decides as much in any unit of the input; in the input's own, the FP32 range left lists of
+// coordinates above 1e18 or below 1e-13 to the exact predicate (600,000 particles 216 -> 541 us at 1e19).  Where M
+// is not below 2^100 (or NaN; sources whose h dwarfs the group, or a reach whose square is hardly
+// representable) every pair is undecided; below, nothing overflows.
 //
 // The former screen ran on the vector ALUs, 12 instructions a pair test, and bound the kernel
 // (about 780 of some 1,400 vector instructions per tile of 64 sources and 64 targets); a D'
@@ -85,6 +88,7 @@ struct Exchange {
 };
 
 struct Screen {
+    double k;      // power of two near 1 / (2 R + hg): the unit of all below
     double o[3];   // centre of the group's box
     float reach;   // 2 R + hg, rounded up
     float hg;      // rounded up
@@ -95,12 +99,12 @@ __device__ __forceinline__ float next_up(double v) { return (float)(v * (1.0 + 0
 // Stages source b at ring slot r.
 template <int W>
 __device__ __forceinline__ void stage_source(Tile<W>& tile, int r, const double4& b, int src, const Screen& S) {
-    const double x = b.x - S.o[0], y = b.y - S.o[1], z = b.z - S.o[2];
+    const double x = fma(b.x, S.k, -S.o[0]), y = fma(b.y, S.k, -S.o[1]), z = fma(b.z, S.k, -S.o[2]), h = b.w * S.k;
     tile.v[0][r] = 2.0f * (float)x;
     tile.v[1][r] = 2.0f * (float)y;
     tile.v[2][r] = 2.0f * (float)z;
-    tile.v[3][r] = 2.0f * (float)b.w;
-    tile.v[4][r] = (float)(b.w * b.w - ((x * x + y * y) + z * z));
+    tile.v[3][r] = 2.0f * (float)h;
+    tile.v[4][r] = (float)(h * h - ((x * x + y * y) + z * z));
     tile.src[r] = src;
 }
 
@@ -123,10 +127,10 @@ __device__ __forceinline__ void load_targets(LaneTargets<T>& L, const double4* _
     for (int k = 0; k < L.NC; ++k) {
         const int col = 32 * k + (lane & 31);
         const double4 A = pos4[gx + (col < gy ? col : 0)];  // columns past the group repeat its first target
-        const double x = A.x - S.o[0], y = A.y - S.o[1], z = A.z - S.o[2];
+        const double x = fma(A.x, S.k, -S.o[0]), y = fma(A.y, S.k, -S.o[1]), z = fma(A.z, S.k, -S.o[2]), h = A.w * S.k;
         L.b0[k] = odd ? (float)y : (float)x;
-        L.b1[k] = odd ? (float)A.w : (float)z;
-        L.b2[k] = odd ? (float)(A.w * A.w - ((x * x + y * y) + z * z)) : 1.0f;
+        L.b1[k] = odd ? (float)h : (float)z;
+        L.b2[k] = odd ? (float)(h * h - ((x * x + y * y) + z * z)) : 1.0f;
     }
 }
 
@@ -416,8 +420,12 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W =
                 const double e = fmax(gb.hi[c] - S.o[c], S.o[c] - gb.lo[c]);
                 d2 += e * e;
             }
-            S.reach = next_up(2.0 * sqrt(d2) + gb.hg);
-            S.hg = next_up(gb.hg);
+            const double reach = 2.0 * sqrt(d2) + gb.hg;
+            S.k = inv_pow2(reach);
+            for (int c = 0; c < 3; ++c) S.o[c] *= S.k;
+            // squares in range: near its ends the FP64 predicate rounds to 0 or overflows, and every pair takes it
+            S.reach = reach > 0x1p-400 && reach < 0x1p400 ? next_up(reach * S.k) : INFINITY;
+            S.hg = next_up(gb.hg * S.k);
         }
         load_targets(L, pos4, g.x, g.y, S);
         L.cnt = 0;

@@ -66,3 +66,20 @@ def test_density_in_any_unit(orc, scale, group):
     ref = orc.density(ps.fields(), orc.neighbors(ps.x, ps.y, ps.z, ps.h))
     for a, b in zip((rho, P, c, hn), ref):
         assert np.all(np.abs(a / b - 1.0) <= 1e-12)
+
+
+@pytest.mark.parametrize("group", [8, 64])
+@pytest.mark.parametrize("scale", [1e-158, 1e-140, 1e-119, 1e-14, 3e18, 1e121, 1e140, 1e154])
+def test_neighbors_in_any_unit(orc, scale, group):
+    """The list kernel's screen in units of the group's reach: coordinates far outside the FP32 range, both sides of
+    the reaches (2^-400, 2^400) past which every pair takes the FP64 predicate, and units in which that
+    predicate's squares vanish or overflow."""
+    from gpu_helpers import gpu_neighbors
+    ps = uniform_random(1231, seed=98, h=(0.01, 0.2))
+    for f in ("x", "y", "z", "h"):
+        setattr(ps, f, getattr(ps, f) * scale)
+    ctx = make_ctx(ps.n, group_size=group, nbr_capacity=1024)
+    gpu_keys_order(ctx, parts(ps))
+    off, idx = gpu_neighbors(ctx, ps.n)
+    ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+    assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
