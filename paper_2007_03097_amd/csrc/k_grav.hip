@@ -21,6 +21,7 @@
 constexpr int GW_STACK = 768;
 constexpr int GW_CELLS = 448;
 constexpr int GW_LEAVES = 256;
+constexpr int GW_FOLD = 16;  // partial sums of a target that one lane adds
 // Stack headroom kept free of wide rounds: popping one entry at a time (depth first), the
 // stack grows by at most 7 per tree level below the popped node, so rounds of 64 entries
 // stop DFS_HEADROOM entries short of the top and single-entry rounds cannot overflow it.
@@ -598,17 +599,30 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(FP3
 #pragma unroll
             for (int i = 0; i < 8; ++i) r[i] = G * lanes_sum_d(r[i], T.TP);  // (B: zero if !TWO)
         } else {
-            const double v[8] = {A.gx, A.gy, A.gz, 4.0 * A.ph, B.gx, B.gy, B.gz, 4.0 * B.ph};
+            // With more than GW_FOLD sums a target, the first GW_FOLD of its lanes add the others' first: a group
+            // of one target has up to 256, and one lane took 17 us to add them (a set of one particle 25 -> 41
+            // us, 512 sets of two particles 68 -> 278 us).
+            double v[8] = {A.gx, A.gy, A.gz, 4.0 * A.ph, B.gx, B.gy, B.gz, 4.0 * B.ph};
+            const int tid = threadIdx.x, last = 64 * W - 1;
 #pragma unroll
             for (int h = 0; h < 8; h += 4) {
-                __syncthreads();
+                int P = T.P;
+                while (true) {
+                    __syncthreads();
 #pragma unroll
-                for (int i = 0; i < 4; ++i) St.red[i][threadIdx.x] = v[h + i];
-                __syncthreads();
+                    for (int i = 0; i < 4; ++i) St.red[i][tid] = v[h + i];
+                    __syncthreads();
+                    if (P <= GW_FOLD) break;
+                    if (T.phi < GW_FOLD)
+                        for (int k = GW_FOLD; T.phi + k < P; k += GW_FOLD)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) v[h + i] += St.red[i][tid + k * T.TP];
+                    P = GW_FOLD;
+                }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     double t = v[h + i];  // the lanes with phi = 0 use it
-                    for (int k = 1; k < T.P; ++k) t += St.red[i][min((int)threadIdx.x + k * T.TP, 64 * W - 1)];
+                    for (int k = 1; k < P; ++k) t += St.red[i][min(tid + k * T.TP, last)];
                     r[h + i] = G * t;
                 }
             }

@@ -83,3 +83,24 @@ def test_neighbors_in_any_unit(orc, scale, group):
     off, idx = gpu_neighbors(ctx, ps.n)
     ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
     assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
+
+
+# ---------------------------------------------------------------------------- quadrupole gravity
+@pytest.mark.parametrize("group", [8, 32])
+@pytest.mark.parametrize("per", [1, 2, 3, 5, 9, 15, 16, 17, 31])
+def test_gravity_of_small_groups(orc, per, group):
+    """Groups of one to 31 targets, whose partial sums (up to 256 a target, by two or four wavefronts) are added
+    in one or two rounds: each set's direct sum at theta = 0, with and without the potential's self term."""
+    from gpu_helpers import gpu_gravity
+    ps = uniform_random(40 * per, seed=99)
+    ps.seg_offsets = np.arange(41, dtype=np.int64) * per
+    for eps in (0.05, 0.0):
+        ctx = make_ctx(ps.n, 40, theta=0.0, G=1.0, soft_eps=eps, group_size=group)
+        gpu_keys_order(ctx, parts(ps))
+        got = np.stack(gpu_gravity(ctx, ps.n))
+        for i, j in zip(ps.seg_offsets[:-1], ps.seg_offsets[1:]):
+            gx, gy, gz, phi, sg = orc.gravity_direct(ps.x[i:j], ps.y[i:j], ps.z[i:j], ps.m[i:j], 1.0, eps, scale=True)
+            d = np.sqrt(((got[:3, i:j] - np.stack([gx, gy, gz])) ** 2).sum(0))
+            assert np.all(d <= 1e-12 * sg + 1e-300)
+            assert np.all(np.abs(got[3, i:j] - phi) <= 1e-12 * (np.abs(phi) + (ps.m[i:j] / eps if eps else 0.0)))
+        ctx.close()
