@@ -146,6 +146,7 @@ struct Dims {
     int group_grid;   // grid (multiple of 8) of the per-group kernels of one to four waves (lists, gravity)
     int pair_grid;    // the same for the pair kernels (density, forces)
     int wave_cap;     // wavefronts that a per-group grid may hold
+    int n_sets;       // non-empty sets
     int n_chunks;
     int node_cap;
     int min_level;    // 3 when batched, else 0
@@ -397,6 +398,9 @@ inline const int* group_order(const DevPtrs& d, const Dims& dm) {
     const int64_t units = dm.n / std::max(1, dm.group_size);
     return units > 2048 && units <= 8192 ? d.gorder : nullptr;
 }
+
+// Sets of 64 particles at most on average.
+inline bool tiny_sets(const Dims& dm) { return dm.n <= 64 * (int64_t)dm.n_sets; }
 
 // ---------------------------------------------------------------------------------------
 // Launchers (defined in the .hip files)

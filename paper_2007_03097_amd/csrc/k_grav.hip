@@ -681,7 +681,8 @@ void launch_gravity(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
     // 875 / 816; 131,101 in groups of 32, 534 / 538 and 445 / 456; 500,000 in groups of 64, 1638 / 1639 and
     // 1114 / 1217.  Groups of 16 lack the targets for four (8,000 particles: 153 / 146 / 155).
     const int64_t units = dm.n / std::max(1, dm.group_size);
-    const int W = units > 64 * dm.group_size ? 1 : (units > 1024 || dm.group_size <= 16 || fp32c ? 2 : 4);
+    // Sets of up to 64 particles are one tile, which one wavefront evaluates.
+    const int W = units > 64 * dm.group_size || tiny_sets(dm) ? 1 : (units > 1024 || dm.group_size <= 16 || fp32c ? 2 : 4);
     if (fp32c) {
         if (W > 1) go(k_gravity<true, 2>, 2);
         else go(k_gravity<true, 1>, 1);

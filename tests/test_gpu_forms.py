@@ -104,3 +104,28 @@ def test_gravity_of_small_groups(orc, per, group):
             assert np.all(d <= 1e-12 * sg + 1e-300)
             assert np.all(np.abs(got[3, i:j] - phi) <= 1e-12 * (np.abs(phi) + (ps.m[i:j] / eps if eps else 0.0)))
         ctx.close()
+
+
+# ---------------------------------------------------------------------------- ensembles of small sets
+@pytest.mark.parametrize("sets,per,group", [(400, 1, 64), (512, 2, 8), (512, 2, 64), (90, 64, 32), (90, 65, 32)])
+def test_ensembles_of_small_sets(orc, sets, per, group):
+    """Many more groups than n over the group size (each set ends with one of its own), and both sides of the
+    sets of one tile that one wavefront a group serves: lists, density and gravity of every set."""
+    from gpu_helpers import gpu_gravity, gpu_neighbors
+    n = sets * per
+    ps = uniform_random(n, seed=101, h=(0.1, 0.3))
+    ps.seg_offsets = np.arange(sets + 1, dtype=np.int64) * per
+    ctx = make_ctx(n, sets, theta=0.0, G=1.0, soft_eps=0.05, group_size=group)
+    gpu_keys_order(ctx, parts(ps))
+    off, idx = gpu_neighbors(ctx, n)
+    rho = gpu_density(ctx, n)[0]
+    got = np.stack(gpu_gravity(ctx, n))
+    for i in range(0, n, per):
+        f = {k: getattr(ps, k)[i:i + per] for k in ("x", "y", "z", "vx", "vy", "vz", "m", "h", "u")}
+        csr = orc.neighbors(f["x"], f["y"], f["z"], f["h"])
+        assert np.array_equal(np.diff(off[i:i + per + 1]), np.diff(csr[0]))
+        assert np.array_equal(idx[off[i]:off[i + per]] - i, csr[1])
+        assert np.all(np.abs(rho[i:i + per] / orc.density(f, csr)[0] - 1.0) <= 1e-12)
+        gx, gy, gz, _, sg = orc.gravity_direct(f["x"], f["y"], f["z"], f["m"], 1.0, 0.05, scale=True)
+        d = np.sqrt(((got[:3, i:i + per] - np.stack([gx, gy, gz])) ** 2).sum(0))
+        assert np.all(d <= 1e-12 * sg + 1e-300)
