@@ -684,7 +684,10 @@ void launch_gravity(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
     // Sets of up to 64 particles are one tile, which one wavefront evaluates.
     const int W = units > 64 * dm.group_size || tiny_sets(dm) ? 1 : (units > 1024 || dm.group_size <= 16 || fp32c ? 2 : 4);
     if (fp32c) {
-        if (W > 1) go(k_gravity<true, 2>, 2);
+        // FP32C sums are the same bit for bit by one and by two wavefronts, so a cap on the wavefronts that leaves
+        // fewer than two a group goes to more groups at once (50,000 particles, one a CU: 618 -> 456 us).  FP64 sums
+        // are not, and results do not depend on the cap: there it costs up to twice the time of one a group.
+        if (W > 1 && dm.group_grid <= dm.wave_cap / 2) go(k_gravity<true, 2>, 2);
         else go(k_gravity<true, 1>, 1);
     } else {
         if (W > 2) go(k_gravity<false, 4>, 4);
