@@ -380,11 +380,13 @@ __device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C, W>& St, cons
     }
 }
 
-// The targets of one octree leaf: lane tp + TP ph serves target tp and (FP64, TWO) target tp + TP, the
+// The targets of one octree leaf: lane tp + TP ph serves target tp and (TWO) target tp + TP, the
 // P = 64 / TP lanes of a target splitting the staged sources.  Two targets a lane halve the LDS reads
 // and fill more lane slots (18 targets: 126 of 128, one a lane: 54 of 64; 40 targets: 120 of 128 and
-// 40 of 64): 262,144 particles 2.45 -> 2.20 ms with the register bound that keeps four waves per SIMD
-// (2.42 ms without it).  The FP32C sums, whose last bits depend on the split, keep one target.
+// 40 of 64), but have twice the sums to combine and more registers: FP64 takes them for leaf
+// sizes over 16.  Polytropes, ms, one / two: 262,144 particles in leaves of 64 at theta = 0.5 1.61 / 1.37, of 32
+// 1.57 / 1.57, of 16 2.45 / 2.59 and at theta = 1 0.55 / 0.63; 4,194,304 in leaves of 64 at theta = 1 5.24 / 5.15,
+// of 16 8.73 / 9.63.  The FP32C sums, whose last bits depend on the split, keep one target.
 struct LaneTarget {
     double4 a, b;
     int qa, qb;
@@ -850,7 +852,7 @@ struct FmmArgs {
 };
 
 // Leaf L by W wavefronts: the first one replays the recursion and fills the lists, all of them evaluate.
-template <bool FP32C, int W>
+template <bool FP32C, bool TWO, int W>
 __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, bool phi) {
     DevCtl* ctl = K.ctl;
     const int* __restrict__ parent = K.parent;
@@ -887,7 +889,6 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
     const double4 cl = S.Pth.com[D];
     for (int t0 = 0; t0 < tl.y; t0 += FM_TARGETS) {
         const int cc = min(FM_TARGETS, tl.y - t0);
-        constexpr bool TWO = !FP32C;
         LaneTarget T;
         T.TP = TWO ? (cc + 1) >> 1 : cc;
         T.P = 64 * W / T.TP;
@@ -898,7 +899,7 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
         T.va = T.ph < T.P;
         T.vb = TWO && T.va && tp + T.TP < cc;
         T.a = T.va ? pos4[T.qa] : make_double4(0, 0, 0, 0);
-        T.b = T.vb ? pos4[T.qb] : T.a;
+        T.b = T.vb ? pos4[T.qb] : make_double4(0, 0, 0, 0);  // (not T.a: a choice of addresses puts T in scratch memory)
         // initial pairs: (X_e+1, C) for every other child C of every ancestor X_e
         const int n0 = lane < D ? S.Pth.topo[lane].y - 1 : 0;
         const int incl = wave_incl_scan(n0);
@@ -1036,7 +1037,7 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
         for (int h = 0; h < (TWO ? 2 : 1); ++h) {
             unit_sync<W>();
             if (FP32C) S.St.part.pm[tid] = make_double4(A.kx.value(), A.ky.value(), A.kz.value(), A.kp.value());
-            else S.St.part.pm[tid] = h ? make_double4(B.gx, B.gy, B.gz, 4.0 * B.ph) : make_double4(A.gx, A.gy, A.gz, 4.0 * A.ph);
+            else S.St.part.pm[tid] = TWO && h ? make_double4(B.gx, B.gy, B.gz, 4.0 * B.ph) : make_double4(A.gx, A.gy, A.gz, 4.0 * A.ph);
             unit_sync<W>();
             if (!(h ? T.vb : T.va) || T.ph != 0) continue;
             double4 r = S.St.part.pm[tid];
@@ -1084,7 +1085,7 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
 // of 64 1000 / 1010 / 583, 50,000 in leaves of 64 850 / 847 / 721; no difference past that.  Four leaves a
 // workgroup, sizes in order and the heavy leaves together: 262,144 particles 2.18 -> 1.56 ms.
 // The FP32C sums, whose last bits depend on the split, keep one wavefront a leaf.
-template <bool FP32C>
+template <bool FP32C, bool TWO>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FP32C ? 1 : 4))) k_fmm(const FmmArgs K) {
     __shared__ __align__(32) char lds[4 * sizeof(FmmLds<1>)];
     static_assert(sizeof(FmmLds<4>) <= sizeof(lds), "the workgroup's form fits the four wavefronts' areas");
@@ -1096,7 +1097,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FP32C 
     for (int j = blockIdx.x / 8;; j += step) {
         if (j < heavy) {
             if constexpr (!FP32C)
-                fmm_leaf<FP32C, 4>(K, *reinterpret_cast<FmmLds<4>*>(lds), K.leaf_node[K.order[first + j]], phi);
+                fmm_leaf<FP32C, TWO, 4>(K, *reinterpret_cast<FmmLds<4>*>(lds), K.leaf_node[K.order[first + j]], phi);
             __syncthreads();
             continue;
         }
@@ -1104,7 +1105,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FP32C 
         if (u >= l1) break;
         const int w = u + (int)(threadIdx.x >> 6);
         if (w < l1)
-            fmm_leaf<FP32C, 1>(K, reinterpret_cast<FmmLds<1>*>(lds)[threadIdx.x >> 6], K.leaf_node[K.order[w]], phi);
+            fmm_leaf<FP32C, TWO, 1>(K, reinterpret_cast<FmmLds<1>*>(lds)[threadIdx.x >> 6], K.leaf_node[K.order[w]], phi);
     }
 }
 
@@ -1126,6 +1127,8 @@ void launch_fmm(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, doub
     const int grid = std::min(8 * (int)((dm.n / std::max(1, dm.leaf_size) + 23) / 8), 8 * std::max(1, dm.wave_cap / 32));
     const FmmArgs K{d.ctl, order, d.leaf_node, d.parent, d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4,
                     accumulate, gx, gy, gz, d.phi, d.vel4, de};
-    if (fp32c) hipLaunchKernelGGL(k_fmm<true>, dim3(grid), dim3(256), 0, s, K);
-    else hipLaunchKernelGGL(k_fmm<false>, dim3(grid), dim3(256), 0, s, K);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, K); };
+    if (fp32c) go(k_fmm<true, false>);
+    else if (dm.leaf_size > 16) go(k_fmm<false, true>);  // see LaneTarget
+    else go(k_fmm<false, false>);
 }
