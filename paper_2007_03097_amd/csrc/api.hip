@@ -254,6 +254,7 @@ static sph_status prepare(sph_ctx* c, const sph_particles* p) {
     dm.min_level = dm.batched ? 3 : 0;
     dm.curve = c->cfg.key_curve;
     dm.mass_moments = c->cfg.G != 0.0;
+    dm.group_gravity = c->cfg.G != 0.0 && c->cfg.gravity_scheme == SPH_GRAVITY_QUADRUPOLE;
     const bool same = c->tab.n == p->n && c->tab.n_seg == n_seg && c->tab.seg == seg;
     std::vector<int4> chunks;
     std::vector<int> rank(n_seg, 0);

@@ -758,17 +758,21 @@ struct FmmPath {
 
 // Integer coordinates of the cell of every node: its first particle, quantised as for the
 // keys and truncated to the node's level; packed 21 bits per axis into the free fourth
-// component of mom2 (the walk then reads them with the node's topology, not after it).
+// component of mom2 (the walk then reads them with the node's topology, not after it).  Also each leaf's
+// level and particle count (at most 64) for k_unit_order, in leaf order: level << 8 | count.
 __global__ void __launch_bounds__(256) k_fmm_cells(const DevCtl* __restrict__ ctl, const int4* __restrict__ topo,
                                                     const int2* __restrict__ range, const double4* __restrict__ pos4,
-                                                    double4* mom2) {
+                                                    const int* __restrict__ node_first, double4* mom2, u32* leaf_info) {
     const double lo[3] = {ctl->box[0], ctl->box[1], ctl->box[2]};
     const double S = ctl->scale[0];
     const u32 top = (1u << MAX_LEVEL) - 1u;
     const int nn = ctl->n_nodes;
     for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < nn; b += gridDim.x * blockDim.x) {
         const double4 p = pos4[range[b].x];
-        const int sh = MAX_LEVEL - topo[b].z;
+        const int4 t = topo[b];
+        const int f = node_first[b];
+        if (f < 0) leaf_info[~f] = ((u32)t.z << 8) | (u32)min(t.y, 64);
+        const int sh = MAX_LEVEL - t.z;
         const u64 c = (u64)(quantise(p.x, lo[0], S, top) >> sh) | ((u64)(quantise(p.y, lo[1], S, top) >> sh) << 21) |
                       ((u64)(quantise(p.z, lo[2], S, top) >> sh) << 42);
         mom2[b].w = __longlong_as_double((long long)c);
@@ -1119,10 +1123,11 @@ void launch_fmm(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, doub
     const double th4 = 4.0 * (theta * theta);
     const double* ncell = &d.mom2[0].w;  // stride 4 doubles
     const int cg = std::min(2048, (dm.node_cap + 255) / 256);
+    u32* leaf_info = d.val_b;  // the sort's scratch: free from one build to the next
     hipLaunchKernelGGL(k_fmm_cells, dim3(cg), dim3(256), 0, s, d.ctl, d.topo, d.range,
-                       d.pos4, d.mom2);
+                       d.pos4, d.node_first, d.mom2, leaf_info);
     int* order = reinterpret_cast<int*>(d.gsize);  // free once the groups are emitted
-    launch_unit_order(s, d.ctl, nullptr, d.leaf_node, d.topo, order);
+    launch_unit_order(s, d.ctl, nullptr, leaf_info, order);
     // four leaves a workgroup, about 3 n / leaf_size of them; the kernel loops over any beyond that
     const int grid = std::min(8 * (int)((dm.n / std::max(1, dm.leaf_size) + 23) / 8), 8 * std::max(1, dm.wave_cap / 32));
     const FmmArgs K{d.ctl, order, d.leaf_node, d.parent, d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4,

@@ -396,30 +396,31 @@ __global__ void __launch_bounds__(GROUP_TILE) k_emit_groups(int n, int batched, 
     if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) ctl->n_groups = first + own;
 }
 
-// Order in which the workgroups take their units (target groups, or leaves for leaf_node): within each
+// Order in which the workgroups take their units (target groups, or leaves for leaf_info): within each
 // XCD's contiguous share, the units of most targets first, so that what is left at the end is short (a
 // unit takes 100 to 400 us whatever the set's size).  Before them the heavy leaves: the at most 16
 // coarsest ones that lie two levels or more above the share's average.  One workgroup per share counts
 // and places its units.  Gravity, 1,000,003 particles in groups of 64, FP32C: 1.96 -> 1.80 ms; 131,101 in
-// groups of 32, FP64: 0.451 -> 0.370 ms; 4,194,304: 12.78 -> 12.61.
+// groups of 32, FP64: 0.451 -> 0.370 ms; 4,194,304: 12.78 -> 12.61.  What is left of its own time are the passes
+// over a share's units, a load each: a leaf's level and particle count come in one word (k_fmm_cells) in
+// leaf order, where the leaf's node and its record took two dependent ones (560,000 leaves 168 -> 121 us).
 __global__ void __launch_bounds__(1024) k_unit_order(DevCtl* ctl, const int4* __restrict__ group,
-                                                     const int* __restrict__ leaf_node, const int4* __restrict__ topo,
-                                                     int* __restrict__ order) {
+                                                     const u32* __restrict__ leaf_info, int* __restrict__ order) {
     __shared__ int at[65], lev[MAX_LEVEL + 1], heavy_at, cut;
     const int tid = threadIdx.x;
     if (tid < 65) at[tid] = 0;
     if (tid <= MAX_LEVEL) lev[tid] = 0;
     int u0, u1, step;  // (eight workgroups: step 1 from the share's first unit)
-    group_range(leaf_node ? ctl->n_leaves : ctl->n_groups, u0, u1, step);
+    group_range(leaf_info ? ctl->n_leaves : ctl->n_groups, u0, u1, step);
     __syncthreads();
-    if (leaf_node) {
-        for (int u = u0 + tid; u < u1; u += 1024) atomicAdd(&lev[topo[leaf_node[u]].z], 1);
+    if (leaf_info) {
+        for (int u = u0 + tid; u < u1; u += 1024) atomicAdd(&lev[leaf_info[u] >> 8], 1);
         __syncthreads();
     }
     if (tid == 0) {
         cut = -1;
         heavy_at = 0;
-        if (leaf_node) {
+        if (leaf_info) {
             long long sum = 0, n = u1 - u0;
             for (int l = 0; l <= MAX_LEVEL; ++l) sum += (long long)l * lev[l];
             int k = 0;
@@ -432,14 +433,15 @@ __global__ void __launch_bounds__(1024) k_unit_order(DevCtl* ctl, const int4* __
     }
     __syncthreads();
     const int c = cut;
-    const int wide = leaf_node && ctl->n_leaves <= 4096 ? 16 : INT_MAX;
+    const int wide = leaf_info && ctl->n_leaves <= 4096 ? 16 : INT_MAX;
     auto size = [&](int u) {  // 0: heavy
-        const int4 t = leaf_node ? topo[leaf_node[u]] : group[u];
-        return leaf_node && (t.z <= c || t.y >= wide) ? 0 : min(t.y, 64);
+        if (!leaf_info) return group[u].y;
+        const u32 t = leaf_info[u];
+        return (int)(t >> 8) <= c || (int)(t & 0xff) >= wide ? 0 : (int)(t & 0xff);
     };
     for (int u = u0 + tid; u < u1; u += 1024) atomicAdd(&at[size(u)], 1);
     __syncthreads();
-    if (tid == 0 && leaf_node) ctl->fmm_heavy[blockIdx.x] = at[0];
+    if (tid == 0 && leaf_info) ctl->fmm_heavy[blockIdx.x] = at[0];
     if (tid < 64) {  // first place of size 64 - tid
         const int k = at[64 - tid];
         const int incl = wave_incl_scan(k);
@@ -452,8 +454,8 @@ __global__ void __launch_bounds__(1024) k_unit_order(DevCtl* ctl, const int4* __
     }
 }
 
-void launch_unit_order(hipStream_t s, DevCtl* ctl, const int4* group, const int* leaf_node, const int4* topo, int* order) {
-    hipLaunchKernelGGL(k_unit_order, dim3(8), dim3(1024), 0, s, ctl, group, leaf_node, topo, order);
+void launch_unit_order(hipStream_t s, DevCtl* ctl, const int4* group, const u32* leaf_info, int* order) {
+    hipLaunchKernelGGL(k_unit_order, dim3(8), dim3(1024), 0, s, ctl, group, leaf_info, order);
 }
 
 // ---- nodes in breadth-first order: eight lanes per node
@@ -800,7 +802,7 @@ static void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm, const 
                        d.parent, d.range, d.gsize, d.gcount);
     hipLaunchKernelGGL(k_emit_groups, dim3((n + GROUP_TILE - 1) / GROUP_TILE), dim3(GROUP_TILE), 0, s, n, dm.batched,
                        d.ctl, d.gsize, d.gcount, d.key_a, d.seg_root_rank, d.group);
-    if (dm.mass_moments || group_order(d, dm)) launch_unit_order(s, d.ctl, d.group, nullptr, d.topo, d.gorder);
+    if (dm.group_gravity || group_order(d, dm)) launch_unit_order(s, d.ctl, d.group, nullptr, d.gorder);
 }
 
 void build_input_tree(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out) {
