@@ -424,7 +424,7 @@ int64_t group_hist_words(int64_t n);
 void build_input_tree(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out);
 // after sort_step_keys: the resident state moves from set a to set b = swapped(a), octree and groups
 void build_step_tree(hipStream_t s, const DevPtrs& a, const DevPtrs& b, const Dims& dm);
-void launch_unit_order(hipStream_t s, DevCtl* ctl, const int4* group, const u32* leaf_info, int* order);
+void launch_unit_order(hipStream_t s, DevCtl* ctl, const int4* group, const u32* leaf_info, int wide_leaves, int* order);
 void launch_tree_export(hipStream_t s, const DevPtrs& d, const Dims& dm, u64* key, int32_t* level,
                         int32_t* leaf, int64_t* start, int64_t* count);
 // k_walk.hip

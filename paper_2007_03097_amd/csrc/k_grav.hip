@@ -384,9 +384,10 @@ __device__ int eval_leaves(int nleaf, int* leaves, GravStage<FP32C, W>& St, cons
 // P = 64 / TP lanes of a target splitting the staged sources.  Two targets a lane halve the LDS reads
 // and fill more lane slots (18 targets: 126 of 128, one a lane: 54 of 64; 40 targets: 120 of 128 and
 // 40 of 64), but have twice the sums to combine and more registers: FP64 takes them for leaf
-// sizes over 16.  Polytropes, ms, one / two: 262,144 particles in leaves of 64 at theta = 0.5 1.61 / 1.37, of 32
-// 1.57 / 1.57, of 16 2.45 / 2.59 and at theta = 1 0.55 / 0.63; 4,194,304 in leaves of 64 at theta = 1 5.24 / 5.15,
-// of 16 8.73 / 9.63.  The FP32C sums, whose last bits depend on the split, keep one target.
+// sizes over 16, at wide angles (theta >= 0.7, short lists) over 32.  Polytropes, ms, one / two: 262,144 particles
+// in leaves of 64 at theta = 0.5 1.61 / 1.37, of 32 1.57 / 1.57 and at theta = 0.8 0.40 / 0.43, of 16 2.45 / 2.59;
+// 4,194,304 at theta = 1 in leaves of 64 5.24 / 5.15, of 32 6.43 / 6.96, of 16 8.73 / 9.63.  The FP32C sums, whose
+// last bits depend on the split, keep one target.
 struct LaneTarget {
     double4 a, b;
     int qa, qb;
@@ -1084,10 +1085,11 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
 // around it down to the particles: eight such leaves of the 262,144-particle polytrope ran 0.7 ms longer
 // than all other work in one wavefront each.  With at most 4,096 leaves (four
 // workgroups a CU hold 1,024 at once) leaves of 16 targets and more count as heavy too; smaller ones are
-// bound by the walk, which one wavefront does.  With the tree, us, for limits of 0 / 1,024 / 4,096 leaves:
-// 3,000 particles in leaves of 48 264 / 206 / 212, 20,011 in leaves of 32 448 / 442 / 362, 35,000 in leaves
-// of 64 1000 / 1010 / 583, 50,000 in leaves of 64 850 / 847 / 721; no difference past that.  Four leaves a
-// workgroup, sizes in order and the heavy leaves together: 262,144 particles 2.18 -> 1.56 ms.
+// bound by the walk, which one wavefront does.  Where the angle is wide, leaves have less to evaluate beside
+// their walk, and the limit is 3,072.  At theta = 0.5, us, for limits of 0 / 1,024 / 2,048 / 4,096 leaves: 3,000 particles in leaves of
+// 48 176 / 71 / 72 / 71, 20,011 in leaves of 32 210 / 209 / 170 / 170, 35,000 in leaves of 64 517 / 519 / 309 / 314,
+// 50,000 in leaves of 64 655 / 656 / 655 / 450; at theta = 1, 3,072 / 4,096: a flat 60,000 in leaves of 32 42 / 73.
+// Four leaves a workgroup, sizes in order and the heavy leaves together: 262,144 particles 2.18 -> 1.56 ms.
 // The FP32C sums, whose last bits depend on the split, keep one wavefront a leaf.
 template <bool FP32C, bool TWO>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FP32C ? 1 : 4))) k_fmm(const FmmArgs K) {
@@ -1127,13 +1129,18 @@ void launch_fmm(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, doub
     hipLaunchKernelGGL(k_fmm_cells, dim3(cg), dim3(256), 0, s, d.ctl, d.topo, d.range,
                        d.pos4, d.node_first, d.mom2, leaf_info);
     int* order = reinterpret_cast<int*>(d.gsize);  // free once the groups are emitted
-    launch_unit_order(s, d.ctl, nullptr, leaf_info, order);
-    // four leaves a workgroup, about 3 n / leaf_size of them; the kernel loops over any beyond that
-    const int grid = std::min(8 * (int)((dm.n / std::max(1, dm.leaf_size) + 23) / 8), 8 * std::max(1, dm.wave_cap / 32));
+    const bool wide_angle = theta >= 0.7;
+    const int wide_leaves = wide_angle ? 3072 : 4096;
+    launch_unit_order(s, d.ctl, nullptr, leaf_info, wide_leaves, order);
+    // four leaves a workgroup, about 3 n / leaf_size of them; the kernel loops over any beyond that.  Few leaves
+    // may all be heavy, one a workgroup (8,000 uniform particles in leaves of 64 on a quarter of the workgroups:
+    // 209 -> 110 us).
+    const int fours = dm.n / std::max(1, dm.leaf_size), ones = fp32c ? 0 : (int)std::min<int64_t>(3ll * fours, wide_leaves);
+    const int grid = std::min(8 * ((std::max(fours, ones) + 23) / 8), 8 * std::max(1, dm.wave_cap / 32));
     const FmmArgs K{d.ctl, order, d.leaf_node, d.parent, d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4,
                     accumulate, gx, gy, gz, d.phi, d.vel4, de};
     auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, K); };
     if (fp32c) go(k_fmm<true, false>);
-    else if (dm.leaf_size > 16) go(k_fmm<false, true>);  // see LaneTarget
+    else if (dm.leaf_size > (wide_angle ? 32 : 16)) go(k_fmm<false, true>);  // see LaneTarget
     else go(k_fmm<false, false>);
 }

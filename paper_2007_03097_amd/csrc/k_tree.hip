@@ -399,13 +399,15 @@ __global__ void __launch_bounds__(GROUP_TILE) k_emit_groups(int n, int batched, 
 // Order in which the workgroups take their units (target groups, or leaves for leaf_info): within each
 // XCD's contiguous share, the units of most targets first, so that what is left at the end is short (a
 // unit takes 100 to 400 us whatever the set's size).  Before them the heavy leaves: the at most 16
-// coarsest ones that lie two levels or more above the share's average.  One workgroup per share counts
+// coarsest ones that lie two levels or more above the share's average, and with at most wide_leaves leaves in
+// all every one of 16 particles and more (launch_fmm).  One workgroup per share counts
 // and places its units.  Gravity, 1,000,003 particles in groups of 64, FP32C: 1.96 -> 1.80 ms; 131,101 in
 // groups of 32, FP64: 0.451 -> 0.370 ms; 4,194,304: 12.78 -> 12.61.  What is left of its own time are the passes
 // over a share's units, a load each: a leaf's level and particle count come in one word (k_fmm_cells) in
 // leaf order, where the leaf's node and its record took two dependent ones (560,000 leaves 168 -> 121 us).
 __global__ void __launch_bounds__(1024) k_unit_order(DevCtl* ctl, const int4* __restrict__ group,
-                                                     const u32* __restrict__ leaf_info, int* __restrict__ order) {
+                                                     const u32* __restrict__ leaf_info, int wide_leaves,
+                                                     int* __restrict__ order) {
     __shared__ int at[65], lev[MAX_LEVEL + 1], heavy_at, cut;
     const int tid = threadIdx.x;
     if (tid < 65) at[tid] = 0;
@@ -433,7 +435,7 @@ __global__ void __launch_bounds__(1024) k_unit_order(DevCtl* ctl, const int4* __
     }
     __syncthreads();
     const int c = cut;
-    const int wide = leaf_info && ctl->n_leaves <= 4096 ? 16 : INT_MAX;
+    const int wide = leaf_info && ctl->n_leaves <= wide_leaves ? 16 : INT_MAX;
     auto size = [&](int u) {  // 0: heavy
         if (!leaf_info) return group[u].y;
         const u32 t = leaf_info[u];
@@ -454,8 +456,8 @@ __global__ void __launch_bounds__(1024) k_unit_order(DevCtl* ctl, const int4* __
     }
 }
 
-void launch_unit_order(hipStream_t s, DevCtl* ctl, const int4* group, const u32* leaf_info, int* order) {
-    hipLaunchKernelGGL(k_unit_order, dim3(8), dim3(1024), 0, s, ctl, group, leaf_info, order);
+void launch_unit_order(hipStream_t s, DevCtl* ctl, const int4* group, const u32* leaf_info, int wide_leaves, int* order) {
+    hipLaunchKernelGGL(k_unit_order, dim3(8), dim3(1024), 0, s, ctl, group, leaf_info, wide_leaves, order);
 }
 
 // ---- nodes in breadth-first order: eight lanes per node
@@ -802,7 +804,7 @@ static void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm, const 
                        d.parent, d.range, d.gsize, d.gcount);
     hipLaunchKernelGGL(k_emit_groups, dim3((n + GROUP_TILE - 1) / GROUP_TILE), dim3(GROUP_TILE), 0, s, n, dm.batched,
                        d.ctl, d.gsize, d.gcount, d.key_a, d.seg_root_rank, d.group);
-    if (dm.group_gravity || group_order(d, dm)) launch_unit_order(s, d.ctl, d.group, nullptr, d.gorder);
+    if (dm.group_gravity || group_order(d, dm)) launch_unit_order(s, d.ctl, d.group, nullptr, 0, d.gorder);
 }
 
 void build_input_tree(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* u, int64_t* order_out) {

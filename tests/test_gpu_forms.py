@@ -129,3 +129,26 @@ def test_ensembles_of_small_sets(orc, sets, per, group):
         gx, gy, gz, _, sg = orc.gravity_direct(f["x"], f["y"], f["z"], f["m"], 1.0, 0.05, scale=True)
         d = np.sqrt(((got[:3, i:i + per] - np.stack([gx, gy, gz])) ** 2).sum(0))
         assert np.all(d <= 1e-12 * sg + 1e-300)
+
+
+# ---------------------------------------------------------------------------- node-node gravity
+@pytest.mark.parametrize("theta", [0.69, 0.7])
+@pytest.mark.parametrize("leaf", [16, 17, 32, 33])
+def test_fmm_of_heavy_leaves(orc, leaf, theta):
+    """Both sides of the leaf sizes and the angle at which a lane takes one target or two, in a set of few
+    leaves, most of them heavy (a workgroup each), on the full grid and on one that loops over the leaves."""
+    import paper_2007_03097_amd as sph
+    from gpu_helpers import gpu_gravity
+    ps = uniform_random(7001, seed=102)
+    out = []
+    for waves in (0, 1):
+        ctx = make_ctx(ps.n, theta=theta, G=1.0, soft_eps=0.01, leaf_size=leaf, waves_per_cu=waves,
+                       gravity_scheme=sph.SPH_GRAVITY_FMM)
+        k, o = gpu_keys_order(ctx, parts(ps))
+        out.append(np.stack(gpu_gravity(ctx, ps.n)))
+        ctx.close()
+    assert np.array_equal(out[0], out[1])
+    box = orc.bbox(ps.x, ps.y, ps.z)
+    r = orc.fmm_gravity(ps.x[o], ps.y[o], ps.z[o], ps.m[o], orc.octree(k[o], leaf), box, orc.scale(box, 21), theta, 1.0, 0.01)
+    d = np.sqrt(((out[0][:3, o] - np.stack([r["gx"], r["gy"], r["gz"]])) ** 2).sum(0))
+    assert np.all(d <= 1e-12 * r["sg"]) and np.all(np.abs(out[0][3, o] - r["phi"]) <= 1e-12 * r["sp"])
