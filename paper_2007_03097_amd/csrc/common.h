@@ -53,6 +53,7 @@ struct DevCtl {
     int level_count[24];          // nodes per level
     int level_off[24];            // exclusive prefix of level_count
     int walk_level;               // level at which a single set's neighbour walks start (k_top_moments)
+    int n_sub, n_big;             // subtrees handed out whole, nodes above them (k_finalize)
     int fmm_heavy[8];             // leaves of an XCD's share that a whole workgroup takes (node-node gravity)
     u64 box_enc[512 * 6];         // per segment: ordered-integer min x,y,z then max x,y,z
     double box[512 * 6];          // decoded per-segment box lo.xyz, hi.xyz
@@ -120,7 +121,8 @@ struct DevPtrs {
     int4* group;                  // group_cap: {start, count, segment root rank (-1 = root), 0}
     u32* gsize;                   // n_cap: size of the target group starting at a position, else 0; after the groups'
                                   // emission the order of the leaves in node-node gravity (k_unit_order)
-    int* gorder;                  // n_cap: order in which the group kernels take the groups (k_unit_order)
+    int* gorder;                  // n_cap: order in which the group kernels take the groups (k_unit_order); during the build
+                                  // the roots of the subtrees handed out whole and, from its end, the nodes above them
     int* gcount;                  // group_hist_words(n_cap): groups starting in each tile of positions
     u16* nbr;                     // n_cap * nbr_cap: list slots, indices into the group's union
     int* nbr_cnt;                 // n_cap

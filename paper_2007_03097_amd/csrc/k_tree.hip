@@ -294,6 +294,7 @@ __global__ void __launch_bounds__(TB) k_emit_nodes(int n, const signed char* __r
             if (lane == TREE_ROWS - 1) {
                 ctl->n_nodes = off < node_cap ? off : node_cap;
                 ctl->n_leaves = tot;
+                ctl->n_sub = ctl->n_big = 0;
                 leaf_start[tot] = n;
                 if (off > node_cap) set_err(ctl, ERR_NODE_CAP);
             }
@@ -497,7 +498,10 @@ __device__ __forceinline__ double max8(double v) {
 }
 
 struct NodeArgs {
-    const DevCtl* ctl;
+    DevCtl* ctl;
+    int n;
+    int sub_max;  // largest number of particles of a subtree that one workgroup finishes; 0: cut at a level
+    int* list;    // their roots and, from the end, {level, node} of the nodes above them
     int batched;
     int mass;  // build masses and moments too (gravity on), else only boxes, h_max and ranges
     const u64* key;
@@ -610,9 +614,26 @@ __device__ __forceinline__ void internal_node(const NodeArgs& A, NodeSums& S, in
     store_moments(A, p, M, cx, cy, cz, acc, j);
 }
 
+// A node at level l whose first particle is at sorted position s holds more than sub_max particles: so far
+// on, the keys still share its digits.
+__device__ __forceinline__ bool node_is_big(const NodeArgs& A, int s, int l) {
+    return A.n - s > A.sub_max && lcp_digits(A.key[s], A.key[s + A.sub_max]) >= l;
+}
+
+// Appends v of the active lanes with `add` to the list of subtree roots: one atomic for all of them.
+__device__ __forceinline__ void add_root(const NodeArgs& A, bool add, int v) {
+    const u64 m = __ballot(add);
+    if (!add) return;
+    const int leader = __builtin_ctzll(m);
+    int at = 0;
+    if (lane_id() == leader) at = atomicAdd(&A.ctl->n_sub, (int)__popcll(m));
+    A.list[__shfl(at, leader, 64) + __popcll(m & lanemask_lt())] = v;
+}
+
 // Topology of every node (leaf -> particle range; internal -> children range) and the leaves'
 // geometry and moments, whatever their level: the bottom-up kernels below then only combine
-// children.
+// children.  With sub_max also how they share the internal nodes: those that hold more particles are
+// done last, by one workgroup; the subtrees below them are handed out whole.
 __global__ void __launch_bounds__(256) k_finalize(NodeArgs A, const unsigned char* __restrict__ node_level,
                                                    const int* __restrict__ node_start, const int* __restrict__ node_first,
                                                    const signed char* __restrict__ lcp,
@@ -645,14 +666,34 @@ __global__ void __launch_bounds__(256) k_finalize(NodeArgs A, const unsigned cha
             const int nc = __ffs((int)~mask) - 1;  // children are the leading run (1 .. 8)
             if (j < nc) A.parent[f + j] = b;
             if (j == 0) A.topo[b] = make_int4(f, nc, l, 0);
+            if (A.sub_max == 0) continue;
+            const bool big = node_is_big(A, s, l);
+            if (big && j == 0) {
+                const int at = A.n - 2 - 2 * atomicAdd(&A.ctl->n_big, 1);
+                A.list[at] = l;
+                A.list[at + 1] = b;
+            }
+            bool root = b == 0 && j == 0 && !big;
+            if (big && j < nc) {
+                const int cf = node_first[f + j];
+                root = cf >= 0 && cf < nn && !node_is_big(A, node_start[f + j], l + 1);
+            }
+            add_root(A, root, big ? f + j : b);
         }
     }
 }
 
-// Level from which whole subtrees are handed out: the first with at least SUB_ROOTS nodes, so that
-// flat sets (a tube fills 64 cells at level 4) still occupy the chip and the levels above, which
-// one workgroup finishes, hold few nodes.
-constexpr int SUB_ROOTS = 256;
+// Which subtrees are handed out whole, one workgroup each.  Sets of up to SUB_LISTED particles: those of
+// the first level with at least SUB_ROOTS nodes, so that flat sets (a tube fills 64 cells at level 4) still
+// occupy the chip and the levels above, which one workgroup finishes, hold few nodes.  Larger ones: those of at
+// most a 128th of the particles (between the 64th and the 256th or 512th that two levels' cells hold
+// in flat and in full sets); cut at a level, a cluster of half the particles within one of its cells was
+// one workgroup's: 4,194,304 particles 1,365 -> 142 us.  Finding them costs 3-8 us, more than
+// it saves in ordinary smaller sets.  The lists fit: at most 127 nodes a level lie above the subtrees, two words
+// each, and no more than 8 roots below each, some 27,000 words of n.
+constexpr int SUB_ROOTS = 256, SUB_SHARE = 128;
+constexpr int TOP_MAX = (MAX_LEVEL + 1) * SUB_SHARE;
+constexpr int64_t SUB_LISTED = 1 << 18;
 constexpr int SUB_THREADS = 256;
 __device__ __forceinline__ int subtree_cut(const DevCtl* ctl) {
     int l = 3;
@@ -660,7 +701,7 @@ __device__ __forceinline__ int subtree_cut(const DevCtl* ctl) {
     return l;
 }
 
-// Internal nodes at levels >= the cut: one workgroup per node of the cut finishes its whole subtree
+// Internal nodes of the subtrees: one workgroup finishes a whole subtree
 // bottom-up.  A subtree's nodes at each level are one contiguous run in breadth-first order
 // (from the first child of its first internal node to the last child of its last internal
 // node), so the runs are found top-down, then the levels are done deepest first with the
@@ -675,11 +716,13 @@ __global__ void __launch_bounds__(SUB_THREADS) k_subtree_moments(NodeArgs A) {
     __shared__ NodeSums S[SUB_THREADS / NODE_LANES];
     __shared__ int run_lo[MAX_LEVEL + 1], run_hi[MAX_LEVEL + 1], deepest;
     const int lane = lane_id(), j = threadIdx.x & (NODE_LANES - 1);
-    const int cut = subtree_cut(A.ctl);
-    const int nroot = A.ctl->level_count[cut], r0 = A.ctl->level_off[cut];
+    const bool listed = A.sub_max > 0;
+    const int level = listed ? 0 : subtree_cut(A.ctl);
+    const int nroot = listed ? A.ctl->n_sub : A.ctl->level_count[level], r0 = A.ctl->level_off[level];
     for (int ri = blockIdx.x; ri < nroot; ri += gridDim.x) {
+        const int root = listed ? A.list[ri] : r0 + ri, cut = listed ? A.topo[root].z : level;
         if (threadIdx.x < 64) {  // internal nodes of each level of the subtree lie in run_lo .. run_hi
-            int lo = r0 + ri, hi = lo, deep = cut - 1;
+            int lo = root, hi = lo, deep = cut - 1;
             for (int l = cut; l < MAX_LEVEL; ++l) {
                 int first = -1, cfirst = 0, last = -1, clast = 0;
                 for (int k0 = lo; k0 <= hi && first < 0; k0 += 64) {
@@ -727,27 +770,53 @@ __global__ void __launch_bounds__(SUB_THREADS) k_subtree_moments(NodeArgs A) {
     }
 }
 
-// Internal nodes of the levels above the cut in one workgroup, a barrier between levels.
-// Also finds the level at which the neighbour walks start: the last one with at most WALK_START nodes
-// and no leaf above it.
+// Internal nodes above the subtrees in one workgroup, a barrier between levels.
+// Also finds (in its last wavefront, which seldom has nodes) the level at which the neighbour walks start: the last
+// one with at most WALK_START nodes and no leaf above it.
 __global__ void __launch_bounds__(1024) k_top_moments(NodeArgs A, DevCtl* ctl) {
     __shared__ NodeSums S[1024 / NODE_LANES];
+    __shared__ int node[TOP_MAX];
+    __shared__ unsigned char level[TOP_MAX];
+    __shared__ u32 levels;
     const int j = threadIdx.x & (NODE_LANES - 1);
-    if (threadIdx.x < 64) {
+    const bool listed = A.sub_max > 0;
+    const int nb = listed ? min(ctl->n_big, TOP_MAX) : 0;
+    if (listed) {
+        if (threadIdx.x == 0) levels = 0u;
+        __syncthreads();
+        for (int k = threadIdx.x; k < nb; k += 1024) {
+            const int l = A.list[A.n - 2 - 2 * k];
+            node[k] = A.list[A.n - 1 - 2 * k];
+            level[k] = (unsigned char)l;
+            atomicOr(&levels, 1u << l);
+        }
+    }
+    if (threadIdx.x >= 960) {
         int l = 0;
         while (l < MAX_LEVEL && A.ctl->level_count[l + 1] > 0 && A.ctl->level_count[l + 1] <= WALK_START) {
-            const int b0 = A.ctl->level_off[l], nb = A.ctl->level_count[l];  // at most WALK_START nodes
-            if (__ballot(lane_id() < nb && A.topo[b0 + min(lane_id(), nb - 1)].w)) break;
+            const int b0 = A.ctl->level_off[l], nl = A.ctl->level_count[l];  // at most WALK_START nodes
+            if (__ballot(lane_id() < nl && A.topo[b0 + min(lane_id(), nl - 1)].w)) break;
             ++l;
         }
-        if (threadIdx.x == 0) ctl->walk_level = l;
+        if (threadIdx.x == 960) ctl->walk_level = l;
     }
-    for (int level = subtree_cut(A.ctl) - 1; level >= 0; --level) {
-        const int b0 = A.ctl->level_off[level], nb = A.ctl->level_count[level];
-        for (int k = threadIdx.x / NODE_LANES; k < nb; k += 1024 / NODE_LANES) {
-            const int4 tp = A.topo[b0 + k];
-            if (!tp.w) internal_node(A, S[threadIdx.x / NODE_LANES], b0 + k, tp, j);
+    if (!listed) {
+        for (int l = subtree_cut(A.ctl) - 1; l >= 0; --l) {
+            const int b0 = A.ctl->level_off[l], nl = A.ctl->level_count[l];
+            for (int k = threadIdx.x / NODE_LANES; k < nl; k += 1024 / NODE_LANES) {
+                const int4 tp = A.topo[b0 + k];
+                if (!tp.w) internal_node(A, S[threadIdx.x / NODE_LANES], b0 + k, tp, j);
+            }
+            __syncthreads();
         }
+        return;
+    }
+    __syncthreads();
+    for (u32 todo = levels; todo;) {
+        const int l = 31 - __clz((int)todo);
+        todo &= ~(1u << l);
+        for (int k = threadIdx.x / NODE_LANES; k < nb; k += 1024 / NODE_LANES)
+            if (level[k] == l) internal_node(A, S[threadIdx.x / NODE_LANES], node[k], A.topo[node[k]], j);
         __syncthreads();
     }
 }
@@ -790,7 +859,7 @@ static void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm, const 
     };
     if (tb == TB_SMALL) emit(k_emit_nodes<TB_SMALL>);
     else emit(k_emit_nodes<TB_LARGE>);
-    const NodeArgs A{d.ctl, dm.batched, dm.mass_moments, d.key_a, d.topo, d.parent, d.pos4, d.m,
+    const NodeArgs A{d.ctl, n, n > SUB_LISTED ? (n + SUB_SHARE - 1) / SUB_SHARE : 0, d.gorder, dm.batched, dm.mass_moments, d.key_a, d.topo, d.parent, d.pos4, d.m,
                      d.nbox_lo, d.nbox_hi, d.mom0, d.mom1, d.mom2, d.range};
     // about 4 n / leaf_size nodes of eight lanes; the kernel loops over any beyond that
     hipLaunchKernelGGL(k_finalize, dim3(grid_cap(4 * (n / dm.leaf_size) + 64, 256 / NODE_LANES, 8192)), dim3(256), 0, s,

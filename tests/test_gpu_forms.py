@@ -152,3 +152,66 @@ def test_fmm_of_heavy_leaves(orc, leaf, theta):
     r = orc.fmm_gravity(ps.x[o], ps.y[o], ps.z[o], ps.m[o], orc.octree(k[o], leaf), box, orc.scale(box, 21), theta, 1.0, 0.01)
     d = np.sqrt(((out[0][:3, o] - np.stack([r["gx"], r["gy"], r["gz"]])) ** 2).sum(0))
     assert np.all(d <= 1e-12 * r["sg"]) and np.all(np.abs(out[0][3, o] - r["phi"]) <= 1e-12 * r["sp"])
+
+
+# ---------------------------------------------------------------------------- node moments of uneven sets
+@pytest.mark.parametrize("case", ["cluster", "clusters", "point"])
+def test_moments_of_uneven_sets(orc, case):
+    """Sets of more than 2^18 particles, whose subtrees are handed out by their number of particles: half of them in
+    one cell of the first levels, in cells of several depths, and on one point (a chain of nodes that
+    each hold them all).  Masses, centres and second moments through the quadrupole field of the oracle's walk on its
+    own tree: 99% of particles to 1e-9, the rest only where a borderline opening decision flips."""
+    from gpu_helpers import gpu_gravity
+    n = 270_001
+    ps = uniform_random(n, seed=103)
+    rng = np.random.default_rng(104)
+    ps.m = rng.uniform(0.5, 1.5, n) / n
+    if case == "cluster":
+        for f in ("x", "y", "z"):
+            getattr(ps, f)[: n // 2] = 0.5 + 1e-3 * getattr(ps, f)[: n // 2]
+    elif case == "clusters":
+        for k, w in enumerate((1e-1, 1e-2, 1e-3, 1e-4)):
+            c = rng.uniform(0.1, 0.9, 3)
+            for f, o in zip(("x", "y", "z"), c):
+                a = getattr(ps, f)[k * 50_000:(k + 1) * 50_000]
+                a[:] = o + w * (a - 0.5)
+    else:
+        for f in ("x", "y", "z"):
+            getattr(ps, f)[:3000] = 0.3
+    ctx = make_ctx(n, theta=0.8, G=1.0, soft_eps=0.01, leaf_size=32, group_size=64)
+    k, o = gpu_keys_order(ctx, parts(ps))
+    g = np.stack(gpu_gravity(ctx, n)[:3], axis=1)
+    t, cells = orc.octree(k[o], 32), orc.octree(k[o], 256)
+    gs, gc = [], []
+    for s0, c0 in zip(cells["start"][cells["leaf"]], cells["count"][cells["leaf"]]):
+        for j in range(0, int(c0), 64):
+            gs.append(s0 + j)
+            gc.append(min(64, int(c0) - j))
+    L = max(np.ptp(ps.x), np.ptp(ps.y), np.ptp(ps.z))
+    ref = np.empty((n, 3))
+    ref[o] = np.stack(orc.tree_gravity(ps.x[o], ps.y[o], ps.z[o], ps.m[o], t, L, 0.8, 1.0, 0.01, np.array(gs),
+                                       np.array(gc))[:3], axis=1)
+    d = np.linalg.norm(g - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert np.quantile(d, 0.99) <= 1e-9 and d.max() <= 1e-2, (np.quantile(d, 0.99), d.max())
+
+
+def test_moments_of_a_large_ensemble(orc):
+    """The same with 400 sets, whose first three levels are refined whatever they hold: lists (boxes and largest h of
+    the nodes) of some sets exact, their gravity near the direct sum."""
+    from gpu_helpers import gpu_gravity, gpu_neighbors
+    sets, per = 400, 701
+    n = sets * per
+    ps = uniform_random(n, seed=105, h=(0.02, 0.1))
+    ps.seg_offsets = np.arange(sets + 1, dtype=np.int64) * per
+    ctx = make_ctx(n, sets, theta=0.6, G=1.0, soft_eps=0.05, nbr_capacity=512)
+    gpu_keys_order(ctx, parts(ps))
+    off, idx = gpu_neighbors(ctx, n)
+    got = np.stack(gpu_gravity(ctx, n))
+    for i in range(0, n, 57 * per):
+        x, y, z, m, h = (getattr(ps, f)[i:i + per] for f in ("x", "y", "z", "m", "h"))
+        csr = orc.neighbors(x, y, z, h)
+        assert np.array_equal(np.diff(off[i:i + per + 1]), np.diff(csr[0]))
+        assert np.array_equal(idx[off[i]:off[i + per]] - i, csr[1])
+        ref = np.stack(orc.gravity_direct(x, y, z, m, 1.0, 0.05)[:3])
+        d = np.sqrt(((got[:3, i:i + per] - ref) ** 2).sum(0)) / np.sqrt((ref ** 2).sum(0))
+        assert np.sqrt((d ** 2).mean()) <= 1e-2
