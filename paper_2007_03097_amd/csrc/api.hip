@@ -554,7 +554,7 @@ sph_status sph_find_neighbors(sph_ctx* c, int64_t* offsets_out, int32_t* idx_out
             HIPCHK(c, hipStreamSynchronize(c->stream));
             return fail(c, SPH_E_CAPACITY, "%lld neighbour entries > capacity %lld", (long long)total, (long long)capacity);
         }
-        if (n > 0) launch_csr_fill(c->stream, d, c->dm, d.csr_tmp, idx_out);
+        if (n > 0) launch_csr_fill(c->stream, d, c->dm, d.csr_tmp, idx_out, total);
     }
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));

@@ -436,7 +436,7 @@ void launch_density(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
                     const double* u_eos, int kinetic_in_u);
 void launch_csr_count(hipStream_t s, const DevPtrs& d, const Dims& dm, int64_t* counts_caller);
 void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp);
-void launch_csr_fill(hipStream_t s, const DevPtrs& d, const Dims& dm, const int64_t* offsets, int32_t* idx);
+void launch_csr_fill(hipStream_t s, const DevPtrs& d, const Dims& dm, const int64_t* offsets, int32_t* idx, int64_t total);
 // k_sph.hip
 void launch_thermo_from_caller(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* rho,
                                const double* P, const double* cs);

@@ -572,23 +572,23 @@ void launch_csr_count(hipStream_t s, const DevPtrs& d, const Dims& dm, int64_t* 
                                      counts_caller);
 }
 
-// One workgroup per group, one wave per target.  The targets' neighbour IDs are distinct, so an
+// One workgroup per group, one wave per target, or 16 or 8 lanes where no list of the group is longer (200,003
+// particles of one neighbour in groups of 64, whole query: 96 -> 77 us).  The targets' neighbour IDs are distinct, so an
 // entry's place in its list is the number of smaller IDs in it: each lane holds one entry and
 // counts them against the others broadcast from their lanes, without LDS sorts or divergence.
 // The former one-thread insertion sort in global memory was bound by its chains of dependent
 // loads and stores: 1,070 us for 200,003 particles of 38 neighbours, now 84 us (30 MB of lists: 0.4 TB/s; the counting bounds it).
-constexpr int CSR_THREADS = 256;
-constexpr int CSR_UNION = 4096;  // union IDs staged in LDS; larger unions read them from memory
-
+template <int CSR_THREADS>
 __global__ void __launch_bounds__(CSR_THREADS) k_csr_fill(const DevCtl* __restrict__ ctl, int cap,
                                                           const int4* __restrict__ group, const u32* __restrict__ id,
                                                           const int* __restrict__ cnt, const int* __restrict__ gidx,
                                                           const u16* __restrict__ nbr, const int* __restrict__ uni,
                                                           const int* __restrict__ ucnt,
                                                           const int64_t* __restrict__ off, int32_t* __restrict__ idx) {
+    constexpr int CSR_UNION = 16 * CSR_THREADS;  // union IDs staged in LDS; larger unions read them from memory
     __shared__ int uid[CSR_UNION];
     __shared__ int64_t toff[64];  // per target: its place in idx and its count
-    __shared__ int tcnt[64];
+    __shared__ int tcnt[64], longest;
     const int lane = lane_id(), w = threadIdx.x >> 6;
     int g0, g1, gstep;
     group_range(ctl->n_groups, g0, g1, gstep);
@@ -600,12 +600,39 @@ __global__ void __launch_bounds__(CSR_THREADS) k_csr_fill(const DevCtl* __restri
         __syncthreads();
         if (staged)
             for (int i = threadIdx.x; i < nu; i += CSR_THREADS) uid[i] = (int)id[un[i]];
-        if (threadIdx.x < g.y) {  // at most 64 targets
-            const int q = g.x + threadIdx.x;
-            toff[threadIdx.x] = off[id[q]];
-            tcnt[threadIdx.x] = gidx[q] < 0 ? 0 : cnt[q];
+        if (threadIdx.x < 64) {  // at most 64 targets
+            int c = 0;
+            if (threadIdx.x < g.y) {
+                const int q = g.x + threadIdx.x;
+                toff[threadIdx.x] = off[id[q]];
+                tcnt[threadIdx.x] = c = gidx[q] < 0 ? 0 : cnt[q];
+            }
+            c = (int)wave_reduce_u32((u32)c, [](u32 a, u32 b) { return max(a, b); });
+            if (threadIdx.x == 0) longest = c;
         }
         __syncthreads();
+        auto few = [&](auto width) {  // width lanes a target, an entry each
+            constexpr int N = decltype(width)::value;
+            const int k = threadIdx.x % N;
+            for (int t = threadIdx.x / N; t < g.y; t += CSR_THREADS / N) {
+                const int c = tcnt[t];
+                int v = 0x7fffffff;
+                if (k < c) {
+                    const int u = nbr[(size_t)g.x * cap + t + k * g.y];
+                    v = staged ? uid[u] : (int)id[un[u]];
+                }
+                int rank = 0;
+#pragma unroll
+                for (int j = 0; j < N; ++j) rank += __shfl(v, j, N) < v ? 1 : 0;
+                if (k < c) idx[toff[t] + rank] = v;
+            }
+        };
+        const int most = longest;
+        if (most <= 16) {
+            if (most <= 8) few(std::integral_constant<int, 8>());
+            else few(std::integral_constant<int, 16>());
+            continue;
+        }
         for (int t = w; t < g.y; t += CSR_THREADS / 64) {
             const int c = __builtin_amdgcn_readfirstlane(tcnt[t]);
             const u16* lst = nbr + (size_t)g.x * cap + t;
@@ -632,8 +659,15 @@ __global__ void __launch_bounds__(CSR_THREADS) k_csr_fill(const DevCtl* __restri
     }
 }
 
-void launch_csr_fill(hipStream_t s, const DevPtrs& d, const Dims& dm, const int64_t* offsets, int32_t* idx) {
-    if (dm.n > 0)
-        hipLaunchKernelGGL(k_csr_fill, dim3(dm.pair_grid), dim3(CSR_THREADS), 0, s, d.ctl, dm.nbr_cap, d.group, d.id,
-                           d.nbr_cnt, d.nbr_base, d.nbr, d.uni, d.ucnt, offsets, idx);
+void launch_csr_fill(hipStream_t s, const DevPtrs& d, const Dims& dm, const int64_t* offsets, int32_t* idx, int64_t total) {
+    if (dm.n <= 0) return;
+    auto go = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, dm.nbr_cap, d.group, d.id, d.nbr_cnt,
+                           d.nbr_base, d.nbr, d.uni, d.ucnt, offsets, idx);
+    };
+    // Many small groups of short lists: a wavefront each.  200,003 particles of a lattice, whole query, us, 256 / 64
+    // threads: one neighbour each, groups of 8 100 / 81, of 16 84 / 76; 58 neighbours, of 8 214 / 204, of 16
+    // 198 / 212; 60,000 of 58, of 8 112 / 123.
+    if (dm.group_size <= 16 && dm.n / dm.group_size > 4096 && total <= 24 * (int64_t)dm.n) go(k_csr_fill<64>, 64);
+    else go(k_csr_fill<256>, 256);
 }

@@ -215,3 +215,20 @@ def test_moments_of_a_large_ensemble(orc):
         ref = np.stack(orc.gravity_direct(x, y, z, m, 1.0, 0.05)[:3])
         d = np.sqrt(((got[:3, i:i + per] - ref) ** 2).sum(0)) / np.sqrt((ref ** 2).sum(0))
         assert np.sqrt((d ** 2).mean()) <= 1e-2
+
+
+# ---------------------------------------------------------------------------- CSR rows of short lists
+@pytest.mark.parametrize("group", [8, 16, 64])
+@pytest.mark.parametrize("n,mean", [(2001, 6), (2001, 10), (40_001, 3), (70_001, 6), (70_001, 30)])
+def test_csr_of_short_lists(orc, n, mean, group):
+    """Groups whose longest list has up to 8, up to 16 and more entries, by workgroups of four wavefronts and of one;
+    a few groups of one set are long."""
+    from gpu_helpers import gpu_neighbors
+    h0 = (mean / (n * 32.0 / 3.0 * np.pi)) ** (1.0 / 3.0)
+    ps = uniform_random(n, seed=106, h=(0.7 * h0, 1.3 * h0))
+    ps.x[:300], ps.y[:300], ps.z[:300] = (0.5 + 0.3 * h0 * np.random.default_rng(107).uniform(-1, 1, (3, 300)))
+    ctx = make_ctx(n, group_size=group, nbr_capacity=1024)
+    gpu_keys_order(ctx, parts(ps))
+    off, idx = gpu_neighbors(ctx, n)
+    ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+    assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
