@@ -225,9 +225,13 @@ static bool few_groups(const Dims& dm) { return dm.n <= 512 * (int64_t)dm.group_
 // FP64 sums over small groups take 128 threads: with 256 a thread would have three or four entries of its
 // target's list, too few beside what it does once.  1.0M particles in 56 boxes, groups of 16: density 216
 // -> 171 us, forces 363 -> 300 us; 123,480 of the tube 33 -> 27 and 52 -> 40 us; groups of 32 keep 256
-// (density 148 and 143, forces 248 and 297 us).  The FP32C sums, whose last bits depend on the
+// (density 148 and 143, forces 248 and 297 us).  Where lists may be long (by their capacity) it takes more groups
+// until the chip is as full with 128 threads each: 20,011 particles in groups of 16, forces, us, 256 / 128
+// threads: 39 neighbours 18 / 14, 160 25 / 35, 610 65 / 101.  The FP32C sums, whose last bits depend on the
 // split, keep 256.
-static bool narrow_groups(const Dims& dm) { return dm.group_size <= 16 && !few_groups(dm); }
+static bool narrow_groups(const Dims& dm) {
+    return dm.group_size <= 16 && dm.n > (dm.nbr_cap > 192 ? 2048 : 512) * (int64_t)dm.group_size;
+}
 
 template <bool FP32C, int NT, int CH>
 __global__ void __launch_bounds__(NT) k_density(
@@ -517,7 +521,8 @@ void launch_forces(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, d
     // 300).  Few groups take the largest: 3,375 in groups of 32, FP32C 9.0 / 8.2 / 7.2.
     auto pick = [&](auto f, auto th) {
         constexpr bool F = decltype(f)::value, TH = decltype(th)::value;
-        if (dm.group_size > 32 || few_groups(dm)) go(k_forces<F, TH, 256, F ? 512 : 464>, 256);
+        if (dm.group_size > 32 || few_groups(dm) || (!F && dm.group_size <= 16 && !narrow_groups(dm)))
+            go(k_forces<F, TH, 256, F ? 512 : 464>, 256);
         else if (dm.group_size > 16) go(k_forces<F, TH, 256, 320>, 256);
         else if constexpr (F) go(k_forces<F, TH, 256, 256>, 256);
         else go(k_forces<F, TH, 128, 192>, 128);

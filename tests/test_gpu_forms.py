@@ -232,3 +232,24 @@ def test_csr_of_short_lists(orc, n, mean, group):
     off, idx = gpu_neighbors(ctx, n)
     ref = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
     assert np.array_equal(off, ref[0]) and np.array_equal(idx, ref[1])
+
+
+# ---------------------------------------------------------------------------- pair sums over long lists
+@pytest.mark.parametrize("cap", [192, 193])
+@pytest.mark.parametrize("n", [4097, 16384, 16385])
+def test_pair_sums_by_list_capacity(orc, n, cap):
+    """Groups of 8 take workgroups of 128 or 256 threads by the number of groups and the lists' capacity: FP64
+    density and forces at both sides of each limit, 1e-12 of the sum of the terms' magnitudes."""
+    from gpu_helpers import gpu_forces
+    h0 = (40.0 / (n * 32.0 / 3.0 * np.pi)) ** (1.0 / 3.0)
+    ps = uniform_random(n, seed=108, h=(0.5 * h0, 1.2 * h0))
+    ctx = make_ctx(n, group_size=8, nbr_capacity=cap)
+    gpu_keys_order(ctx, parts(ps))
+    rho, P, c, hn = gpu_density(ctx, n)
+    csr = orc.neighbors(ps.x, ps.y, ps.z, ps.h)
+    for a, b in zip((rho, P, c, hn), orc.density(ps.fields(), csr)):
+        assert np.max(np.abs(a - b) / np.abs(b)) <= 1e-12
+    ax, ay, az, du = gpu_forces(ctx, n)
+    r_ax, r_ay, r_az, r_du, Sa, Su = orc.forces(ps.fields(), rho, P, c, csr)
+    assert np.all(np.sqrt((ax - r_ax) ** 2 + (ay - r_ay) ** 2 + (az - r_az) ** 2) <= 1e-12 * Sa)
+    assert np.all(np.abs(du - r_du) <= 1e-12 * Su)
