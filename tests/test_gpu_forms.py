@@ -253,3 +253,80 @@ def test_pair_sums_by_list_capacity(orc, n, cap):
     r_ax, r_ay, r_az, r_du, Sa, Su = orc.forces(ps.fields(), rho, P, c, csr)
     assert np.all(np.sqrt((ax - r_ax) ** 2 + (ay - r_ay) ** 2 + (az - r_az) ** 2) <= 1e-12 * Sa)
     assert np.all(np.abs(du - r_du) <= 1e-12 * Su)
+
+
+# ---------------------------------------------------------------------------- quadrupole walk, every form
+@pytest.mark.parametrize("group", [8, 16, 32, 64])
+def test_gravity_forms_against_the_walk(orc, group):
+    """5,000 particles by one wavefront a group (8), two (16) and four (32, 64; FP32C two): FP64 against the oracle's
+    walk over the same groups, 99% to 1e-9 (the rest where a borderline opening decision flips), and FP32C
+    against FP64, whose decisions it shares, within FP32 rounding."""
+    from gpu_helpers import gpu_gravity
+    from workloads import polytrope_n1
+    ps = polytrope_n1(5000, seed=109)
+    ps.m = np.random.default_rng(110).uniform(0.5, 1.5, ps.n) / ps.n
+    res = []
+    for prec in (0, 1):
+        ctx = make_ctx(ps.n, theta=0.5, G=1.0, soft_eps=0.01, precision=prec, leaf_size=16, group_size=group)
+        k, o = gpu_keys_order(ctx, parts(ps))
+        res.append(np.stack(gpu_gravity(ctx, ps.n), axis=1))
+        ctx.close()
+    cells = orc.octree(k[o], 4 * group)
+    gs, gc = [], []
+    for s0, c0 in zip(cells["start"][cells["leaf"]], cells["count"][cells["leaf"]]):
+        for j in range(0, int(c0), group):
+            gs.append(s0 + j)
+            gc.append(min(group, int(c0) - j))
+    L = max(np.ptp(ps.x), np.ptp(ps.y), np.ptp(ps.z))
+    ref = np.empty((ps.n, 4))
+    ref[o] = np.stack(orc.tree_gravity(ps.x[o], ps.y[o], ps.z[o], ps.m[o], orc.octree(k[o], 16), L, 0.5, 1.0, 0.01,
+                                       np.array(gs), np.array(gc)), axis=1)
+    gm = np.linalg.norm(ref[:, :3], axis=1)
+    d, dp = np.linalg.norm(res[0][:, :3] - ref[:, :3], axis=1) / gm, np.abs(res[0][:, 3] / ref[:, 3] - 1.0)
+    assert np.quantile(d, 0.99) <= 1e-9 and d.max() <= 1e-3 and np.quantile(dp, 0.99) <= 1e-9
+    d, dp = np.linalg.norm(res[1][:, :3] - res[0][:, :3], axis=1) / gm, np.abs(res[1][:, 3] / res[0][:, 3] - 1.0)
+    assert np.median(d) <= 2e-7 and d.max() <= 1e-5
+    assert np.median(dp) <= 1e-7 and dp.max() <= 1e-6
+
+
+# ---------------------------------------------------------------------------- sorts, every pass
+def _points(n, copies):
+    """Random points, each `copies` times, at random places of the input: ties across tiles and runs."""
+    ps = uniform_random(n, seed=111 + n % 97, h=1e-4)
+    k = np.random.default_rng(n).permutation(n) // copies
+    for f in ("x", "y", "z", "vx", "vy", "vz"):
+        setattr(ps, f, np.ascontiguousarray(getattr(ps, f)[k]))
+    return ps
+
+
+@pytest.mark.parametrize("n", [40_961, 524_289, 1_600_003, 2_200_003])
+def test_step_sort_ties_in_every_pass(orc, n):
+    """Tiles of 1,024 keys and passes of 8 and 8 ways; of 4,096 and 4, 4, 4, 4; and 4, 4, 4, 4, 2; and ten
+    of 2: the step's sort, from the previous key order, with equal keys (16 particles a point) in the order of the IDs."""
+    import torch
+    import paper_2007_03097_amd as sph
+    from gpu_helpers import to_np
+    ps = _points(n, 16)
+    ctx = make_ctx(n, nbr_capacity=64)
+    pa = parts(ps, with_accel=True)
+    keys = torch.zeros(n, dtype=torch.int64, device="cuda")
+    order = torch.zeros(n, dtype=torch.int64, device="cuda")
+    for flags in (sph.SPH_STEP_PRIMED, sph.SPH_STEP_RESUME):
+        sph.sph_step(ctx.h, pa, 0.3, 1, flags)   # far enough to mix the order
+        sph.sph_key_order(ctx.h, keys, order)
+        k = to_np(keys).view(np.uint64)
+        assert np.array_equal(k, orc.keys(*(to_np(pa[f]) for f in ("x", "y", "z"))))
+        assert np.array_equal(to_np(order), orc.order(k))
+        assert np.unique(k).size < n
+    ctx.close()
+
+
+@pytest.mark.parametrize("copies", [1, 16])
+@pytest.mark.parametrize("n", [1_600_003, 2_200_003])
+def test_caller_sort_of_large_sets(orc, n, copies):
+    """Two-way passes over runs of like length, keys in any order, equal keys by index."""
+    ps = _points(n, copies)
+    ctx = make_ctx(n, nbr_capacity=16)
+    k, o = gpu_keys_order(ctx, parts(ps))
+    assert np.array_equal(k, orc.keys(ps.x, ps.y, ps.z)) and np.array_equal(o, orc.order(k))
+    ctx.close()
