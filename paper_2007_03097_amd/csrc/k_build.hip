@@ -571,18 +571,18 @@ __device__ __forceinline__ int ms_split_global(const u64* __restrict__ key, cons
 }
 
 // Small sets: the place of a key is the number of keys before it.  A workgroup holds RANK_KEYS keys
-// in RANK_PARTS lanes each, every lane counting over its part of all keys, staged in LDS RANK_STAGE at
-// a time; equal keys (rare) are told apart by a second pass over the lanes concerned.  n^2 work on
+// in RANK_PARTS lanes each, every lane counting over its part of all keys, which are staged in LDS
+// together; equal keys (rare) are told apart by a second pass over the lanes concerned.  n^2 work on
 // the whole chip against the tile sort's n log^2 n on one or two CUs: 4,096 keys 15-21 -> 6.5 us, 8,192
 // (a tile sort and a merge) 34 -> 16 us; at 16,384 it would take 64 us against 40.
-constexpr int RANK_THREADS = 1024, RANK_KEYS = 16, RANK_PARTS = RANK_THREADS / RANK_KEYS, RANK_STAGE = 8192;
-constexpr int RANK_MAX = 8192;
+constexpr int RANK_THREADS = 1024, RANK_KEYS = 16, RANK_PARTS = RANK_THREADS / RANK_KEYS;
+constexpr int RANK_MAX = 8192;  // keys of the largest set, which LDS holds
 
 template <bool TIE>
 __global__ void __launch_bounds__(RANK_THREADS) k_rank_sort(const u64* __restrict__ key, u64* __restrict__ kout,
                                                             u32* __restrict__ vout, int n,
                                                             const u32* __restrict__ tie) {
-    __shared__ u64 sk[RANK_STAGE];
+    __shared__ u64 sk[RANK_MAX];
     __shared__ int part[RANK_THREADS / 64][RANK_KEYS];
     // lanes l and l + 16 m of a wave hold key l % 16; wave w, lane group m: part 4 w + m
     const int kk = threadIdx.x % RANK_KEYS, p = threadIdx.x / RANK_KEYS;
