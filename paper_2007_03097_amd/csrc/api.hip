@@ -372,10 +372,10 @@ static sph_status build_from_caller(sph_ctx* c, const sph_particles* p, const do
         HIPCHK(c, hipMemcpyAsync(d.ctl->box, box_host, sizeof(double) * 6 * dm.n_seg, hipMemcpyHostToDevice, c->stream));
         launch_set_box(c->stream, d, dm, 1);
     } else {
-        launch_bbox(c->stream, d, dm, p->x, p->y, p->z, nullptr);
+        launch_bbox(c->stream, d, dm, p->x, p->y, p->z);
         launch_set_box(c->stream, d, dm, 0);
     }
-    launch_keys(c->stream, d, dm, p->x, p->y, p->z, p->vx, p->vy, p->vz, p->m, p->h, p->u, (u64*)keys_out, 1);
+    launch_keys(c->stream, d, dm, p->x, p->y, p->z, p->vx, p->vy, p->vz, p->m, p->h, p->u, (u64*)keys_out);
     sort_caller_keys(c->stream, d, dm.n);
     build_input_tree(c->stream, d, dm, p->u, order_out);
     HIPCHK(c, hipGetLastError());

@@ -121,8 +121,8 @@ struct DevPtrs {
     int4* group;                  // group_cap: {start, count, segment root rank (-1 = root), 0}
     u32* gsize;                   // n_cap: size of the target group starting at a position, else 0; after the groups'
                                   // emission the order of the leaves in node-node gravity (k_unit_order)
-    int* gorder;                  // n_cap: order in which the group kernels take the groups (k_unit_order); during the build
-                                  // the roots of the subtrees handed out whole and, from its end, the nodes above them
+    int* gorder;                  // n_cap: order in which the group kernels take the groups (k_unit_order); in the
+                                  // build the roots of the subtrees handed out whole and, from its end, the nodes above
     int* gcount;                  // group_hist_words(n_cap): groups starting in each tile of positions
     u16* nbr;                     // n_cap * nbr_cap: list slots, indices into the group's union
     int* nbr_cnt;                 // n_cap
@@ -409,14 +409,12 @@ inline bool tiny_sets(const Dims& dm) { return dm.n <= 64 * (int64_t)dm.n_sets; 
 // Launchers (defined in the .hip files)
 
 // k_build.hip
-void launch_fill_u32(hipStream_t s, u32* p, u32 v, int n);
 void launch_fill_i32(hipStream_t s, int* p, int v, int n);
-void launch_bbox(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
-                 const double* z, const u32* perm_or_null);
+void launch_bbox(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y, const double* z);
 void launch_set_box(hipStream_t s, const DevPtrs& d, const Dims& dm, int from_host_box);
 void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
                  const double* z, const double* vx, const double* vy, const double* vz, const double* m,
-                 const double* h, const double* u, u64* keys_out_caller, int caller_order);
+                 const double* h, const double* u, u64* keys_out_caller);
 void sort_caller_keys(hipStream_t s, const DevPtrs& d, int n);
 void sort_step_keys(hipStream_t s, const DevPtrs& d, const Dims& dm);
 // k_tree.hip
@@ -436,7 +434,8 @@ void launch_density(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
                     const double* u_eos, int kinetic_in_u);
 void launch_csr_count(hipStream_t s, const DevPtrs& d, const Dims& dm, int64_t* counts_caller);
 void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp);
-void launch_csr_fill(hipStream_t s, const DevPtrs& d, const Dims& dm, const int64_t* offsets, int32_t* idx, int64_t total);
+void launch_csr_fill(hipStream_t s, const DevPtrs& d, const Dims& dm, const int64_t* offsets, int32_t* idx,
+                     int64_t total);
 // k_sph.hip
 void launch_thermo_from_caller(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* rho,
                                const double* P, const double* cs);
@@ -454,7 +453,6 @@ struct ScatterArgs {
 };
 void launch_scatter_caller(hipStream_t s, const DevPtrs& d, int n, const ScatterArgs& a);
 void launch_fill_zero(hipStream_t s, int n, double* dst);
-void launch_gather_caller(hipStream_t s, const DevPtrs& d, int n, const double* src_caller, double* dst);
 void launch_box_init(hipStream_t s, const DevPtrs& d, const Dims& dm);
 void launch_kick_drift(hipStream_t s, const DevPtrs& d, const Dims& dm, bool pre_kick, int adaptive_h);
 void launch_kick(hipStream_t s, const DevPtrs& d, const Dims& dm, int adaptive_h);

@@ -11,18 +11,12 @@
 
 // ---------------------------------------------------------------------------------------
 // fills
-__global__ void k_fill_u32(u32* p, u32 v, int n) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
-}
 __global__ void k_fill_i32(int* p, int v, int n) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = v;
 }
 static int grid_for(int n, int bs = 256, int cap = 4096) {
     int g = (n + bs - 1) / bs;
     return g < 1 ? 1 : (g > cap ? cap : g);
-}
-void launch_fill_u32(hipStream_t s, u32* p, u32 v, int n) {
-    if (n > 0) hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(n)), dim3(256), 0, s, p, v, n);
 }
 void launch_fill_i32(hipStream_t s, int* p, int v, int n) {
     if (n > 0) hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(n)), dim3(256), 0, s, p, v, n);
@@ -72,8 +66,7 @@ void launch_box_init(hipStream_t s, const DevPtrs& d, const Dims& dm) {
     hipLaunchKernelGGL(k_box_init, dim3((dm.n_seg + 255) / 256), dim3(256), 0, s, d.ctl, dm.n_seg);
 }
 
-void launch_bbox(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
-                 const double* z, const u32*) {
+void launch_bbox(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y, const double* z) {
     const int slots = dm.batched ? dm.n_seg : BOX_SLOTS;
     hipLaunchKernelGGL(k_box_init, dim3((slots + 255) / 256), dim3(256), 0, s, d.ctl, slots);
     if (dm.n_chunks > 0)
@@ -203,7 +196,7 @@ __global__ void __launch_bounds__(256) k_keys(DevCtl* ctl, const int4* chunk, in
 
 void launch_keys(hipStream_t s, const DevPtrs& d, const Dims& dm, const double* x, const double* y,
                  const double* z, const double* vx, const double* vy, const double* vz, const double* m,
-                 const double* h, const double* u, u64* keys_out_caller, int) {
+                 const double* h, const double* u, u64* keys_out_caller) {
     if (dm.n_chunks > 0)
         hipLaunchKernelGGL(k_keys, dim3(dm.n_chunks), dim3(256), 0, s, d.ctl, d.chunk, dm.batched, dm.curve, x, y, z, vx, vy,
                            vz, m, h, u, d.key_b, keys_out_caller, d.rec);
@@ -391,7 +384,7 @@ void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
 // Merge sort of (u64 key, u32 value), value = the input index: tiles of MS_TILE keys sorted in
 // LDS by one workgroup each (two resident per CU), then merge passes: 2-way over runs that double (merge path:
 // every workgroup finds where its MS_OUT outputs start in both runs and merges them in LDS), or by rank
-// over four or eight runs (k_ms_rank below).
+// over four or eight runs (k_ms_rank below).  Sets of up to RANK_MAX keys skip both (k_rank_sort).
 //
 // Equal keys are ordered by `tie[value]` (the particle ID; tie == nullptr: the value itself), in
 // the comparison, so the input may be in any order: the step sorts from the previous key order,
@@ -400,8 +393,9 @@ void scan_i64_inplace(hipStream_t s, int64_t* a, int n, void* tmp) {
 //
 // What bounds it: launches for small sets; LDS reads in the tiles, memory in the passes for
 // large ones.  Measured per sort against an LSD radix sort of 8-bit digits (8 passes of three
-// kernels at any size, for 63 key bits): 4,096 keys 134 -> 15-21 us (6.5 us by rank, below), 123K 144 -> 59 us (43 by more ways), 1M 183 ->
-// 101 us (a pass 8.9 us, 2.7 TB/s; the tiles 30 us), 4M 400 -> 365 us (a pass 28 us, 3.6 TB/s).
+// kernels at any size, for 63 key bits): 4,096 keys 134 -> 15-21 us (6.5 us by rank, below), 123K 144 -> 59 us
+// (43 by more ways), 1M 183 -> 101 us (a pass 8.9 us, 2.7 TB/s; the tiles 30 us; 95 by four ways), 4M 400 -> 365 us
+// (a pass 28 us, 3.6 TB/s).
 // Tiles of 8,192 keys save a pass and lose as much (47 us at 1M); 8 keys a thread instead of 4
 // leave fewer waves to hide the LDS latency (tiles 34 us, a pass 10.3 us at 1M).
 constexpr int MS_ITEMS = 4, MS_TILE = 1024 * MS_ITEMS, MS_TILE_MID = 256 * MS_ITEMS;
@@ -409,7 +403,7 @@ constexpr int MM_ITEMS = 4, MM_THREADS = 512, MS_OUT = MM_THREADS * MM_ITEMS;
 constexpr u32 MS_PAD = 0xffffffffu;  // value of a filler entry past the end of the last tile
 
 // Slot of item i in LDS: one spare slot after every 8 items, so that the lanes of a wave, whose
-// items lie 8 apart, start in different banks.
+// items lie MS_ITEMS apart, start in different banks.
 __device__ __forceinline__ int ms_slot(int i) { return i + (i >> 3); }
 
 // Order of two items with equal keys (rare: duplicates, and the fillers of the last tile).
@@ -519,7 +513,7 @@ __global__ void __launch_bounds__(TILE / MS_ITEMS) k_ms_tile(const u64* key, u64
             const int a0 = i0 & ~(2 * run - 1);
             const int b0 = min(a0 + run, pad), e = min(a0 + 2 * run, pad);
             const int d = i0 - a0;
-            // nearly sorted input (a step's): the thread's 8 items stay where they are when all
+            // nearly sorted input (a step's): the thread's items stay where they are when all
             // of them precede the other run (in A) or follow it (in B)
             const bool in_a = i0 < b0;
             const bool stays = b0 == e || (in_a ? k[MS_ITEMS - 1] < sk[ms_slot(b0)] : sk[ms_slot(b0 - 1)] < k[0]);

@@ -2,8 +2,8 @@
 // and quadrupole moments).
 //
 // One, two or four wavefronts per target group, two targets per lane.  The wide walk (by the first of them)
-// tests up to 64 nodes at once against the group's box: a cell B is accepted for the whole group when its particle box does not touch
-// the group box and b_B < theta d, b_B being the distance from B's centre of mass to the
+// tests up to 64 nodes at once against the group's box: a cell B is accepted for the whole group when its
+// particle box does not touch the group box and b_B < theta d, b_B being the distance from B's centre of mass to the
 // farthest corner of its particle box (B's radius about the centre of mass) and d the
 // distance from the centre of mass to the group box (theta = 0 opens everything: the exact
 // direct sum).  Accepted
@@ -93,7 +93,8 @@ struct TargetSums {
 // a = (M/8, com), b = (Qxx, Qyy, Qzz, -tr(I) eps^2)/32, d = (Qxy, Qxz, Qyz, -)/32, and the sum holds phi/4.
 // The kernel is bound by its FP64 instructions (at 4M particles it runs at what the FMA probe
 // sustains of the issue rate): 35 per term, 37 with the potential, against 39 and 44 with the
-// trace carried along (15.7 -> 14.2 ms) and 1/s itself (node-node gravity of 262,144 particles 1.61 -> 1.58 ms, the walk of 4M unchanged).
+// trace carried along (15.7 -> 14.2 ms) and 1/s itself (node-node gravity of 262,144 particles 1.61 -> 1.58 ms,
+// the walk of 4M unchanged).
 template <bool PH = true>
 __device__ __forceinline__ void cell_term(const double4 me, const double4 a, const double4 b, const double4 d,
                                           double e2, TargetSums& S) {
@@ -685,7 +686,8 @@ void launch_gravity(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
     // 1114 / 1217.  Groups of 16 lack the targets for four (8,000 particles: 153 / 146 / 155).
     const int64_t units = dm.n / std::max(1, dm.group_size);
     // Sets of up to 64 particles are one tile, which one wavefront evaluates.
-    const int W = units > 64 * dm.group_size || tiny_sets(dm) ? 1 : (units > 1024 || dm.group_size <= 16 || fp32c ? 2 : 4);
+    const bool one = units > 64 * dm.group_size || tiny_sets(dm);
+    const int W = one ? 1 : (units > 1024 || dm.group_size <= 16 || fp32c ? 2 : 4);
     if (fp32c) {
         // FP32C sums are the same bit for bit by one and by two wavefronts, so a cap on the wavefronts that leaves
         // fewer than two a group goes to more groups at once (50,000 particles, one a CU: 618 -> 456 us).  FP64 sums
@@ -1042,7 +1044,8 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
         for (int h = 0; h < (TWO ? 2 : 1); ++h) {
             unit_sync<W>();
             if (FP32C) S.St.part.pm[tid] = make_double4(A.kx.value(), A.ky.value(), A.kz.value(), A.kp.value());
-            else S.St.part.pm[tid] = TWO && h ? make_double4(B.gx, B.gy, B.gz, 4.0 * B.ph) : make_double4(A.gx, A.gy, A.gz, 4.0 * A.ph);
+            else if (TWO && h) S.St.part.pm[tid] = make_double4(B.gx, B.gy, B.gz, 4.0 * B.ph);
+            else S.St.part.pm[tid] = make_double4(A.gx, A.gy, A.gz, 4.0 * A.ph);
             unit_sync<W>();
             if (!(h ? T.vb : T.va) || T.ph != 0) continue;
             double4 r = S.St.part.pm[tid];
@@ -1086,9 +1089,10 @@ __device__ __forceinline__ void fmm_leaf(const FmmArgs& K, FmmLds<W>& S, int L, 
 // than all other work in one wavefront each.  With at most 4,096 leaves (four
 // workgroups a CU hold 1,024 at once) leaves of 16 targets and more count as heavy too; smaller ones are
 // bound by the walk, which one wavefront does.  Where the angle is wide, leaves have less to evaluate beside
-// their walk, and the limit is 3,072.  At theta = 0.5, us, for limits of 0 / 1,024 / 2,048 / 4,096 leaves: 3,000 particles in leaves of
-// 48 176 / 71 / 72 / 71, 20,011 in leaves of 32 210 / 209 / 170 / 170, 35,000 in leaves of 64 517 / 519 / 309 / 314,
-// 50,000 in leaves of 64 655 / 656 / 655 / 450; at theta = 1, 3,072 / 4,096: a flat 60,000 in leaves of 32 42 / 73.
+// their walk, and the limit is 3,072.  At theta = 0.5, us, for limits of 0 / 1,024 / 2,048 / 4,096 leaves: 3,000
+// particles in leaves of 48 176 / 71 / 72 / 71, 20,011 in leaves of 32 210 / 209 / 170 / 170, 35,000
+// in leaves of 64 517 / 519 / 309 / 314, 50,000 in leaves of 64 655 / 656 / 655 / 450; at theta = 1, 3,072 / 4,096:
+// a flat 60,000 in leaves of 32 42 / 73.
 // Four leaves a workgroup, sizes in order and the heavy leaves together: 262,144 particles 2.18 -> 1.56 ms.
 // The FP32C sums, whose last bits depend on the split, keep one wavefront a leaf.
 template <bool FP32C, bool TWO>
@@ -1135,7 +1139,8 @@ void launch_fmm(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, doub
     // four leaves a workgroup, about 3 n / leaf_size of them; the kernel loops over any beyond that.  Few leaves
     // may all be heavy, one a workgroup (8,000 uniform particles in leaves of 64 on a quarter of the workgroups:
     // 209 -> 110 us).
-    const int fours = dm.n / std::max(1, dm.leaf_size), ones = fp32c ? 0 : (int)std::min<int64_t>(3ll * fours, wide_leaves);
+    const int fours = dm.n / std::max(1, dm.leaf_size);
+    const int ones = fp32c ? 0 : (int)std::min<int64_t>(3ll * fours, wide_leaves);
     const int grid = std::min(8 * ((std::max(fours, ones) + 23) / 8), 8 * std::max(1, dm.wave_cap / 32));
     const FmmArgs K{d.ctl, order, d.leaf_node, d.parent, d.topo, d.range, d.mom0, ncell, d.pos4, d.m, G, eps, th4,
                     accumulate, gx, gy, gz, d.phi, d.vel4, de};

@@ -218,7 +218,9 @@ struct DensSrc<true, CH> {
         mass[i] = (float)mb;
     }
     __device__ __forceinline__ float4 rec(int i) const { return pos[i]; }
-    __device__ __forceinline__ static float4 target(const double4 p, const double4& o, double) { return offset_rec(p, o); }
+    __device__ __forceinline__ static float4 target(const double4 p, const double4& o, double) {
+        return offset_rec(p, o);
+    }
 };
 // Sets whose workgroups (256 threads, 40 KB) are resident at once.
 static bool few_groups(const Dims& dm) { return dm.n <= 512 * (int64_t)dm.group_size; }
@@ -235,8 +237,9 @@ static bool narrow_groups(const Dims& dm) {
 
 template <bool FP32C, int NT, int CH>
 __global__ void __launch_bounds__(NT) k_density(
-    const DevCtl* __restrict__ ctl, const int* __restrict__ order, const int4* __restrict__ group, int gsz, int cap, const u16* __restrict__ nbr,
-    const int* __restrict__ nbr_cnt, const int* __restrict__ uni, const int* __restrict__ ucnt,
+    const DevCtl* __restrict__ ctl, const int* __restrict__ order, const int4* __restrict__ group, int cap,
+    const u16* __restrict__ nbr, const int* __restrict__ nbr_cnt, const int* __restrict__ uni,
+    const int* __restrict__ ucnt,
     const double4* __restrict__ pos4, const double4* __restrict__ vel4, const double* __restrict__ m,
     const double* __restrict__ u_eos, int kin, double gamma, double h_coeff, double* __restrict__ rho,
     double* __restrict__ P, double* __restrict__ cs, double* __restrict__ hnext, double4* __restrict__ thr4,
@@ -307,8 +310,8 @@ void launch_density(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, 
                     const double* u_eos, int kin) {
     if (dm.n <= 0) return;
     auto go = [&](auto kern, int threads) {
-        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, group_order(d, dm), d.group, dm.group_size, dm.nbr_cap, d.nbr,
-                           d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.m, u_eos, kin, gamma, h_coeff, d.rho, d.P,
+        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, group_order(d, dm), d.group, dm.nbr_cap,
+                           d.nbr, d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.m, u_eos, kin, gamma, h_coeff, d.rho, d.P,
                            d.cs, d.hnext, d.thr4, d.thrf);
     };
     if (fp32c) go(k_density<true, 256, 512>, 256);
@@ -333,8 +336,9 @@ struct ForceSrc<true, CH> {
 };
 template <bool FP32C, bool THERMO, int NT, int CH>
 __global__ void __launch_bounds__(NT) k_forces(
-    const DevCtl* __restrict__ ctl, const int* __restrict__ order, const int4* __restrict__ group, int gsz, int cap, const u16* __restrict__ nbr,
-    const int* __restrict__ nbr_cnt, const int* __restrict__ uni, const int* __restrict__ ucnt,
+    const DevCtl* __restrict__ ctl, const int* __restrict__ order, const int4* __restrict__ group, int cap,
+    const u16* __restrict__ nbr, const int* __restrict__ nbr_cnt, const int* __restrict__ uni,
+    const int* __restrict__ ucnt,
     const double4* __restrict__ pos4, const double4* __restrict__ vel4, const double4* __restrict__ thr4,
     const float4* __restrict__ thrf, double alpha, double beta, double eps_av,
     double* __restrict__ ax, double* __restrict__ ay, double* __restrict__ az, double* __restrict__ du) {
@@ -482,7 +486,7 @@ __global__ void __launch_bounds__(NT) k_forces(
             fx = sx.value(); fy = sy.value(); fz = sz.value(); fu = su.value();
         }
         __syncthreads();
-        double* red = reinterpret_cast<double*>(&S);  // 4 x 256 doubles
+        double* red = reinterpret_cast<double*>(&S);  // 4 NT doubles
         red[tid] = fx;
         red[NT + tid] = fy;
         red[2 * NT + tid] = fz;
@@ -509,16 +513,16 @@ void launch_forces(hipStream_t s, const DevPtrs& d, const Dims& dm, int fp32c, d
                    double eps_av, int thermo) {
     if (dm.n <= 0) return;
     auto go = [&](auto kern, int threads) {
-        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, group_order(d, dm), d.group, dm.group_size,
+        hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, group_order(d, dm), d.group,
                            dm.nbr_cap, d.nbr, d.nbr_cnt, d.uni, d.ucnt, d.pos4, d.vel4, d.thr4, d.thrf, alpha,
                            beta, eps_av, d.ax, d.ay, d.az, d.du);
     };
     // Union members staged a round.  A wave runs each round as long as its busiest target, so a union in one
     // round wastes fewer lanes, but the records (88 bytes, 80 in FP32C) bound the workgroups a CU holds.
-    // Forces alone, us, at 256 / 320 / 464 (FP32C 512): 987,840 particles in groups of 64, FP64 239 / - / 204 (214 with the correction of 1/T^2);
-    // 1.2M in 64 boxes, groups of 64, FP32C 306 / 289 / 276; 1.0M in 56 boxes, groups of 32, FP64 269 / 249 /
-    // 269; the same in groups of 16, FP32C 316 / 338 / 441, FP64 365 / 391 / 451 and with 128 threads 326 (192:
-    // 300).  Few groups take the largest: 3,375 in groups of 32, FP32C 9.0 / 8.2 / 7.2.
+    // Forces alone, us, at 256 / 320 / 464 (FP32C 512): 987,840 particles in groups of 64, FP64 239 / - / 204 (214 with
+    // the correction of 1/T^2); 1.2M in 64 boxes, groups of 64, FP32C 306 / 289 / 276; 1.0M in 56 boxes, groups of 32,
+    // FP64 269 / 249 / 269; the same in groups of 16, FP32C 316 / 338 / 441, FP64 365 / 391 / 451 and with 128
+    // threads 326 (192: 300).  Few groups take the largest: 3,375 in groups of 32, FP32C 9.0 / 8.2 / 7.2.
     auto pick = [&](auto f, auto th) {
         constexpr bool F = decltype(f)::value, TH = decltype(th)::value;
         if (dm.group_size > 32 || few_groups(dm) || (!F && dm.group_size <= 16 && !narrow_groups(dm)))

@@ -5,7 +5,8 @@
 static inline dim3 g256(int n) { return dim3((n + 255) / 256); }
 
 // Up to four key-ordered arrays to the caller's order in one launch (a call's results; four
-// launches cost a small set more than the copies do: 50,021 particles 8 x 3.9 -> 2 x 5.5 us); a NULL destination is skipped.
+// launches cost a small set more than the copies do: 50,021 particles 8 x 3.9 -> 2 x 5.5 us); a NULL
+// destination is skipped.
 __global__ void k_scatter_caller(int n, const u32* __restrict__ id, ScatterArgs a) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= n) return;
@@ -35,14 +36,6 @@ __global__ void k_fill_zero(int n, double* dst) {
 }
 void launch_fill_zero(hipStream_t s, int n, double* dst) {
     if (n > 0 && dst) hipLaunchKernelGGL(k_fill_zero, g256(n), dim3(256), 0, s, n, dst);
-}
-
-__global__ void k_gather_caller(int n, const u32* __restrict__ id, const double* __restrict__ src, double* dst) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < n) dst[q] = src[id[q]];
-}
-void launch_gather_caller(hipStream_t s, const DevPtrs& d, int n, const double* src_caller, double* dst) {
-    if (n > 0) hipLaunchKernelGGL(k_gather_caller, g256(n), dim3(256), 0, s, n, d.id, src_caller, dst);
 }
 
 // v' = v + dt/2 a; u' = u + dt/2 du; x += dt v'; predictors v^ = v' + dt/2 a, u^ = u' + dt/2 du.

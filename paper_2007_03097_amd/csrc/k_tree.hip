@@ -839,7 +839,7 @@ static void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm, const 
         if (tb == TB_SMALL) run(k_order_levels<decltype(w)::value, TB_SMALL, Move>);
         else run(k_order_levels<decltype(w)::value, TB_LARGE, Move>);
     };
-    switch (dm.leaf_size) {  // the autotuner's leaf sizes and the node-node scheme's 64
+    switch (dm.leaf_size) {  // the autotuner's leaf sizes (its 48 for the node-node scheme takes the general form)
         case 8: levels(std::integral_constant<int, 8>()); break;
         case 12: levels(std::integral_constant<int, 12>()); break;
         case 16: levels(std::integral_constant<int, 16>()); break;
@@ -859,7 +859,8 @@ static void build_octree(hipStream_t s, const DevPtrs& d, const Dims& dm, const 
     };
     if (tb == TB_SMALL) emit(k_emit_nodes<TB_SMALL>);
     else emit(k_emit_nodes<TB_LARGE>);
-    const NodeArgs A{d.ctl, n, n > SUB_LISTED ? (n + SUB_SHARE - 1) / SUB_SHARE : 0, d.gorder, dm.batched, dm.mass_moments, d.key_a, d.topo, d.parent, d.pos4, d.m,
+    const int sub_max = n > SUB_LISTED ? (n + SUB_SHARE - 1) / SUB_SHARE : 0;
+    const NodeArgs A{d.ctl, n, sub_max, d.gorder, dm.batched, dm.mass_moments, d.key_a, d.topo, d.parent, d.pos4, d.m,
                      d.nbox_lo, d.nbox_hi, d.mom0, d.mom1, d.mom2, d.range};
     // about 4 n / leaf_size nodes of eight lanes; the kernel loops over any beyond that
     hipLaunchKernelGGL(k_finalize, dim3(grid_cap(4 * (n / dm.leaf_size) + 64, 256 / NODE_LANES, 8192)), dim3(256), 0, s,

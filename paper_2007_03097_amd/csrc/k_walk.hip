@@ -378,14 +378,11 @@ __device__ void match_candidates(int nc, int* cand, int* coff, Tile<W>& tile, in
 
 // W wavefronts per group: the first one walks the tree, all of them match the candidates, a tile each.
 template <int T, int W>
-__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ? 5 : 1))) k_nbr_lists(DevCtl* ctl, const int* __restrict__ order,
-                                                      const int4* __restrict__ group, int cap,
-                                                      const int4* __restrict__ topo,
-                                                      const double4* __restrict__ nbox_lo,
-                                                      const double4* __restrict__ nbox_hi,
-                                                      const double4* __restrict__ pos4, u16* __restrict__ nbr,
-                                                      int* __restrict__ nbr_cnt, int* __restrict__ list_base,
-                                                      int* __restrict__ uni, int* __restrict__ ucnt_out) {
+__global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(W == 1 ? 5 : 1))) k_nbr_lists(
+    DevCtl* ctl, const int* __restrict__ order, const int4* __restrict__ group, int cap, const int4* __restrict__ topo,
+    const double4* __restrict__ nbox_lo, const double4* __restrict__ nbox_hi, const double4* __restrict__ pos4,
+    u16* __restrict__ nbr, int* __restrict__ nbr_cnt, int* __restrict__ list_base, int* __restrict__ uni,
+    int* __restrict__ ucnt_out) {
     __shared__ int stack[WALK_STACK];
     __shared__ int cand[WALK_CAND];
     __shared__ int coff[WALK_CAND + 1];
@@ -577,7 +574,8 @@ void launch_csr_count(hipStream_t s, const DevPtrs& d, const Dims& dm, int64_t* 
 // entry's place in its list is the number of smaller IDs in it: each lane holds one entry and
 // counts them against the others broadcast from their lanes, without LDS sorts or divergence.
 // The former one-thread insertion sort in global memory was bound by its chains of dependent
-// loads and stores: 1,070 us for 200,003 particles of 38 neighbours, now 84 us (30 MB of lists: 0.4 TB/s; the counting bounds it).
+// loads and stores: 1,070 us for 200,003 particles of 38 neighbours, now 84 us (30 MB of lists: 0.4 TB/s; the
+// counting bounds it).
 template <int CSR_THREADS>
 __global__ void __launch_bounds__(CSR_THREADS) k_csr_fill(const DevCtl* __restrict__ ctl, int cap,
                                                           const int4* __restrict__ group, const u32* __restrict__ id,
@@ -659,7 +657,8 @@ __global__ void __launch_bounds__(CSR_THREADS) k_csr_fill(const DevCtl* __restri
     }
 }
 
-void launch_csr_fill(hipStream_t s, const DevPtrs& d, const Dims& dm, const int64_t* offsets, int32_t* idx, int64_t total) {
+void launch_csr_fill(hipStream_t s, const DevPtrs& d, const Dims& dm, const int64_t* offsets, int32_t* idx,
+                     int64_t total) {
     if (dm.n <= 0) return;
     auto go = [&](auto kern, int threads) {
         hipLaunchKernelGGL(kern, dim3(dm.pair_grid), dim3(threads), 0, s, d.ctl, dm.nbr_cap, d.group, d.id, d.nbr_cnt,
