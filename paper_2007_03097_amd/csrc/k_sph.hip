@@ -108,10 +108,10 @@ struct Entries {
     }
 };
 
-// Both passes are bound by VALU issue (FP64 at 987,840 particles: 65-70% of the issue slots, the rest waits
+// Both passes are bound by VALU issue (FP64 at 987,840 particles: 65-76% of the issue slots, the rest waits
 // for list entries and at the group's ends), so the pair term is written for few instructions: density
-// 145 -> 119 us, forces 279 -> 214 us with PairGeo, the byte offsets and batches of Entries and the
-// force pass's one round.
+// 145 -> 129 us (119 without DensAcc's residual), forces 279 -> 214 us with PairGeo, the byte offsets and
+// batches of Entries and the force pass's one round.
 //
 // Geometry of one pair in FP64 from one reciprocal square root: with T = h_a + h_b = 2 h_ab,
 // y = 1/(r T) gives r/T = r^2 y and 1/T^2 = (r^2 y) y, without a square root or a reciprocal of its own.
